@@ -194,9 +194,8 @@ int bs_profile_read(bs_ctx *ctx, int which, double *total_ms, int64_t *launches)
 int bs_profile_reset(bs_ctx *ctx);
 
 /* Tuning knob: pages per chunk of decode-attention work (even, 2..64).  Smaller chunks give more
- * parallelism and more partial states to merge.  Default: 64 for private tails and for prefix nodes
- * whose work items carry at most 16 query rows, 32 for nodes with more (every chunk of such a node
- * costs one partial state per member row); a call sets both. */
+ * workgroups, larger ones fewer partial states.  Without it the chunk is chosen for each step: 64
+ * pages where the step has enough work for the whole chip, down to 8 where it has not. */
 int bs_set_chunk_pages(bs_ctx *ctx, int32_t pages);
 
 /* Tuning knobs of the BS_FLAG_OVERLAP schedule. */

@@ -90,9 +90,7 @@ struct bs_ctx {
   int n_cu = 256;
   int forced_tiles = 0;            // bs_set_gemm_tiles
   // tunables
-  int chunk_pages = 64;       // pages per chunk of decode-attention work: private tails and nodes with few member rows
-  int chunk_pages_wide = 32;  // nodes whose items carry more than 16 query rows: four wavefronts share an item, and every
-                              // chunk costs one partial state per member row
+  int chunk_pages = 0;  // pages per chunk of decode-attention work; 0: chosen for each step (see chunk_choice)
   // profiling
   bool prof = false;
   struct Span { hipEvent_t a, b; };
@@ -317,10 +315,45 @@ int validate(bs_ctx *c, const bs_batch *b, int64_t n_pages) {
 // ---------------------------------------------------------------------------------
 // plan: everything the kernels need, packed in one int32 blob
 // ---------------------------------------------------------------------------------
-int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows) {
+constexpr int CHUNK_MAX = 64, CHUNK_MIN = 8;  // pages (a lane of a wavefront holds one page id of its chunk)
+constexpr long CHUNK_UNITS = 512, CHUNK_UNITS_WIDE = 1536;  // units of (chunk, KV head) below which chunks are cut shorter
+// pages per chunk: `wide` for the nodes whose items carry more than 16 query rows, `other` for the rest
+struct Chunks { int other, wide; };
+constexpr Chunks NOALLOC_CHUNKS = {CHUNK_MAX, CHUNK_MAX / 2};  // the division that bs_attention_noalloc's limits count in
+
+// Pages per chunk of decode-attention work.  A CU streams at most about 36 GB/s of KV pages however many
+// of its wavefronts ask for them, and a wavefront serves its chunk at one page per 0.3 us (64 query
+// rows: 1.2 us), so a step of few sequences is bound by how many CUs have a chunk and by how long one
+// chunk takes: it is cut until there are 512 units of (chunk, KV head), or 1536 where prefix nodes
+// carry more than 16 query rows.  Every chunk costs a partial state per member row, hence no chunk under
+// eight pages, and large steps keep the longest chunk that the kernels take.  Measured (attention +
+// merge, 8B layer; this rule against chunks of 64 pages, 32 under wide nodes): 7 sequences of 2000
+// tokens 25 against 30 us, one of 4000 16 against 28, 40 behind one prefix of 4096 40 against 52,
+// 20 behind two of 1024 28 against 49; 256 of 1024 and 640 behind a two-level tree the same.
+Chunks chunk_choice(const bs_ctx *c, const bs_batch *b) {
+  if (c->chunk_pages > 0) return {c->chunk_pages, c->chunk_pages};
+  const int grp = c->cfg.n_q_heads / c->cfg.n_kv_heads, max_members = std::max(1, 64 / grp);
+  long pages = 0;
+  bool wide = false;
+  for (int n = 0; n < b->n_nodes; ++n) {
+    const long cnt = b->node_seq_count[n], np = b->node_page_start[n + 1] - b->node_page_start[n];
+    if (cnt <= 0 || np <= 0) continue;
+    pages += np * ((cnt + max_members - 1) / max_members);
+    wide = wide || cnt * grp > 16;
+  }
+  for (int s = b->n_prefill; s < b->n_seq; ++s) {
+    const int leaf = b->n_nodes > 0 ? b->seq_leaf_node[s] : -1;
+    pages += (b->kv_len[s] + c->cfg.page_size - 1) / c->cfg.page_size - (leaf >= 0 ? c->path_pages[leaf] : 0);
+  }
+  const long ch = pages * c->cfg.n_kv_heads / (wide ? CHUNK_UNITS_WIDE : CHUNK_UNITS);
+  const int pages_each = (int)std::min<long>(CHUNK_MAX, std::max<long>(CHUNK_MIN, (ch + 1) / 2 * 2));
+  return {pages_each, pages_each};
+}
+
+int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chunks) {
+  const int ch = chunks.other;
   const int ps = c->cfg.page_size;
   const int grp = c->cfg.n_q_heads / c->cfg.n_kv_heads;
-  const int ch = c->chunk_pages;
   const int nn = b->n_nodes;
   p.n_seq = b->n_seq; p.n_prefill = b->n_prefill; p.n_rows = b->n_rows; p.n_decode = b->n_seq - b->n_prefill;
   p.n_prefill_rows = b->n_seq ? b->row_start[b->n_prefill] : 0;
@@ -339,7 +372,7 @@ int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows) {
     const int cnt = b->node_seq_count[n];
     const int n_groups = cnt > 0 ? (cnt + max_members - 1) / max_members : 1;
     // the chunk size of a node is one for all its member groups: their partial states share slot numbers
-    const int chn = ((cnt + n_groups - 1) / n_groups) * grp > 16 ? c->chunk_pages_wide : ch;
+    const int chn = ((cnt + n_groups - 1) / n_groups) * grp > 16 ? chunks.wide : ch;
     const int nch = (np + chn - 1) / chn;
     c->path_chunks[n] = above + nch;
     if (cnt <= 0 || np <= 0) continue;
@@ -985,7 +1018,7 @@ int bs_resolve_rows(bs_ctx *c, const bs_batch *b, int32_t *page_out, int32_t *sl
   int rc = validate(c, b, max_page + 1);
   if (rc) return rc;
   Plan p;
-  if ((rc = build_plan(c, b, p, true))) return rc;
+  if ((rc = build_plan(c, b, p, true, chunk_choice(c, b)))) return rc;
   for (int r = 0; r < b->n_rows; ++r) {
     page_out[r] = c->blob[p.off_row_page + r];
     slot_out[r] = c->blob[p.off_row_slot + r];
@@ -1151,7 +1184,7 @@ int bs_blend_step(bs_ctx *c, const bs_weights *w, const bs_batch *b, const void 
   gemm_force_variant(c->forced_tiles);
   hipStream_t st = (hipStream_t)stream_;
   Plan p;
-  if ((rc = build_plan(c, b, p, true))) return rc;
+  if ((rc = build_plan(c, b, p, true, chunk_choice(c, b)))) return rc;
   if ((rc = ensure_rows(c, p.n_rows))) return rc;
   if ((rc = ensure_slots(c, p.n_slots))) return rc;
   if ((rc = upload_plan(c, p, st))) return rc;
@@ -1175,7 +1208,7 @@ int bs_blend_layers(bs_ctx *c, int32_t n_layers, const bs_weights *w, const bs_b
   gemm_force_variant(c->forced_tiles);
   hipStream_t st = (hipStream_t)stream_;
   Plan p;
-  if ((rc = build_plan(c, b, p, true))) return rc;
+  if ((rc = build_plan(c, b, p, true, chunk_choice(c, b)))) return rc;
   if ((rc = ensure_rows(c, p.n_rows))) return rc;
   if ((rc = ensure_slots(c, p.n_slots))) return rc;
   if ((rc = upload_plan(c, p, st))) return rc;
@@ -1212,7 +1245,7 @@ int bs_attention(bs_ctx *c, const bs_batch *b, const void *q, void *out, const v
   HIP_TRY(c, hipSetDevice(c->device));
   hipStream_t st = (hipStream_t)stream_;
   Plan p;
-  if ((rc = build_plan(c, b, p, false))) return rc;
+  if ((rc = build_plan(c, b, p, false, chunk_choice(c, b)))) return rc;
   if ((rc = ensure_slots(c, p.n_slots))) return rc;
   if ((rc = upload_plan(c, p, st))) return rc;
   if ((rc = run_attention(c, p, (const uint16_t *)q, (uint16_t *)out, (const uint16_t *)pool, st))) return rc;
@@ -1236,17 +1269,34 @@ int bs_attention_noalloc(bs_ctx *c, const bs_batch *b, const void *q, void *out,
   HIP_TRY(c, hipSetDevice(c->device));
   hipStream_t st = (hipStream_t)stream_;
   Plan p;
-  if ((rc = build_plan(c, b, p, false))) return rc;
-  // layout of the scratch array: descriptor blob | m | l | acc of the partial states (m and l padded
-  // to whole 16-byte units, so that the accumulators after them stay 16-byte aligned)
+  // What fits is decided by the fixed division of the contexts, so that it does not depend on how finely
+  // chunk_choice would cut them; the finer division is taken where it fits as well.
+  // Layout of the scratch array: descriptor blob | m | l | acc of the partial states (m and l padded
+  // to whole 16-byte units, so that the accumulators after them stay 16-byte aligned).
+  const Chunks fine = chunk_choice(c, b), fixed = c->chunk_pages > 0 ? fine : NOALLOC_CHUNKS;
   const size_t hq = c->cfg.n_q_heads, dh = c->cfg.head_dim;
-  const size_t ml_floats = ((size_t)p.n_slots * hq + 3) / 4 * 4;
-  const size_t state_bytes = (2 * ml_floats + (size_t)p.n_slots * hq * dh) * sizeof(float);
-  if ((size_t)p.total_ints * sizeof(int32_t) > BS_NOALLOC_BLOB_BYTES)
+  size_t ml_floats = 0, state_bytes = 0;
+  auto plan = [&](Chunks chunks) -> int {
+    p = Plan();
+    const int rc_plan = build_plan(c, b, p, false, chunks);
+    ml_floats = ((size_t)p.n_slots * hq + 3) / 4 * 4;
+    state_bytes = (2 * ml_floats + (size_t)p.n_slots * hq * dh) * sizeof(float);
+    return rc_plan;
+  };
+  auto blob_fits = [&]() { return (size_t)p.total_ints * sizeof(int32_t) <= BS_NOALLOC_BLOB_BYTES; };
+  auto states_fit = [&]() { return state_bytes <= BS_NOALLOC_SCRATCH_BYTES - BS_NOALLOC_BLOB_BYTES; };
+  if ((rc = plan(fixed))) return rc;
+  if (!blob_fits())
     return fail(c, BS_EINVAL, "bs_attention_noalloc: descriptor of %ld bytes exceeds the limit of %u", p.total_ints * 4L, BS_NOALLOC_BLOB_BYTES);
-  if (state_bytes > BS_NOALLOC_SCRATCH_BYTES - BS_NOALLOC_BLOB_BYTES)
+  if (!states_fit())
     return fail(c, BS_EINVAL, "bs_attention_noalloc: %ld partial softmax states (%zu bytes) exceed the limit of %u bytes",
                 p.n_slots, state_bytes, BS_NOALLOC_SCRATCH_BYTES - BS_NOALLOC_BLOB_BYTES);
+  // (a division that chunk_choice cuts finer has at most CHUNK_UNITS_WIDE items more, so the host vectors
+  // reserved by bs_create hold it)
+  if (fine.other < fixed.other && (p.total_ints + 8 * CHUNK_UNITS_WIDE) * sizeof(int32_t) <= BS_NOALLOC_BLOB_BYTES) {
+    if ((rc = plan(fine))) return rc;
+    if (!states_fit() && (rc = plan(fixed))) return rc;
+  }
   // the kernels take their buffers from the context; for this call they are parts of the scratch array
   int32_t *const blob0 = c->d_blob;
   float *const acc0 = c->part_acc, *const m0 = c->part_m, *const l0 = c->part_l;
@@ -1420,7 +1470,6 @@ int bs_set_chunk_pages(bs_ctx *c, int32_t pages) {
   if (!c) return BS_EINVAL;
   if (pages < 2 || pages > 64 || (pages & 1)) return fail(c, BS_EINVAL, "chunk_pages %d (even, 2..64)", pages);
   c->chunk_pages = pages;
-  c->chunk_pages_wide = pages;
   return BS_OK;
 }
 

@@ -31,7 +31,11 @@ using namespace attn_dev;
 
 
 // One launch for both kinds of item, one wavefront per SIMD (the 16-row items stream as fast
-// with one wavefront per SIMD as with two).  Grid order: wide workgroups first, narrow ones
+// with one wavefront per SIMD as with two) and per workgroup: a CU streams about 36 GB/s of pages
+// however many of its wavefronts ask, so a step with few units wants each on a CU of its own.
+// Measured against workgroups of four wavefronts: one sequence of 4000 tokens 60 -> 21 us, 7 of 2000
+// 62 -> 24, 64 of 2000 126 -> 104, 640 behind a two-level tree 369 -> 352, full launches the same.
+// Grid order: wide workgroups first, narrow ones
 // after, longest first within a kind.  Where the wide workgroups are at least a third of the
 // grid, one of them alternates with two narrow ones for as long as both kinds last (what is
 // left of the wide kind goes first): a wavefront with 64 query rows spends part of its time
@@ -39,12 +43,12 @@ using namespace attn_dev;
 // -9 % with 1280 wide and 2048 narrow workgroups, +2 % with 390 and 1812, hence the rule).
 // The period is odd on purpose: workgroups go to the eight XCDs in turn, and a period of
 // four would send every wide workgroup to the same two of them.
-template <int DH, bool NT_NARROW>
+template <int DH, int WPW, bool NT_NARROW, bool ACC_A>
 __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, int n_wide_units, int n_narrow_units, int b, int wave,
                                                  int lane, uint16_t *q_sh) {
   constexpr int WQB = 4;  // blocks of 16 query rows of a wide item
   const int hkv = a.s.n_kv_heads;
-  const int nw = (n_wide_units + 3) >> 2, nn = (n_narrow_units + 3) >> 2;  // workgroups of each kind
+  const int nw = (n_wide_units + WPW - 1) / WPW, nn = (n_narrow_units + WPW - 1) / WPW;  // workgroups of each kind
   const int mixed = 2 * nw >= nn ? min(nw, nn >> 1) : 0;                   // periods of one wide + two narrow
   const int lead = nw - mixed;                                             // wide workgroups ahead of the mixed part
   bool wide;
@@ -60,22 +64,29 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, int n_wide
     wide = false;
     wg = 2 * mixed + (b - lead - 3 * mixed);
   }
-  const int unit = wg * 4 + wave;
+  const int unit = wg * WPW + wave;
   if (wide) {
-    if (unit < n_wide_units) decode_unit<DH, WQB>(a, unit / hkv, unit % hkv, wave, lane, q_sh);
+    if (unit < n_wide_units) decode_unit<DH, WQB, false, ACC_A>(a, unit / hkv, unit % hkv, wave, lane, q_sh);
   } else {
-    if (unit < n_narrow_units) decode_unit<DH, 1, NT_NARROW>(a, n_wide_units / hkv + unit / hkv, unit % hkv, wave, lane, q_sh);
+    if (unit < n_narrow_units) decode_unit<DH, 1, NT_NARROW, ACC_A>(a, n_wide_units / hkv + unit / hkv, unit % hkv, wave, lane, q_sh);
   }
 }
 
-constexpr int DECODE_Q_LDS(int dh) { return dh > 64 ? 4 * 4 * 16 * (dh + 8) : 8; }  // bf16 elements: queries of four wide units
+constexpr int DECODE_Q_LDS(int dh, int waves) { return dh > 64 ? waves * 4 * 16 * (dh + 8) : 8; }  // bf16 elements: queries of a wide unit per wavefront
 
 template <int DH>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void decode_attn_kernel(const DecodeArgs a, int n_wide_units, int n_narrow_units) {
-  __shared__ __align__(16) uint16_t q_sh[DECODE_Q_LDS(DH)];
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void decode_attn_kernel(const DecodeArgs a, int n_wide_units, int n_narrow_units) {
+  __shared__ __align__(16) uint16_t q_sh[DECODE_Q_LDS(DH, 1)];
   // a launch of decode units alone: non-temporal loads for the 16-row units (see ld16_kv)
-  decode_workgroup<DH, true>(a, n_wide_units, n_narrow_units, blockIdx.x, wave, threadIdx.x & 63, q_sh);
+  decode_workgroup<DH, 1, true, true>(a, n_wide_units, n_narrow_units, blockIdx.x, 0, threadIdx.x & 63, q_sh);
+}
+
+// 16-row units alone (no prefix node with more than 16 member rows): under half of a SIMD's registers,
+// so two wavefronts share a SIMD, and no accumulator has to be copied.
+template <int DH>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_narrow_kernel(const DecodeArgs a) {
+  const int unit = (int)blockIdx.x;
+  decode_unit<DH, 1, true>(a, unit / a.s.n_kv_heads, unit % a.s.n_kv_heads, 0, threadIdx.x & 63, nullptr);
 }
 
 // ------------------------------------------------------------------------------
@@ -83,7 +94,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 //   M = max_p m_p;  w_p = 2^(m_p - M);  out = sum_p w_p acc_p / sum_p w_p l_p
 // ------------------------------------------------------------------------------
 // A wavefront covers 256/dh heads of one sequence, so its loads of the partial outputs are
-// 16 bytes per lane, and the partial states are added four at a time with their loads
+// 16 bytes per lane, and the partial states are added eight at a time with all their loads
 // issued together: the kernel is a chain of a few memory round trips, not bandwidth.
 template <int DH>
 __global__ __launch_bounds__(256) void decode_merge_kernel(const MergeArgs a) {
@@ -101,61 +112,44 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(const MergeArgs a) {
   const bool ok = head_raw < hq;
   const int head = ok ? head_raw : hq - 1;  // lanes past the last head repeat it and store nothing
   const int s0 = a.part_start[seq], n = a.part_start[seq + 1] - s0;
-  float mx = NEG_BIG;
-  for (int p = li; p < n; p += LPH) mx = fmaxf(mx, a.part_m[(size_t)(s0 + p) * hq + head]);
-#pragma unroll
-  for (int o = LPH / 2; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-  float ls = 0.f;
-  for (int p = li; p < n; p += LPH) {
-    const size_t b = (size_t)(s0 + p) * hq + head;
-    ls += fast_exp2(a.part_m[b] - mx) * a.part_l[b];
-  }
-#pragma unroll
-  for (int o = LPH / 2; o >= 1; o >>= 1) ls += __shfl_xor(ls, o, 64);
+  float mx = NEG_BIG, ls = 0.f;
   f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-  int p = 0;
-  for (; p + 4 <= n; p += 4) {
-    float w[4];
-    f32x4_t v[4];
+  // A batch of states in one round trip: exponents, sums and outputs are requested together and
+  // weighted against the largest exponent so far (places past the last state repeat it with weight 0).
+  auto batch = [&](int p, auto count) __attribute__((always_inline)) {
+    constexpr int B = decltype(count)::value;
+    float m[B], l[B];
+    f32x4_t v[B];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const size_t b = (size_t)(s0 + p + u) * hq + head;
-      w[u] = a.part_m[b];
-      v[u] = *reinterpret_cast<const f32x4_t *>(a.part_acc + b * DH + li * 4);
+    for (int u = 0; u < B; ++u) {
+      const size_t at = (size_t)(s0 + min(p + u, n - 1)) * hq + head;
+      m[u] = a.part_m[at];
+      l[u] = a.part_l[at];
+      v[u] = *reinterpret_cast<const f32x4_t *>(a.part_acc + at * DH + li * 4);
     }
+    float m_new = mx;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) acc += fast_exp2(w[u] - mx) * v[u];
-  }
-  for (; p < n; ++p) {
-    const size_t b = (size_t)(s0 + p) * hq + head;
-    acc += fast_exp2(a.part_m[b] - mx) * *reinterpret_cast<const f32x4_t *>(a.part_acc + b * DH + li * 4);
-  }
+    for (int u = 0; u < B; ++u) m_new = fmaxf(m_new, m[u]);
+    const float alpha = fast_exp2(mx - m_new);
+    mx = m_new;
+    ls *= alpha;
+    acc *= alpha;
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const float w = p + u < n ? fast_exp2(m[u] - mx) : 0.f;
+      ls += w * l[u];
+      acc += w * v[u];
+    }
+  };
+  int p = 0;
+  for (; p + 4 < n; p += 8) batch(p, std::integral_constant<int, 8>{});
+  if (p < n) batch(p, std::integral_constant<int, 4>{});
   if (!ok) return;
   const float inv = 1.f / ls;
   u32x2_t o2;
   o2.x = pack_bf16x2(acc[0] * inv, acc[1] * inv);
   o2.y = pack_bf16x2(acc[2] * inv, acc[3] * inv);
   *reinterpret_cast<u32x2_t *>(a.out + (size_t)a.row_start[seq] * (hq * DH) + head * DH + li * 4) = o2;
-}
-
-// acc *= alpha for an MFMA accumulator that lives in the accumulation registers.  Written out
-// by hand so that the only vector-ALU use of the output accumulators inside the block loop
-// is this rarely taken path: left to the compiler, the register copies it needs are hoisted
-// to the top of every iteration.  The trailing wait states separate the last register write
-// from a following MFMA that reads it.
-__device__ __forceinline__ void scale_acc(f32x16_t &acc, float alpha) {
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    float e = acc[r], t;
-    asm(  // not volatile: the compiler must see that it touches no memory
-        "v_accvgpr_read_b32 %1, %0\n\t"
-        "v_mul_f32 %1, %1, %2\n\t"
-        "v_accvgpr_write_b32 %0, %1\n\t"
-        "s_nop 3"
-        : "+a"(e), "=&v"(t)
-        : "v"(alpha));
-    acc[r] = e;
-  }
 }
 
 // ------------------------------------------------------------------------------
@@ -413,7 +407,7 @@ __global__ __launch_bounds__(256) void prefill_attn_kernel(const PrefillArgs a, 
 template <int DH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void blended_attn_kernel(
     const DecodeArgs d, int n_wide_units, int n_narrow_units, const PrefillArgs pf, int n_pf_wgs, int period) {
-  __shared__ __align__(16) uint16_t q_sh[DECODE_Q_LDS(DH)];
+  __shared__ __align__(16) uint16_t q_sh[DECODE_Q_LDS(DH, 4)];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int n_dec = ((n_wide_units + 3) >> 2) + ((n_narrow_units + 3) >> 2);
@@ -433,7 +427,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   if (prefill)
     prefill_workgroup<DH>(pf, 4, idx, wave, lane);
   else
-    decode_workgroup<DH, false>(d, n_wide_units, n_narrow_units, idx, wave, lane, q_sh);
+    decode_workgroup<DH, 4, false, true>(d, n_wide_units, n_narrow_units, idx, wave, lane, q_sh);
 }
 
 // What the GEMM launches of a step have left of its queue of 16-row units, on the whole chip:
@@ -461,10 +455,13 @@ hipError_t launch_decode_queue(const DecodeQueue &q, int n_workgroups, hipStream
 
 hipError_t launch_decode_attn(const DecodeArgs &a, int n_wide, int n_narrow, hipStream_t stream) {
   const int n_wide_units = n_wide * a.s.n_kv_heads, n_narrow_units = n_narrow * a.s.n_kv_heads;
-  const int wgs = (n_wide_units + 3) / 4 + (n_narrow_units + 3) / 4;  // a workgroup holds units of one kind
-  if (wgs <= 0) return hipSuccess;
-  const dim3 grid(wgs), block(256);
-  if (a.s.head_dim == 128)
+  const dim3 grid(n_wide_units + n_narrow_units), block(64);
+  if (grid.x == 0) return hipSuccess;
+  if (n_wide <= 0 && a.s.head_dim == 128)
+    hipLaunchKernelGGL((decode_narrow_kernel<128>), grid, block, 0, stream, a);
+  else if (n_wide <= 0 && a.s.head_dim == 64)
+    hipLaunchKernelGGL((decode_narrow_kernel<64>), grid, block, 0, stream, a);
+  else if (a.s.head_dim == 128)
     hipLaunchKernelGGL((decode_attn_kernel<128>), grid, block, 0, stream, a, n_wide_units, n_narrow_units);
   else if (a.s.head_dim == 64)
     hipLaunchKernelGGL((decode_attn_kernel<64>), grid, block, 0, stream, a, n_wide_units, n_narrow_units);

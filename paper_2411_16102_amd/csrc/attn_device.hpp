@@ -40,6 +40,35 @@ __device__ __forceinline__ u32x2_t mask_tokens(u32x2_t v, int t0, int limit) {
   return v;
 }
 
+// the same for eight tokens t0 .. t0+7
+__device__ __forceinline__ u32x4_t mask_tokens8(u32x4_t v, int t0, int limit) {
+  const u32x2_t lo = mask_tokens(u32x2_t{v.x, v.y}, t0, limit), hi = mask_tokens(u32x2_t{v.z, v.w}, t0 + 4, limit);
+  return u32x4_t{lo.x, lo.y, hi.x, hi.y};
+}
+
+// acc *= alpha for MFMA accumulators that live in the accumulation registers (kernels that run one
+// wavefront per SIMD).  Written out by hand so that the only vector-ALU use of the output
+// accumulators inside the token loop is this rarely taken path: left to the compiler, the register
+// copies it needs are hoisted to the top of every iteration (three copies of every accumulator per
+// step of a 16-row unit).  The trailing wait states separate the last register write from a
+// following MFMA that reads it.
+template <class V>
+__device__ __forceinline__ void scale_acc(V &acc, float alpha) {
+  constexpr int N = sizeof(V) / 4;
+#pragma unroll
+  for (int r = 0; r < N; ++r) {
+    float e = acc[r], t;
+    asm(  // not volatile: the compiler must see that it touches no memory
+        "v_accvgpr_read_b32 %1, %0\n\t"
+        "v_mul_f32 %1, %1, %2\n\t"
+        "v_accvgpr_write_b32 %0, %1\n\t"
+        "s_nop 3"
+        : "+a"(e), "=&v"(t)
+        : "v"(alpha));
+    acc[r] = e;
+  }
+}
+
 // ------------------------------------------------------------------------------
 // decode attention: one wavefront per (item, KV head), up to 16 * NQB query rows
 // ------------------------------------------------------------------------------
@@ -49,7 +78,16 @@ __device__ __forceinline__ u32x2_t mask_tokens(u32x2_t v, int t0, int limit) {
 // the accumulators are rescaled a few times per chunk instead of once per page.
 constexpr float TAU = 8.0f;
 
-template <int DH, int NQB, bool NT = false>
+//
+// A pair of pages (32 tokens) is one contraction step of the PV product.  A contraction allows any
+// order of its tokens as long as both operands agree on it, and the rows of a key tile may enter the
+// score MFMA in any order: score row 4 g + r of the pair's first (second) MFMA is the key of token
+// 8 g + r (8 g + 4 + r) of the pair, so that a lane's eight probabilities belong to eight adjacent
+// tokens of one page and the lane's value operand is ONE 16-byte load of a V^T row instead of two
+// 8-byte ones from two pages: 16 loads per pair and lane instead of 24.
+//
+// ACC_A: the accumulators live in the accumulation registers (see scale_acc).
+template <int DH, int NQB, bool NT = false, bool ACC_A = false>
 __device__ __forceinline__ void decode_unit(const DecodeArgs &a, int item, int kvh, int wave, int lane, uint16_t *q_sh) {
   constexpr int KC = DH / 32;  // 32-wide chunks of the head dimension (QK^T contraction)
   constexpr int DB = DH / 16;  // 16-row blocks of the head dimension (PV output rows)
@@ -121,26 +159,26 @@ __device__ __forceinline__ void decode_unit(const DecodeArgs &a, int item, int k
   // loaded once and used by all NQB blocks of 16 query rows.
   struct Frags {
     u32x4_t k[2][KC];
-    u32x2_t v0[DB], v1[DB];
+    u32x4_t v[DB];
   };
   auto page_of = [&](int i) -> size_t {
     return (size_t)__builtin_amdgcn_readlane(my_page, i < n_pg ? i : n_pg - 1);
   };
+  // key row of this lane in the first score MFMA: page jq / 8 of the pair, slot 8 ((jq / 4) % 2) + jq % 4
+  // (four slots on in the second MFMA); value rows: page g4 / 2 of the pair, slots 8 (g4 % 2) .. +7
+  const uint32_t k_off = (uint32_t)((8 * ((jq >> 2) & 1) + (jq & 3)) * DH + 8 * g4);
+  const uint32_t v_off = (uint32_t)(jq * 16 + 8 * (g4 & 1));
   auto load_pages = [&](size_t p0, size_t p1, Frags &f) {
-    const uint16_t *k0 = a.kv_pool + ((p0 * 2 + 0) * hkv + kvh) * tile + jq * DH + 8 * g4;
-    const uint16_t *k1 = a.kv_pool + ((p1 * 2 + 0) * hkv + kvh) * tile + jq * DH + 8 * g4;
-    const uint16_t *v0 = a.kv_pool + ((p0 * 2 + 1) * hkv + kvh) * tile + jq * 16 + 4 * g4;
-    const uint16_t *v1 = a.kv_pool + ((p1 * 2 + 1) * hkv + kvh) * tile + jq * 16 + 4 * g4;
+    const uint16_t *b0 = a.kv_pool + (p0 * 2 * hkv + kvh) * tile, *b1 = a.kv_pool + (p1 * 2 * hkv + kvh) * tile;
+    const uint16_t *kp = (jq < 8 ? b0 : b1) + k_off;
+    const uint16_t *vp = (g4 < 2 ? b0 : b1) + (size_t)hkv * tile + v_off;
 #pragma unroll
     for (int c = 0; c < KC; ++c) {
-      f.k[0][c] = ld16_kv<NT>(k0 + 32 * c);
-      f.k[1][c] = ld16_kv<NT>(k1 + 32 * c);
+      f.k[0][c] = ld16_kv<NT>(kp + 32 * c);
+      f.k[1][c] = ld16_kv<NT>(kp + 4 * DH + 32 * c);
     }
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      f.v0[db] = ld8_kv<NT>(v0 + db * 256);
-      f.v1[db] = ld8_kv<NT>(v1 + db * 256);
-    }
+    for (int db = 0; db < DB; ++db) f.v[db] = ld16_kv<NT>(vp + db * 256);
   };
   auto load = [&](int pr, Frags &f) {
     const int i0 = 2 * (pr < n_pairs ? pr : n_pairs - 1);
@@ -152,10 +190,7 @@ __device__ __forceinline__ void decode_unit(const DecodeArgs &a, int item, int k
     if constexpr (Q_LDS) asm volatile("" : "+v"(q_off));  // keep the query reads inside the loop
     if (ragged) {  // never let stale slots (possibly NaN bit patterns) meet a zero probability
 #pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        f.v0[db] = mask_tokens(f.v0[db], tb + 4 * g4, n_tok);
-        f.v1[db] = mask_tokens(f.v1[db], tb + 16 + 4 * g4, n_tok);
-      }
+      for (int db = 0; db < DB; ++db) f.v[db] = mask_tokens8(f.v[db], tb + 8 * g4, n_tok);
     }
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) {
@@ -166,34 +201,38 @@ __device__ __forceinline__ void decode_unit(const DecodeArgs &a, int item, int k
         s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(f.k[0][c]), qv, s0, 0, 0, 0);
         s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(f.k[1][c]), qv, s1, 0, 0, 0);
       }
-      float sv[8];
+      float sv[8];  // tokens tb + 8 g4 + 0 .. 7
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        sv[r] = s0[r] * sc;
-        sv[4 + r] = s1[r] * sc;
+        sv[r] = s0[r];
+        sv[4 + r] = s1[r];
       }
       if (ragged) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          if (tb + 4 * g4 + r >= n_tok) sv[r] = NEG_BIG;
-          if (tb + 16 + 4 * g4 + r >= n_tok) sv[4 + r] = NEG_BIG;
-        }
+        for (int r = 0; r < 8; ++r)
+          if (tb + 8 * g4 + r >= n_tok) sv[r] = NEG_BIG;
       }
-      float mx = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
-      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      if (__builtin_amdgcn_ballot_w64(mx > m[qb] + TAU) != 0) {  // wave-uniform: somebody's reference must move
+      // the scale is positive: the maximum commutes with it.  Whether any reference must move needs no
+      // exchange between the lanes of a row: some lane of the row sees its own maximum exceed it.
+      float mx = sc * fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
+      if (__builtin_amdgcn_ballot_w64(mx > m[qb] + TAU) != 0) {  // wave-uniform
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
         const float m_new = fmaxf(m[qb], mx);
         const float alpha = fast_exp2(m[qb] - m_new);
         m[qb] = m_new;
         l[qb] *= alpha;
 #pragma unroll
-        for (int db = 0; db < DB; ++db) o[qb][db] *= alpha;
+        for (int db = 0; db < DB; ++db) {
+          if constexpr (ACC_A) scale_acc(o[qb][db], alpha);
+          else o[qb][db] *= alpha;
+        }
       }
+      const float neg_m = -m[qb];
       float ps = 0.f;
 #pragma unroll
       for (int r = 0; r < 8; ++r) {
-        sv[r] = fast_exp2(sv[r] - m[qb]);
+        sv[r] = fast_exp2(__builtin_fmaf(sv[r], sc, neg_m));
         ps += sv[r];
       }
       l[qb] += ps;
@@ -204,14 +243,8 @@ __device__ __forceinline__ void decode_unit(const DecodeArgs &a, int item, int k
       pw.w = pack_bf16x2(sv[6], sv[7]);
       const bf16x8_t pf = as_bf16x8(pw);
 #pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        u32x4_t vw;
-        vw.x = f.v0[db].x;
-        vw.y = f.v0[db].y;
-        vw.z = f.v1[db].x;
-        vw.w = f.v1[db].y;
-        o[qb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vw), pf, o[qb][db], 0, 0, 0);
-      }
+      for (int db = 0; db < DB; ++db)
+        o[qb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(f.v[db]), pf, o[qb][db], 0, 0, 0);
     }
   };
 

@@ -208,6 +208,27 @@ def test_attention_wide_items_alternate_with_narrow_ones(lib, root_pages, n_memb
     check_attention(shape, batch, q, tens, out)
 
 
+@pytest.mark.parametrize("shape", [W.LayerShape(256, 4, 2, 64, 256), W.LayerShape(512, 8, 2, 128, 256)])
+@pytest.mark.parametrize("lens,root_pages", [([1], 0), ([127, 128, 129], 0), ([4001, 16], 0), ([33] * 70, 0),
+                                             ([40] * 9, 9), ([17, 300] * 5, 33)])
+def test_attention_of_few_sequences(lib, shape, lens, root_pages):
+    # the library's own division into chunks where the step cannot fill the chip (8 pages at the least:
+    # contexts that end before, at and behind a chunk), decode rows alone, with and without a prefix
+    # node; the two entry points divide and compute alike
+    import torch
+    rng = np.random.default_rng(len(lens) * 100 + root_pages)
+    nodes = [(-1, root_pages)] if root_pages else []
+    batch = W.assemble_batch(16, [(1, 16 * root_pages + n, 0 if nodes else -1) for n in lens], 0, nodes, rng)
+    tens = W.make_tensors(shape, batch, 7)
+    q = W.round_to_bf16(rng.standard_normal((batch.n_rows, shape.n_q_heads * shape.head_dim), dtype=np.float32))
+    layer = lib.Layer(shape, device=0)
+    pool = layer.pack_pool(tens.k_pool, tens.v_pool)
+    tq = torch.from_numpy(q).cuda().to(torch.bfloat16)
+    out = layer.attention(batch, tq, pool, batch.n_pages)
+    check_attention(shape, batch, q, tens, to_np(out))
+    assert torch.equal(out, layer.attention_noalloc(batch, tq, pool, batch.n_pages, torch.zeros_like(tq)))
+
+
 def test_attention_ignores_stale_slots(lib):
     # slots past kv_len in the last page hold NaN bit patterns: they must never reach the output
     import torch
