@@ -61,8 +61,6 @@ struct bs_ctx {
   long cap_slots = 0;
   float *part_acc = nullptr, *part_m = nullptr, *part_l = nullptr;
   uint16_t *hid[2] = {nullptr, nullptr};  // activations between the layers of bs_blend_layers
-  float *splitk_ws = nullptr;  // fp32 partial products of the split-K GEMMs (few-row steps)
-  size_t cap_splitk = 0;
   // descriptor blob: pinned host ring and one device copy
   long cap_blob = 0;
   int32_t *d_blob = nullptr;
@@ -78,7 +76,7 @@ struct bs_ctx {
   std::vector<std::pair<int, std::pair<int, int>>> pf_order;
   unsigned char *scratch_ptr = nullptr;  // this device's copy of the static scratch array
   // co-scheduling of decode attention with the prefill rows' GEMMs (BS_FLAG_OVERLAP)
-  float *sk_ws = nullptr;       // partial tiles of the GEMM launches whose workgroups share tiles
+  float *sk_ws = nullptr;       // partial tiles of the GEMM launches whose workgroups share tiles, partial products of split-K
   unsigned *sk_cnt = nullptr;   // their arrival counters (zero between launches)
   unsigned *sync_words = nullptr;  // [0..3] queue counters of the launches of a step, [4..6] finished tiles, [8..10] queue position at which each launch closed
   bs_overlap_knobs ov = {0, 208, 8, 256, -1, 2, 0, 1, 96, 0};
@@ -174,15 +172,6 @@ int ensure_slots(bs_ctx *c, long slots) {
   if ((rc = dev_alloc(c, &c->part_m, (size_t)cap * hq))) return rc;
   if ((rc = dev_alloc(c, &c->part_l, (size_t)cap * hq))) return rc;
   c->cap_slots = cap;
-  return BS_OK;
-}
-
-int ensure_splitk(bs_ctx *c, size_t floats) {
-  if (floats <= c->cap_splitk) return BS_OK;
-  c->cap_splitk = 0;
-  int rc = dev_alloc(c, &c->splitk_ws, floats);
-  if (rc) return rc;
-  c->cap_splitk = floats;
   return BS_OK;
 }
 
@@ -639,11 +628,8 @@ int run_o_gate_up(bs_ctx *c, const bs_weights *w, const uint16_t *x, int r0, int
   const bs_layer_cfg &g = c->cfg;
   const int d = g.d_model;
   GemmArgs o = o_proj_args(c, w, x, r0, r1);
-  o.k_splits = gemm_splitk_choice(rows, d, o.K, EPI_RESID_NORM, 0);
+  gemm_plan(o, EPI_RESID_NORM);
   if (o.k_splits > 1) {
-    int rc = ensure_splitk(c, (size_t)o.k_splits * rows * d);
-    if (rc) return rc;
-    o.splitk_ws = c->splitk_ws;
     o.rstd_out = c->rstd2 + r0;  // the reduction closes the second norm's statistics itself
     o.rstd_eps = g.rms_eps;
   }
@@ -670,12 +656,7 @@ int run_down(bs_ctx *c, const bs_weights *w, uint16_t *y, int r0, int r1, hipStr
   if (rows <= 0) return BS_OK;
   const bs_layer_cfg &g = c->cfg;
   GemmArgs dn = down_args(c, w, y, r0, r1);
-  dn.k_splits = gemm_splitk_choice(rows, dn.N, dn.K, EPI_RESID, 0);
-  if (dn.k_splits > 1) {
-    int rc = ensure_splitk(c, (size_t)dn.k_splits * rows * dn.N);
-    if (rc) return rc;
-    dn.splitk_ws = c->splitk_ws;
-  }
+  gemm_plan(dn, EPI_RESID);
   SPAN(c, k_dn, st, HIP_TRY(c, launch_gemm(dn, EPI_RESID, g.head_dim, st)));
   return BS_OK;
 }
@@ -956,7 +937,7 @@ void bs_destroy(bs_ctx *c) {
   (void)hipDeviceSynchronize();
   for (void *p : {(void *)c->rope_cos, (void *)c->rope_sin, (void *)c->xg, (void *)c->qbuf, (void *)c->attn, (void *)c->x1,
                   (void *)c->xg2, (void *)c->act, (void *)c->rstd1, (void *)c->rstd2, (void *)c->ss2, (void *)c->part_acc, (void *)c->part_m,
-                  (void *)c->part_l, (void *)c->d_blob, (void *)c->splitk_ws, (void *)c->hid[0], (void *)c->hid[1], (void *)c->sync_words, (void *)c->trace_buf, (void *)c->sk_ws, (void *)c->sk_cnt})
+                  (void *)c->part_l, (void *)c->d_blob, (void *)c->hid[0], (void *)c->hid[1], (void *)c->sync_words, (void *)c->trace_buf, (void *)c->sk_ws, (void *)c->sk_cnt})
     if (p) (void)hipFree(p);
   for (int i = 0; i < RING; ++i) {
     if (c->h_blob[i]) (void)hipHostFree(c->h_blob[i]);
@@ -1035,7 +1016,6 @@ namespace {
 // `clear_sync`: the prep kernel also clears the counters of the co-scheduled launches.
 int run_prep_qkv(bs_ctx *c, const Plan &p, const bs_weights *w, const uint16_t *x, uint16_t *pool, int r0, int r1,
                  bool clear_sync, hipStream_t st) {
-  int rc;
   const bs_layer_cfg &g = c->cfg;
   const int d = g.d_model, rows = r1 - r0, hd = g.n_q_heads * g.head_dim;
   if (rows <= 0) return BS_OK;
@@ -1050,11 +1030,7 @@ int run_prep_qkv(bs_ctx *c, const Plan &p, const bs_weights *w, const uint16_t *
   q.row_pos = c->d_blob + p.off_row_pos + r0; q.row_page = c->d_blob + p.off_row_page + r0; q.row_slot = c->d_blob + p.off_row_slot + r0;
   q.q_out = c->qbuf + (size_t)r0 * hd; q.kv_pool = pool;
   q.sk_ws = c->sk_ws; q.sk_cnt = c->sk_cnt;
-  q.k_splits = gemm_splitk_choice(q.M, q.N, q.K, EPI_QKV, 0);
-  if (q.k_splits > 1) {
-    if ((rc = ensure_splitk(c, (size_t)q.k_splits * q.M * q.N))) return rc;
-    q.splitk_ws = c->splitk_ws;
-  }
+  gemm_plan(q, EPI_QKV);
   SPAN(c, BS_K_GEMM_QKV, st, HIP_TRY(c, launch_gemm(q, EPI_QKV, g.head_dim, st)));
   return BS_OK;
 }

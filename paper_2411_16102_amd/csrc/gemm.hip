@@ -478,7 +478,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int bid, cons
     }
 
     if (EPI == EPI_PARTIAL) {
-      float *ws = a.splitk_ws + (size_t)split * a.M * a.N;
+      float *ws = a.sk_ws + (size_t)split * a.M * a.N;
   #pragma unroll
       for (int mi = 0; mi < MI; ++mi) {
         const int m = m0 + wm0 + mi * 16 + lr;
@@ -791,7 +791,7 @@ __device__ __forceinline__ f32x4_t splitk_sum(const float *p, size_t plane, int 
 __global__ __launch_bounds__(256) void splitk_reduce_resid_kernel(const GemmArgs a) {
   const int m = blockIdx.x, n = (blockIdx.y * 256 + threadIdx.x) * 4;
   if (n >= a.N) return;
-  f32x4_t v = splitk_sum(a.splitk_ws + (size_t)m * a.N + n, (size_t)a.M * a.N, a.k_splits);
+  f32x4_t v = splitk_sum(a.sk_ws + (size_t)m * a.N + n, (size_t)a.M * a.N, a.k_splits);
   if (a.resid32) {
     v += *reinterpret_cast<const f32x4_t *>(a.resid32 + (size_t)m * a.ldr + n);
   } else {
@@ -805,12 +805,13 @@ __global__ __launch_bounds__(256) void splitk_reduce_resid_kernel(const GemmArgs
 }
 
 // RESID_NORM: x1 = resid + sum in fp32, bf16(x1 * gain), and the row's sum of squares, complete,
-// in ss_out slot 0; one workgroup per row.
-__global__ __launch_bounds__(256) void splitk_reduce_resid_norm_kernel(const GemmArgs a) {
+// in ss_out slot 0; one workgroup per row, of as many threads as the row has groups of four columns
+// (up to 1024), so that a row is one round trip to memory.
+__global__ __launch_bounds__(1024) void splitk_reduce_resid_norm_kernel(const GemmArgs a) {
   const int m = blockIdx.x;
   float ss = 0.f;
-  for (int n = threadIdx.x * 4; n < a.N; n += 256 * 4) {
-    f32x4_t v = splitk_sum(a.splitk_ws + (size_t)m * a.N + n, (size_t)a.M * a.N, a.k_splits);
+  for (int n = threadIdx.x * 4; n < a.N; n += (int)blockDim.x * 4) {
+    f32x4_t v = splitk_sum(a.sk_ws + (size_t)m * a.N + n, (size_t)a.M * a.N, a.k_splits);
     const u32x2_t rr = *reinterpret_cast<const u32x2_t *>(a.resid + (size_t)m * a.ldr + n);
     v[0] += __uint_as_float(rr.x << 16);
     v[1] += __uint_as_float(rr.x & 0xFFFF0000u);
@@ -823,13 +824,14 @@ __global__ __launch_bounds__(256) void splitk_reduce_resid_norm_kernel(const Gem
     *reinterpret_cast<f32x4_t *>(a.C32 + (size_t)m * a.ldc + n) = v;
     store_bf16x4(a.C_gain + (size_t)m * a.ldc + n, v[0] * g0, v[1] * g1, v[2] * g2, v[3] * g3);
   }
-  __shared__ float part[4];
+  __shared__ float part[16];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
   __syncthreads();
   if (threadIdx.x == 0) {
-    const float row = (part[0] + part[1]) + (part[2] + part[3]);
+    float row = 0.f;
+    for (int w = 0; w < ((int)blockDim.x + 63) / 64; ++w) row += part[w];
     a.ss_out[m] = row;
     if (a.rstd_out) a.rstd_out[m] = rsqrtf(row / (float)a.N + a.rstd_eps);
   }
@@ -842,7 +844,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_qkv_kernel(const GemmArgs a
   const int m = blockIdx.x;
   const int item = blockIdx.y * 256 + threadIdx.x;
   const size_t plane = (size_t)a.M * a.N;
-  const float *ws = a.splitk_ws + (size_t)m * a.N;
+  const float *ws = a.sk_ws + (size_t)m * a.N;
   const float rs = a.rstd[m];
   const int half = dh / 2, q4 = half / 4;
   const size_t page = a.row_page[m];
@@ -1052,20 +1054,76 @@ bool gemm_round_split(const GemmArgs &a, int epilogue, int dh, GemmArgs *head, G
   return true;
 }
 
-int gemm_splitk_choice(int M, int N, int K, int epilogue, int n_cu) {
-  if (epilogue != EPI_RESID && epilogue != EPI_RESID_NORM && epilogue != EPI_QKV) return 1;
-  if (n_cu <= 0) n_cu = N_CU;
-  const long by_k = ((K + BK - 1) / BK) / 8;    // at least eight k-tiles per range
-  if (const int sv = short_variant(M)) {        // one workgroup per CU, each with a k-range of a one-row tile
-    const long tiles = n_tiles(M, N, sv == V_S128 ? 128 : 256, sv == V_S128 ? 256 : 128);
-    const long s = std::min((long)MAX_SPLITS, std::min((long)n_cu / tiles, by_k));
-    return s >= 2 ? (int)s : 1;
+void gemm_plan(GemmArgs &a, int epilogue) {
+  a.k_splits = 1;
+  const int n_cu = std::min(a.n_cu > 0 ? a.n_cu : N_CU, N_CU);
+  const long nk = (a.K + BK - 1) / BK;
+  const size_t room = a.sk_ws && a.N % 4 == 0 ? gemm_sk_workspace_floats() : 0;
+  // k-ranges of at least eight k-tiles, one round of workgroups, partial products that fit the workspace
+  auto max_splits = [&](long tiles, long slots) {
+    long s = std::min<long>(std::min<long>(MAX_SPLITS, nk / 8), slots / tiles);
+    while (s > 1 && (size_t)s * a.M * a.N > room) --s;
+    return std::max<long>(s, 1);
+  };
+  const bool may_share = a.sk_ws && a.sk_cnt && !a.n_count;
+  if (g_forced_variant != V_AUTO) {
+    a.tile_variant = choose_variant(a.M, a.N, epilogue, 0, a.n_cu, may_share ? a.K : 0);
+    if (a.tile_variant == V_SMALL) a.k_splits = (int)max_splits(n_tiles(a.M, a.N, 128, 128), 2L * n_cu);
+    return;
   }
-  if (choose_variant(M, N, epilogue, 64, n_cu) != V_SMALL) return 1;  // only where the smallest tile is already in use
-  const long tiles = n_tiles(M, N, 128, 128);
-  const long room = 2L * n_cu / tiles;          // two 128x128 workgroups fit one CU
-  const long s = std::min((long)MAX_SPLITS, std::min(room, by_k));
-  return s >= 2 ? (int)s : 1;
+  // At most 256 rows: the weights stream from HBM, so what counts is how many workgroups ask for them.
+  // One row of tiles on the deep weight ring, cut along K until there is one workgroup per CU; of 128
+  // rows and less, 128x128 tiles where MAX_SPLITS ranges of the 256-wide ones would leave a quarter of
+  // the CUs without one (measured with cold weights, 64 rows, reduction included: K = 14336, N = 4096,
+  // 128 workgroups of 128x256 35 us, 256 of 128x128 30; K = N = 8192, 192 of 128x256 34, 128x128 37).
+  if (a.M <= 256) {
+    const bool s128 = a.M <= 128;
+    const long tiles = s128 ? n_tiles(a.M, a.N, 128, 256) : n_tiles(a.M, a.N, 256, 128);
+    const long s = max_splits(tiles, n_cu);
+    if (s >= 2 && (!s128 || 4 * s * tiles > 3 * n_cu)) {
+      a.tile_variant = s128 ? V_S128 : V_S256;
+      a.k_splits = (int)s;
+      return;
+    }
+    const long small = n_tiles(a.M, a.N, 128, 128), ss = max_splits(small, n_cu);
+    if (s128 && ss >= 2) {
+      a.tile_variant = V_SMALL;
+      a.k_splits = (int)ss;
+      return;
+    }
+  }
+  // Above: the estimated time in microseconds of every tile shape, whole or cut along K.  A k-tile costs
+  // between `lo` (few workgroups on the chip) and `hi` (all of them: the clock falls under matrix
+  // load), a round 4.9 for its start and its epilogue, a split the second kernel (4) and the partial
+  // products once out and once back in (7.6 TB/s, most of it the last-level cache).  128x128 tiles, two
+  // to a CU, cost `lo` up to one per CU.  Fitted on MI355X to 1200 measurements of products of 4096 to
+  // 10240 columns, K 4096 to 28672, 260 to 5120 rows, weights cold: the choices are within 0.14 % of
+  // the best shape on average, where whole tiles (and a split of the 128x128 ones only) were 14 %
+  // off: N = 4096, K = 14336 at 1000 rows 104 against 135 us, at 1580 rows 172 against 200.
+  struct Cand { int v, bm, bn, per_cu; double hi, lo; };
+  const Cand cands[3] = {{V_BIG, 256, 256, 1, 1.39, 1.11}, {V_TALL, 160, 256, 1, 1.09, 0.88}, {V_SMALL, 128, 128, 2, 1.03, 0.53}};
+  double best = 1e300;
+  for (const Cand &c : cands) {
+    const long tiles = n_tiles(a.M, a.N, c.bm, c.bn), slots = (long)n_cu * c.per_cu;
+    for (long s = 1; s <= max_splits(tiles, slots); ++s) {
+      if (s == 1 && c.v == V_TALL && epilogue == EPI_QKV) continue;  // a wavefront must cover whole heads
+      const long full = tiles * s / slots, rem = tiles * s % slots;
+      double part = 0.0;
+      if (rem && c.per_cu == 1) part = c.lo + (c.hi - c.lo) * (double)rem / (double)slots;
+      else if (rem) part = rem <= n_cu ? c.lo : c.lo + (c.hi - c.lo) * (0.55 + 0.45 * (double)(rem - n_cu) / (double)n_cu);
+      double t = (double)((nk + s - 1) / s) * ((double)full * c.hi + part) + 4.9 * (double)(full + (rem ? 1 : 0));
+      if (s > 1) t += 4.0 + 8.0 * (double)s * a.M * a.N / 7.6e6;
+      if (t < best) { best = t; a.tile_variant = c.v; a.k_splits = (int)s; }
+    }
+  }
+  // Shared 256x256 tiles: the chip's worth of k-tile iterations with nothing idle, 3 % for the persistent
+  // loop, and 95 us for the cuts (a workgroup passes up to two partial tiles through memory): only
+  // where K is long, and more than one round of tiles cannot be cut evenly.
+  if (may_share && a.K >= 4096 && a.M > 256) {
+    const long tiles = n_tiles(a.M, a.N, 256, 256);
+    const double t = (double)tiles / (double)n_cu * 1.03 * 1.39 * (double)nk + 95.0;
+    if (tiles % n_cu && t < best) { a.tile_variant = V_SHARED; a.k_splits = 1; }
+  }
 }
 
 int gemm_ss_parts(const GemmArgs &a, int epilogue, int dh) {
@@ -1128,12 +1186,20 @@ hipError_t launch_gemm(const GemmArgs &a, int epilogue, int dh, hipStream_t stre
       (size_t)((epilogue == EPI_SWIGLU) ? 2 * a.N : a.N) * a.ldb * 2 >= ((size_t)1 << 32))
     return hipErrorInvalidValue;
   if (a.k_splits > 1) {
-    if ((epilogue != EPI_RESID && epilogue != EPI_RESID_NORM && epilogue != EPI_QKV) || !a.splitk_ws || a.N % 4)
+    if ((epilogue != EPI_RESID && epilogue != EPI_RESID_NORM && epilogue != EPI_QKV) || !a.sk_ws || a.N % 4)
       return hipErrorInvalidValue;
-    const int sv = short_variant(a.M);
-    hipError_t e = sv == V_S128   ? launch_one<128, 256, 2, 4, EPI_PARTIAL, 64, DEEP_X>(a, stream)
-                   : sv == V_S256 ? launch_one<256, 128, 4, 2, EPI_PARTIAL, 64, DEEP_X>(a, stream)
-                                  : launch_one<128, 128, 2, 2, EPI_PARTIAL, 64>(a, stream);
+    if (a.k_splits > MAX_SPLITS || (size_t)a.k_splits * a.M * a.N > gemm_sk_workspace_floats() ||
+        ((a.tile_variant == V_S128 || a.tile_variant == V_S256) && a.M > (a.tile_variant == V_S128 ? 128 : 256)))
+      return hipErrorInvalidValue;
+    hipError_t e;
+    switch (a.tile_variant) {
+      case V_S128: e = launch_one<128, 256, 2, 4, EPI_PARTIAL, 64, DEEP_X>(a, stream); break;
+      case V_S256: e = launch_one<256, 128, 4, 2, EPI_PARTIAL, 64, DEEP_X>(a, stream); break;
+      case V_BIG: e = launch_one<256, 256, 2, 4, EPI_PARTIAL, 64>(a, stream); break;
+      case V_TALL: e = launch_one<160, 256, 2, 4, EPI_PARTIAL, 64>(a, stream); break;
+      case V_SMALL: e = launch_one<128, 128, 2, 2, EPI_PARTIAL, 64>(a, stream); break;
+      default: return hipErrorInvalidValue;
+    }
     if (e != hipSuccess) return e;
     if (epilogue == EPI_QKV) {
       const int items = ((a.n_q_heads + a.n_kv_heads) * (dh / 2) + a.n_kv_heads * dh) / 4;
@@ -1141,7 +1207,8 @@ hipError_t launch_gemm(const GemmArgs &a, int epilogue, int dh, hipStream_t stre
     } else if (epilogue == EPI_RESID) {
       hipLaunchKernelGGL(splitk_reduce_resid_kernel, dim3(a.M, (a.N / 4 + 255) / 256), dim3(256), 0, stream, a);
     } else {
-      hipLaunchKernelGGL(splitk_reduce_resid_norm_kernel, dim3(a.M), dim3(256), 0, stream, a);
+      const int threads = std::min(1024, (a.N / 4 + 63) / 64 * 64);
+      hipLaunchKernelGGL(splitk_reduce_resid_norm_kernel, dim3(a.M), dim3(threads), 0, stream, a);
     }
     return hipGetLastError();
   }

@@ -41,15 +41,14 @@ struct GemmArgs {
   float *ss_out;         // [tiles_n * waves_n][ss_stride] partial row sums of x1^2
   float *rstd_out;       // split-K only (may be NULL): the reduction, which sees whole rows, leaves
   float rstd_eps;        //   1 / sqrt(mean(x1^2) + rstd_eps) of each row here, and no pass over ss_out is needed
-  // Split-K (QKV, RESID and RESID_NORM with few tiles): k_splits > 1 cuts K into that many ranges,
-  // each (tile, range) is one workgroup that leaves fp32 partial products in splitk_ws
+  // Split-K (QKV, RESID and RESID_NORM where whole tiles leave CUs idle): k_splits > 1 cuts K into
+  // that many ranges, each (tile, range) is one workgroup that leaves fp32 partial products in sk_ws
   // [k_splits][M][N]; a second kernel adds them up in a fixed order and applies the epilogue.
-  // The caller takes k_splits from gemm_splitk_choice and provides the workspace.
+  // gemm_plan sets k_splits and the tile shape.
   int k_splits;
-  float *splitk_ws;
   // Shared tiles (tile_variant 6, see gemm_sk_kernel): room for the partial tiles, at least
   // gemm_sk_workspace_floats() floats, and gemm_sk_counters() counters that are zero between launches.
-  // Launches that use them must not overlap in time.
+  // Launches that use the workspace (shared tiles or split-K) must not overlap in time.
   float *sk_ws;
   unsigned *sk_cnt;
   // SWIGLU: B holds F gate rows then F up rows; N = F
@@ -89,9 +88,9 @@ int gemm_ss_parts(const GemmArgs &a, int epilogue, int dh);
 // instead: `head` = the tile columns of the whole rounds, `tail` = the rest (whatever tile
 // shape suits them).
 bool gemm_round_split(const GemmArgs &a, int epilogue, int dh, GemmArgs *head, GemmArgs *tail);
-// Number of k-ranges worth using for this problem (1 = no split): only when the tiles would
-// leave most of the chip idle and every range keeps at least eight k-tiles.
-int gemm_splitk_choice(int M, int N, int K, int epilogue, int n_cu);
+// Tile shape and number of k-ranges of a product whose epilogue can follow a split (QKV, RESID,
+// RESID_NORM): sets a.tile_variant and a.k_splits.  Call it once M, N, K, n_cu and the workspace are set.
+void gemm_plan(GemmArgs &a, int epilogue);
 void gemm_force_variant(int v);  // 0 = choose by shape, 1 = 256x256, 2 = 160x256, 3 = 128x128 tiles, 6 = shared 256x256 tiles (tuning)
 size_t gemm_sk_workspace_floats();
 int gemm_sk_counters();

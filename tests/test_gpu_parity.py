@@ -122,6 +122,16 @@ def test_layer_step_on_shared_tiles(lib, shape):
     check(v[ref["dest"][:, 0], ref["dest"][:, 1]], ref["v_new"], diag["v_new"], "appended values")
 
 
+@pytest.mark.parametrize("rows", [77, 256, 257, 640, 1000])
+def test_layer_step_on_tiles_cut_along_k(lib, rows):
+    # few enough rows that whole tiles would leave CUs idle: the down projection (193 k-tiles, the last one
+    # partial) is cut into ranges of 128x128, 256x128, 160x256 (640 rows) and 256x256 tiles (1000 rows)
+    shape = W.LayerShape(4096, 8, 2, 128, 12296)
+    seqs = [(rows - 13, rows - 3, -1)] + [(1, 20 + 9 * i, -1) for i in range(13)]
+    batch = W.assemble_batch(16, seqs, 1, [], np.random.default_rng(rows))
+    check_step(lib, shape, batch, W.make_tensors(shape, batch, rows, gains="random"))
+
+
 def attention_reference(shape, batch, q, k_pool, v_pool, storage="exact"):
     out = np.zeros((batch.n_rows, shape.n_q_heads * shape.head_dim))
     for s in range(batch.n_seq):
