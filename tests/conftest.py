@@ -17,3 +17,11 @@ def lib():
     """The HIP library binding; fails loudly if the shared object is not built."""
     import paper_2411_16102_amd as pkg
     return pkg.load()
+
+
+@pytest.fixture(autouse=True)
+def _earlier_contexts_are_gone():
+    """A context that an earlier test left in a reference cycle (an exception it caught holds the frame) is
+    freed now, not whenever the collector runs: test_zz_no_alloc watches the free device memory."""
+    import gc
+    gc.collect()
