@@ -301,6 +301,13 @@ int validate(bs_ctx *c, const bs_batch *b, int64_t n_pages) {
   return BS_OK;
 }
 
+AttnShape attn_shape(const bs_ctx *c) {
+  AttnShape s;
+  s.n_q_heads = c->cfg.n_q_heads; s.n_kv_heads = c->cfg.n_kv_heads; s.head_dim = c->cfg.head_dim; s.page_size = c->cfg.page_size;
+  s.scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)c->cfg.head_dim));
+  return s;
+}
+
 // ---------------------------------------------------------------------------------
 // plan: everything the kernels need, packed in one int32 blob
 // ---------------------------------------------------------------------------------
@@ -430,13 +437,14 @@ int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chu
       }
     }
   }
-  // prefill work: (sequence, block of 64 query rows), longest contexts first
+  // prefill work: (sequence, block of query rows of one workgroup), longest contexts first
+  const int wg_rows = 64 * (4 / prefill_heads_per_wg(attn_shape(c)));
   c->pf_work.clear();
   std::vector<std::pair<int, std::pair<int, int>>> &order = c->pf_order;
   order.clear();
   for (int s = 0; s < b->n_prefill; ++s) {
     const int q = b->row_start[s + 1] - b->row_start[s];
-    for (int k = 0; k * 64 < q; ++k) order.push_back({-(b->kv_len[s] - q + std::min(q, k * 64 + 64)), {s, k}});
+    for (int k = 0; k * wg_rows < q; ++k) order.push_back({-(b->kv_len[s] - q + std::min(q, (k + 1) * wg_rows)), {s, k}});
   }
   std::stable_sort(order.begin(), order.end(), [](const auto &x, const auto &y) { return x.first < y.first; });
   p.n_pf_work = (int)order.size();
@@ -517,13 +525,6 @@ int span_end(bs_ctx *c, int which, hipStream_t s, bs_ctx::Span &sp) {
     rc_ = span_end(ctx, which, stream, sp_);                 \
     if (rc_) return rc_;                                     \
   } while (0)
-
-AttnShape attn_shape(const bs_ctx *c) {
-  AttnShape s;
-  s.n_q_heads = c->cfg.n_q_heads; s.n_kv_heads = c->cfg.n_kv_heads; s.head_dim = c->cfg.head_dim; s.page_size = c->cfg.page_size;
-  s.scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)c->cfg.head_dim));
-  return s;
-}
 
 PrefillArgs prefill_args(const bs_ctx *c, const Plan &p, const uint16_t *q, uint16_t *out, const uint16_t *pool) {
   PrefillArgs a;

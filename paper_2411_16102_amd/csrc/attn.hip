@@ -153,48 +153,116 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(const MergeArgs a) {
 }
 
 // ------------------------------------------------------------------------------
-// prefill attention: one wavefront per (64 query rows, query head); the
-// wavefronts of a workgroup are the heads of one KV group and walk the same pages
+// prefill attention: a workgroup of four wavefronts, each (64 query rows, one query head); the
+// four share a KV head and walk the same pages
 // ------------------------------------------------------------------------------
-// Two blocks of 32 query rows share every key and value fragment the wavefront loads: the
-// operands come straight from global memory (a lane's key fragment is 16 bytes of a
-// 256-byte row, so a load instruction touches 32 cache lines), and twice the rows per load
-// is half the L1 accesses per MFMA.  The accumulators of 64 rows x dh 128 leave room for
-// one wavefront per SIMD only, so vector-ALU and matrix work of a block overlap only as far
-// as the instruction order below lets them.  A variant that stages keys and values in LDS
-// for eight wavefronts of 32 rows (one workgroup-wide load per block, one barrier per block)
-// was measured slower: its wavefronts move in lockstep and the LDS, matrix and
-// vector-ALU phases of a block add up instead of overlapping.
+// Keys and values of a block of 32 tokens (two pages) travel global -> LDS once per workgroup, each
+// wavefront requesting one of the four tiles, into a ring of PF_RING blocks; fragments then come
+// out of LDS.  (Read straight from global memory by every wavefront, 24 loads of 64 scattered pieces
+// per block and wavefront, a block took 3300 clocks of a CU; its MFMAs need 1024.)  It takes 2200
+// now: issue 1200, of that 900 vector-ALU; 600 waiting for a pipe, 400 for LDS and barriers.
+// Measured, 8B layer: 28 x 64 rows behind 6000 tokens 334 -> 220 us, 8 x 1024 rows 154 -> 121, 32 rows
+// behind 8000 tokens 333 -> 220, 128 x 64 rows 73 -> 66, where starting workgroups is most of it.
+//
+// What then bounds a block is the issue of one wavefront per SIMD (the accumulators of 64 rows x dh
+// 128 leave no room for two): 32 MFMAs of 32 clocks against about 900 clocks of softmax arithmetic.
+// They overlap by software pipelining: while block t's scores turn into probabilities, the scores of
+// block t+1 are computed, then the PV product of block t, one MFMA at a time with its share of the
+// arithmetic behind it; the key fragments of block t+2 and the value fragments of block t are read
+// from LDS in between.  One barrier per two blocks.
+//
+// LDS: a key tile is [16 tokens][dh], its 16-byte chunks XOR-swizzled by score row so that a
+// fragment read (16 rows, two chunks) touches every bank once; a value tile is [dh][16 tokens], the
+// two chunks of a row exchanged in every other group of eight rows, for the same reason.  Keys enter
+// the score product in the order that leaves a lane eight adjacent tokens of one page (token bits 2
+// and 3 exchanged), so a value fragment is one 16-byte read.
+constexpr int PF_RING = 8;  // blocks of 32 tokens: while blocks t, t+1 are computed, t-2, t-1 make room for t+6, t+7; t+3 must have landed
+constexpr int PF_LDS(int dh) { return PF_RING * 4 * 16 * dh * 2; }
+
+// 16 bytes per lane, lane i to `lds` + 16 i, without passing through registers
+__device__ __forceinline__ void dma_to_lds(const void *src, unsigned char *lds) {
+  __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void *)lds, 16, 0, 0);
+}
+__device__ __forceinline__ int swap_bits_2_3(int v) { return (v & ~12) | ((v & 4) << 1) | ((v & 8) >> 1); }
+
+// s = k q^T + s (FIRST: + 0) with the accumulators in ordinary registers, where the softmax reads them
+// (left to the compiler, a kernel of more than 256 registers keeps every MFMA result in accumulation
+// registers and copies it out: 130 copies per block).  The compiler does not see the latency: whoever
+// reads s leaves at least eight MFMAs, which execute in order, or score_settle between.
+template <bool FIRST>
+__device__ __forceinline__ void score_mfma(f32x16_t &s, bf16x8_t k, bf16x8_t q) {
+  if constexpr (FIRST)
+    asm("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(s) : "v"(k), "v"(q));
+  else
+    asm("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(s) : "v"(k), "v"(q));
+}
+__device__ __forceinline__ void score_settle(f32x16_t &a, f32x16_t &b) {
+  asm("s_nop 15\n\ts_nop 15" : "+v"(a), "+v"(b));
+}
+
 template <int DH>
-__device__ __forceinline__ void prefill_workgroup(const PrefillArgs &a, int heads_per_wg, int b, int wave, int lane) {
+__device__ __forceinline__ void prefill_workgroup(const PrefillArgs &a, int heads_per_wg, int b, int wave, int lane, unsigned char *smem) {
   constexpr int KC = DH / 16;  // k-steps of the 32x32x16 score MFMA
   constexpr int DB = DH / 32;  // 32-row blocks of the output
   constexpr int NQ = 2;        // blocks of 32 query rows per wavefront
+  constexpr int TILE = 16 * DH * 2;     // bytes of one K or V tile of a (page, head)
+  constexpr int CPR = DH / 8;           // 16-byte chunks of a key row
+  constexpr int LD = TILE / 1024;       // loads of 1 KB per tile
+  constexpr int BLK = 4 * TILE;         // K, V of the first page, K, V of the second
   const int hkv = a.s.n_kv_heads, hq = a.s.n_q_heads, grp = hq / hkv;
   const int wg_per_work = hq / heads_per_wg;
   const int w = b / wg_per_work;
-  const int seq = a.work[2 * w], qblk = a.work[2 * w + 1];  // block of 64 query rows
-  const int head = (b % wg_per_work) * heads_per_wg + wave;
+  const int seq = a.work[2 * w], qblk = a.work[2 * w + 1];  // block of 64 * (4 / heads_per_wg) query rows
+  const int head = (b % wg_per_work) * heads_per_wg + wave % heads_per_wg;
   const int kvh = head / grp;
   const int r0 = a.row_start[seq], q_len = a.row_start[seq + 1] - r0;
   const int kv_len = a.kv_len[seq];
   const int lr = lane & 31, g2 = lane >> 5;
-  const size_t tile = (size_t)16 * DH;
-  const int32_t *pages = a.page_ids + a.page_start[seq];
+  // (through the constant address space: nobody writes the page table, and its loads stay on the scalar
+  // unit, where a wait for one does not wait for the tiles in flight)
+  const auto *pages = (const __attribute__((address_space(4))) int32_t *)(a.page_ids + a.page_start[seq]);
   const int n_pg = (kv_len + 15) >> 4;
-  const uint32_t v_off = lr * 16 + 4 * g2;  // this lane's element within a value tile [dh][16 tokens]
+  const int wg_row0 = qblk * 64 * (4 / heads_per_wg);
+  const int row_w = wg_row0 + 64 * (wave / heads_per_wg);  // first row of this wavefront
 
-  int n_q[NQ], my_pos[NQ], last_tb[NQ], first_pos[NQ];
+  // blocks of 32 tokens that the workgroup walks, and those that this wavefront needs
+  const int wg_rows = min(64 * (4 / heads_per_wg), q_len - wg_row0);
+  const int n_wg = (kv_len - q_len + wg_row0 + wg_rows - 1) / 32 + 1;
+  const int n_tb = row_w < q_len ? (kv_len - q_len + min(row_w + 64, q_len) - 1) / 32 + 1 : 0;
+
+  // ---- global -> LDS: wavefront w requests tile w of a block (page w / 2; keys or values) ----
+  uint32_t src[LD];  // byte offset within the tile of the chunk that this lane's LDS place holds
+#pragma unroll
+  for (int i = 0; i < LD; ++i) {
+    const int p = i * 64 + lane;  // place in the tile, in chunks
+    if (wave & 1) {
+      const int dh = p >> 1;
+      src[i] = (uint32_t)(dh * 32 + (((p & 1) ^ ((dh >> 3) & 1)) << 4));
+    } else {
+      const int tok = p / CPR, rho = swap_bits_2_3(tok), f = CPR == 16 ? rho : rho >> 1;
+      src[i] = (uint32_t)(tok * DH * 2 + (((p % CPR) ^ f) << 4));
+    }
+  }
+  auto page_of = [&](int tb) __attribute__((always_inline)) { return pages[min(2 * tb + (wave >> 1), n_pg - 1)]; };
+  const unsigned char *tiles = reinterpret_cast<const unsigned char *>(a.kv_pool) + (size_t)((wave & 1) * hkv + kvh) * TILE;
+  const uint32_t page_stride = (uint32_t)(2 * hkv * TILE);
+  auto request = [&](int page, int slot) __attribute__((always_inline)) {
+    const unsigned char *t0 = tiles + (uint64_t)(uint32_t)page * page_stride;
+#pragma unroll
+    for (int i = 0; i < LD; ++i)
+      dma_to_lds(t0 + src[i], smem + slot * BLK + wave * TILE + i * 1024);
+  };
+
+  int n_q[NQ], my_pos[NQ], first_pos[NQ];
   bf16x8_t qf[NQ][KC];
   f32x16_t o[NQ][DB];
   float m[NQ], l[NQ];
 #pragma unroll
   for (int qb = 0; qb < NQ; ++qb) {
-    const int row0 = qblk * 64 + qb * 32;
+    const int row0 = row_w + qb * 32;
     n_q[qb] = min(32, q_len - row0);                       // <= 0: the block does not exist
     first_pos[qb] = kv_len - q_len + row0;
     my_pos[qb] = min(first_pos[qb] + lr, kv_len - 1);
-    last_tb[qb] = n_q[qb] > 0 ? (first_pos[qb] + n_q[qb] - 1) / 32 : -1;  // last block of 32 tokens it attends to
     const bool ok = lr < n_q[qb];
     const uint16_t *p = a.q + (size_t)(r0 + (ok ? row0 + lr : 0)) * (hq * DH) + head * DH + 8 * g2;
 #pragma unroll
@@ -211,172 +279,199 @@ __device__ __forceinline__ void prefill_workgroup(const PrefillArgs &a, int head
     l[qb] = 0.f;
   }
 
-  const int n_tb = max(last_tb[0], last_tb[1]) + 1;
-  // Software pipeline, one block of 32 tokens deep: while block tb is computed, the values of
-  // block tb+1 travel into the second value buffer, its keys into the key registers (as soon
-  // as the score MFMAs of block tb have read them) and the page ids of block tb+2 into scalar
-  // registers.  Steps past the end re-read the last block (never used).
-  struct PagePair { int p0, p1; };
-  auto page_pair = [&](int tb) __attribute__((always_inline)) {
-    const int t = tb < n_tb ? tb : n_tb - 1;
-    PagePair pp;
-    pp.p0 = pages[2 * t];
-    pp.p1 = (2 * t + 1 < n_pg) ? pages[2 * t + 1] : pp.p0;
-    return pp;
-  };
-  auto load_k = [&](PagePair pp, u32x4_t (&kf)[KC]) __attribute__((always_inline)) {
-    const size_t pk = (lr < 16) ? pp.p0 : pp.p1;
-    const uint16_t *kp = a.kv_pool + ((pk * 2 + 0) * hkv + kvh) * tile + (lr & 15) * DH + 8 * g2;
 #pragma unroll
-    for (int c = 0; c < KC; ++c) kf[c] = ld16(kp + 16 * c);
+  for (int i = 0; i < PF_RING - 2; ++i) request(page_of(min(i, n_wg - 1)), i);
+
+  // ---- LDS -> registers ----
+  const int tok = swap_bits_2_3(lr & 15), kf_sw = CPR == 16 ? (lr & 15) : ((lr & 15) >> 1);
+  const uint32_t k_off = (uint32_t)((lr >> 4) * 2 * TILE + tok * DH * 2 + ((g2 ^ kf_sw) << 4));
+  const uint32_t v_off = (uint32_t)(TILE + lr * 32 + ((g2 ^ ((lr >> 3) & 1)) << 4));
+  u32x4_t kf[KC], va[DB][2];
+  auto read_k = [&](uint32_t blk, int c) __attribute__((always_inline)) {
+    kf[c] = *reinterpret_cast<const u32x4_t *>(smem + ((blk + k_off) ^ (uint32_t)(c << 5)));
   };
-  // values of a block as loaded: [32-row block of dh][16-token half of the block][8 tokens]
-  auto load_v = [&](PagePair pp, u32x2_t (&r)[DB][4]) __attribute__((always_inline)) {
-    const uint16_t *v0 = a.kv_pool + (((size_t)pp.p0 * 2 + 1) * hkv + kvh) * tile;  // wave-uniform bases,
-    const uint16_t *v1 = a.kv_pool + (((size_t)pp.p1 * 2 + 1) * hkv + kvh) * tile;  // lane offset v_off
+  auto read_v = [&](uint32_t blk, int i) __attribute__((always_inline)) {  // i = 2 db + page
+    va[i >> 1][i & 1] = *reinterpret_cast<const u32x4_t *>(smem + blk + v_off + (i & 1) * 2 * TILE + (i >> 1) * 1024);
+  };
+
+  // Element r of s: token tb*32 + 16*(r/8) + 8*g2 + r%8 against the query at my_pos.  The running
+  // maximum, lazily, as in the decode kernel: rescale only when somebody's maximum has grown by more
+  // than 2^TAU.  `mx`: this lane's maximum over s before masking.
+  auto max_of = [&](const f32x16_t &s) __attribute__((always_inline)) {
+    float mx = fmaxf(s[0], s[1]);
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      r[db][0] = ld8(v0 + v_off + 512 * db);
-      r[db][1] = ld8(v0 + v_off + 512 * db + 8);
-      r[db][2] = ld8(v1 + v_off + 512 * db);
-      r[db][3] = ld8(v1 + v_off + 512 * db + 8);
+    for (int r = 2; r < 16; r += 2) mx = fmaxf(fmaxf(mx, s[r]), s[r + 1]);
+    return mx;
+  };
+  auto settle = [&](f32x16_t &s, float mx, int tb, int qb) __attribute__((always_inline)) {
+    if (tb * 32 + 31 > first_pos[qb]) {  // wave-uniform: the block holds tokens some query must not see
+      const int lim = my_pos[qb] - tb * 32 - 8 * g2;
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (16 * (r >> 3) + (r & 7) > lim) s[r] = NEG_BIG;
+      mx = max_of(s);
+    }
+    mx *= a.s.scale_log2e;  // the scale is positive: the maximum commutes with it
+    if (__builtin_amdgcn_ballot_w64(mx > m[qb] + TAU) != 0) {
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float m_new = fmaxf(m[qb], mx);
+      const float alpha = fast_exp2(m[qb] - m_new);
+      m[qb] = m_new;
+      l[qb] *= alpha;
+#pragma unroll
+      for (int db = 0; db < DB; ++db) scale_acc(o[qb][db], alpha);
     }
   };
-  // block tb: keys in kf and values in vr have been requested; `next` holds the pages of block tb+1
-  auto block = [&](int tb, u32x4_t (&kf)[KC], u32x2_t (&vr)[DB][4], u32x2_t (&vn)[DB][4], PagePair &next, auto two) __attribute__((always_inline)) {
-    const PagePair after = page_pair(tb + 2);
-    load_v(next, vn);
-    if (tb * 32 + 32 > kv_len) {  // wave-uniform: the block runs past the context
+  f32x16_t s_a[NQ], s_b[NQ];  // scores of two successive blocks
+
+  constexpr int AHEAD = PF_RING - 6;  // at the top of block t, t even: blocks t+4 .. t+PF_RING-3 may still be in flight
+  constexpr auto wait_vm = [](int n) { return (n & 0xF) | ((n >> 4) << 14) | 0xF70; };  // s_waitcnt vmcnt(n)
+  constexpr int FIRST_WAIT = wait_vm((PF_RING - 4) * LD), WAIT_AHEAD = wait_vm(AHEAD * LD);
+  static_assert(PF_RING == 8 && (PF_RING - 4) * LD < 64, "outstanding loads must fit the vmcnt field");
+
+  // blocks 0 and 1 (and the queries, requested before them) have landed: scores of block 0, key fragments of block 1
+  __builtin_amdgcn_s_waitcnt(FIRST_WAIT);
+  __builtin_amdgcn_s_barrier();
+#pragma unroll
+  for (int c = 0; c < KC; ++c) read_k(0, c);
+#pragma unroll
+  for (int qb = 0; qb < NQ; ++qb) {
+    score_mfma<true>(s_a[qb], as_bf16x8(kf[0]), qf[qb][0]);
+#pragma unroll
+    for (int c = 1; c < KC; ++c) score_mfma<false>(s_a[qb], as_bf16x8(kf[c]), qf[qb][c]);
+  }
+  score_settle(s_a[0], s_a[1]);
+#pragma unroll
+  for (int c = 0; c < KC; ++c) read_k(BLK, c);
+  settle(s_a[0], max_of(s_a[0]), 0, 0);
+  settle(s_a[1], max_of(s_a[1]), 0, 1);
+  // Probabilities, two at a time: pair e (of 16) is elements 2 (e % 8), + 1 of query block e / 8.  The
+  // first EARLY of query block 0 are taken one block ahead, beside the last PV MFMAs of the block before.
+  constexpr int EARLY = 4;
+  u32x4_t pw[NQ][2];
+  float ps[NQ] = {0.f, 0.f};  // sums of the block's probabilities so far
+  float ex[2];  // exponentials of the pair before: summed and packed one pair later, when they have arrived
+  auto exps = [&](const f32x16_t (&s)[NQ], int e, float (&x)[2]) __attribute__((always_inline)) {
+    const int qb = e >> 3, r = (e & 7) * 2;
+    x[0] = fast_exp2(__builtin_fmaf(s[qb][r], a.s.scale_log2e, -m[qb]));
+    x[1] = fast_exp2(__builtin_fmaf(s[qb][r + 1], a.s.scale_log2e, -m[qb]));
+    asm volatile("" : "+v"(x[0]), "+v"(x[1]));  // here, and not where the compiler would first need them
+  };
+  auto take = [&](int e) __attribute__((always_inline)) {
+    const int qb = e >> 3;
+    ps[qb] += ex[0];
+    ps[qb] += ex[1];
+    uint32_t two = pack_bf16x2(ex[0], ex[1]);
+    asm volatile("" : "+v"(two), "+v"(ps[qb]));
+    pw[qb][(e & 7) >> 2][e & 3] = two;
+  };
+  // pair e: its exponentials; the pair before it is taken
+  auto weight = [&](const f32x16_t (&s)[NQ], int e) __attribute__((always_inline)) {
+    float x[2];
+    exps(s, e, x);
+    if (e > 0) take(e - 1);
+    ex[0] = x[0];
+    ex[1] = x[1];
+  };
+#pragma unroll
+  for (int e = 0; e < EARLY; ++e) weight(s_a, e);
+
+  int page0 = page_of(min(PF_RING - 2, n_wg - 1)), page1 = page_of(min(PF_RING - 1, n_wg - 1));
+  auto block = [&](int tb, f32x16_t (&s_cur)[NQ], f32x16_t (&s_nxt)[NQ], bool first, auto last) __attribute__((always_inline)) {
+    if (first) {  // the first block of a pair
+      // this wavefront's tiles up to block tb+3 have landed, after the barrier everybody's, and nobody reads blocks tb-2, tb-1 any more
+      __builtin_amdgcn_s_waitcnt(WAIT_AHEAD);
+      __builtin_amdgcn_s_barrier();
+      request(page0, (tb + PF_RING - 2) % PF_RING);
+      request(page1, (tb + PF_RING - 1) % PF_RING);
+      page0 = page_of(min(tb + PF_RING, n_wg - 1));
+      page1 = page_of(min(tb + PF_RING + 1, n_wg - 1));
+    }
+    const uint32_t v_blk = (uint32_t)(tb % PF_RING * BLK), k_blk = (uint32_t)((tb + 2) % PF_RING * BLK);
+    if (tb >= n_tb) return;  // wave-uniform: a wavefront of earlier rows is done, it only feeds the ring
+
+    // One MFMA and its share of the other work: scores of block tb+1 (N_QK MFMAs), then PV of block tb
+    // for query block 0 and for query block 1.  Pairs of probabilities EARLY .. 15 go beside the scores and
+    // the first PV product; beside the second, query block 0 of block tb+1 settles and gives its first pairs.
+    constexpr int N_QK = NQ * KC, N_PV = 2 * DB, N_W = N_QK + N_PV;
+    constexpr bool LAST = decltype(last)::value;  // nothing follows; the only block that can run past the context
+    auto weights_of = [&](int j) __attribute__((always_inline)) {  // slot j of N_W
+#pragma unroll
+      for (int e = EARLY + j * (16 - EARLY) / N_W; e < EARLY + (j + 1) * (16 - EARLY) / N_W; ++e) weight(s_cur, e);
+      if (j == N_W - 1) take(15);
+    };
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < N_QK; ++j) {
+      const int c = j / NQ, qb = j % NQ;
+      if constexpr (!LAST) {
+        if (c == 0) score_mfma<true>(s_nxt[qb], as_bf16x8(kf[c]), qf[qb][c]);
+        else score_mfma<false>(s_nxt[qb], as_bf16x8(kf[c]), qf[qb][c]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (j < 2 * DB) read_v(v_blk, j);
+      weights_of(j);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (LAST) {
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int h = 0; h < 4; ++h) vr[db][h] = mask_tokens(vr[db][h], tb * 32 + 8 * h + 4 * g2, kv_len);
+        for (int h = 0; h < 2; ++h) va[db][h] = mask_tokens8(va[db][h], tb * 32 + 16 * h + 8 * g2, kv_len);
     }
-    u32x4_t va[DB][2];
+    float mx0 = 0.f, mx1 = 0.f;  // maxima of s_nxt: its last MFMA is N_PV MFMAs old when they are taken
+    auto pv = [&](int qb, int j) __attribute__((always_inline)) {
+      const int db = j % DB, h = j / DB;
+      o[qb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(va[db][h]), as_bf16x8(pw[qb][h]), o[qb][db], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    };
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      va[db][0] = u32x4_t{vr[db][0].x, vr[db][0].y, vr[db][1].x, vr[db][1].y};
-      va[db][1] = u32x4_t{vr[db][2].x, vr[db][2].y, vr[db][3].x, vr[db][3].y};
+    for (int j = 0; j < N_PV; ++j) {
+      pv(0, j);
+      if (!LAST && j < KC) read_k(k_blk, j);
+      weights_of(N_QK + j);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    // Order of issue: both score products, then softmax of the first query block (its VALU
-    // work runs while the matrix pipe is still busy with the second product), its PV product,
-    // softmax of the second block under that product, and the second PV product.
-    auto scores = [&](int qb) {
-      f32x16_t s;
+    l[0] += ps[0];
+    ps[0] = 0.f;
+    const bool more = !LAST && tb + 1 < n_tb;  // (if not, what is taken of block tb+1 below is never used)
+    if constexpr (!LAST) {
+      mx0 = max_of(s_nxt[0]);
+      if (more) settle(s_nxt[0], mx0, tb + 1, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] = 0.f;
-#pragma unroll
-      for (int c = 0; c < KC; ++c)
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[c]), qf[qb][c], s, 0, 0, 0);
-      return s;
-    };
-    // element r of s: token tb*32 + 8*(r/4) + 4*g2 + r%4 against the query at my_pos
-    // softmax of one query block in two parts.  `prepare` (mask, running maximum, the rare
-    // rescale) branches; `weights` (exponentials, row sums, bf16 packing) does not, so that
-    // the scheduler may slide it under the MFMAs of the other query block.
-    auto prepare = [&](f32x16_t &s, int qb) __attribute__((always_inline)) {
-      if (tb * 32 + 31 > first_pos[qb]) {  // wave-uniform: the block holds tokens some query must not see
-        const int lim = my_pos[qb] - tb * 32 - 4 * g2;
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (8 * (r >> 2) + (r & 3) > lim) s[r] = NEG_BIG;
-      }
-      float mx = fmaxf(s[0], s[1]);
-#pragma unroll
-      for (int r = 2; r < 16; r += 2) mx = fmaxf(fmaxf(mx, s[r]), s[r + 1]);
-      mx *= a.s.scale_log2e;  // the scale is positive: the maximum commutes with it
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      // lazy reference exponent, as in the decode kernel: rescale only when somebody's maximum
-      // has grown by more than 2^TAU
-      if (__builtin_amdgcn_ballot_w64(mx > m[qb] + TAU) != 0) {
-        const float m_new = fmaxf(m[qb], mx);
-        const float alpha = fast_exp2(m[qb] - m_new);
-        m[qb] = m_new;
-        l[qb] *= alpha;
-#pragma unroll
-        for (int db = 0; db < DB; ++db) scale_acc(o[qb][db], alpha);
-      }
-    };
-    auto weights = [&](f32x16_t &s, int qb, u32x4_t &pw0, u32x4_t &pw1) __attribute__((always_inline)) {
-      const float neg_m = -m[qb];
-      float ps = 0.f;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        s[r] = fast_exp2(__builtin_fmaf(s[r], a.s.scale_log2e, neg_m));
-        ps += s[r];
-      }
-      l[qb] += ps;
-      pw0.x = pack_bf16x2(s[0], s[1]);
-      pw0.y = pack_bf16x2(s[2], s[3]);
-      pw0.z = pack_bf16x2(s[4], s[5]);
-      pw0.w = pack_bf16x2(s[6], s[7]);
-      pw1.x = pack_bf16x2(s[8], s[9]);
-      pw1.y = pack_bf16x2(s[10], s[11]);
-      pw1.z = pack_bf16x2(s[12], s[13]);
-      pw1.w = pack_bf16x2(s[14], s[15]);
-    };
-    auto pv = [&](int qb, const u32x4_t &pw0, const u32x4_t &pw1) __attribute__((always_inline)) {
-#pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        o[qb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(va[db][0]), as_bf16x8(pw0), o[qb][db], 0, 0, 0);
-        o[qb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(va[db][1]), as_bf16x8(pw1), o[qb][db], 0, 0, 0);
-      }
-    };
-    u32x4_t pa0, pa1, pb0, pb1;
-    if constexpr (decltype(two)::value) {  // the second query block exists
-      // (past the first block's last position its scores are all masked and add nothing)
-      f32x16_t s0 = scores(0);
-      f32x16_t s1 = scores(1);
-      load_k(next, kf);
-      prepare(s0, 0);
-      prepare(s1, 1);
-      __builtin_amdgcn_sched_barrier(0);
-      weights(s0, 0, pa0, pa1);
-      __builtin_amdgcn_sched_barrier(0);
-      // the first PV product, one MFMA at a time, with the second block's weights in between
-      pv(0, pa0, pa1);
-      weights(s1, 1, pb0, pb1);
-#pragma unroll
-      for (int i = 0; i < 2 * DB; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);           // one MFMA
-        __builtin_amdgcn_sched_group_barrier(0x002, 56 / (2 * DB), 0);  // its share of the VALU work
+    for (int j = 0; j < N_PV; ++j) {
+      pv(1, j);
+      if constexpr (!LAST) {
+        if (j == 0) mx1 = max_of(s_nxt[1]);
+        if (j >= N_PV - EARLY) weight(s_nxt, j - (N_PV - EARLY));
       }
       __builtin_amdgcn_sched_barrier(0);
-      pv(1, pb0, pb1);
-    } else {
-      f32x16_t s0 = scores(0);
-      load_k(next, kf);
-      prepare(s0, 0);
-      weights(s0, 0, pa0, pa1);
-      pv(0, pa0, pa1);
     }
-    next = after;
+    l[1] += ps[1];
+    ps[1] = 0.f;
+    if (more) settle(s_nxt[1], mx1, tb + 1, 1);
   };
-  u32x4_t kf[KC];
-  u32x2_t v_a[DB][4], v_b[DB][4];
-  {
-    const PagePair first = page_pair(0);
-    load_k(first, kf);
-    load_v(first, v_a);
+  int tb = 0;
+  for (; tb + 2 < n_wg; tb += 2) {
+    block(tb, s_a, s_b, true, std::false_type{});
+    block(tb + 1, s_b, s_a, false, std::false_type{});
   }
-  PagePair next = page_pair(1);
-  auto run = [&](auto two) __attribute__((always_inline)) {
-    for (int tb = 0; tb < n_tb; tb += 2) {
-      block(tb, kf, v_a, v_b, next, two);
-      if (tb + 1 < n_tb) block(tb + 1, kf, v_b, v_a, next, two);
-    }
-  };
-  if (n_q[1] > 0)  // wave-uniform: the second block of query rows exists
-    run(std::true_type{});
-  else
-    run(std::false_type{});
+  if (tb + 1 < n_wg) {
+    block(tb, s_a, s_b, true, std::false_type{});
+    s_a[0] = s_b[0];
+    s_a[1] = s_b[1];
+  }
+  block(n_wg - 1, s_a, s_b, n_wg % 2 == 1, std::true_type{});
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // the look-ahead loads have landed before the LDS is released
 #pragma unroll
   for (int qb = 0; qb < NQ; ++qb) {
     float ls = l[qb];
     ls += __shfl_xor(ls, 32, 64);
     if (lr < n_q[qb]) {
       const float inv = 1.f / ls;
-      uint16_t *dst = a.out + (size_t)(r0 + qblk * 64 + qb * 32 + lr) * (hq * DH) + head * DH;
+      uint16_t *dst = a.out + (size_t)(r0 + row_w + qb * 32 + lr) * (hq * DH) + head * DH;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -391,9 +486,10 @@ __device__ __forceinline__ void prefill_workgroup(const PrefillArgs &a, int head
 }
 
 template <int DH>
-__global__ __launch_bounds__(256) void prefill_attn_kernel(const PrefillArgs a, int heads_per_wg) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void prefill_attn_kernel(const PrefillArgs a, int heads_per_wg) {
+  extern __shared__ __align__(256) unsigned char attn_smem[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  prefill_workgroup<DH>(a, heads_per_wg, blockIdx.x, wave, threadIdx.x & 63);
+  prefill_workgroup<DH>(a, heads_per_wg, blockIdx.x, wave, threadIdx.x & 63, attn_smem);
 }
 
 // Prefill and decode attention of one step in one launch.  A prefill workgroup is bound by the
@@ -407,7 +503,7 @@ __global__ __launch_bounds__(256) void prefill_attn_kernel(const PrefillArgs a, 
 template <int DH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void blended_attn_kernel(
     const DecodeArgs d, int n_wide_units, int n_narrow_units, const PrefillArgs pf, int n_pf_wgs, int period) {
-  __shared__ __align__(16) uint16_t q_sh[DECODE_Q_LDS(DH, 4)];
+  extern __shared__ __align__(256) unsigned char attn_smem[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int n_dec = ((n_wide_units + 3) >> 2) + ((n_narrow_units + 3) >> 2);
@@ -425,9 +521,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     idx = prefill ? mixed + r : (period - 1) * mixed + r - (n_pf_wgs - mixed);
   }
   if (prefill)
-    prefill_workgroup<DH>(pf, 4, idx, wave, lane);
+    prefill_workgroup<DH>(pf, 4, idx, wave, lane, attn_smem);
   else
-    decode_workgroup<DH, 4, false, true>(d, n_wide_units, n_narrow_units, idx, wave, lane, q_sh);
+    decode_workgroup<DH, 4, false, true>(d, n_wide_units, n_narrow_units, idx, wave, lane, reinterpret_cast<uint16_t *>(attn_smem));
 }
 
 // What the GEMM launches of a step have left of its queue of 16-row units, on the whole chip:
@@ -438,6 +534,23 @@ __global__ __launch_bounds__(512) void decode_queue_kernel(const DecodeQueue q) 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   decode_queue_worker<DH>(q, wave, threadIdx.x & 63,
                           q.trace ? q.trace + (size_t)TRACE_WORDS * (8 * blockIdx.x + wave) : nullptr);
+}
+
+// LDS of a blended launch: the ring of a prefill workgroup or the queries of four wide decode units
+constexpr int BLENDED_LDS(int dh) {
+  return PF_LDS(dh) > 2 * DECODE_Q_LDS(dh, 4) ? PF_LDS(dh) : 2 * DECODE_Q_LDS(dh, 4);
+}
+
+// a launch of 256-thread workgroups with `lds` bytes of dynamic LDS (`configured`: once per kernel)
+template <class Kernel, class... Args>
+hipError_t launch_with_lds(Kernel kernel, bool &configured, int grid, int lds, hipStream_t stream, Args... args) {
+  if (!configured) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    configured = true;
+  }
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), lds, stream, args...);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -494,28 +607,26 @@ hipError_t launch_blended_attn(const DecodeArgs &d, int n_wide, int n_narrow, co
   // 70B shapes: 3 and 5 are the fastest, the long ones cost 1-3 % of the launch); odd, so that the prefill
   // workgroups visit every XCD in turn
   const int period = n_dec >= 4 * n_pf ? 5 : 3;
-  const dim3 grid(n_dec + n_pf), block(256);
+  static bool configured[2] = {false, false};
   if (d.s.head_dim == 128)
-    hipLaunchKernelGGL((blended_attn_kernel<128>), grid, block, 0, stream, d, n_wide_units, n_narrow_units, pf, n_pf, period);
-  else if (d.s.head_dim == 64)
-    hipLaunchKernelGGL((blended_attn_kernel<64>), grid, block, 0, stream, d, n_wide_units, n_narrow_units, pf, n_pf, period);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
+    return launch_with_lds(blended_attn_kernel<128>, configured[0], n_dec + n_pf, BLENDED_LDS(128), stream, d, n_wide_units, n_narrow_units, pf, n_pf, period);
+  if (d.s.head_dim == 64)
+    return launch_with_lds(blended_attn_kernel<64>, configured[1], n_dec + n_pf, BLENDED_LDS(64), stream, d, n_wide_units, n_narrow_units, pf, n_pf, period);
+  return hipErrorInvalidValue;
+}
+
+int prefill_heads_per_wg(const AttnShape &s) {
+  const int grp = s.n_q_heads / s.n_kv_heads;
+  return grp % 4 == 0 ? 4 : (grp % 2 == 0 ? 2 : 1);
 }
 
 hipError_t launch_prefill_attn(const PrefillArgs &a, hipStream_t stream) {
   if (a.n_work <= 0) return hipSuccess;
-  const int grp = a.s.n_q_heads / a.s.n_kv_heads;
-  const int hpw = (grp % 4 == 0) ? 4 : ((grp % 2 == 0) ? 2 : 1);  // heads of one KV group share a workgroup
-  const dim3 grid(a.n_work * (a.s.n_q_heads / hpw)), block(64 * hpw);
-  if (a.s.head_dim == 128)
-    hipLaunchKernelGGL((prefill_attn_kernel<128>), grid, block, 0, stream, a, hpw);
-  else if (a.s.head_dim == 64)
-    hipLaunchKernelGGL((prefill_attn_kernel<64>), grid, block, 0, stream, a, hpw);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
+  const int hpw = prefill_heads_per_wg(a.s), grid = a.n_work * (a.s.n_q_heads / hpw);
+  static bool configured[2] = {false, false};
+  if (a.s.head_dim == 128) return launch_with_lds(prefill_attn_kernel<128>, configured[0], grid, PF_LDS(128), stream, a, hpw);
+  if (a.s.head_dim == 64) return launch_with_lds(prefill_attn_kernel<64>, configured[1], grid, PF_LDS(64), stream, a, hpw);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace bs

@@ -73,7 +73,7 @@ hipError_t launch_decode_merge(const MergeArgs &a, hipStream_t stream);
 
 struct PrefillArgs {
   AttnShape s;
-  const int32_t *work;  // [n_work][2] = (sequence, block of 64 query rows)
+  const int32_t *work;  // [n_work][2] = (sequence, block of 64 * (4 / prefill_heads_per_wg) query rows)
   int n_work;
   const int32_t *row_start, *kv_len, *page_start, *page_ids;
   const uint16_t *q;
@@ -81,6 +81,7 @@ struct PrefillArgs {
   uint16_t *out;
 };
 hipError_t launch_prefill_attn(const PrefillArgs &a, hipStream_t stream);
+int prefill_heads_per_wg(const AttnShape &s);  // query heads of one KV group that share a workgroup: 4, 2 or 1
 
 // both kinds in one launch (prefill workgroups dealt evenly among the decode ones); needs a step with
 // prefill work and decode items, and a group size that is a multiple of four

@@ -239,6 +239,29 @@ def test_attention_of_few_sequences(lib, shape, lens, root_pages):
     assert torch.equal(out, layer.attention_noalloc(batch, tq, pool, batch.n_pages, torch.zeros_like(tq)))
 
 
+@pytest.mark.parametrize("shape", [W.LayerShape(256, 4, 1, 64, 256), W.LayerShape(256, 4, 2, 128, 256), W.LayerShape(128, 2, 2, 64, 256)])
+@pytest.mark.parametrize("rows,cached", [(1, 0), (16, 16), (32, 1), (33, 31), (64, 0), (65, 190), (129, 0), (257, 255), (300, 517)])
+def test_prefill_attention_edges(lib, shape, rows, cached):
+    # four, two and one query heads per workgroup (one, two and four blocks of 64 query rows); walks of one
+    # to 26 blocks of 32 tokens (odd and even, shorter and longer than the ring of eight), last ones
+    # partial; wavefronts without rows.  Slots behind the context hold NaN.
+    import torch
+    batch = W.assemble_batch(16, [(rows, rows + cached, -1), (5, 5 + cached // 2, -1)], 2, [], np.random.default_rng(rows))
+    tens = W.make_tensors(shape, batch, 3)
+    kp, vp = tens.k_pool.copy(), tens.v_pool.copy()
+    for s in range(batch.n_seq):
+        L = int(batch.kv_len[s])
+        if L % 16:
+            pg = int(batch.page_ids[int(batch.page_start[s]) + (L - 1) // 16])
+            kp[pg, L % 16:] = 0x7FC0
+            vp[pg, L % 16:] = 0x7FC0
+    q = W.round_to_bf16(np.random.default_rng(cached).standard_normal((batch.n_rows, shape.n_q_heads * shape.head_dim), dtype=np.float32))
+    layer = lib.Layer(shape, device=0)
+    pool = layer.pack_pool(kp, vp)
+    out = to_np(layer.attention(batch, torch.from_numpy(q).cuda().to(torch.bfloat16), pool, batch.n_pages))
+    check_attention(shape, batch, q, tens, out)
+
+
 def test_attention_ignores_stale_slots(lib):
     # slots past kv_len in the last page hold NaN bit patterns: they must never reach the output
     import torch
