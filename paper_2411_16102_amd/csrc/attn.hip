@@ -188,16 +188,13 @@ __device__ __forceinline__ int swap_bits_2_3(int v) { return (v & ~12) | ((v & 4
 // s = k q^T + s (FIRST: + 0) with the accumulators in ordinary registers, where the softmax reads them
 // (left to the compiler, a kernel of more than 256 registers keeps every MFMA result in accumulation
 // registers and copies it out: 130 copies per block).  The compiler does not see the latency: whoever
-// reads s leaves at least eight MFMAs, which execute in order, or score_settle between.
+// reads s leaves at least eight MFMAs, which execute in order, or mfma_settle between.
 template <bool FIRST>
 __device__ __forceinline__ void score_mfma(f32x16_t &s, bf16x8_t k, bf16x8_t q) {
   if constexpr (FIRST)
     asm("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(s) : "v"(k), "v"(q));
   else
     asm("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(s) : "v"(k), "v"(q));
-}
-__device__ __forceinline__ void score_settle(f32x16_t &a, f32x16_t &b) {
-  asm("s_nop 15\n\ts_nop 15" : "+v"(a), "+v"(b));
 }
 
 template <int DH>
@@ -340,7 +337,7 @@ __device__ __forceinline__ void prefill_workgroup(const PrefillArgs &a, int head
 #pragma unroll
     for (int c = 1; c < KC; ++c) score_mfma<false>(s_a[qb], as_bf16x8(kf[c]), qf[qb][c]);
   }
-  score_settle(s_a[0], s_a[1]);
+  mfma_settle(s_a[0], s_a[1]);
 #pragma unroll
   for (int c = 0; c < KC; ++c) read_k(BLK, c);
   settle(s_a[0], max_of(s_a[0]), 0, 0);

@@ -69,6 +69,22 @@ __device__ __forceinline__ void scale_acc(V &acc, float alpha) {
   }
 }
 
+// s = k q^T + s (FIRST: + 0) with the result in ordinary registers, for kernels that run one wavefront
+// per SIMD (left to the compiler, a kernel of more than 256 registers keeps every MFMA result in
+// accumulation registers and copies it out).  The compiler does not see the latency: whoever reads s
+// leaves at least four further MFMAs, which execute in order, or mfma_settle between.
+template <bool FIRST>
+__device__ __forceinline__ void score_mfma16(f32x4_t &s, bf16x8_t k, bf16x8_t q) {
+  if constexpr (FIRST)
+    asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(s) : "v"(k), "v"(q));
+  else
+    asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(s) : "v"(k), "v"(q));
+}
+template <class V>
+__device__ __forceinline__ void mfma_settle(V &a, V &b) {
+  asm("s_nop 15\n\ts_nop 15" : "+v"(a), "+v"(b));
+}
+
 // ------------------------------------------------------------------------------
 // decode attention: one wavefront per (item, KV head), up to 16 * NQB query rows
 // ------------------------------------------------------------------------------
@@ -129,13 +145,6 @@ __device__ __forceinline__ void decode_unit(const DecodeArgs &a, int item, int k
         qf[qb][c] = as_bf16x8(v);
     }
   }
-  auto q_frag = [&](int qb, int c) -> bf16x8_t {
-    if constexpr (Q_LDS)
-      return as_bf16x8(*reinterpret_cast<const u32x4_t *>(&q_sh[q_off + qb * 16 * QLD + 32 * c]));
-    else
-      return qf[qb][c];
-  };
-
   f32x4_t o[NQB][DB];
   float m[NQB], l[NQB];
 #pragma unroll
@@ -192,15 +201,54 @@ __device__ __forceinline__ void decode_unit(const DecodeArgs &a, int item, int k
 #pragma unroll
       for (int db = 0; db < DB; ++db) f.v[db] = mask_tokens8(f.v[db], tb + 8 * g4, n_tok);
     }
-#pragma unroll
-    for (int qb = 0; qb < NQB; ++qb) {
-      f32x4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+    // The scores of the next query block are issued ahead of the softmax of this one: the matrix pipe works
+    // under the vector arithmetic, and a score is read only after the MFMAs of the block behind it.
+    // Query fragments that live in LDS are read one block further ahead, all of a block at a time (left to
+    // the compiler, each is read, waited for and used before the next: sixteen LDS round trips per pair of
+    // pages of a 64-row unit).
+    f32x4_t sx[2][2];
+    bf16x8_t qn[2][KC];
+    auto ask_q = [&](int qb) {
 #pragma unroll
       for (int c = 0; c < KC; ++c) {
-        const bf16x8_t qv = q_frag(qb, c);
-        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(f.k[0][c]), qv, s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(f.k[1][c]), qv, s1, 0, 0, 0);
+        if constexpr (Q_LDS)
+          qn[qb & 1][c] = as_bf16x8(*reinterpret_cast<const u32x4_t *>(&q_sh[q_off + qb * 16 * QLD + 32 * c]));
+        else
+          qn[qb & 1][c] = qf[qb][c];
       }
+      if constexpr (Q_LDS) asm volatile("" ::: "memory");  // the reads stay here
+    };
+    auto scores = [&](int qb) {
+      f32x4_t &s0 = sx[qb & 1][0], &s1 = sx[qb & 1][1];
+      if constexpr (!ACC_A) s0 = s1 = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < KC; ++c) {
+        const bf16x8_t qv = qn[qb & 1][c];
+        if constexpr (!ACC_A) {
+          s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(f.k[0][c]), qv, s0, 0, 0, 0);
+          s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(f.k[1][c]), qv, s1, 0, 0, 0);
+        } else if (c == 0) {
+          score_mfma16<true>(s0, as_bf16x8(f.k[0][c]), qv);
+          score_mfma16<true>(s1, as_bf16x8(f.k[1][c]), qv);
+        } else {
+          score_mfma16<false>(s0, as_bf16x8(f.k[0][c]), qv);
+          score_mfma16<false>(s1, as_bf16x8(f.k[1][c]), qv);
+        }
+      }
+    };
+    ask_q(0);
+    if constexpr (NQB > 1) ask_q(1);
+    scores(0);
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb) {
+      if constexpr (NQB > 1) {
+        if (qb + 2 < NQB) ask_q(qb + 2);
+        if (qb + 1 < NQB) scores(qb + 1);
+        if constexpr (ACC_A) __builtin_amdgcn_sched_barrier(0);
+      } else if constexpr (ACC_A) {
+        mfma_settle(sx[0][0], sx[0][1]);
+      }
+      const f32x4_t s0 = sx[qb & 1][0], s1 = sx[qb & 1][1];
       float sv[8];  // tokens tb + 8 g4 + 0 .. 7
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -250,8 +298,13 @@ __device__ __forceinline__ void decode_unit(const DecodeArgs &a, int item, int k
 
   // the item names its first two pages itself: the first loads need not wait for the page list
   Frags fa, fb;
+  // Left to itself the compiler sends some of the first set behind the second, so that every iteration
+  // waits for most of both.  For 64-row units the order is fixed (512 sequences behind two prefixes of
+  // 4096: 121 -> 113 us); 16-row units stream faster without (256 of 1024 tokens 185 us, fixed 191).
   load_pages((size_t)it.page0, (size_t)it.page1, fa);
+  if constexpr (NQB > 1) __builtin_amdgcn_sched_barrier(0);
   load(1, fb);
+  if constexpr (NQB > 1) __builtin_amdgcn_sched_barrier(0);
   for (int pr = 0; pr < n_pairs; pr += 2) {
     compute(pr, fa);
     if constexpr (NQB > 1) __builtin_amdgcn_sched_barrier(0);  // refill only once the set is dead
