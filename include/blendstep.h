@@ -283,6 +283,17 @@ int bs_attention(bs_ctx *ctx, const bs_batch *batch, const void *q, void *out,
 int bs_attention_noalloc(bs_ctx *ctx, const bs_batch *batch, const void *q, void *out,
                          const void *kv_pool, int64_t n_pages, void *stream);
 
+/* Host-only: how the attention of a batch would be divided, by bs_attention (noalloc = 0) or by
+ * bs_attention_noalloc (1; the error of that call where it would refuse the batch).  Works on a host-only
+ * context; touches no GPU. */
+typedef struct bs_division {
+  int32_t items, wide_items;       /* decode work items; those with more than 16 query rows */
+  int32_t longest_item_tokens[2];  /* of the items with up to / with more than 16 query rows (0: none) */
+  int64_t states;                  /* partial softmax states */
+  int64_t descriptor_words;        /* 32-bit words of the planned descriptor */
+} bs_division;
+int bs_attention_division(bs_ctx *ctx, const bs_batch *batch, int64_t n_pages, int32_t noalloc, bs_division *out);
+
 #ifdef __cplusplus
 }
 #endif

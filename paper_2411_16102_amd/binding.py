@@ -49,6 +49,11 @@ class OverlapKnobs(C.Structure):
                                          "ride_percent", "attention_waves", "carry_down", "drain_in_last", "head_cus_max", "always")]
 
 
+class Division(C.Structure):
+    _fields_ = [("items", C.c_int32), ("wide_items", C.c_int32), ("longest_item_tokens", C.c_int32 * 2),
+                ("states", C.c_int64), ("descriptor_words", C.c_int64)]
+
+
 class SplitInfo(C.Structure):
     _fields_ = [("n_split", C.c_int32), ("rounds", C.c_int32), ("monotone", C.c_int32),
                 ("recompute_tokens", C.c_int64)]
@@ -132,6 +137,7 @@ def raw():
         lib.bs_get_overlap.argtypes = [C.c_void_p, C.POINTER(OverlapKnobs)]
         lib.bs_attention_noalloc.argtypes = [C.c_void_p, C.POINTER(BatchDesc), C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64,
                                              C.c_void_p]
+        lib.bs_attention_division.argtypes = [C.c_void_p, C.POINTER(BatchDesc), C.c_int64, C.c_int32, C.POINTER(Division)]
         lib.bs_overlap_report.argtypes = [C.c_void_p, C.POINTER(C.c_int64)]
         lib.bs_overlap_trace.argtypes = [C.c_void_p, C.c_int]
         lib.bs_overlap_trace_read.argtypes = [C.c_void_p, C.c_int32, C.POINTER(C.c_uint64), C.c_int64, C.POINTER(C.c_int64)]
@@ -326,6 +332,14 @@ class Layer:
         d, keep = marshal_batch(batch)
         self._check(self.lib.bs_attention_noalloc(self.h, C.byref(d), C.c_void_p(q.data_ptr()), C.c_void_p(out.data_ptr()),
                                                   C.c_void_p(kv_pool.data_ptr()), n_pages, self._stream(stream)))
+        return out
+
+    def attention_division(self, batch, noalloc: bool = False, n_pages: Optional[int] = None) -> Division:
+        """How attention (attention_noalloc) divides a batch; host only."""
+        d, keep = marshal_batch(batch)
+        out = Division()
+        self._check(self.lib.bs_attention_division(self.h, C.byref(d), batch.n_pages if n_pages is None else n_pages,
+                                                   int(noalloc), C.byref(out)))
         return out
 
     def gemm_nt(self, a, b, stream=None):

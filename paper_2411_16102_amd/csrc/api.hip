@@ -346,6 +346,45 @@ Chunks chunk_choice(const bs_ctx *c, const bs_batch *b) {
   return {pages_each, pages_each};
 }
 
+// pages per chunk of a node with cnt member rows (one for all its member groups: their partial states
+// share slot numbers)
+int node_chunk(int cnt, int n_groups, int grp, Chunks chunks) {
+  return ((cnt + n_groups - 1) / n_groups) * grp > 16 ? chunks.wide : chunks.other;
+}
+
+// What build_plan would make of a (validated) batch, counted and not built: decode items, partial
+// states, words of the descriptor.
+struct PlanSize { long items = 0, slots = 0, ints = 0; };
+
+PlanSize plan_size(bs_ctx *c, const bs_batch *b, Chunks chunks) {
+  const int ps = c->cfg.page_size, grp = c->cfg.n_q_heads / c->cfg.n_kv_heads, nn = b->n_nodes;
+  const int max_members = std::max(1, 64 / grp);
+  PlanSize z;
+  c->path_chunks.assign((size_t)nn, 0);
+  for (int n = 0; n < nn; ++n) {
+    const int np = b->node_page_start[n + 1] - b->node_page_start[n], cnt = b->node_seq_count[n];
+    const int n_groups = cnt > 0 ? (cnt + max_members - 1) / max_members : 1;
+    const int chn = node_chunk(cnt, n_groups, grp, chunks), nch = (np + chn - 1) / chn;
+    c->path_chunks[n] = (b->node_parent[n] >= 0 ? c->path_chunks[b->node_parent[n]] : 0) + nch;
+    if (cnt > 0) z.items += (long)n_groups * nch;
+  }
+  long pf_blocks = 0;
+  for (int s = 0; s < b->n_seq; ++s) {
+    if (s < b->n_prefill) {
+      pf_blocks += (b->row_start[s + 1] - b->row_start[s] + 63) / 64;  // the finest division of the prefill rows
+      continue;
+    }
+    const int leaf = nn > 0 ? b->seq_leaf_node[s] : -1;
+    const int tail_pg = (b->kv_len[s] + ps - 1) / ps - (leaf >= 0 ? c->path_pages[leaf] : 0);
+    const long nch = (tail_pg + chunks.other - 1) / chunks.other;
+    z.items += nch;
+    z.slots += nch + (leaf >= 0 ? c->path_chunks[leaf] : 0);
+  }
+  z.ints = 4L * b->n_seq + 3 + 3L * b->n_rows + 2 * pf_blocks + 8 * z.items + (nn > 0 ? b->node_page_start[nn] : 0) +
+           (b->n_seq ? b->page_start[b->n_seq] : 0);
+  return z;
+}
+
 int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chunks) {
   const int ch = chunks.other;
   const int ps = c->cfg.page_size;
@@ -367,8 +406,7 @@ int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chu
     const int above = par >= 0 ? c->path_chunks[par] : 0;
     const int cnt = b->node_seq_count[n];
     const int n_groups = cnt > 0 ? (cnt + max_members - 1) / max_members : 1;
-    // the chunk size of a node is one for all its member groups: their partial states share slot numbers
-    const int chn = ((cnt + n_groups - 1) / n_groups) * grp > 16 ? chunks.wide : ch;
+    const int chn = node_chunk(cnt, n_groups, grp, chunks);
     const int nch = (np + chn - 1) / chn;
     c->path_chunks[n] = above + nch;
     if (cnt <= 0 || np <= 0) continue;
@@ -475,15 +513,50 @@ int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chu
   return BS_OK;
 }
 
-// Stages the plan in the pinned ring and copies it to `dst` (the context's descriptor buffer, grown
-// on demand, or - no_grow - a buffer of the caller's that is known to be large enough, with the
-// staging slots of bs_create, which are).
-int upload_plan(bs_ctx *c, const Plan &p, hipStream_t stream, int32_t *dst = nullptr, bool no_grow = false) {
+// floats of the m (and l) array of `slots` partial states in the scratch array of bs_attention_noalloc
+size_t noalloc_ml_floats(const bs_ctx *c, long slots) { return ((size_t)slots * c->cfg.n_q_heads + 3) / 4 * 4; }
+size_t noalloc_state_bytes(const bs_ctx *c, long slots) {
+  return (2 * noalloc_ml_floats(c, slots) + (size_t)slots * c->cfg.n_q_heads * c->cfg.head_dim) * sizeof(float);
+}
+bool noalloc_blob_fits(const PlanSize &z) { return (size_t)z.ints * sizeof(int32_t) <= BS_NOALLOC_BLOB_BYTES; }
+bool noalloc_states_fit(const bs_ctx *c, const PlanSize &z) {
+  return noalloc_state_bytes(c, z.slots) <= BS_NOALLOC_SCRATCH_BYTES - BS_NOALLOC_BLOB_BYTES;
+}
+
+int check_noalloc_counts(bs_ctx *c, const bs_batch *b, int64_t n_pages) {
+  if (n_pages > (1 << 20)) return fail(c, BS_EINVAL, "bs_attention_noalloc: n_pages %lld exceeds the limit of %d", (long long)n_pages, 1 << 20);
+  if (b && ((long)b->n_seq > (1 << 15) || (long)b->n_nodes > (1 << 15) || (long)b->n_rows > (1 << 20)))
+    return fail(c, BS_EINVAL, "bs_attention_noalloc: more than %d sequences or prefix nodes", 1 << 15);
+  return BS_OK;
+}
+
+// The plan of bs_attention_noalloc.  What fits is decided by the fixed division of the contexts, so that it
+// does not depend on how finely chunk_choice would cut them; the finer division is taken where it fits as well.
+int plan_noalloc(bs_ctx *c, const bs_batch *b, Plan &p) {
+  const Chunks fine = chunk_choice(c, b), fixed = c->chunk_pages > 0 ? fine : NOALLOC_CHUNKS;
+  const PlanSize z = plan_size(c, b, fixed);
+  if (!noalloc_blob_fits(z))
+    return fail(c, BS_EINVAL, "bs_attention_noalloc: descriptor of %ld bytes exceeds the limit of %u", z.ints * 4L, BS_NOALLOC_BLOB_BYTES);
+  if (!noalloc_states_fit(c, z))
+    return fail(c, BS_EINVAL, "bs_attention_noalloc: %ld partial softmax states (%zu bytes) exceed the limit of %u bytes",
+                z.slots, noalloc_state_bytes(c, z.slots), BS_NOALLOC_SCRATCH_BYTES - BS_NOALLOC_BLOB_BYTES);
+  bool take_fine = false;
+  if (fine.other < fixed.other) {
+    const PlanSize zf = plan_size(c, b, fine);
+    take_fine = noalloc_blob_fits(zf) && noalloc_states_fit(c, zf);
+  }
+  return build_plan(c, b, p, false, take_fine ? fine : fixed);
+}
+
+// Stages the plan in the pinned ring and copies it to the context's descriptor buffer, grown on demand,
+// or to `dst`, a buffer of `room` words of the caller's, with the staging slots of bs_create (nothing grows).
+int upload_plan(bs_ctx *c, const Plan &p, hipStream_t stream, int32_t *dst = nullptr, long room = 0) {
   const int slot = c->ring_pos;
   c->ring_pos = (c->ring_pos + 1) % RING;
   if (c->h_ev_live[slot]) HIP_TRY(c, hipEventSynchronize(c->h_ev[slot]));
-  if (no_grow) {
-    if (p.total_ints > c->h_cap[slot]) return fail(c, BS_EINVAL, "descriptor of %ld words exceeds the staging slot", p.total_ints);
+  if (dst) {
+    if (p.total_ints > std::min(room, c->h_cap[slot]))
+      return fail(c, BS_EINVAL, "descriptor of %ld words exceeds its buffer of %ld", p.total_ints, room);
   } else {
     int rc = ensure_blob(c, p.total_ints, slot);
     if (rc) return rc;
@@ -1009,6 +1082,30 @@ int bs_resolve_rows(bs_ctx *c, const bs_batch *b, int32_t *page_out, int32_t *sl
   });
 }
 
+int bs_attention_division(bs_ctx *c, const bs_batch *b, int64_t n_pages, int32_t noalloc, bs_division *out) {
+  return guarded(c, [&]() -> int {
+  if (!c) return BS_EINVAL;
+  if (!out) return fail(c, BS_EINVAL, "bs_attention_division: NULL argument");
+  int rc = validate(c, b, n_pages);
+  if (rc) return rc;
+  *out = bs_division{};
+  if (b->n_rows == 0) return BS_OK;
+  Plan p;
+  if (noalloc) {
+    if ((rc = check_noalloc_counts(c, b, n_pages)) || (rc = plan_noalloc(c, b, p))) return rc;
+  } else if ((rc = build_plan(c, b, p, false, chunk_choice(c, b)))) {
+    return rc;
+  }
+  bs_division d{};
+  d.wide_items = p.n_wide; d.items = p.n_wide + p.n_narrow; d.states = p.n_slots; d.descriptor_words = p.total_ints;
+  const DecodeItem *it = reinterpret_cast<const DecodeItem *>(c->blob.data() + p.off_items);
+  for (int i = 0; i < d.items; ++i)
+    d.longest_item_tokens[i < p.n_wide] = std::max(d.longest_item_tokens[i < p.n_wide], it[i].n_tokens);
+  *out = d;
+  return BS_OK;
+  });
+}
+
 }  // extern "C"
 
 namespace {
@@ -1236,44 +1333,19 @@ int bs_attention_noalloc(bs_ctx *c, const bs_batch *b, const void *q, void *out,
   if (!c) return BS_EINVAL;
   if (c->device == BS_DEVICE_NONE) return fail(c, BS_EINVAL, "host-only context");
   if (!c->scratch_ptr) return fail(c, BS_EHIP, "bs_attention_noalloc: no scratch array on device %d", c->device);
-  if (n_pages > (1 << 20)) return fail(c, BS_EINVAL, "bs_attention_noalloc: n_pages %lld exceeds the limit of %d", (long long)n_pages, 1 << 20);
-  if (b && ((long)b->n_seq > (1 << 15) || (long)b->n_nodes > (1 << 15) || (long)b->n_rows > (1 << 20)))
-    return fail(c, BS_EINVAL, "bs_attention_noalloc: more than %d sequences or prefix nodes", 1 << 15);
-  int rc = validate(c, b, n_pages);
+  int rc = check_noalloc_counts(c, b, n_pages);
+  if (rc) return rc;
+  rc = validate(c, b, n_pages);
   if (rc) return rc;
   if (b->n_rows == 0) return BS_OK;
   if (!q || !out || !pool) return fail(c, BS_EINVAL, "bs_attention_noalloc: NULL pointer");
   HIP_TRY(c, hipSetDevice(c->device));
   hipStream_t st = (hipStream_t)stream_;
   Plan p;
-  // What fits is decided by the fixed division of the contexts, so that it does not depend on how finely
-  // chunk_choice would cut them; the finer division is taken where it fits as well.
+  if ((rc = plan_noalloc(c, b, p))) return rc;
   // Layout of the scratch array: descriptor blob | m | l | acc of the partial states (m and l padded
   // to whole 16-byte units, so that the accumulators after them stay 16-byte aligned).
-  const Chunks fine = chunk_choice(c, b), fixed = c->chunk_pages > 0 ? fine : NOALLOC_CHUNKS;
-  const size_t hq = c->cfg.n_q_heads, dh = c->cfg.head_dim;
-  size_t ml_floats = 0, state_bytes = 0;
-  auto plan = [&](Chunks chunks) -> int {
-    p = Plan();
-    const int rc_plan = build_plan(c, b, p, false, chunks);
-    ml_floats = ((size_t)p.n_slots * hq + 3) / 4 * 4;
-    state_bytes = (2 * ml_floats + (size_t)p.n_slots * hq * dh) * sizeof(float);
-    return rc_plan;
-  };
-  auto blob_fits = [&]() { return (size_t)p.total_ints * sizeof(int32_t) <= BS_NOALLOC_BLOB_BYTES; };
-  auto states_fit = [&]() { return state_bytes <= BS_NOALLOC_SCRATCH_BYTES - BS_NOALLOC_BLOB_BYTES; };
-  if ((rc = plan(fixed))) return rc;
-  if (!blob_fits())
-    return fail(c, BS_EINVAL, "bs_attention_noalloc: descriptor of %ld bytes exceeds the limit of %u", p.total_ints * 4L, BS_NOALLOC_BLOB_BYTES);
-  if (!states_fit())
-    return fail(c, BS_EINVAL, "bs_attention_noalloc: %ld partial softmax states (%zu bytes) exceed the limit of %u bytes",
-                p.n_slots, state_bytes, BS_NOALLOC_SCRATCH_BYTES - BS_NOALLOC_BLOB_BYTES);
-  // (a division that chunk_choice cuts finer has at most CHUNK_UNITS_WIDE items more, so the host vectors
-  // reserved by bs_create hold it)
-  if (fine.other < fixed.other && (p.total_ints + 8 * CHUNK_UNITS_WIDE) * sizeof(int32_t) <= BS_NOALLOC_BLOB_BYTES) {
-    if ((rc = plan(fine))) return rc;
-    if (!states_fit() && (rc = plan(fixed))) return rc;
-  }
+  const size_t ml_floats = noalloc_ml_floats(c, p.n_slots);
   // the kernels take their buffers from the context; for this call they are parts of the scratch array
   int32_t *const blob0 = c->d_blob;
   float *const acc0 = c->part_acc, *const m0 = c->part_m, *const l0 = c->part_l;
@@ -1282,7 +1354,7 @@ int bs_attention_noalloc(bs_ctx *c, const bs_batch *b, const void *q, void *out,
   c->part_m = reinterpret_cast<float *>(ptr + BS_NOALLOC_BLOB_BYTES);
   c->part_l = c->part_m + ml_floats;
   c->part_acc = c->part_l + ml_floats;
-  rc = upload_plan(c, p, st, c->d_blob, true);
+  rc = upload_plan(c, p, st, c->d_blob, BS_NOALLOC_BLOB_BYTES / sizeof(int32_t));
   if (!rc) rc = run_attention(c, p, (const uint16_t *)q, (uint16_t *)out, (const uint16_t *)pool, st);
   c->d_blob = blob0;
   c->part_acc = acc0; c->part_m = m0; c->part_l = l0;

@@ -156,3 +156,73 @@ def test_tuning_knobs_reject_values_outside_their_range(host_layer):
     host_layer.set_overlap(head_cus_min=48, ride_percent=50)
     assert host_layer.get_overlap()["head_cus_min"] == 48 and host_layer.get_overlap()["ride_percent"] == 50
     host_layer.set_overlap(**good)
+
+
+NOALLOC_WORDS = (1 << 20) // 4   # descriptor limit of bs_attention_noalloc, in 32-bit words
+
+
+def _near_the_descriptor_limit(fill_pages):
+    # one KV head: 242 private tails of 57 pages and one shared page (32 query rows) are cut into chunks of
+    # eight pages, 1694 items more than chunks of 64; prefill tables of `fill_pages` pages fill the descriptor
+    seqs = []
+    while fill_pages > 0:
+        pages = min(1024, fill_pages)
+        seqs.append((1, 16 * pages, -1))
+        fill_pages -= pages
+    n_prefill = len(seqs)
+    seqs += [(1, 16 + 20, 0)] * 2 + [(1, 57 * 16, -1)] * 242
+    return W.assemble_batch(16, seqs, n_prefill, [(-1, 1)], None)
+
+
+def test_noalloc_division_never_outgrows_the_descriptor_buffer():
+    lay = binding.Layer(W.LayerShape(256, 16, 1, 64, 256), device=-1)
+    empty = _near_the_descriptor_limit(0)
+    coarse, fine = lay.attention_division(empty, noalloc=True), lay.attention_division(empty)
+    assert fine.longest_item_tokens[0] == 128 and fine.items - (242 + 2 + 1) == 242 * 7
+    assert (coarse.items, coarse.descriptor_words) == (fine.items, fine.descriptor_words)   # far from the limit: taken as it is
+    seen = set()
+    for fill in range(228_500, 236_001, 150):
+        b = _near_the_descriptor_limit(fill)
+        want_fine = lay.attention_division(b).descriptor_words
+        got = lay.attention_division(b, noalloc=True)
+        assert got.descriptor_words <= NOALLOC_WORDS
+        assert (got.descriptor_words == want_fine) == (want_fine <= NOALLOC_WORDS)
+        seen.add(want_fine <= NOALLOC_WORDS)
+    assert seen == {True, False}
+    # what the fixed division of 64 (32) pages fits is accepted, what it does not fit is refused
+    over = _near_the_descriptor_limit(236_000)
+    spare = NOALLOC_WORDS - lay.attention_division(over, noalloc=True).descriptor_words
+    with pytest.raises(binding.BlendStepError, match="descriptor"):
+        lay.attention_division(_near_the_descriptor_limit(236_000 + spare + 64), noalloc=True)
+
+
+@pytest.mark.parametrize("seed", range(8))
+def test_attention_division_counts(seed):
+    # partial states and items of a batch against a plain count
+    shape = [W.LayerShape(256, 4, 2, 64, 256), W.LayerShape(256, 16, 1, 64, 256), W.LayerShape(256, 8, 8, 64, 256)][seed % 3]
+    grp = shape.n_q_heads // shape.n_kv_heads
+    b = W.batch_random(seed, n_prefill=3, n_decode=60, max_q=200, max_ctx=3000, n_roots=3)
+    lay = binding.Layer(shape, device=-1)
+    lay.set_chunk_pages(4)
+    got = lay.attention_division(b, noalloc=False)
+    path = {-1: (0, 0)}   # node -> pages, chunks up to and including it
+    items = wide = states = 0
+    for n in range(b.n_nodes):
+        pages = int(b.node_page_start[n + 1] - b.node_page_start[n])
+        above = path[int(b.node_parent[n])]
+        path[n] = (above[0] + pages, above[1] + -(-pages // 4))
+        cnt, most = int(b.node_seq_count[n]), max(1, 64 // grp)
+        groups = -(-cnt // most)
+        for g in range(groups):
+            members = cnt * (g + 1) // groups - cnt * g // groups
+            items += -(-pages // 4)
+            wide += -(-pages // 4) * (members * grp > 16)
+    for s in range(b.n_prefill, b.n_seq):
+        pages, chunks = path[int(b.seq_leaf_node[s])]
+        tail = -(-(-(-int(b.kv_len[s]) // 16) - pages) // 4)
+        items += tail
+        states += chunks + tail
+    assert (got.items, got.wide_items, got.states) == (items, wide, states)
+    blocks = 0 if b.n_prefill == 0 else sum(-(-int(q) // (64 * (4 // (4 if grp % 4 == 0 else 2 if grp % 2 == 0 else 1))))
+                                            for q in b.q_len()[:b.n_prefill])
+    assert got.descriptor_words == 4 * b.n_seq + 3 + 3 * b.n_rows + 2 * blocks + 8 * items + b.node_page_ids.size + b.page_ids.size
