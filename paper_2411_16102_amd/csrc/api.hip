@@ -317,7 +317,7 @@ constexpr long CHUNK_UNITS = 512, CHUNK_UNITS_WIDE = 1536;  // units of (chunk, 
 struct Chunks { int other, wide; };
 constexpr Chunks NOALLOC_CHUNKS = {CHUNK_MAX, CHUNK_MAX / 2};  // the division that bs_attention_noalloc's limits count in
 
-// Pages per chunk of decode-attention work.  A CU streams at most about 36 GB/s of KV pages however many
+// Pages per chunk of decode-attention work of a step.  A CU streams at most about 36 GB/s of KV pages however many
 // of its wavefronts ask for them, and a wavefront serves its chunk at one page per 0.3 us (64 query
 // rows: 1.2 us), so a step of few sequences is bound by how many CUs have a chunk and by how long one
 // chunk takes: it is cut until there are 512 units of (chunk, KV head), or 1536 where prefix nodes
@@ -530,22 +530,34 @@ int check_noalloc_counts(bs_ctx *c, const bs_batch *b, int64_t n_pages) {
   return BS_OK;
 }
 
+// The division of bs_attention and bs_attention_noalloc, one for both, so that they agree bit for bit: that
+// of chunk_choice, but where the limits of bs_attention_noalloc hold the fixed division and not that one, the
+// finest between the two that they hold.
+Chunks attention_chunks(bs_ctx *c, const bs_batch *b) {
+  const Chunks chosen = chunk_choice(c, b);
+  if (c->chunk_pages > 0) return chosen;
+  auto fits = [&](Chunks chunks) {
+    const PlanSize z = plan_size(c, b, chunks);
+    return noalloc_blob_fits(z) && noalloc_states_fit(c, z);
+  };
+  if (fits(chosen) || !fits(NOALLOC_CHUNKS)) return chosen;
+  for (int p = chosen.other + 2; p < CHUNK_MAX; p += 2) {
+    const Chunks between = {p, std::min(p, NOALLOC_CHUNKS.wide)};
+    if (fits(between)) return between;
+  }
+  return NOALLOC_CHUNKS;
+}
+
 // The plan of bs_attention_noalloc.  What fits is decided by the fixed division of the contexts, so that it
-// does not depend on how finely chunk_choice would cut them; the finer division is taken where it fits as well.
+// does not depend on how finely chunk_choice would cut them.
 int plan_noalloc(bs_ctx *c, const bs_batch *b, Plan &p) {
-  const Chunks fine = chunk_choice(c, b), fixed = c->chunk_pages > 0 ? fine : NOALLOC_CHUNKS;
-  const PlanSize z = plan_size(c, b, fixed);
+  const PlanSize z = plan_size(c, b, c->chunk_pages > 0 ? Chunks{c->chunk_pages, c->chunk_pages} : NOALLOC_CHUNKS);
   if (!noalloc_blob_fits(z))
     return fail(c, BS_EINVAL, "bs_attention_noalloc: descriptor of %ld bytes exceeds the limit of %u", z.ints * 4L, BS_NOALLOC_BLOB_BYTES);
   if (!noalloc_states_fit(c, z))
     return fail(c, BS_EINVAL, "bs_attention_noalloc: %ld partial softmax states (%zu bytes) exceed the limit of %u bytes",
                 z.slots, noalloc_state_bytes(c, z.slots), BS_NOALLOC_SCRATCH_BYTES - BS_NOALLOC_BLOB_BYTES);
-  bool take_fine = false;
-  if (fine.other < fixed.other) {
-    const PlanSize zf = plan_size(c, b, fine);
-    take_fine = noalloc_blob_fits(zf) && noalloc_states_fit(c, zf);
-  }
-  return build_plan(c, b, p, false, take_fine ? fine : fixed);
+  return build_plan(c, b, p, false, attention_chunks(c, b));
 }
 
 // Stages the plan in the pinned ring and copies it to the context's descriptor buffer, grown on demand,
@@ -1093,7 +1105,7 @@ int bs_attention_division(bs_ctx *c, const bs_batch *b, int64_t n_pages, int32_t
   Plan p;
   if (noalloc) {
     if ((rc = check_noalloc_counts(c, b, n_pages)) || (rc = plan_noalloc(c, b, p))) return rc;
-  } else if ((rc = build_plan(c, b, p, false, chunk_choice(c, b)))) {
+  } else if ((rc = build_plan(c, b, p, false, attention_chunks(c, b)))) {
     return rc;
   }
   bs_division d{};
@@ -1319,7 +1331,7 @@ int bs_attention(bs_ctx *c, const bs_batch *b, const void *q, void *out, const v
   HIP_TRY(c, hipSetDevice(c->device));
   hipStream_t st = (hipStream_t)stream_;
   Plan p;
-  if ((rc = build_plan(c, b, p, false, chunk_choice(c, b)))) return rc;
+  if ((rc = build_plan(c, b, p, false, attention_chunks(c, b)))) return rc;
   if ((rc = ensure_slots(c, p.n_slots))) return rc;
   if ((rc = upload_plan(c, p, st))) return rc;
   if ((rc = run_attention(c, p, (const uint16_t *)q, (uint16_t *)out, (const uint16_t *)pool, st))) return rc;

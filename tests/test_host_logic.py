@@ -174,26 +174,37 @@ def _near_the_descriptor_limit(fill_pages):
     return W.assemble_batch(16, seqs, n_prefill, [(-1, 1)], None)
 
 
+def _fields(d):
+    return (d.items, d.wide_items, list(d.longest_item_tokens), d.states, d.descriptor_words)
+
+
 def test_noalloc_division_never_outgrows_the_descriptor_buffer():
     lay = binding.Layer(W.LayerShape(256, 16, 1, 64, 256), device=-1)
     empty = _near_the_descriptor_limit(0)
     coarse, fine = lay.attention_division(empty, noalloc=True), lay.attention_division(empty)
     assert fine.longest_item_tokens[0] == 128 and fine.items - (242 + 2 + 1) == 242 * 7
     assert (coarse.items, coarse.descriptor_words) == (fine.items, fine.descriptor_words)   # far from the limit: taken as it is
-    seen = set()
+    lay.set_chunk_pages(8)
+    fine_words = [lay.attention_division(_near_the_descriptor_limit(f)).descriptor_words for f in (228_500, 236_000)]
+    assert fine_words[0] <= NOALLOC_WORDS < fine_words[1]   # the finer division stops fitting within the range
+    lay = binding.Layer(W.LayerShape(256, 16, 1, 64, 256), device=-1)
     for fill in range(228_500, 236_001, 150):
         b = _near_the_descriptor_limit(fill)
-        want_fine = lay.attention_division(b).descriptor_words
         got = lay.attention_division(b, noalloc=True)
         assert got.descriptor_words <= NOALLOC_WORDS
-        assert (got.descriptor_words == want_fine) == (want_fine <= NOALLOC_WORDS)
-        seen.add(want_fine <= NOALLOC_WORDS)
-    assert seen == {True, False}
-    # what the fixed division of 64 (32) pages fits is accepted, what it does not fit is refused
-    over = _near_the_descriptor_limit(236_000)
-    spare = NOALLOC_WORDS - lay.attention_division(over, noalloc=True).descriptor_words
-    with pytest.raises(binding.BlendStepError, match="descriptor"):
-        lay.attention_division(_near_the_descriptor_limit(236_000 + spare + 64), noalloc=True)
+        assert _fields(got) == _fields(lay.attention_division(b))
+    # what the fixed division (chunks of 64 pages: no node here is longer than one) fits is accepted, what it
+    # does not fit is refused
+    fixed = binding.Layer(W.LayerShape(256, 16, 1, 64, 256), device=-1)
+    fixed.set_chunk_pages(64)
+    spare = NOALLOC_WORDS - fixed.attention_division(_near_the_descriptor_limit(236_000)).descriptor_words
+    for fill in range(236_000 + spare - 70, 236_000 + spare + 10, 10):   # (a prefill segment takes nine words beside its table)
+        b = _near_the_descriptor_limit(fill)
+        if fixed.attention_division(b).descriptor_words <= NOALLOC_WORDS:
+            assert lay.attention_division(b, noalloc=True).descriptor_words <= NOALLOC_WORDS
+        else:
+            with pytest.raises(binding.BlendStepError, match="descriptor"):
+                lay.attention_division(b, noalloc=True)
 
 
 @pytest.mark.parametrize("seed", range(8))
@@ -226,3 +237,26 @@ def test_attention_division_counts(seed):
     blocks = 0 if b.n_prefill == 0 else sum(-(-int(q) // (64 * (4 // (4 if grp % 4 == 0 else 2 if grp % 2 == 0 else 1))))
                                             for q in b.q_len()[:b.n_prefill])
     assert got.descriptor_words == 4 * b.n_seq + 3 + 3 * b.n_rows + 2 * blocks + 8 * items + b.node_page_ids.size + b.page_ids.size
+
+
+@pytest.mark.parametrize("shape", [W.LLAMA3_8B, W.LLAMA3_70B, W.LayerShape(256, 16, 1, 64, 256)])
+@pytest.mark.parametrize("members,prefix_pages,tails", [(8, 4, 40), (40, 64, 300), (50, 256, 20), (70, 80, 100), (100, 64, 60),
+                                                        (200, 100, 20), (16, 128, 2000), (300, 40, 30)])
+def test_both_attention_entry_points_divide_alike(shape, members, prefix_pages, tails):
+    # from steps cut into short chunks, over those whose short chunks the scratch array of bs_attention_noalloc
+    # does not hold, to large ones with nodes of more than 16 query rows; refusals follow the fixed division
+    lay = binding.Layer(shape, device=-1)
+    seqs = [(1, 16 * prefix_pages + tails + 3 * i, 0) for i in range(members)] + [(1, 7 + tails, -1)] * 3
+    b = W.assemble_batch(16, seqs, 0, [(-1, prefix_pages)], None)
+    grp = shape.n_q_heads // shape.n_kv_heads
+    groups = -(-members // max(1, 64 // grp))
+    chunk = 32 if -(-members // groups) * grp > 16 else 64
+    states = members * -(-prefix_pages // chunk) + sum(-(-(-(-int(k) // 16) - prefix_pages) // 64) for k in b.kv_len[:members]) + \
+        3 * -(-(7 + tails) // 1024)
+    hq = shape.n_q_heads
+    fits = (states * hq + 3) // 4 * 4 * 8 + states * hq * shape.head_dim * 4 <= 15 << 20
+    if fits:
+        assert _fields(lay.attention_division(b, noalloc=True)) == _fields(lay.attention_division(b))
+    else:
+        with pytest.raises(binding.BlendStepError, match="partial softmax states"):
+            lay.attention_division(b, noalloc=True)

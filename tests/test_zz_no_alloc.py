@@ -33,6 +33,23 @@ def test_noalloc_attention_matches_the_allocating_entry_point(lib):
         assert bool(torch.isfinite(out.float()).all())
 
 
+@pytest.mark.parametrize("members,prefix_pages,tail,loose", [(400, 100, 1000, 300), (50, 256, 20, 3), (400, 8, 100, 300)])
+def test_noalloc_attention_matches_on_default_chunks(lib, members, prefix_pages, tail, loose):
+    # wide nodes in a step that is large enough for the longest chunks, one whose short chunks the scratch array
+    # would not hold, and one of many short contexts
+    import torch
+    shape = W.LayerShape(512, 32, 8, 128, 256) if members < 300 else W.LayerShape(512, 8, 2, 64, 256)
+    layer = lib.Layer(shape, device=0)
+    seqs = [(1, 16 * prefix_pages + tail + i, 0) for i in range(members)] + [(1, tail + 5 * i, -1) for i in range(loose)]
+    batch = W.assemble_batch(16, seqs, 0, [(-1, prefix_pages)], np.random.default_rng(members))
+    gen = torch.Generator(device="cuda").manual_seed(members)
+    q = torch.randn((batch.n_rows, shape.n_q_heads * shape.head_dim), generator=gen, device="cuda").to(torch.bfloat16)
+    pool = torch.randn(batch.n_pages * (layer.page_bytes() // 2), generator=gen, device="cuda").to(torch.bfloat16)
+    ref = layer.attention(batch, q, pool, batch.n_pages)
+    out = layer.attention_noalloc(batch, q, pool, batch.n_pages, torch.zeros_like(q))
+    assert torch.equal(out, ref) and bool(torch.isfinite(out.float()).all())
+
+
 def test_noalloc_attention_refuses_what_does_not_fit(lib):
     import torch
     # 8B heads: one partial state is 32 x 130 floats = 16.6 KB, so 15 MiB hold 945 of them; 1200 decode
