@@ -290,6 +290,7 @@ int bs_attention_noalloc(bs_ctx *ctx, const bs_batch *batch, const void *q, void
 typedef struct bs_division {
   int32_t items, wide_items;       /* decode work items; those with more than 16 query rows */
   int32_t longest_item_tokens[2];  /* of the items with up to / with more than 16 query rows (0: none) */
+  int32_t prefill_rows;            /* query rows that a prefill workgroup covers: 64, 128 or 256 (0: no prefill rows) */
   int64_t states;                  /* partial softmax states */
   int64_t descriptor_words;        /* 32-bit words of the planned descriptor */
 } bs_division;

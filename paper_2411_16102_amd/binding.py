@@ -50,7 +50,7 @@ class OverlapKnobs(C.Structure):
 
 
 class Division(C.Structure):
-    _fields_ = [("items", C.c_int32), ("wide_items", C.c_int32), ("longest_item_tokens", C.c_int32 * 2),
+    _fields_ = [("items", C.c_int32), ("wide_items", C.c_int32), ("longest_item_tokens", C.c_int32 * 2), ("prefill_rows", C.c_int32),
                 ("states", C.c_int64), ("descriptor_words", C.c_int64)]
 
 

@@ -44,6 +44,7 @@ struct Plan {
        off_part_start = 0, off_pf_work = 0, off_items = 0, off_pages = 0, total_ints = 0;
   long total_node_pages = 0, n_slots = 0;
   int n_pf_work = 0;
+  PrefillRoute pf_route{false, 4, 64};
   int n_wide = 0, n_narrow = 0;  // decode items with up to 64 / up to 16 query rows (wide ones first)
 };
 
@@ -476,7 +477,8 @@ int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chu
     }
   }
   // prefill work: (sequence, block of query rows of one workgroup), longest contexts first
-  const int wg_rows = 64 * (4 / prefill_heads_per_wg(attn_shape(c)));
+  p.pf_route = prefill_route(attn_shape(c), b->n_prefill, b->row_start, b->kv_len);
+  const int wg_rows = p.pf_route.rows;
   c->pf_work.clear();
   std::vector<std::pair<int, std::pair<int, int>>> &order = c->pf_order;
   order.clear();
@@ -635,7 +637,7 @@ DecodeArgs decode_args(const bs_ctx *c, const Plan &p, const uint16_t *q, const 
 int run_prefill_attn(bs_ctx *c, const Plan &p, const uint16_t *q, uint16_t *out, const uint16_t *pool, hipStream_t st) {
   if (p.n_pf_work == 0) return BS_OK;
   const PrefillArgs a = prefill_args(c, p, q, out, pool);
-  SPAN(c, BS_K_ATTN_PREFILL, st, HIP_TRY(c, launch_prefill_attn(a, st)));
+  SPAN(c, BS_K_ATTN_PREFILL, st, HIP_TRY(c, launch_prefill_attn(a, p.pf_route, st)));
   return BS_OK;
 }
 
@@ -1109,6 +1111,7 @@ int bs_attention_division(bs_ctx *c, const bs_batch *b, int64_t n_pages, int32_t
     return rc;
   }
   bs_division d{};
+  d.prefill_rows = p.n_pf_work ? p.pf_route.rows : 0;
   d.wide_items = p.n_wide; d.items = p.n_wide + p.n_narrow; d.states = p.n_slots; d.descriptor_words = p.total_ints;
   const DecodeItem *it = reinterpret_cast<const DecodeItem *>(c->blob.data() + p.off_items);
   for (int i = 0; i < d.items; ++i)

@@ -73,15 +73,21 @@ hipError_t launch_decode_merge(const MergeArgs &a, hipStream_t stream);
 
 struct PrefillArgs {
   AttnShape s;
-  const int32_t *work;  // [n_work][2] = (sequence, block of 64 * (4 / prefill_heads_per_wg) query rows)
+  const int32_t *work;  // [n_work][2] = (sequence, block of PrefillRoute::rows query rows)
   int n_work;
   const int32_t *row_start, *kv_len, *page_start, *page_ids;
   const uint16_t *q;
   const uint16_t *kv_pool;
   uint16_t *out;
 };
-hipError_t launch_prefill_attn(const PrefillArgs &a, hipStream_t stream);
-int prefill_heads_per_wg(const AttnShape &s);  // query heads of one KV group that share a workgroup: 4, 2 or 1
+// Which prefill kernel a step takes and what one of its workgroups covers.
+struct PrefillRoute {
+  bool direct;  // keys and values straight from global memory (group sizes that are no multiple of four only)
+  int heads;    // query heads of one KV group that share a workgroup: 4, 2 or 1
+  int rows;     // query rows of a workgroup
+};
+PrefillRoute prefill_route(const AttnShape &s, int n_prefill, const int32_t *row_start, const int32_t *kv_len);
+hipError_t launch_prefill_attn(const PrefillArgs &a, const PrefillRoute &route, hipStream_t stream);
 
 // both kinds in one launch (prefill workgroups dealt evenly among the decode ones); needs a step with
 // prefill work and decode items, and a group size that is a multiple of four

@@ -262,6 +262,31 @@ def test_prefill_attention_edges(lib, shape, rows, cached):
     check_attention(shape, batch, q, tens, out)
 
 
+@pytest.mark.parametrize("heads,dh", [((16, 16), 64), ((8, 8), 128), ((24, 8), 64), ((16, 8), 128)])
+@pytest.mark.parametrize("segments,rows,cached", [(90, 1, 0), (60, 16, 16), (60, 32, 1), (48, 33, 31), (40, 64, 0), (36, 65, 190), (96, 70, 47)])
+def test_prefill_attention_without_the_ring(lib, heads, dh, segments, rows, cached):
+    # many short chunks of one, two and three query heads per KV head; walks of one to 11 blocks of 32 tokens, last ones
+    # partial, one or both blocks of 32 query rows.  Slots behind the contexts hold NaN.
+    import torch
+    shape = W.LayerShape(256, heads[0], heads[1], dh, 256)
+    batch = W.assemble_batch(16, [(rows, rows + cached + i % 3, -1) for i in range(segments)] + [(1, 33, -1)], segments, [],
+                             np.random.default_rng(rows))
+    layer = lib.Layer(shape, device=0)
+    assert layer.attention_division(batch).prefill_rows == 64
+    tens = W.make_tensors(shape, batch, 3)
+    kp, vp = tens.k_pool.copy(), tens.v_pool.copy()
+    for s in range(batch.n_seq):
+        L = int(batch.kv_len[s])
+        if L % 16:
+            pg = int(batch.page_ids[int(batch.page_start[s]) + (L - 1) // 16])
+            kp[pg, L % 16:] = 0x7FC0
+            vp[pg, L % 16:] = 0x7FC0
+    q = W.round_to_bf16(np.random.default_rng(cached).standard_normal((batch.n_rows, shape.n_q_heads * shape.head_dim), dtype=np.float32))
+    pool = layer.pack_pool(kp, vp)
+    out = to_np(layer.attention(batch, torch.from_numpy(q).cuda().to(torch.bfloat16), pool, batch.n_pages))
+    check_attention(shape, batch, q, tens, out)
+
+
 def test_attention_ignores_stale_slots(lib):
     # slots past kv_len in the last page hold NaN bit patterns: they must never reach the output
     import torch

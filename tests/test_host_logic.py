@@ -234,8 +234,8 @@ def test_attention_division_counts(seed):
         items += tail
         states += chunks + tail
     assert (got.items, got.wide_items, got.states) == (items, wide, states)
-    blocks = 0 if b.n_prefill == 0 else sum(-(-int(q) // (64 * (4 // (4 if grp % 4 == 0 else 2 if grp % 2 == 0 else 1))))
-                                            for q in b.q_len()[:b.n_prefill])
+    blocks = sum(-(-int(q) // got.prefill_rows) for q in b.q_len()[:b.n_prefill])
+    assert got.prefill_rows in ((64,) if grp % 4 == 0 else (64, 256 if grp % 2 else 128))
     assert got.descriptor_words == 4 * b.n_seq + 3 + 3 * b.n_rows + 2 * blocks + 8 * items + b.node_page_ids.size + b.page_ids.size
 
 
@@ -260,3 +260,15 @@ def test_both_attention_entry_points_divide_alike(shape, members, prefix_pages, 
     else:
         with pytest.raises(binding.BlendStepError, match="partial softmax states"):
             lay.attention_division(b, noalloc=True)
+
+
+@pytest.mark.parametrize("heads,dh,segments,rows,cached,want", [
+    ((32, 32), 128, 128, 16, 0, 64), ((32, 32), 64, 128, 64, 0, 64), ((24, 8), 128, 32, 64, 1000, 64), ((16, 8), 64, 128, 64, 500, 64),
+    ((8, 8), 128, 8, 16, 500, 64), ((32, 32), 128, 4, 1024, 0, 256), ((8, 8), 64, 1, 64, 2000, 256), ((16, 8), 128, 1, 2048, 2000, 128),
+    ((24, 8), 64, 4, 1024, 0, 256), ((32, 8), 128, 128, 16, 0, 64), ((32, 8), 64, 4, 1024, 0, 64)])
+def test_prefill_kernel_by_chunks(heads, dh, segments, rows, cached, want):
+    # group sizes that are no multiple of four: many short chunks go 64 rows to a workgroup (without the LDS
+    # ring), long or few ones 256 (128) to a ring; each choice is the faster side of a timed pair
+    lay = binding.Layer(W.LayerShape(256, heads[0], heads[1], dh, 256), device=-1)
+    b = W.assemble_batch(16, [(rows, rows + cached, -1)] * segments, segments, [], None)
+    assert lay.attention_division(b).prefill_rows == want
