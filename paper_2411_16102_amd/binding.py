@@ -138,6 +138,7 @@ def raw():
         lib.bs_attention_noalloc.argtypes = [C.c_void_p, C.POINTER(BatchDesc), C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64,
                                              C.c_void_p]
         lib.bs_attention_division.argtypes = [C.c_void_p, C.POINTER(BatchDesc), C.c_int64, C.c_int32, C.POINTER(Division)]
+        lib.bs_gemm_division.argtypes = [C.c_void_p, C.c_int32, C.c_int32, _i32p, _i32p]
         lib.bs_overlap_report.argtypes = [C.c_void_p, C.POINTER(C.c_int64)]
         lib.bs_overlap_trace.argtypes = [C.c_void_p, C.c_int]
         lib.bs_overlap_trace_read.argtypes = [C.c_void_p, C.c_int32, C.POINTER(C.c_uint64), C.c_int64, C.POINTER(C.c_int64)]
@@ -341,6 +342,12 @@ class Layer:
         self._check(self.lib.bs_attention_division(self.h, C.byref(d), batch.n_pages if n_pages is None else n_pages,
                                                    int(noalloc), C.byref(out)))
         return out
+
+    def gemm_division(self, product: str, rows: int):
+        """(tile shape, ranges along K) of the "qkv", "o" or "down" projection over `rows` rows; host only."""
+        tiles, ranges = C.c_int32(), C.c_int32()
+        self._check(self.lib.bs_gemm_division(self.h, ("qkv", "o", "down").index(product), rows, C.byref(tiles), C.byref(ranges)))
+        return tiles.value, ranges.value
 
     def gemm_nt(self, a, b, stream=None):
         m, k = a.shape

@@ -27,6 +27,7 @@
 // columns) to be conflict-free.  Waits on the LDS-DMA loads are placed by hand
 // (s_waitcnt vmcnt + s_barrier); the compiler does not track them.
 #include <algorithm>
+#include <numeric>
 #include "gemm.hpp"
 #include "attn_device.hpp"
 #include "common.hpp"
@@ -1093,15 +1094,21 @@ void gemm_plan(GemmArgs &a, int epilogue) {
     }
   }
   // Above: the estimated time in microseconds of every tile shape, whole or cut along K.  A k-tile costs
-  // between `lo` (few workgroups on the chip) and `hi` (all of them: the clock falls under matrix
-  // load), a round 4.9 for its start and its epilogue, a split the second kernel (4) and the partial
-  // products once out and once back in (7.6 TB/s, most of it the last-level cache).  128x128 tiles, two
-  // to a CU, cost `lo` up to one per CU.  Fitted on MI355X to 1200 measurements of products of 4096 to
-  // 10240 columns, K 4096 to 28672, 260 to 5120 rows, weights cold: the choices are within 0.14 % of
-  // the best shape on average, where whole tiles (and a split of the 128x128 ones only) were 14 %
-  // off: N = 4096, K = 14336 at 1000 rows 104 against 135 us, at 1580 rows 172 against 200.
+  // between `lo` (few workgroups on the chip) and `hi` (all of them: the clock falls under matrix load); 128x128
+  // tiles, two to a CU, cost `lo` up to one per CU.  A round of whole tiles has its start and its epilogue, a
+  // cut product the second kernel and the partial products once out and once back in (6.4 TB/s, most of it the
+  // last-level cache); the output projection whole needs the pass that closes the second norm.  Fitted on
+  // MI355X to the three products of twelve layers (256 to 12288 columns, K 256 to 28672) at 40 row counts from
+  // 257 to 5120, weights cold, every shape and cut timed: within 0.5 % of the best on average, and of 1314
+  // products nine are more than 3 % (at most 11 %) slower than with whole tiles and cuts of 128x128 ones only,
+  // which are 15 % off the best.  One cost for every epilogue, fitted to 4096 columns and more, was 1.5 % off
+  // and up to 28 % slower than those where the product is narrow or short: N = K = 1024 at 359 rows 17.6 against
+  // 14.3 us, QKV of N = 10240, K = 8192 at 359 rows 103 against 90 (now 84).
+  struct Epi { double round, second, closing; };
+  const Epi ep = epilogue == EPI_QKV ? Epi{7.1, 5.2, 0.0} : epilogue == EPI_RESID_NORM ? Epi{6.7, 7.4, 4.0} : Epi{5.7, 4.0, 0.0};
+  constexpr double PARTIAL_ROUND = 5.0, PARTIAL_BYTES_PER_US = 6.4e6;
   struct Cand { int v, bm, bn, per_cu; double hi, lo; };
-  const Cand cands[3] = {{V_BIG, 256, 256, 1, 1.39, 1.11}, {V_TALL, 160, 256, 1, 1.09, 0.88}, {V_SMALL, 128, 128, 2, 1.03, 0.53}};
+  const Cand cands[3] = {{V_BIG, 256, 256, 1, 1.35, 1.09}, {V_TALL, 160, 256, 1, 1.05, 1.06}, {V_SMALL, 128, 128, 2, 1.03, 0.63}};
   double best = 1e300;
   for (const Cand &c : cands) {
     const long tiles = n_tiles(a.M, a.N, c.bm, c.bn), slots = (long)n_cu * c.per_cu;
@@ -1110,19 +1117,22 @@ void gemm_plan(GemmArgs &a, int epilogue) {
       const long full = tiles * s / slots, rem = tiles * s % slots;
       double part = 0.0;
       if (rem && c.per_cu == 1) part = c.lo + (c.hi - c.lo) * (double)rem / (double)slots;
-      else if (rem) part = rem <= n_cu ? c.lo : c.lo + (c.hi - c.lo) * (0.55 + 0.45 * (double)(rem - n_cu) / (double)n_cu);
-      double t = (double)((nk + s - 1) / s) * ((double)full * c.hi + part) + 4.9 * (double)(full + (rem ? 1 : 0));
-      if (s > 1) t += 4.0 + 8.0 * (double)s * a.M * a.N / 7.6e6;
+      else if (rem) part = rem <= n_cu ? c.lo : c.lo + (c.hi - c.lo) * (0.59 + 0.41 * (double)(rem - n_cu) / (double)n_cu);
+      double t = (double)((nk + s - 1) / s) * ((double)full * c.hi + part) + (s > 1 ? PARTIAL_ROUND : ep.round) * (double)(full + (rem ? 1 : 0));
+      t += s > 1 ? ep.second + 8.0 * (double)s * a.M * a.N / PARTIAL_BYTES_PER_US : ep.closing;
       if (t < best) { best = t; a.tile_variant = c.v; a.k_splits = (int)s; }
     }
   }
-  // Shared 256x256 tiles: the chip's worth of k-tile iterations with nothing idle, 3 % for the persistent
-  // loop, and 95 us for the cuts (a workgroup passes up to two partial tiles through memory): only
-  // where K is long, and more than one round of tiles cannot be cut evenly.
+  // Shared 256x256 tiles: the chip's worth of k-tile iterations with nothing idle, and 75 us for the cuts (a
+  // workgroup passes up to two partial tiles through memory).  Where the tiles beyond whole rounds are no
+  // multiple of a quarter round, the workgroups walk K in eight and more phases and share fewer panels in L2:
+  // a tenth of a microsecond more per k-tile.  Only where K is long, and more than one round of tiles cannot be
+  // cut evenly (the down projection of the 70B layer at 5120 rows, 2.5 rounds of 448 k-tiles).
   if (may_share && a.K >= 4096 && a.M > 256) {
-    const long tiles = n_tiles(a.M, a.N, 256, 256);
-    const double t = (double)tiles / (double)n_cu * 1.03 * 1.39 * (double)nk + 95.0;
-    if (tiles % n_cu && t < best) { a.tile_variant = V_SHARED; a.k_splits = 1; }
+    const long tiles = n_tiles(a.M, a.N, 256, 256), rem = tiles % n_cu;
+    const double phases = rem ? (double)(n_cu / std::gcd((long)n_cu, rem)) : 1.0;
+    const double t = (double)nk * (1.45 * (double)tiles / (double)n_cu + (phases <= 4 ? 0.0 : phases <= 8 ? 0.1 : 0.11)) + 75.0;
+    if (rem && t < best) { a.tile_variant = V_SHARED; a.k_splits = 1; }
   }
 }
 

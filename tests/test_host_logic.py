@@ -272,3 +272,14 @@ def test_prefill_kernel_by_chunks(heads, dh, segments, rows, cached, want):
     lay = binding.Layer(W.LayerShape(256, heads[0], heads[1], dh, 256), device=-1)
     b = W.assemble_batch(16, [(rows, rows + cached, -1)] * segments, segments, [], None)
     assert lay.attention_division(b).prefill_rows == want
+
+
+@pytest.mark.parametrize("shape,product,rows,want", [
+    (W.LayerShape(1024, 16, 4, 64, 4096), "o", 359, (3, 2)), (W.LayerShape(1024, 16, 4, 64, 4096), "qkv", 300, (3, 2)),
+    (W.LayerShape(2048, 32, 8, 64, 8192), "down", 1000, (1, 8)), (W.LLAMA3_70B, "qkv", 359, (1, 3)),
+    (W.LLAMA3_8B, "down", 1580, (1, 2)), (W.LLAMA3_8B, "o", 5120, (2, 1)), (W.LLAMA3_70B, "down", 5120, (6, 1)),
+    (W.LLAMA3_70B, "qkv", 2200, (1, 1)), (W.LLAMA3_70B, "o", 77, (4, 8)), (W.LLAMA3_8B, "o", 77, (3, 8)), (W.TINY, "o", 257, (3, 1))])
+def test_gemm_division_narrow_short_and_large(shape, product, rows, want):
+    # the measured best or within 3 % of it: narrow and short products that a cost fitted to large ones left
+    # whole, long ones cut, and the products that stay whole
+    assert binding.Layer(shape, device=-1).gemm_division(product, rows) == want
