@@ -312,21 +312,24 @@ AttnShape attn_shape(const bs_ctx *c) {
 // ---------------------------------------------------------------------------------
 // plan: everything the kernels need, packed in one int32 blob
 // ---------------------------------------------------------------------------------
-constexpr int CHUNK_MAX = 64, CHUNK_MIN = 8;  // pages (a lane of a wavefront holds one page id of its chunk)
-constexpr long CHUNK_UNITS = 512, CHUNK_UNITS_WIDE = 1536;  // units of (chunk, KV head) below which chunks are cut shorter
+constexpr int CHUNK_MAX = 64, CHUNK_MAX_WIDE = 32, CHUNK_MIN = 8;  // pages (a lane of a wavefront holds one page id of its chunk)
+// units of (chunk, KV head) below which chunks are cut shorter: steps without wide nodes; beside wide nodes; wide nodes
+constexpr long CHUNK_UNITS = 512, CHUNK_UNITS_BESIDE = 256, CHUNK_UNITS_WIDE = 768;
 // pages per chunk: `wide` for the nodes whose items carry more than 16 query rows, `other` for the rest
 struct Chunks { int other, wide; };
-constexpr Chunks NOALLOC_CHUNKS = {CHUNK_MAX, CHUNK_MAX / 2};  // the division that bs_attention_noalloc's limits count in
+constexpr Chunks NOALLOC_CHUNKS = {CHUNK_MAX, CHUNK_MAX_WIDE};  // the division that bs_attention_noalloc's limits count in
 
 // Pages per chunk of decode-attention work of a step.  A CU streams at most about 36 GB/s of KV pages however many
 // of its wavefronts ask for them, and a wavefront serves its chunk at one page per 0.3 us (64 query
 // rows: 1.2 us), so a step of few sequences is bound by how many CUs have a chunk and by how long one
-// chunk takes: it is cut until there are 512 units of (chunk, KV head), or 1536 where prefix nodes
-// carry more than 16 query rows.  Every chunk costs a partial state per member row, hence no chunk under
-// eight pages, and large steps keep the longest chunk that the kernels take.  Measured (attention +
-// merge, 8B layer; this rule against chunks of 64 pages, 32 under wide nodes): 7 sequences of 2000
-// tokens 25 against 30 us, one of 4000 16 against 28, 40 behind one prefix of 4096 40 against 52,
-// 20 behind two of 1024 28 against 49; 256 of 1024 and 640 behind a two-level tree the same.
+// chunk takes.  Every chunk costs a partial state per member row.  So the pages of a step are cut until there
+// are 512 units of (chunk, KV head); where prefix nodes carry more than 16 query rows their chunks are cut
+// until there would be 768, and never longer than 32 pages, the others until there would be 256; no chunk
+// under eight pages.  Measured (attention + merge) on 240 batches of 8 to 700 sequences, most of them behind wide
+// nodes of 4 to 300 pages, against chunks of 64 pages, 32 in wide nodes: 14 % faster on average (20 sequences
+// behind two prefixes of 1024 tokens 28 against 49 us, 7 of 2000 tokens 25 against 30), in six of them 3 to
+// 8 % slower.  One length for both kinds, cut until there are 1536 units, was 12 % faster on average and
+// slower in 43 (287 sequences behind six prefixes of 2416 tokens, 24 heads in 8 groups: 68 us against 54).
 Chunks chunk_choice(const bs_ctx *c, const bs_batch *b) {
   if (c->chunk_pages > 0) return {c->chunk_pages, c->chunk_pages};
   const int grp = c->cfg.n_q_heads / c->cfg.n_kv_heads, max_members = std::max(1, 64 / grp);
@@ -335,16 +338,19 @@ Chunks chunk_choice(const bs_ctx *c, const bs_batch *b) {
   for (int n = 0; n < b->n_nodes; ++n) {
     const long cnt = b->node_seq_count[n], np = b->node_page_start[n + 1] - b->node_page_start[n];
     if (cnt <= 0 || np <= 0) continue;
-    pages += np * ((cnt + max_members - 1) / max_members);
-    wide = wide || cnt * grp > 16;
+    const long n_groups = (cnt + max_members - 1) / max_members;
+    pages += np * n_groups;
+    wide = wide || ((cnt + n_groups - 1) / n_groups) * grp > 16;
   }
   for (int s = b->n_prefill; s < b->n_seq; ++s) {
     const int leaf = b->n_nodes > 0 ? b->seq_leaf_node[s] : -1;
     pages += (b->kv_len[s] + c->cfg.page_size - 1) / c->cfg.page_size - (leaf >= 0 ? c->path_pages[leaf] : 0);
   }
-  const long ch = pages * c->cfg.n_kv_heads / (wide ? CHUNK_UNITS_WIDE : CHUNK_UNITS);
-  const int pages_each = (int)std::min<long>(CHUNK_MAX, std::max<long>(CHUNK_MIN, (ch + 1) / 2 * 2));
-  return {pages_each, pages_each};
+  auto cut = [&](long units, int most) {
+    const long ch = pages * c->cfg.n_kv_heads / units;
+    return (int)std::min<long>(most, std::max<long>(CHUNK_MIN, (ch + 1) / 2 * 2));
+  };
+  return {cut(wide ? CHUNK_UNITS_BESIDE : CHUNK_UNITS, CHUNK_MAX), cut(CHUNK_UNITS_WIDE, CHUNK_MAX_WIDE)};
 }
 
 // pages per chunk of a node with cnt member rows (one for all its member groups: their partial states
@@ -543,11 +549,11 @@ Chunks attention_chunks(bs_ctx *c, const bs_batch *b) {
     return noalloc_blob_fits(z) && noalloc_states_fit(c, z);
   };
   if (fits(chosen) || !fits(NOALLOC_CHUNKS)) return chosen;
-  for (int p = chosen.other + 2; p < CHUNK_MAX; p += 2) {
-    const Chunks between = {p, std::min(p, NOALLOC_CHUNKS.wide)};
-    if (fits(between)) return between;
-  }
-  return NOALLOC_CHUNKS;
+  Chunks between = chosen;
+  do {  // (both reach the fixed division, which fits)
+    between = {std::min(between.other + 2, CHUNK_MAX), std::min(between.wide + 2, CHUNK_MAX_WIDE)};
+  } while (!fits(between));
+  return between;
 }
 
 // The plan of bs_attention_noalloc.  What fits is decided by the fixed division of the contexts, so that it

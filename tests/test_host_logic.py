@@ -162,16 +162,15 @@ NOALLOC_WORDS = (1 << 20) // 4   # descriptor limit of bs_attention_noalloc, in 
 
 
 def _near_the_descriptor_limit(fill_pages):
-    # one KV head: 242 private tails of 57 pages and one shared page (32 query rows) are cut into chunks of
-    # eight pages, 1694 items more than chunks of 64; prefill tables of `fill_pages` pages fill the descriptor
+    # one KV head: 80 contexts of 57 pages are cut into chunks of eight pages, 560 items more than chunks
+    # of 64; prefill tables of `fill_pages` pages fill the descriptor
     seqs = []
     while fill_pages > 0:
         pages = min(1024, fill_pages)
         seqs.append((1, 16 * pages, -1))
         fill_pages -= pages
     n_prefill = len(seqs)
-    seqs += [(1, 16 + 20, 0)] * 2 + [(1, 57 * 16, -1)] * 242
-    return W.assemble_batch(16, seqs, n_prefill, [(-1, 1)], None)
+    return W.assemble_batch(16, seqs + [(1, 57 * 16, -1)] * 80, n_prefill, [], None)
 
 
 def _fields(d):
@@ -182,23 +181,23 @@ def test_noalloc_division_never_outgrows_the_descriptor_buffer():
     lay = binding.Layer(W.LayerShape(256, 16, 1, 64, 256), device=-1)
     empty = _near_the_descriptor_limit(0)
     coarse, fine = lay.attention_division(empty, noalloc=True), lay.attention_division(empty)
-    assert fine.longest_item_tokens[0] == 128 and fine.items - (242 + 2 + 1) == 242 * 7
+    assert fine.longest_item_tokens[0] == 128 and fine.items == 80 * 8
     assert (coarse.items, coarse.descriptor_words) == (fine.items, fine.descriptor_words)   # far from the limit: taken as it is
     lay.set_chunk_pages(8)
-    fine_words = [lay.attention_division(_near_the_descriptor_limit(f)).descriptor_words for f in (228_500, 236_000)]
+    fine_words = [lay.attention_division(_near_the_descriptor_limit(f)).descriptor_words for f in (248_000, 254_000)]
     assert fine_words[0] <= NOALLOC_WORDS < fine_words[1]   # the finer division stops fitting within the range
     lay = binding.Layer(W.LayerShape(256, 16, 1, 64, 256), device=-1)
-    for fill in range(228_500, 236_001, 150):
+    for fill in range(248_000, 254_001, 150):
         b = _near_the_descriptor_limit(fill)
         got = lay.attention_division(b, noalloc=True)
         assert got.descriptor_words <= NOALLOC_WORDS
         assert _fields(got) == _fields(lay.attention_division(b))
-    # what the fixed division (chunks of 64 pages: no node here is longer than one) fits is accepted, what it
+    # what the fixed division (chunks of 64 pages) fits is accepted, what it
     # does not fit is refused
     fixed = binding.Layer(W.LayerShape(256, 16, 1, 64, 256), device=-1)
     fixed.set_chunk_pages(64)
-    spare = NOALLOC_WORDS - fixed.attention_division(_near_the_descriptor_limit(236_000)).descriptor_words
-    for fill in range(236_000 + spare - 70, 236_000 + spare + 10, 10):   # (a prefill segment takes nine words beside its table)
+    spare = NOALLOC_WORDS - fixed.attention_division(_near_the_descriptor_limit(254_000)).descriptor_words
+    for fill in range(254_000 + spare - 70, 254_000 + spare + 10, 10):   # (a prefill segment takes nine words beside its table)
         b = _near_the_descriptor_limit(fill)
         if fixed.attention_division(b).descriptor_words <= NOALLOC_WORDS:
             assert lay.attention_division(b, noalloc=True).descriptor_words <= NOALLOC_WORDS
@@ -283,3 +282,13 @@ def test_gemm_division_narrow_short_and_large(shape, product, rows, want):
     # the measured best or within 3 % of it: narrow and short products that a cost fitted to large ones left
     # whole, long ones cut, and the products that stay whole
     assert binding.Layer(shape, device=-1).gemm_division(product, rows) == want
+
+
+@pytest.mark.parametrize("heads,n,tail,groups,pages,want", [
+    ((24, 8), 287, 32, 6, 151, (32, 512)), ((32, 8), 640, 400, 4, 128, (400, 512)),    # large steps: no wide chunk beyond 32 pages
+    ((32, 8), 20, 16, 2, 64, (16, 128)), ((64, 8), 105, 181, 6, 5, (181, 80)),        # few: cut; tails beside wide nodes stay whole
+    ((32, 8), 7, 2000, 0, 0, (224, 0)), ((32, 8), 256, 1024, 0, 0, (1024, 0)), ((16, 8), 8, 3000, 2, 100, (416, 0))])
+def test_chunks_of_decode_attention(heads, n, tail, groups, pages, want):
+    lay = binding.Layer(W.LayerShape(256, heads[0], heads[1], 128, 256), device=-1)
+    b = W.assemble_batch(16, [(1, tail + 16 * pages, i * groups // n if groups else -1) for i in range(n)], 0, [(-1, pages)] * groups, None)
+    assert tuple(lay.attention_division(b).longest_item_tokens) == want
