@@ -770,14 +770,10 @@ constexpr int BLENDED_LDS(int dh) {
   return PF_LDS(dh) > 2 * DECODE_Q_LDS(dh, 4) ? PF_LDS(dh) : 2 * DECODE_Q_LDS(dh, 4);
 }
 
-// a launch of 256-thread workgroups with `lds` bytes of dynamic LDS (`configured`: once per kernel)
+// a launch of 256-thread workgroups with `lds` bytes of dynamic LDS (`once`: one per kernel)
 template <class Kernel, class... Args>
-hipError_t launch_with_lds(Kernel kernel, bool &configured, int grid, int lds, hipStream_t stream, Args... args) {
-  if (!configured) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-    configured = true;
-  }
+hipError_t launch_with_lds(Kernel kernel, OncePerDevice &once, int grid, int lds, hipStream_t stream, Args... args) {
+  if (const hipError_t e = allow_lds(once, reinterpret_cast<const void *>(kernel), lds)) return e;
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), lds, stream, args...);
   return hipGetLastError();
 }
@@ -836,11 +832,11 @@ hipError_t launch_blended_attn(const DecodeArgs &d, int n_wide, int n_narrow, co
   // 70B shapes: 3 and 5 are the fastest, the long ones cost 1-3 % of the launch); odd, so that the prefill
   // workgroups visit every XCD in turn
   const int period = n_dec >= 4 * n_pf ? 5 : 3;
-  static bool configured[2] = {false, false};
+  static OncePerDevice once[2];
   if (d.s.head_dim == 128)
-    return launch_with_lds(blended_attn_kernel<128>, configured[0], n_dec + n_pf, BLENDED_LDS(128), stream, d, n_wide_units, n_narrow_units, pf, n_pf, period);
+    return launch_with_lds(blended_attn_kernel<128>, once[0], n_dec + n_pf, BLENDED_LDS(128), stream, d, n_wide_units, n_narrow_units, pf, n_pf, period);
   if (d.s.head_dim == 64)
-    return launch_with_lds(blended_attn_kernel<64>, configured[1], n_dec + n_pf, BLENDED_LDS(64), stream, d, n_wide_units, n_narrow_units, pf, n_pf, period);
+    return launch_with_lds(blended_attn_kernel<64>, once[1], n_dec + n_pf, BLENDED_LDS(64), stream, d, n_wide_units, n_narrow_units, pf, n_pf, period);
   return hipErrorInvalidValue;
 }
 
@@ -892,9 +888,9 @@ hipError_t launch_prefill_attn(const PrefillArgs &a, const PrefillRoute &route, 
     else return hipErrorInvalidValue;
     return hipGetLastError();
   }
-  static bool configured[2] = {false, false};
-  if (a.s.head_dim == 128) return launch_with_lds(prefill_attn_kernel<128>, configured[0], grid, PF_LDS(128), stream, a, hpw);
-  if (a.s.head_dim == 64) return launch_with_lds(prefill_attn_kernel<64>, configured[1], grid, PF_LDS(64), stream, a, hpw);
+  static OncePerDevice once[2];
+  if (a.s.head_dim == 128) return launch_with_lds(prefill_attn_kernel<128>, once[0], grid, PF_LDS(128), stream, a, hpw);
+  if (a.s.head_dim == 64) return launch_with_lds(prefill_attn_kernel<64>, once[1], grid, PF_LDS(64), stream, a, hpw);
   return hipErrorInvalidValue;
 }
 

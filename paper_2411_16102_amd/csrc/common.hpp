@@ -3,6 +3,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "once.hpp"
 
 namespace bs {
 
@@ -58,6 +59,14 @@ __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
+}
+
+// allows launches of `kernel` on the current device `lds` bytes of dynamic LDS
+inline hipError_t allow_lds(OncePerDevice &once, const void *kernel, int lds) {
+  int device = 0;
+  const hipError_t e = hipGetDevice(&device);
+  if (e != hipSuccess) return e;
+  return (hipError_t)once(device, [&] { return (int)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds); });
 }
 
 }  // namespace bs

@@ -878,13 +878,8 @@ hipError_t launch_one(const GemmArgs &a, hipStream_t stream) {
   constexpr int OUT_BN = (EPI == EPI_SWIGLU) ? BN / 2 : BN;
   constexpr int LDS = DEEP ? 160 * 1024 : NU * (BM > BN ? BM : BN) * BK * 2;
   auto kern = gemm_kernel<BM, BN, WAVES_M, WAVES_N, EPI, DH, DEEP>;
-  static bool configured = false;
-  if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-    if (e != hipSuccess) return e;
-    configured = true;
-  }
+  static OncePerDevice once;
+  if (const hipError_t e = allow_lds(once, reinterpret_cast<const void *>(kern), LDS)) return e;
   const int n_cols = a.n_count ? a.n_count : a.N;
   const int tiles = ((a.M + BM - 1) / BM) * ((n_cols + OUT_BN - 1) / OUT_BN) * (EPI == EPI_PARTIAL ? a.k_splits : 1);
   if (tiles <= 0) return hipSuccess;
@@ -901,13 +896,8 @@ hipError_t launch_sk(const GemmArgs &a, hipStream_t stream) {
   static_assert(BM == 256 && BN == 256, "the workspace slots are sized for 256x256 tiles");
   if (!a.sk_ws || !a.sk_cnt || a.n_count || a.k_splits > 1) return hipErrorInvalidValue;
   auto kern = gemm_sk_kernel<BM, BN, WAVES_M, WAVES_N, EPI, DH>;
-  static bool configured = false;
-  if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-    if (e != hipSuccess) return e;
-    configured = true;
-  }
+  static OncePerDevice once;
+  if (const hipError_t e = allow_lds(once, reinterpret_cast<const void *>(kern), LDS)) return e;
   const long tiles = (long)((a.M + BM - 1) / BM) * ((a.N + OUT_BN - 1) / OUT_BN);
   if (tiles <= 0) return hipSuccess;
   const int G = a.n_cu > 0 && a.n_cu < SK_MAX_G ? a.n_cu : SK_MAX_G;
@@ -937,13 +927,8 @@ hipError_t launch_ride(const GemmArgs &a, const GemmRide &r, hipStream_t stream)
   constexpr int LDS = NU * (BM > BN ? BM : BN) * BK * 2;
   static_assert(LDS == 160 * 1024, "a workgroup of either kind must take the whole LDS of its CU");
   auto kern = gemm_attn_kernel<BM, BN, WAVES_M, WAVES_N, EPI, 64, ADH>;
-  static bool configured = false;
-  if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-    if (e != hipSuccess) return e;
-    configured = true;
-  }
+  static OncePerDevice once;
+  if (const hipError_t e = allow_lds(once, reinterpret_cast<const void *>(kern), LDS)) return e;
   const int tiles = ((a.M + BM - 1) / BM) * ((a.N + OUT_BN - 1) / OUT_BN);
   if (tiles <= 0) return hipErrorInvalidValue;
   // (a negative margin: no tile closes the queue, the launch drains it)

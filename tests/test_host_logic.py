@@ -1,5 +1,7 @@
 """CPU-side checks of the library: exported symbols, descriptor validation and
 bit-exact page resolution against the oracle's resolver.  No GPU is touched."""
+import os
+
 import numpy as np
 import pytest
 
@@ -292,3 +294,41 @@ def test_chunks_of_decode_attention(heads, n, tail, groups, pages, want):
     lay = binding.Layer(W.LayerShape(256, heads[0], heads[1], 128, 256), device=-1)
     b = W.assemble_batch(16, [(1, tail + 16 * pages, i * groups // n if groups else -1) for i in range(n)], 0, [(-1, pages)] * groups, None)
     assert tuple(lay.attention_division(b).longest_item_tokens) == want
+
+
+def test_a_setting_of_a_device_is_made_on_each_device(tmp_path):
+    # kernels whose launches need more than 64 KB of LDS are allowed it per device: from two devices, again after
+    # a failure, and from threads that race for it
+    import subprocess
+    src = tmp_path / "once.cpp"
+    src.write_text("""
+#include <cstdio>
+#include <thread>
+#include <vector>
+#include "once.hpp"
+int main() {
+  bs::OncePerDevice once;
+  int made[3] = {0, 0, 0};
+  for (int turn = 0; turn < 3; ++turn)
+    for (int d = 0; d < 2; ++d)
+      if (once(d, [&] { ++made[d]; return 0; })) return 1;
+  if (made[0] != 1 || made[1] != 1) return 2;
+  if (once(2, [&] { ++made[2]; return 7; }) != 7 || once(2, [&] { ++made[2]; return 0; }) != 0 || made[2] != 2) return 3;
+  if (once(64, [&] { return 5; }) != 5) return 4;
+  bs::OncePerDevice shared;
+  std::atomic<int> seen{0};
+  std::vector<std::thread> threads;
+  for (int t = 0; t < 8; ++t)
+    threads.emplace_back([&] {
+      std::atomic<bool> mine{false};
+      for (int i = 0; i < 1000; ++i)
+        if (shared(i % 48, [&] { mine = true; return 0; })) seen = -1000000;
+      if (mine) ++seen;
+    });
+  for (auto &t : threads) t.join();
+  return seen >= 1 ? 0 : 5;
+}
+""")
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2411_16102_amd", "csrc")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-pthread", "-I", csrc, "-o", str(tmp_path / "once"), str(src)])
+    assert subprocess.call([str(tmp_path / "once")]) == 0
