@@ -43,7 +43,7 @@ using namespace attn_dev;
 // -9 % with 1280 wide and 2048 narrow workgroups, +2 % with 390 and 1812, hence the rule).
 // The period is odd on purpose: workgroups go to the eight XCDs in turn, and a period of
 // four would send every wide workgroup to the same two of them.
-template <int DH, int WPW, bool NT_NARROW, bool ACC_A>
+template <int DH, int WPW, bool NT_NARROW>
 __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, int n_wide_units, int n_narrow_units, int b, int wave,
                                                  int lane, uint16_t *q_sh) {
   constexpr int WQB = 4;  // blocks of 16 query rows of a wide item
@@ -66,9 +66,9 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, int n_wide
   }
   const int unit = wg * WPW + wave;
   if (wide) {
-    if (unit < n_wide_units) decode_unit<DH, WQB, false, ACC_A>(a, unit / hkv, unit % hkv, wave, lane, q_sh);
+    if (unit < n_wide_units) decode_unit<DH, WQB, false, true>(a, unit / hkv, unit % hkv, wave, lane, q_sh);
   } else {
-    if (unit < n_narrow_units) decode_unit<DH, 1, NT_NARROW, ACC_A>(a, n_wide_units / hkv + unit / hkv, unit % hkv, wave, lane, q_sh);
+    if (unit < n_narrow_units) decode_unit<DH, 1, NT_NARROW, true>(a, n_wide_units / hkv + unit / hkv, unit % hkv, wave, lane, q_sh);
   }
 }
 
@@ -78,7 +78,7 @@ template <int DH>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void decode_attn_kernel(const DecodeArgs a, int n_wide_units, int n_narrow_units) {
   __shared__ __align__(16) uint16_t q_sh[DECODE_Q_LDS(DH, 1)];
   // a launch of decode units alone: non-temporal loads for the 16-row units (see ld16_kv)
-  decode_workgroup<DH, 1, true, true>(a, n_wide_units, n_narrow_units, blockIdx.x, 0, threadIdx.x & 63, q_sh);
+  decode_workgroup<DH, 1, true>(a, n_wide_units, n_narrow_units, blockIdx.x, 0, threadIdx.x & 63, q_sh);
 }
 
 // 16-row units alone (no prefix node with more than 16 member rows): under half of a SIMD's registers,
@@ -188,7 +188,8 @@ __device__ __forceinline__ int swap_bits_2_3(int v) { return (v & ~12) | ((v & 4
 // s = k q^T + s (FIRST: + 0) with the accumulators in ordinary registers, where the softmax reads them
 // (left to the compiler, a kernel of more than 256 registers keeps every MFMA result in accumulation
 // registers and copies it out: 130 copies per block).  The compiler does not see the latency: whoever
-// reads s leaves at least eight MFMAs, which execute in order, or mfma_settle between.
+// reads s leaves at least four further MFMAs, which execute in order (two would cover the 12 wait states of
+// this one), or mfma_settle between.
 template <bool FIRST>
 __device__ __forceinline__ void score_mfma(f32x16_t &s, bf16x8_t k, bf16x8_t q) {
   if constexpr (FIRST)
@@ -416,6 +417,7 @@ __device__ __forceinline__ void prefill_workgroup(const PrefillArgs &a, int head
     // for query block 0 and for query block 1.  Pairs of probabilities EARLY .. 15 go beside the scores and
     // the first PV product; beside the second, query block 0 of block tb+1 settles and gives its first pairs.
     constexpr int N_QK = NQ * KC, N_PV = 2 * DB, N_W = N_QK + N_PV;
+    static_assert(N_PV >= 4, "the scores of block tb+1 are read behind the first PV product alone (see score_mfma)");
     constexpr bool LAST = decltype(last)::value;  // nothing follows; the only block that can run past the context
     auto weights_of = [&](int j) __attribute__((always_inline)) {  // slot j of N_W
 #pragma unroll
@@ -752,7 +754,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   if (prefill)
     prefill_workgroup<DH>(pf, 4, idx, wave, lane, attn_smem);
   else
-    decode_workgroup<DH, 4, false, true>(d, n_wide_units, n_narrow_units, idx, wave, lane, reinterpret_cast<uint16_t *>(attn_smem));
+    decode_workgroup<DH, 4, false>(d, n_wide_units, n_narrow_units, idx, wave, lane, reinterpret_cast<uint16_t *>(attn_smem));
 }
 
 // What the GEMM launches of a step have left of its queue of 16-row units, on the whole chip:

@@ -107,6 +107,7 @@ template <int DH, int NQB, bool NT = false, bool ACC_A = false>
 __device__ __forceinline__ void decode_unit(const DecodeArgs &a, int item, int kvh, int wave, int lane, uint16_t *q_sh) {
   constexpr int KC = DH / 32;  // 32-wide chunks of the head dimension (QK^T contraction)
   constexpr int DB = DH / 16;  // 16-row blocks of the head dimension (PV output rows)
+  static_assert(2 * KC >= 4 && DB >= 4, "a block's scores are read behind the next block's or a PV product (see score_mfma16)");
   const int hkv = a.s.n_kv_heads, hq = a.s.n_q_heads, grp = hq / hkv;
   const DecodeItem it = a.items[item];
   const int n_rows = it.n_members * grp;
