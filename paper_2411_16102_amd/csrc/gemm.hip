@@ -953,18 +953,20 @@ thread_local int g_forced_variant = V_AUTO;  // set by the calling entry point f
 
 long n_tiles(int m, int n, int bm, int bn) { return (long)((m + bm - 1) / bm) * ((n + bn - 1) / bn); }
 
-// Estimated time of a launch in units of one full round of 256x256 tiles: full rounds of
-// workgroups (the 128x128 tile runs two per CU) cost T each; a last, partly filled round costs
-// T (a + (1 - a) fill): workgroups that share the chip with fewer others run faster, but not in
-// proportion.  T and a were fitted on MI355X to the four GEMM shapes of the 8B layer at 384 to
-// 2560 rows (the 160x256 tile: 0.072 ms per full round at K = 4096 where the 256x256 tile takes
-// 0.100 and 512 tiles of 128x128 take 0.075).
 // few rows: one tile row on the deep weight ring (0 where the rows do not fit one tile, or a shape is forced)
 int short_variant(int m) {
   if (g_forced_variant != V_AUTO || m > 256) return 0;
   return m <= 128 ? V_S128 : V_S256;
 }
 
+// Tile shape of a gate/up or plain product, or of any with a forced shape (QKV, output and down projection:
+// gemm_plan).
+// Estimated time of a launch in units of one full round of 256x256 tiles: full rounds of
+// workgroups (the 128x128 tile runs two per CU) cost T each; a last, partly filled round costs
+// T (a + (1 - a) fill): workgroups that share the chip with fewer others run faster, but not in
+// proportion.  T and a were fitted on MI355X to the four GEMM shapes of the 8B layer at 384 to
+// 2560 rows (the 160x256 tile: 0.072 ms per full round at K = 4096 where the 256x256 tile takes
+// 0.100 and 512 tiles of 128x128 take 0.075).
 // share_k: the contraction length if the launch may share tiles between workgroups (it has the
 // workspace for it and covers all columns), else 0
 int choose_variant(int m, int n_b_rows, int epilogue, int dh, int n_cu, int share_k = 0) {
@@ -990,8 +992,7 @@ int choose_variant(int m, int n_b_rows, int epilogue, int dh, int n_cu, int shar
   // Shared 256x256 tiles: the chip's worth of k-tile iterations with nothing idle, 3 % for the
   // persistent loop, and what the cuts cost: a workgroup passes up to two partial tiles through
   // memory, about 0.08 ms per launch whatever its size (measured on the GEMMs of the 8B and 70B
-  // layers), i.e. 53 k-tiles' worth of a round.  It pays only where K is long: the down
-  // projection of the 70B layer at 5120 rows, 2.5 rounds of 448 k-tiles, 1.92 against 2.11 ms.
+  // layers), i.e. 53 k-tiles' worth of a round.  It pays only where K is long.
   if (share_k >= 4096 && m > 256) {
     const long tiles = n_tiles(m, n_b_rows, 256, 256);
     const long g = std::min<long>(n_cu, N_CU);
