@@ -20,9 +20,10 @@ def to_np(t):
     return t.float().cpu().numpy().astype(np.float64)
 
 
-def run_step(lib, shape, batch, tens, flags=0):
+def run_step(lib, shape, batch, tens, flags=0, tiles=0):
     import torch
     layer = lib.Layer(shape, device=0)
+    layer.set_gemm_tiles(tiles)
     dev = layer.upload(tens, batch)
     y = layer.blend_step(dev, batch, flags=flags)
     torch.cuda.synchronize()
@@ -30,10 +31,10 @@ def run_step(lib, shape, batch, tens, flags=0):
     return to_np(y), to_np(k), to_np(v), layer
 
 
-def check_step(lib, shape, batch, tens, flags=0):
+def check_step(lib, shape, batch, tens, flags=0, tiles=0):
     ref = O.layer_step(shape, tens, batch)
     diag = O.layer_step(shape, tens, batch, storage="bf16")
-    y, k, v, layer = run_step(lib, shape, batch, tens, flags)
+    y, k, v, layer = run_step(lib, shape, batch, tens, flags, tiles)
     check(y, ref["y"], diag["y"], "rows=%d" % batch.n_rows)
     # KV append: exactly the destination slots change, and they hold k, v of the rows
     k0 = W.bf16_bits_to_f32(tens.k_pool).astype(np.float64)
@@ -125,9 +126,25 @@ def test_layer_step_on_shared_tiles(lib, shape):
 @pytest.mark.parametrize("rows", [77, 256, 257, 640, 1000])
 def test_layer_step_on_tiles_cut_along_k(lib, rows):
     # few enough rows that whole tiles would leave CUs idle: the down projection (193 k-tiles, the last one
-    # partial) is cut into ranges of 128x128, 256x128, 160x256 (640 rows) and 256x256 tiles (1000 rows)
+    # partial) is cut into ranges of 128x128, 256x128, 160x256 and 256x256 tiles
     shape = W.LayerShape(4096, 8, 2, 128, 12296)
+    assert lib.Layer(shape, device=-1).gemm_division("down", rows) == {77: (3, 8), 256: (5, 8), 257: (2, 8), 640: (2, 4), 1000: (1, 4)}[rows]
     seqs = [(rows - 13, rows - 3, -1)] + [(1, 20 + 9 * i, -1) for i in range(13)]
+    batch = W.assemble_batch(16, seqs, 1, [], np.random.default_rng(rows))
+    check_step(lib, shape, batch, W.make_tensors(shape, batch, rows, gains="random"))
+
+
+@pytest.mark.parametrize("shape,rows,want", [
+    # 128x256 tiles on the deep weight ring: every product of at most 128 rows, and QKV of 64-wide heads
+    (W.LayerShape(6656, 32, 16, 128, 4104), 97, [(4, 8), (4, 8), (4, 8)]), (W.LayerShape(6656, 32, 16, 128, 4104), 128, [(4, 8), (4, 8), (4, 8)]),
+    (W.LayerShape(4096, 64, 64, 64, 512), 100, [(4, 5), (3, 8), (3, 1)]),
+    # 160x256 and 256x256 tiles cut along K under the QKV and the output projection
+    (W.LayerShape(4096, 64, 8, 64, 1032), 271, [(2, 6), (2, 8), (3, 1)]), (W.LayerShape(5120, 40, 8, 128, 520), 389, [(2, 3), (2, 4), (3, 1)]),
+    (W.LayerShape(5120, 40, 8, 128, 520), 499, [(1, 4), (1, 5), (3, 1)]), (W.LayerShape(4096, 32, 32, 128, 520), 389, [(1, 2), (2, 5), (3, 1)])])
+def test_layer_step_on_wide_tiles_cut_along_k(lib, shape, rows, want):
+    layer = lib.Layer(shape, device=-1)
+    assert [layer.gemm_division(p, rows) for p in ("qkv", "o", "down")] == want
+    seqs = [(rows - 21, rows - 5, -1)] + [(1, 20 + 9 * i, -1) for i in range(21)]
     batch = W.assemble_batch(16, seqs, 1, [], np.random.default_rng(rows))
     check_step(lib, shape, batch, W.make_tensors(shape, batch, rows, gains="random"))
 
@@ -334,20 +351,39 @@ def test_random_batches_head_dim_128(lib, seed):
     check_step(lib, shape, batch, tens)
 
 
-def test_many_rows_use_large_tiles(lib):
-    # enough rows for the 256x256-tile instances, ragged in every dimension
+@pytest.mark.parametrize("heads", [(3, 3), (4, 2), (6, 2), (10, 2)])
+@pytest.mark.parametrize("dh", [64, 128])
+def test_step_with_few_heads_per_group(lib, heads, dh):
+    # one, two, three and five query heads per KV head: long and short chunks beside decode rows with and without a prefix
+    shape = W.LayerShape(256, heads[0], heads[1], dh, 264)
+    seqs = [(300, 517, -1), (40, 90, -1), (257, 257, -1)] + [(1, 200 + 13 * i, 0) for i in range(40)] + [(1, 7 + 31 * i, -1) for i in range(20)]
+    batch = W.assemble_batch(16, seqs, 3, [(-1, 11)], np.random.default_rng(heads[0]))
+    check_step(lib, shape, batch, W.make_tensors(shape, batch, dh, gains="random"))
+
+
+@pytest.mark.parametrize("tiles", [0, 1, 2])
+def test_many_rows_use_large_tiles(lib, tiles):
+    # several rows of tiles, ragged in every dimension: as chosen (128x128, cut along K or whole), and every
+    # product on whole 256x256 and 160x256 tiles (QKV, whose wavefronts must cover whole heads, not on the latter)
     shape = W.LayerShape(1024, 8, 2, 128, 2056)
+    layer = lib.Layer(shape, device=-1)
+    layer.set_gemm_tiles(tiles)
+    got = [layer.gemm_division(p, 1141) for p in ("qkv", "o", "down")]
+    assert got == ([(3, 1), (3, 2), (3, 3)], [(1, 1)] * 3, [(3, 2), (2, 1), (2, 1)])[tiles]
     batch = W.assemble_batch(16, [(700, 700, -1), (391, 500, -1)] + [(1, 200 + 7 * i, -1) for i in range(50)], 2,
                              [], np.random.default_rng(5))
     tens = W.make_tensors(shape, batch, 5)
-    check_step(lib, shape, batch, tens)
+    check_step(lib, shape, batch, tens, tiles=tiles)
 
 
 @pytest.mark.parametrize("n_decode,q_rows", [(60, 40), (120, 80), (97, 0)])
 def test_few_rows_take_the_deep_weight_ring(lib, n_decode, q_rows):
-    # at most 128 / 256 rows: the QKV, output and down projections run as k-ranges of a single
-    # row of tiles on the pipeline with its own look-ahead for the weight panel
+    # at most 256 rows: the QKV, output and down projections run as k-ranges of a single row of 256x128 tiles on the
+    # pipeline with its own look-ahead for the weight panel; of 128 rows and less, this narrow, on 128x128 tiles
+    # (wide ones on 128x256 tiles: test_layer_step_on_wide_tiles_cut_along_k)
     shape = W.LayerShape(1024, 8, 2, 128, 2048)
+    layer = lib.Layer(shape, device=-1)
+    assert [layer.gemm_division(p, n_decode + q_rows)[0] for p in ("qkv", "o", "down")] == [5 if n_decode + q_rows > 128 else 3] * 3
     seqs = ([(q_rows, q_rows + 30, -1)] if q_rows else []) + [(1, 50 + 11 * i, -1) for i in range(n_decode)]
     batch = W.assemble_batch(16, seqs, 1 if q_rows else 0, [], np.random.default_rng(n_decode))
     tens = W.make_tensors(shape, batch, 7, gains="random")
