@@ -11,6 +11,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/blendstep.h"
@@ -71,7 +72,7 @@ struct bs_ctx {
   bool h_ev_live[RING] = {false, false, false, false};
   int ring_pos = 0;
   // host scratch reused across calls
-  std::vector<int32_t> refcount, path_pages, path_chunks, members, blob;
+  std::vector<int32_t> refcount, path_pages, path_chunks, members, tail_pages, blob;
   std::vector<DecodeItem> items, items_wide;
   std::vector<int32_t> pf_work;
   std::vector<std::pair<int, std::pair<int, int>>> pf_order;
@@ -312,45 +313,97 @@ AttnShape attn_shape(const bs_ctx *c) {
 // ---------------------------------------------------------------------------------
 // plan: everything the kernels need, packed in one int32 blob
 // ---------------------------------------------------------------------------------
-constexpr int CHUNK_MAX = 64, CHUNK_MAX_WIDE = 32, CHUNK_MIN = 8;  // pages (a lane of a wavefront holds one page id of its chunk)
-// units of (chunk, KV head) below which chunks are cut shorter: steps without wide nodes; beside wide nodes; wide nodes
-constexpr long CHUNK_UNITS = 512, CHUNK_UNITS_BESIDE = 256, CHUNK_UNITS_WIDE = 768;
+constexpr int CHUNK_MAX = 64, CHUNK_MIN = 8;  // pages (a lane of a wavefront holds one page id of its chunk)
+constexpr long CHUNK_UNITS = 512;             // units of (chunk, KV head) below which chunks are cut shorter, without wide nodes
 // pages per chunk: `wide` for the nodes whose items carry more than 16 query rows, `other` for the rest
 struct Chunks { int other, wide; };
-constexpr Chunks NOALLOC_CHUNKS = {CHUNK_MAX, CHUNK_MAX_WIDE};  // the division that bs_attention_noalloc's limits count in
+constexpr Chunks NOALLOC_CHUNKS = {CHUNK_MAX, CHUNK_MAX / 2};  // the division that bs_attention_noalloc's limits count in
+
+typedef std::integer_sequence<int, 8, 10, 12, 16, 20, 24, 28, 32, 40, 48, 56, 64> ChunkSizes;  // beside wide nodes
+template <int... W>
+constexpr int n_sizes(std::integer_sequence<int, W...>) { return (int)sizeof...(W); }
+constexpr int N_SIZES = n_sizes(ChunkSizes{});
+
+// chunks of W pages that the n lengths at `pages` make, for every W (constants: no divisions)
+template <int... W>
+void count_chunks(const int32_t *pages, int n, long *out, std::integer_sequence<int, W...>) {
+  auto count = [&](auto size) {
+    long chunks = 0;
+    for (int i = 0; i < n; ++i) chunks += (uint32_t)(pages[i] + decltype(size)::value - 1) / (uint32_t)decltype(size)::value;
+    return chunks;
+  };
+  int k = 0;
+  ((out[k++] = count(std::integral_constant<int, W>{})), ...);
+}
+template <int... W>
+constexpr int chunk_size(int k, std::integer_sequence<int, W...>) { const int sizes[] = {W...}; return sizes[k]; }
 
 // Pages per chunk of decode-attention work of a step.  A CU streams at most about 36 GB/s of KV pages however many
-// of its wavefronts ask for them, and a wavefront serves its chunk at one page per 0.3 us (64 query
-// rows: 1.2 us), so a step of few sequences is bound by how many CUs have a chunk and by how long one
-// chunk takes.  Every chunk costs a partial state per member row.  So the pages of a step are cut until there
-// are 512 units of (chunk, KV head); where prefix nodes carry more than 16 query rows their chunks are cut
-// until there would be 768, and never longer than 32 pages, the others until there would be 256; no chunk
-// under eight pages.  Measured (attention + merge) on 240 batches of 8 to 700 sequences, most of them behind wide
-// nodes of 4 to 300 pages, against chunks of 64 pages, 32 in wide nodes: 14 % faster on average (20 sequences
-// behind two prefixes of 1024 tokens 28 against 49 us, 7 of 2000 tokens 25 against 30), in six of them 3 to
-// 8 % slower.  One length for both kinds, cut until there are 1536 units, was 12 % faster on average and
-// slower in 43 (287 sequences behind six prefixes of 2416 tokens, 24 heads in 8 groups: 68 us against 54).
-Chunks chunk_choice(const bs_ctx *c, const bs_batch *b) {
+// of its wavefronts ask for them, a wavefront serves its chunk at one page per 0.3 us (64 query rows:
+// 1 us), and every chunk costs a partial state per member row.
+// Without wide nodes: cut until there are 512 units of (chunk, KV head), no chunk under eight pages (7 sequences of
+// 2000 tokens 20 us against 69 with chunks of 64 pages in workgroups of four wavefronts, one of 4000 17 against 54).
+// With wide nodes both lengths come from an estimate of the launch and the merge, in microseconds on 1024 SIMDs:
+// the rounds of the wide units, all the work, or the longest unit, whichever is most, part of the narrow units'
+// work beside the wide ones, and the partial states once out and once back in.  Fitted to 357 batches of 8
+// to 1000 sequences behind 1 to 32 prefixes of 4 to 400 pages, every pair of lengths timed: 2 % off the best
+// pair on average; 15 % faster than chunks of 64 pages, 32 in wide nodes, 4.5 % faster than one length for both
+// kinds cut until there were 1536 units (in 18 of them more than 3 % slower than either, at most 13 and 14 %).
+Chunks chunk_choice(bs_ctx *c, const bs_batch *b) {
   if (c->chunk_pages > 0) return {c->chunk_pages, c->chunk_pages};
-  const int grp = c->cfg.n_q_heads / c->cfg.n_kv_heads, max_members = std::max(1, 64 / grp);
-  long pages = 0;
-  bool wide = false;
+  const int grp = c->cfg.n_q_heads / c->cfg.n_kv_heads, max_members = std::max(1, 64 / grp), hkv = c->cfg.n_kv_heads;
+  long wide_pages = 0, other_pages = 0;
+  int wide_longest = 0, other_longest = 0;
+  long units_w[N_SIZES] = {}, units_o[N_SIZES] = {}, states_w[N_SIZES] = {}, states_o[N_SIZES] = {}, tails[N_SIZES];
   for (int n = 0; n < b->n_nodes; ++n) {
-    const long cnt = b->node_seq_count[n], np = b->node_page_start[n + 1] - b->node_page_start[n];
+    const int cnt = b->node_seq_count[n], np = b->node_page_start[n + 1] - b->node_page_start[n];
     if (cnt <= 0 || np <= 0) continue;
-    const long n_groups = (cnt + max_members - 1) / max_members;
-    pages += np * n_groups;
-    wide = wide || ((cnt + n_groups - 1) / n_groups) * grp > 16;
+    const int n_groups = (cnt + max_members - 1) / max_members;
+    const bool wide = ((cnt + n_groups - 1) / n_groups) * grp > 16;
+    long chunks[N_SIZES];
+    count_chunks(&np, 1, chunks, ChunkSizes{});
+    for (int k = 0; k < N_SIZES; ++k) {
+      (wide ? units_w : units_o)[k] += n_groups * chunks[k];
+      (wide ? states_w : states_o)[k] += cnt * chunks[k];
+    }
+    (wide ? wide_pages : other_pages) += (long)np * n_groups;
+    (wide ? wide_longest : other_longest) = std::max(wide ? wide_longest : other_longest, np);
   }
+  c->tail_pages.clear();
   for (int s = b->n_prefill; s < b->n_seq; ++s) {
     const int leaf = b->n_nodes > 0 ? b->seq_leaf_node[s] : -1;
-    pages += (b->kv_len[s] + c->cfg.page_size - 1) / c->cfg.page_size - (leaf >= 0 ? c->path_pages[leaf] : 0);
+    const int np = (b->kv_len[s] + c->cfg.page_size - 1) / c->cfg.page_size - (leaf >= 0 ? c->path_pages[leaf] : 0);
+    c->tail_pages.push_back(np);
+    other_pages += np;
+    other_longest = std::max(other_longest, np);
   }
-  auto cut = [&](long units, int most) {
-    const long ch = pages * c->cfg.n_kv_heads / units;
-    return (int)std::min<long>(most, std::max<long>(CHUNK_MIN, (ch + 1) / 2 * 2));
-  };
-  return {cut(wide ? CHUNK_UNITS_BESIDE : CHUNK_UNITS, CHUNK_MAX), cut(CHUNK_UNITS_WIDE, CHUNK_MAX_WIDE)};
+  if (wide_pages == 0) {
+    const long ch = other_pages * hkv / CHUNK_UNITS;
+    const int pages_each = (int)std::min<long>(CHUNK_MAX, std::max<long>(CHUNK_MIN, (ch + 1) / 2 * 2));
+    return {pages_each, pages_each};
+  }
+  count_chunks(c->tail_pages.data(), (int)c->tail_pages.size(), tails, ChunkSizes{});
+  const double slots = 1024.0, scale = c->cfg.head_dim == 128 ? 1.0 : 0.62;  // a page of 64-wide heads is half the bytes
+  const double unit_w = 4.4, page_w = 1.0 * scale, unit_o = 3.3, page_o = 0.37 * scale, page_o_full = 0.81 * scale;
+  const double state_us = (double)c->cfg.n_q_heads * c->cfg.head_dim * 8.0 / 4.0e6;
+  Chunks best = NOALLOC_CHUNKS;
+  double best_us = 1e300;
+  for (int kw = 0; kw < N_SIZES; ++kw) {
+    const int w = chunk_size(kw, ChunkSizes{});
+    const double units = (double)units_w[kw] * hkv, full = std::floor(units / slots), rem = units / slots - full;
+    const double rounds = (full + (rem > 0 ? 0.68 + 0.32 * rem : 0.0)) * (unit_w + page_w * (double)wide_pages * hkv / units);
+    const double longest_w = unit_w + page_w * std::min(w, wide_longest);
+    for (int ko = 0; ko < N_SIZES; ++ko) {
+      const int o = chunk_size(ko, ChunkSizes{});
+      const double others = (unit_o * (double)(units_o[ko] + tails[ko]) + page_o_full * (double)other_pages) * hkv / slots;
+      const double work = (unit_w * units + page_w * (double)wide_pages * hkv) / slots + others;
+      const double longest = std::max(longest_w, unit_o + page_o * std::min(o, other_longest));
+      const double us = std::max(std::max(rounds, work), longest) + 0.23 * std::min(rounds, others) +
+                        state_us * (double)(states_w[kw] + states_o[ko] + tails[ko]);
+      if (us < best_us) { best_us = us; best = {o, w}; }
+    }
+  }
+  return best;
 }
 
 // pages per chunk of a node with cnt member rows (one for all its member groups: their partial states
@@ -551,7 +604,7 @@ Chunks attention_chunks(bs_ctx *c, const bs_batch *b) {
   if (fits(chosen) || !fits(NOALLOC_CHUNKS)) return chosen;
   Chunks between = chosen;
   do {  // (both reach the fixed division, which fits)
-    between = {std::min(between.other + 2, CHUNK_MAX), std::min(between.wide + 2, CHUNK_MAX_WIDE)};
+    between = {std::min(between.other + 2, NOALLOC_CHUNKS.other), std::min(between.wide + 2, NOALLOC_CHUNKS.wide)};
   } while (!fits(between));
   return between;
 }
@@ -1013,7 +1066,7 @@ int bs_create(const bs_layer_cfg *cfg, int device, bs_ctx **out) {
     c->pf_order.reserve(1 << 15);
     c->pf_work.reserve(1 << 16);
     c->refcount.reserve(1 << 20);
-    c->path_pages.reserve(1 << 15); c->path_chunks.reserve(1 << 15); c->members.reserve(1 << 15);
+    c->path_pages.reserve(1 << 15); c->tail_pages.reserve(1 << 15); c->path_chunks.reserve(1 << 15); c->members.reserve(1 << 15);
   } catch (const std::bad_alloc &) { c->err = "out of host memory"; return bail(BS_ENOMEM); }
   if ((rc = dev_alloc(c, &c->sync_words, 16))) return bail(rc);
   if (hipMemset(c->sync_words, 0, 16 * sizeof(unsigned)) != hipSuccess) { c->err = "hipMemset failed"; return bail(BS_EHIP); }

@@ -287,7 +287,7 @@ def test_gemm_division_narrow_short_and_large(shape, product, rows, want):
 
 
 @pytest.mark.parametrize("heads,n,tail,groups,pages,want", [
-    ((24, 8), 287, 32, 6, 151, (32, 512)), ((32, 8), 640, 400, 4, 128, (400, 512)),    # large steps: no wide chunk beyond 32 pages
+    ((24, 8), 287, 32, 6, 151, (32, 512)), ((32, 8), 640, 400, 4, 128, (400, 1024)),   # large steps: by rounds of the wide units
     ((32, 8), 20, 16, 2, 64, (16, 128)), ((64, 8), 105, 181, 6, 5, (181, 80)),        # few: cut; tails beside wide nodes stay whole
     ((32, 8), 7, 2000, 0, 0, (224, 0)), ((32, 8), 256, 1024, 0, 0, (1024, 0)), ((16, 8), 8, 3000, 2, 100, (416, 0))])
 def test_chunks_of_decode_attention(heads, n, tail, groups, pages, want):
