@@ -273,7 +273,7 @@ int bs_attention(bs_ctx *ctx, const bs_batch *batch, const void *q, void *out,
 /*   bs_attention_noalloc: bs_attention for callers that cannot allocate device memory during the call
  *   (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).  Same
  *   arguments, same kernels, same result; the descriptor and the partial softmax states of the call live
- *   in a 16 MiB array that is part of the library's code object (every GPU the library runs on holds its
+ *   in a 64 MiB array that is part of the library's code object (every GPU the library runs on holds its
  *   own copy until the process ends) instead of the context's growing workspace.  Limits, checked before
  *   anything is enqueued (BS_EINVAL with a message): the planned descriptor at most 1 MiB, the partial
  *   states at most 15 MiB (one state of n_q_heads x (head_dim + 2) floats per sequence and chunk along its

@@ -26,7 +26,8 @@ using namespace bs;
 // until the process ends.  Host code never uses the array's name as an address: bs_create asks the
 // runtime for the device address once per device and keeps it in g_scratch_ptr.
 #define BS_NOALLOC_BLOB_BYTES (1u << 20)
-#define BS_NOALLOC_SCRATCH_BYTES (16u << 20)
+#define BS_NOALLOC_STATE_BYTES (15u << 20)    // a batch whose states by the fixed division exceed this is refused
+#define BS_NOALLOC_SCRATCH_BYTES (64u << 20)  // room for the states of the division that runs, which may be finer
 static __device__ __align__(256) unsigned char scratch[BS_NOALLOC_SCRATCH_BYTES];
 
 namespace {
@@ -580,8 +581,8 @@ size_t noalloc_state_bytes(const bs_ctx *c, long slots) {
   return (2 * noalloc_ml_floats(c, slots) + (size_t)slots * c->cfg.n_q_heads * c->cfg.head_dim) * sizeof(float);
 }
 bool noalloc_blob_fits(const PlanSize &z) { return (size_t)z.ints * sizeof(int32_t) <= BS_NOALLOC_BLOB_BYTES; }
-bool noalloc_states_fit(const bs_ctx *c, const PlanSize &z) {
-  return noalloc_state_bytes(c, z.slots) <= BS_NOALLOC_SCRATCH_BYTES - BS_NOALLOC_BLOB_BYTES;
+bool noalloc_accepts(const bs_ctx *c, const PlanSize &fixed) {
+  return noalloc_blob_fits(fixed) && noalloc_state_bytes(c, fixed.slots) <= BS_NOALLOC_STATE_BYTES;
 }
 
 int check_noalloc_counts(bs_ctx *c, const bs_batch *b, int64_t n_pages) {
@@ -592,16 +593,17 @@ int check_noalloc_counts(bs_ctx *c, const bs_batch *b, int64_t n_pages) {
 }
 
 // The division of bs_attention and bs_attention_noalloc, one for both, so that they agree bit for bit: that
-// of chunk_choice, but where the limits of bs_attention_noalloc hold the fixed division and not that one, the
-// finest between the two that they hold.
+// of chunk_choice, but for a batch that bs_attention_noalloc accepts and whose division its array does not hold the
+// finest between that one and the fixed one that it holds (64 MiB of array: with 16, 177 sequences behind six
+// prefixes of 240 tokens, 70B heads, had to take longer chunks, 34 us against 30).
 Chunks attention_chunks(bs_ctx *c, const bs_batch *b) {
   const Chunks chosen = chunk_choice(c, b);
   if (c->chunk_pages > 0) return chosen;
   auto fits = [&](Chunks chunks) {
     const PlanSize z = plan_size(c, b, chunks);
-    return noalloc_blob_fits(z) && noalloc_states_fit(c, z);
+    return noalloc_blob_fits(z) && noalloc_state_bytes(c, z.slots) <= BS_NOALLOC_SCRATCH_BYTES - BS_NOALLOC_BLOB_BYTES;
   };
-  if (fits(chosen) || !fits(NOALLOC_CHUNKS)) return chosen;
+  if (fits(chosen) || !noalloc_accepts(c, plan_size(c, b, NOALLOC_CHUNKS))) return chosen;
   Chunks between = chosen;
   do {  // (both reach the fixed division, which fits)
     between = {std::min(between.other + 2, NOALLOC_CHUNKS.other), std::min(between.wide + 2, NOALLOC_CHUNKS.wide)};
@@ -615,10 +617,13 @@ int plan_noalloc(bs_ctx *c, const bs_batch *b, Plan &p) {
   const PlanSize z = plan_size(c, b, c->chunk_pages > 0 ? Chunks{c->chunk_pages, c->chunk_pages} : NOALLOC_CHUNKS);
   if (!noalloc_blob_fits(z))
     return fail(c, BS_EINVAL, "bs_attention_noalloc: descriptor of %ld bytes exceeds the limit of %u", z.ints * 4L, BS_NOALLOC_BLOB_BYTES);
-  if (!noalloc_states_fit(c, z))
+  if (!noalloc_accepts(c, z))
     return fail(c, BS_EINVAL, "bs_attention_noalloc: %ld partial softmax states (%zu bytes) exceed the limit of %u bytes",
-                z.slots, noalloc_state_bytes(c, z.slots), BS_NOALLOC_SCRATCH_BYTES - BS_NOALLOC_BLOB_BYTES);
-  return build_plan(c, b, p, false, attention_chunks(c, b));
+                z.slots, noalloc_state_bytes(c, z.slots), BS_NOALLOC_STATE_BYTES);
+  const int rc = build_plan(c, b, p, false, attention_chunks(c, b));
+  if (!rc && noalloc_state_bytes(c, p.n_slots) > BS_NOALLOC_SCRATCH_BYTES - BS_NOALLOC_BLOB_BYTES)
+    return fail(c, BS_EINVAL, "bs_attention_noalloc: %ld partial softmax states do not fit", p.n_slots);  // (attention_chunks keeps to what fits)
+  return rc;
 }
 
 // Stages the plan in the pinned ring and copies it to the context's descriptor buffer, grown on demand,

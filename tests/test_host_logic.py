@@ -241,7 +241,7 @@ def test_attention_division_counts(seed):
 
 
 @pytest.mark.parametrize("shape", [W.LLAMA3_8B, W.LLAMA3_70B, W.LayerShape(256, 16, 1, 64, 256)])
-@pytest.mark.parametrize("members,prefix_pages,tails", [(8, 4, 40), (40, 64, 300), (50, 256, 20), (70, 80, 100), (100, 64, 60),
+@pytest.mark.parametrize("members,prefix_pages,tails", [(60, 450, 20), (8, 4, 40), (40, 64, 300), (50, 256, 20), (70, 80, 100), (100, 64, 60),
                                                         (200, 100, 20), (16, 128, 2000), (300, 40, 30)])
 def test_both_attention_entry_points_divide_alike(shape, members, prefix_pages, tails):
     # from steps cut into short chunks, over those whose short chunks the scratch array of bs_attention_noalloc
