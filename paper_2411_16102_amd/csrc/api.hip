@@ -345,11 +345,13 @@ constexpr int chunk_size(int k, std::integer_sequence<int, W...>) { const int si
 // Without wide nodes: cut until there are 512 units of (chunk, KV head), no chunk under eight pages (7 sequences of
 // 2000 tokens 20 us against 69 with chunks of 64 pages in workgroups of four wavefronts, one of 4000 17 against 54).
 // With wide nodes both lengths come from an estimate of the launch and the merge, in microseconds on 1024 SIMDs:
-// the rounds of the wide units, all the work, or the longest unit, whichever is most, part of the narrow units'
-// work beside the wide ones, and the partial states once out and once back in.  Fitted to 357 batches of 8
-// to 1000 sequences behind 1 to 32 prefixes of 4 to 400 pages, every pair of lengths timed: 2 % off the best
-// pair on average; 15 % faster than chunks of 64 pages, 32 in wide nodes, 4.5 % faster than one length for both
-// kinds cut until there were 1536 units (in 18 of them more than 3 % slower than either, at most 13 and 14 %).
+// the rounds of the wide units, all the work or the longest unit, whichever is most, part of the narrow units'
+// work beside the wide ones, and the partial states once out and once back in; prefill workgroups of the same
+// launch (four SIMDs each) are work, and stand before the wide units' rounds.  Fitted to 357 batches of 8 to
+// 1000 sequences behind 1 to 32 prefixes of 4 to 400 pages and 63 blended launches, pairs of lengths timed: 2 %
+// (blended: 3 %) off the best pair on average; 15 % (3 %) faster than chunks of 64 pages, 32 in wide nodes, 5 %
+// (3 %) faster than one length for both kinds cut until there were 1536 units (in 22 and 25 of the 420 more than
+// 3 % slower than those).
 Chunks chunk_choice(bs_ctx *c, const bs_batch *b) {
   if (c->chunk_pages > 0) return {c->chunk_pages, c->chunk_pages};
   const int grp = c->cfg.n_q_heads / c->cfg.n_kv_heads, max_members = std::max(1, 64 / grp), hkv = c->cfg.n_kv_heads;
@@ -384,23 +386,35 @@ Chunks chunk_choice(bs_ctx *c, const bs_batch *b) {
     return {pages_each, pages_each};
   }
   count_chunks(c->tail_pages.data(), (int)c->tail_pages.size(), tails, ChunkSizes{});
-  const double slots = 1024.0, scale = c->cfg.head_dim == 128 ? 1.0 : 0.62;  // a page of 64-wide heads is half the bytes
-  const double unit_w = 4.4, page_w = 1.0 * scale, unit_o = 3.3, page_o = 0.37 * scale, page_o_full = 0.81 * scale;
+  const double slots = 1024.0, alone = c->cfg.head_dim == 128 ? 1.0 : 0.9;  // the longest unit runs at its own latency
+  const double unit_w = 6.3, page_w = 0.97, unit_o = 2.9, page_o = 0.59, page_o_full = 0.97, unit_p = 11.0, block_p = 1.2;
+  double prefill = 0.0, longest_prefill = 0.0;
+  if (blended_attn_possible(attn_shape(c))) {
+    double blocks = 0.0, wgs = 0.0;  // blocks of 32 tokens that the workgroups of 64 rows and four heads walk
+    for (int s = 0; s < b->n_prefill; ++s) {
+      const int rows = b->row_start[s + 1] - b->row_start[s], n = (rows + 63) / 64;
+      const double first = (b->kv_len[s] - rows) / 32 + 2, last = (b->kv_len[s] - 1) / 32 + 1;
+      blocks += n * 0.5 * (std::min(first, last) + last);
+      wgs += n;
+      longest_prefill = std::max(longest_prefill, unit_p + block_p * last);
+    }
+    prefill = 4.0 * (block_p * blocks + unit_p * wgs) * (c->cfg.n_q_heads / 4) / slots;
+  }
   const double state_us = (double)c->cfg.n_q_heads * c->cfg.head_dim * 8.0 / 4.0e6;
   Chunks best = NOALLOC_CHUNKS;
   double best_us = 1e300;
   for (int kw = 0; kw < N_SIZES; ++kw) {
     const int w = chunk_size(kw, ChunkSizes{});
     const double units = (double)units_w[kw] * hkv, full = std::floor(units / slots), rem = units / slots - full;
-    const double rounds = (full + (rem > 0 ? 0.68 + 0.32 * rem : 0.0)) * (unit_w + page_w * (double)wide_pages * hkv / units);
-    const double longest_w = unit_w + page_w * std::min(w, wide_longest);
+    const double rounds = (full + (rem > 0 ? 0.74 + 0.26 * rem : 0.0)) * (unit_w + page_w * (double)wide_pages * hkv / units);
+    const double longest_w = unit_w + page_w * alone * std::min(w, wide_longest);
     for (int ko = 0; ko < N_SIZES; ++ko) {
       const int o = chunk_size(ko, ChunkSizes{});
       const double others = (unit_o * (double)(units_o[ko] + tails[ko]) + page_o_full * (double)other_pages) * hkv / slots;
-      const double work = (unit_w * units + page_w * (double)wide_pages * hkv) / slots + others;
-      const double longest = std::max(longest_w, unit_o + page_o * std::min(o, other_longest));
-      const double us = std::max(std::max(rounds, work), longest) + 0.23 * std::min(rounds, others) +
-                        state_us * (double)(states_w[kw] + states_o[ko] + tails[ko]);
+      const double work = (unit_w * units + page_w * (double)wide_pages * hkv) / slots + others + prefill;
+      const double longest = std::max(longest_w, unit_o + page_o * alone * std::min(o, other_longest));
+      const double us = std::max(std::max(rounds + prefill, work), std::max(longest, longest_prefill)) + 0.14 * std::min(rounds, others) +
+                        0.04 * longest + state_us * (double)(states_w[kw] + states_o[ko] + tails[ko]);
       if (us < best_us) { best_us = us; best = {o, w}; }
     }
   }
