@@ -1169,6 +1169,7 @@ int bs_resolve_rows(bs_ctx *c, const bs_batch *b, int32_t *page_out, int32_t *sl
   if (max_page >= (int64_t)0x7fffffff) return fail(c, BS_EINVAL, "page id out of range");
   int rc = validate(c, b, max_page + 1);
   if (rc) return rc;
+  if (b->n_rows == 0) return BS_OK;  // (the node arrays of a batch without sequences are not looked at)
   Plan p;
   if ((rc = build_plan(c, b, p, true, chunk_choice(c, b)))) return rc;
   for (int r = 0; r < b->n_rows; ++r) {

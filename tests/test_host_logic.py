@@ -140,6 +140,16 @@ def test_empty_batch_is_valid(host_layer):
     assert host_layer.validate(b) == 0
 
 
+def test_node_arrays_of_an_empty_batch_are_not_read(host_layer):
+    import ctypes as C
+    starts = (C.c_int32 * 4)(0, 0, 0, 0)
+    d = binding.BatchDesc(n_seq=0, n_prefill=0, n_rows=0, n_nodes=3, node_page_start=C.cast(starts, C.POINTER(C.c_int32)))
+    out = (C.c_int32 * 1)(7)
+    assert host_layer.lib.bs_resolve_rows(host_layer.h, C.byref(d), out, out) == 0 and out[0] == 7
+    div = binding.Division()
+    assert host_layer.lib.bs_attention_division(host_layer.h, C.byref(d), 4, 1, C.byref(div)) == 0 and div.items == 0
+
+
 def test_tuning_knobs_reject_values_outside_their_range(host_layer):
     for bad in (0, 1, 3, 66, -2):
         assert host_layer.lib.bs_set_chunk_pages(host_layer.h, bad) == -1 and "chunk_pages" in host_layer.last_error()
