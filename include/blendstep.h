@@ -195,7 +195,8 @@ int bs_profile_reset(bs_ctx *ctx);
 
 /* Tuning knob: pages per chunk of decode-attention work (even, 2..64).  Smaller chunks give more
  * workgroups, larger ones fewer partial states.  Without it the chunk is chosen for each step: 64
- * pages where the step has enough work for the whole chip, down to 8 where it has not. */
+ * pages where the step has enough work for the whole chip, down to 8 where it has not, apart for
+ * prefix nodes whose work items carry more than 16 query rows and for the rest. */
 int bs_set_chunk_pages(bs_ctx *ctx, int32_t pages);
 
 /* Tuning knobs of the BS_FLAG_OVERLAP schedule. */

@@ -33,8 +33,8 @@ using namespace attn_dev;
 // One launch for both kinds of item, one wavefront per SIMD (the 16-row items stream as fast
 // with one wavefront per SIMD as with two) and per workgroup: a CU streams about 36 GB/s of pages
 // however many of its wavefronts ask, so a step with few units wants each on a CU of its own.
-// Measured against workgroups of four wavefronts: one sequence of 4000 tokens 60 -> 21 us, 7 of 2000
-// 62 -> 24, 64 of 2000 126 -> 104, 640 behind a two-level tree 369 -> 352, full launches the same.
+// Measured (this launch, 8B heads) against workgroups of four wavefronts and chunks of 64 pages: one sequence
+// of 4000 tokens 48 -> 7 us, 7 of 2000 63 -> 14, 64 of 2000 86 -> 85, 256 of 1024 180 -> 179.
 // Grid order: wide workgroups first, narrow ones
 // after, longest first within a kind.  Where the wide workgroups are at least a third of the
 // grid, one of them alternates with two narrow ones for as long as both kinds last (what is
@@ -161,8 +161,8 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(const MergeArgs a) {
 // out of LDS.  (Read straight from global memory by every wavefront, 24 loads of 64 scattered pieces
 // per block and wavefront, a block took 3300 clocks of a CU; its MFMAs need 1024.)  It takes 2200
 // now: issue 1200, of that 900 vector-ALU; 600 waiting for a pipe, 400 for LDS and barriers.
-// Measured, 8B layer: 28 x 64 rows behind 6000 tokens 334 -> 220 us, 8 x 1024 rows 154 -> 121, 32 rows
-// behind 8000 tokens 333 -> 220, 128 x 64 rows 73 -> 66, where starting workgroups is most of it.
+// Measured, 8B heads: 28 x 64 rows behind 6000 tokens 307 -> 207 us, 8 x 1024 rows 137 -> 111, 32 rows
+// behind 8000 tokens 327 -> 216, 128 x 64 rows 70 -> 65, where starting workgroups is most of it.
 //
 // What then bounds a block is the issue of one wavefront per SIMD (the accumulators of 64 rows x dh
 // 128 leave no room for two): 32 MFMAs of 32 clocks against about 900 clocks of softmax arithmetic.
