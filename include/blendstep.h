@@ -22,8 +22,9 @@
  *     workspace than any call before it on the context (more rows, more partial
  *     softmax states, a longer descriptor) frees and reallocates device memory,
  *     which synchronises the device; calls within the sizes already seen do not,
- *     except that a call waits on the host for the fourth-last call's descriptor
- *     copy (its staging slot).  Calls on one context must not overlap in time on
+ *     except that a call whose descriptor does not fit the half of the staging
+ *     buffer that is being filled (2 MiB, more after larger descriptors) waits on
+ *     the host for the copies out of the other half.  Calls on one context must not overlap in time on
  *     different streams (they share the workspace).
  */
 #ifndef BLENDSTEP_H

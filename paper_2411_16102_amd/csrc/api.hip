@@ -8,6 +8,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 #include <mutex>
 #include <new>
 #include <string>
@@ -36,7 +37,7 @@ constexpr int MAX_DEVICES = 64;
 unsigned char *g_scratch_ptr[MAX_DEVICES] = {nullptr};
 std::mutex g_scratch_mutex;
 
-constexpr int RING = 4;
+constexpr long STAGE_HALF = 2 * BS_NOALLOC_BLOB_BYTES / 4;  // 32-bit words of either half of the staging buffer, at first
 constexpr long TRACE_CAP = 8192;  // workgroups per launch that a timeline can hold
 std::string g_create_error;
 
@@ -64,14 +65,14 @@ struct bs_ctx {
   long cap_slots = 0;
   float *part_acc = nullptr, *part_m = nullptr, *part_l = nullptr;
   uint16_t *hid[2] = {nullptr, nullptr};  // activations between the layers of bs_blend_layers
-  // descriptor blob: pinned host ring and one device copy
+  // descriptor blob: pinned staging buffer and one device copy
   long cap_blob = 0;
   int32_t *d_blob = nullptr;
-  int32_t *h_blob[RING] = {nullptr, nullptr, nullptr, nullptr};
-  long h_cap[RING] = {0, 0, 0, 0};
-  hipEvent_t h_ev[RING];
-  bool h_ev_live[RING] = {false, false, false, false};
-  int ring_pos = 0;
+  int32_t *h_stage = nullptr;      // two halves, filled in turn, descriptor behind descriptor
+  long stage_half = 0, stage_at = 0;  // words of a half; place of the next descriptor in the one being filled
+  int stage_cur = 0;
+  hipEvent_t h_ev[2];              // behind every copy out of a half, recorded when the other half is turned to
+  bool h_ev_live[2] = {};
   // host scratch reused across calls
   std::vector<int32_t> refcount, path_pages, path_chunks, members, tail_pages, blob;
   std::vector<DecodeItem> items, items_wide;
@@ -178,18 +179,7 @@ int ensure_slots(bs_ctx *c, long slots) {
   return BS_OK;
 }
 
-int ensure_blob_host(bs_ctx *c, long ints, int slot) {
-  if (ints > c->h_cap[slot]) {
-    const long cap = ints + ints / 4 + 1024;
-    if (c->h_blob[slot]) { HIP_TRY(c, hipHostFree(c->h_blob[slot])); c->h_blob[slot] = nullptr; c->h_cap[slot] = 0; }
-    hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&c->h_blob[slot]), (size_t)cap * sizeof(int32_t), hipHostMallocDefault);
-    if (e != hipSuccess) return fail(c, BS_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(e));
-    c->h_cap[slot] = cap;
-  }
-  return BS_OK;
-}
-
-int ensure_blob(bs_ctx *c, long ints, int slot) {
+int ensure_blob(bs_ctx *c, long ints) {
   if (ints > c->cap_blob) {
     const long cap = ints + ints / 4 + 1024;
     c->cap_blob = 0;
@@ -197,7 +187,20 @@ int ensure_blob(bs_ctx *c, long ints, int slot) {
     if (rc) return rc;
     c->cap_blob = cap;
   }
-  return ensure_blob_host(c, ints, slot);
+  return BS_OK;
+}
+
+// both halves of the staging buffer with room for `ints` words each (nothing may still be read from them)
+int alloc_stage(bs_ctx *c, long ints) {
+  if (c->h_stage) HIP_TRY(c, hipHostFree(c->h_stage));
+  c->h_stage = nullptr;
+  c->stage_half = c->stage_at = 0;
+  c->stage_cur = 0;
+  c->h_ev_live[0] = c->h_ev_live[1] = false;
+  hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&c->h_stage), (size_t)ints * 2 * sizeof(int32_t), hipHostMallocDefault);
+  if (e != hipSuccess) return fail(c, BS_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(e));
+  c->stage_half = ints;
+  return BS_OK;
 }
 
 // ---------------------------------------------------------------------------------
@@ -640,24 +643,41 @@ int plan_noalloc(bs_ctx *c, const bs_batch *b, Plan &p) {
   return rc;
 }
 
-// Stages the plan in the pinned ring and copies it to the context's descriptor buffer, grown on demand,
-// or to `dst`, a buffer of `room` words of the caller's, with the staging slots of bs_create (nothing grows).
-int upload_plan(bs_ctx *c, const Plan &p, hipStream_t stream, int32_t *dst = nullptr, long room = 0) {
-  const int slot = c->ring_pos;
-  c->ring_pos = (c->ring_pos + 1) % RING;
-  if (c->h_ev_live[slot]) HIP_TRY(c, hipEventSynchronize(c->h_ev[slot]));
+// Puts the plan into pinned memory, bound for the context's descriptor buffer, grown on demand, or for `dst`, a
+// buffer of `room` words of the caller's (nothing grows then).  The first kernel of the step brings it over, or
+// launch_upload.
+// Descriptors stand one behind the other in a half of the staging buffer; when one does not fit any more an
+// event is recorded behind the copies out of this half (calls of a context follow one another), and the other
+// half is taken once its own event has passed.  An event for every call would cost the stream 5.5 us each.
+int stage_plan(bs_ctx *c, const Plan &p, hipStream_t stream, Upload &up, int32_t *dst = nullptr, long room = 0) {
+  const long units = (p.total_ints + 3) / 4, words = 4 * units;  // whole 16-byte units on both sides
   if (dst) {
-    if (p.total_ints > std::min(room, c->h_cap[slot]))
+    if (words > std::min(room, c->stage_half))
       return fail(c, BS_EINVAL, "descriptor of %ld words exceeds its buffer of %ld", p.total_ints, room);
-  } else {
-    int rc = ensure_blob(c, p.total_ints, slot);
-    if (rc) return rc;
+  } else if (int rc = ensure_blob(c, words)) {
+    return rc;
   }
   if (p.total_ints == 0) return BS_OK;
-  std::memcpy(c->h_blob[slot], c->blob.data(), sizeof(int32_t) * p.total_ints);
-  HIP_TRY(c, hipMemcpyAsync(dst ? dst : c->d_blob, c->h_blob[slot], sizeof(int32_t) * p.total_ints, hipMemcpyHostToDevice, stream));
-  HIP_TRY(c, hipEventRecord(c->h_ev[slot], stream));
-  c->h_ev_live[slot] = true;
+  if (units > std::numeric_limits<int>::max() - 256) return fail(c, BS_EINVAL, "descriptor of %ld words", p.total_ints);
+  if (words > c->stage_half) {
+    HIP_TRY(c, hipDeviceSynchronize());
+    if (int rc = alloc_stage(c, words + words / 4 + 1024)) return rc;
+  } else if (c->stage_at + words > c->stage_half) {
+    HIP_TRY(c, hipEventRecord(c->h_ev[c->stage_cur], stream));
+    c->h_ev_live[c->stage_cur] = true;
+    const int other = c->stage_cur ^ 1;
+    if (c->h_ev_live[other]) HIP_TRY(c, hipEventSynchronize(c->h_ev[other]));
+    c->h_ev_live[other] = false;
+    c->stage_cur = other;
+    c->stage_at = 0;
+  }
+  int32_t *src = c->h_stage + c->stage_cur * c->stage_half + c->stage_at;
+  std::memcpy(src, c->blob.data(), sizeof(int32_t) * p.total_ints);
+  c->stage_at += words;
+  up.src = reinterpret_cast<const uint4 *>(src);
+  up.dst = reinterpret_cast<uint4 *>(dst ? dst : c->d_blob);
+  up.n16 = (int)units;
+  up.blocks = (int)((units + 255) / 256);
   return BS_OK;
 }
 
@@ -1062,8 +1082,8 @@ int bs_create(const bs_layer_cfg *cfg, int device, bs_ctx **out) {
   hipError_t e = launch_rope_table(c->rope_cos, c->rope_sin, c->cfg.max_positions, half, (double)c->cfg.rope_theta, nullptr);
   if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
   if (e != hipSuccess) { c->err = std::string("rope table: ") + hipGetErrorString(e); return bail(BS_EHIP); }
-  for (int i = 0; i < RING; ++i)
-    if (hipEventCreateWithFlags(&c->h_ev[i], hipEventDisableTiming) != hipSuccess) { c->err = "hipEventCreate failed"; return bail(BS_EHIP); }
+  for (hipEvent_t &ev : c->h_ev)
+    if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) { c->err = "hipEventCreate failed"; return bail(BS_EHIP); }
   {  // this device's copy of the static scratch array (each GPU holds its own, at its own address)
     std::lock_guard<std::mutex> lock(g_scratch_mutex);
     if (device < MAX_DEVICES && !g_scratch_ptr[device]) {
@@ -1074,10 +1094,9 @@ int bs_create(const bs_layer_cfg *cfg, int device, bs_ctx **out) {
     }
     c->scratch_ptr = device < MAX_DEVICES ? g_scratch_ptr[device] : nullptr;
   }
-  // pinned staging for descriptors up to the size bs_attention_noalloc accepts, and host vectors that
+  // pinned staging for descriptors up to the size bs_attention_noalloc accepts and more, and host vectors that
   // such a call then never has to grow
-  for (int i = 0; i < RING; ++i)
-    if ((rc = ensure_blob_host(c, BS_NOALLOC_BLOB_BYTES / sizeof(int32_t), i))) return bail(rc);
+  if ((rc = alloc_stage(c, STAGE_HALF))) return bail(rc);
   try {
     c->blob.reserve(BS_NOALLOC_BLOB_BYTES / sizeof(int32_t));
     c->items.reserve(BS_NOALLOC_BLOB_BYTES / sizeof(DecodeItem));
@@ -1110,10 +1129,8 @@ void bs_destroy(bs_ctx *c) {
                   (void *)c->xg2, (void *)c->act, (void *)c->rstd1, (void *)c->rstd2, (void *)c->ss2, (void *)c->part_acc, (void *)c->part_m,
                   (void *)c->part_l, (void *)c->d_blob, (void *)c->hid[0], (void *)c->hid[1], (void *)c->sync_words, (void *)c->trace_buf, (void *)c->sk_ws, (void *)c->sk_cnt})
     if (p) (void)hipFree(p);
-  for (int i = 0; i < RING; ++i) {
-    if (c->h_blob[i]) (void)hipHostFree(c->h_blob[i]);
-    (void)hipEventDestroy(c->h_ev[i]);
-  }
+  if (c->h_stage) (void)hipHostFree(c->h_stage);
+  for (hipEvent_t ev : c->h_ev) (void)hipEventDestroy(ev);
   for (auto &v : c->spans) for (auto &s : v) { (void)hipEventDestroy(s.a); (void)hipEventDestroy(s.b); }
   for (auto e : c->free_events) (void)hipEventDestroy(e);
   delete c;
@@ -1231,14 +1248,14 @@ int bs_gemm_division(bs_ctx *c, int32_t product, int32_t rows, int32_t *tiles, i
 namespace {
 
 // First norm and fused QKV projection (RoPE, KV append into `pool`) of rows [r0, r1) of x.
-// `clear_sync`: the prep kernel also clears the counters of the co-scheduled launches.
+// `clear_sync`: the prep kernel also clears the counters of the co-scheduled launches; it brings `up` over.
 int run_prep_qkv(bs_ctx *c, const Plan &p, const bs_weights *w, const uint16_t *x, uint16_t *pool, int r0, int r1,
-                 bool clear_sync, hipStream_t st) {
+                 bool clear_sync, const Upload &up, hipStream_t st) {
   const bs_layer_cfg &g = c->cfg;
   const int d = g.d_model, rows = r1 - r0, hd = g.n_q_heads * g.head_dim;
   if (rows <= 0) return BS_OK;
   SPAN(c, BS_K_PREP, st, HIP_TRY(c, launch_norm_prep(x + (size_t)r0 * d, (const uint16_t *)w->g_attn, c->xg + (size_t)r0 * d,
-                                                     c->rstd1 + r0, rows, d, g.rms_eps, clear_sync ? c->sync_words : nullptr, 16, st)));
+                                                     c->rstd1 + r0, rows, d, g.rms_eps, clear_sync ? c->sync_words : nullptr, 16, up, st)));
   GemmArgs q{};
   q.A = c->xg + (size_t)r0 * d; q.lda = d; q.B = (const uint16_t *)w->w_qkv; q.ldb = d;
   q.M = rows; q.N = (g.n_q_heads + 2 * g.n_kv_heads) * g.head_dim; q.K = d;
@@ -1255,10 +1272,10 @@ int run_prep_qkv(bs_ctx *c, const Plan &p, const bs_weights *w, const uint16_t *
 
 // every kernel of one layer for the planned batch: x -> y, appending to `pool`
 int run_layer(bs_ctx *c, const Plan &p, const bs_weights *w, const uint16_t *x, uint16_t *y, uint16_t *pool, hipStream_t st,
-              uint32_t flags) {
+              uint32_t flags, const Upload &up) {
   int rc;
   const int T = p.n_rows;
-  if ((rc = run_prep_qkv(c, p, w, x, pool, 0, T, true, st))) return rc;
+  if ((rc = run_prep_qkv(c, p, w, x, pool, 0, T, true, up, st))) return rc;
 
   // co-scheduling pays where there are GEMM rows that do not wait for decode attention (the
   // prefill rows) and 16-row decode units to run beside them
@@ -1283,7 +1300,7 @@ int run_layer(bs_ctx *c, const Plan &p, const bs_weights *w, const uint16_t *x, 
 // disjoint rows of every workspace buffer, and a part is never more than one layer ahead, so the two
 // alternating hidden-state buffers suffice.  Same kernels, same arithmetic per row as run_layer.
 int run_layers_pipelined(bs_ctx *c, const Plan &p, int n_layers, const bs_weights *w, const uint16_t *x, uint16_t *y,
-                         void *const *pools, hipStream_t st, CoPlan &first, CoPlan &later) {
+                         void *const *pools, hipStream_t st, CoPlan &first, CoPlan &later, const Upload &up) {
   int rc;
   const bs_layer_cfg &g = c->cfg;
   const bs_overlap_knobs &k = c->ov;
@@ -1320,7 +1337,7 @@ int run_layers_pipelined(bs_ctx *c, const Plan &p, int n_layers, const bs_weight
   };
 
   const uint16_t *in = x;
-  if ((rc = run_prep_qkv(c, p, &w[0], in, (uint16_t *)pools[0], 0, T, true, st))) return rc;
+  if ((rc = run_prep_qkv(c, p, &w[0], in, (uint16_t *)pools[0], 0, T, true, up, st))) return rc;
   for (int l = 0; l < n_layers; ++l) {
     const CoPlan &cp = l == 0 ? first : later;
     uint16_t *out = (l == n_layers - 1) ? y : c->hid[l & 1];
@@ -1346,11 +1363,11 @@ int run_layers_pipelined(bs_ctx *c, const Plan &p, int n_layers, const bs_weight
     if (l == n_layers - 1) return run_down(c, &w[l], out, 0, T, st);
     // the decode rows leave this layer and enter the next ...
     if ((rc = run_down(c, &w[l], out, Tp, T, st, BS_K_GEMM_DECODE_ROWS))) return rc;
-    if ((rc = run_prep_qkv(c, p, &w[l + 1], out, (uint16_t *)pools[l + 1], Tp, T, true, st))) return rc;
+    if ((rc = run_prep_qkv(c, p, &w[l + 1], out, (uint16_t *)pools[l + 1], Tp, T, true, Upload{}, st))) return rc;
     // ... whose attention starts beside the prefill rows' down projection of this one
     const DecodeArgs next = decode_args(c, p, c->qbuf, (uint16_t *)pools[l + 1]);
     if ((rc = carry(later, 0, 2, down_args(c, &w[l], out, 0, Tp), next, false))) return rc;
-    if ((rc = run_prep_qkv(c, p, &w[l + 1], out, (uint16_t *)pools[l + 1], 0, Tp, false, st))) return rc;
+    if ((rc = run_prep_qkv(c, p, &w[l + 1], out, (uint16_t *)pools[l + 1], 0, Tp, false, Upload{}, st))) return rc;
     in = out;
   }
   return BS_OK;
@@ -1381,8 +1398,9 @@ int bs_blend_step(bs_ctx *c, const bs_weights *w, const bs_batch *b, const void 
   if ((rc = build_plan(c, b, p, true, chunk_choice(c, b)))) return rc;
   if ((rc = ensure_rows(c, p.n_rows))) return rc;
   if ((rc = ensure_slots(c, p.n_slots))) return rc;
-  if ((rc = upload_plan(c, p, st))) return rc;
-  return run_layer(c, p, w, (const uint16_t *)x_, (uint16_t *)y_, (uint16_t *)pool_, st, flags);
+  Upload up;
+  if ((rc = stage_plan(c, p, st, up))) return rc;
+  return run_layer(c, p, w, (const uint16_t *)x_, (uint16_t *)y_, (uint16_t *)pool_, st, flags, up);
   });
 }
 
@@ -1405,7 +1423,8 @@ int bs_blend_layers(bs_ctx *c, int32_t n_layers, const bs_weights *w, const bs_b
   if ((rc = build_plan(c, b, p, true, chunk_choice(c, b)))) return rc;
   if ((rc = ensure_rows(c, p.n_rows))) return rc;
   if ((rc = ensure_slots(c, p.n_slots))) return rc;
-  if ((rc = upload_plan(c, p, st))) return rc;
+  Upload up;
+  if ((rc = stage_plan(c, p, st, up))) return rc;
   // one descriptor, validated, planned and uploaded once; activations alternate between two
   // workspace buffers so that neither x nor y is touched before / after its own layer
   const uint16_t *in = (const uint16_t *)x_;
@@ -1415,11 +1434,11 @@ int bs_blend_layers(bs_ctx *c, int32_t n_layers, const bs_weights *w, const bs_b
     plan_coscheduled(c, p, &w[0], in, (uint16_t *)y_, first);
     plan_coscheduled(c, p, &w[0], in, (uint16_t *)y_, later, true);
     if (c->ov.always || first.gain_s > 0.0)
-      return run_layers_pipelined(c, p, n_layers, w, in, (uint16_t *)y_, pools, st, first, later);
+      return run_layers_pipelined(c, p, n_layers, w, in, (uint16_t *)y_, pools, st, first, later, up);
   }
   for (int l = 0; l < n_layers; ++l) {
     uint16_t *out = (l == n_layers - 1) ? (uint16_t *)y_ : c->hid[l & 1];
-    if ((rc = run_layer(c, p, &w[l], in, out, (uint16_t *)pools[l], st, flags))) return rc;
+    if ((rc = run_layer(c, p, &w[l], in, out, (uint16_t *)pools[l], st, flags, l == 0 ? up : Upload{}))) return rc;
     in = out;
   }
   return BS_OK;
@@ -1441,7 +1460,9 @@ int bs_attention(bs_ctx *c, const bs_batch *b, const void *q, void *out, const v
   Plan p;
   if ((rc = build_plan(c, b, p, false, attention_chunks(c, b)))) return rc;
   if ((rc = ensure_slots(c, p.n_slots))) return rc;
-  if ((rc = upload_plan(c, p, st))) return rc;
+  Upload up;
+  if ((rc = stage_plan(c, p, st, up))) return rc;
+  HIP_TRY(c, launch_upload(up, st));
   if ((rc = run_attention(c, p, (const uint16_t *)q, (uint16_t *)out, (const uint16_t *)pool, st))) return rc;
   return BS_OK;
   });
@@ -1474,7 +1495,9 @@ int bs_attention_noalloc(bs_ctx *c, const bs_batch *b, const void *q, void *out,
   c->part_m = reinterpret_cast<float *>(ptr + BS_NOALLOC_BLOB_BYTES);
   c->part_l = c->part_m + ml_floats;
   c->part_acc = c->part_l + ml_floats;
-  rc = upload_plan(c, p, st, c->d_blob, BS_NOALLOC_BLOB_BYTES / sizeof(int32_t));
+  Upload up;
+  rc = stage_plan(c, p, st, up, c->d_blob, BS_NOALLOC_BLOB_BYTES / sizeof(int32_t));
+  if (!rc && launch_upload(up, st) != hipSuccess) rc = fail(c, BS_EHIP, "the descriptor's upload could not be launched");
   if (!rc) rc = run_attention(c, p, (const uint16_t *)q, (uint16_t *)out, (const uint16_t *)pool, st);
   c->d_blob = blob0;
   c->part_acc = acc0; c->part_m = m0; c->part_l = l0;

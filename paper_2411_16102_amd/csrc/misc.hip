@@ -7,20 +7,34 @@
 namespace bs {
 namespace {
 
+// Workgroup blockIdx.x of an upload: 4 KB of pinned host memory into the device's copy, one 16-byte load per
+// thread, so that everything asks at once.  Bound by the host link (486 KB 13.5 us).  hipMemcpyAsync instead kept
+// the stream idle for 20 to 27 us between two steps (the copy engine and the handover to it and back), or, for
+// descriptors of a few KB, 9 us (a copy kernel and the gap behind it).
+__device__ __forceinline__ void upload_block(const Upload &up) {
+  const int i = (int)blockIdx.x * 256 + (int)threadIdx.x;
+  if (i < up.n16) up.dst[i] = up.src[i];
+}
+
+__global__ __launch_bounds__(256) void upload_kernel(const Upload up) { upload_block(up); }
+
 // xg = bf16(x * g) (the GEMM operand of the normalised row; the 1/rms factor commutes with the
 // contraction and is applied in the GEMM epilogue) and rstd = 1 / sqrt(mean(x^2) + eps).
+// The first `up.blocks` workgroups bring the step's descriptor over (see upload_block); they hide under the rows.
 // WPR wavefronts per row.  One wavefront per row where there are
 // rows enough for the chip (8192 rows of 4096: 26 us, the bytes at the rate of a copy); with few rows the
 // kernel is the round trips of one row, and four wavefronts share them (see launch_norm_prep).
 template <int WPR>
 __global__ __launch_bounds__(256) void norm_prep_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ g,
                                                        uint16_t *__restrict__ xg, float *__restrict__ rstd, int rows, int d,
-                                                       float eps, unsigned *__restrict__ zero_words, int n_zero) {
+                                                       float eps, unsigned *__restrict__ zero_words, int n_zero, const Upload up) {
+  if ((int)blockIdx.x < up.blocks) return upload_block(up);
+  const int bid = (int)blockIdx.x - up.blocks;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   // the first kernel of a step also clears the step's counters (a fill in a kernel, not a
   // memset on the stream, so that a captured step replays it like any other launch)
-  if (blockIdx.x == 0 && (int)threadIdx.x < n_zero) zero_words[threadIdx.x] = 0u;
-  const int row = WPR == 1 ? (int)blockIdx.x * 4 + wave : (int)blockIdx.x;
+  if (bid == 0 && (int)threadIdx.x < n_zero) zero_words[threadIdx.x] = 0u;
+  const int row = WPR == 1 ? bid * 4 + wave : bid;
   if (row >= rows) return;  // (with four wavefronts per row: all of the workgroup or none)
   const uint16_t *xr = x + (size_t)row * d;
   uint16_t *outr = xg + (size_t)row * d;
@@ -117,13 +131,19 @@ __global__ void kv_pack_kernel(const uint16_t *k, const uint16_t *v, uint16_t *p
 constexpr int NORM_SHARED_ROWS = 1024;
 
 hipError_t launch_norm_prep(const uint16_t *x, const uint16_t *g, uint16_t *xg, float *rstd, int rows, int d,
-                            float eps, unsigned *zero_words, int n_zero, hipStream_t stream) {
-  if (rows <= 0) return hipSuccess;
+                            float eps, unsigned *zero_words, int n_zero, const Upload &up, hipStream_t stream) {
+  if (rows <= 0) return hipErrorInvalidValue;
   const int nz = zero_words ? n_zero : 0;
   if (rows <= NORM_SHARED_ROWS)
-    hipLaunchKernelGGL(norm_prep_kernel<4>, dim3(rows), dim3(256), 0, stream, x, g, xg, rstd, rows, d, eps, zero_words, nz);
+    hipLaunchKernelGGL(norm_prep_kernel<4>, dim3(up.blocks + rows), dim3(256), 0, stream, x, g, xg, rstd, rows, d, eps, zero_words, nz, up);
   else
-    hipLaunchKernelGGL(norm_prep_kernel<1>, dim3((rows + 3) / 4), dim3(256), 0, stream, x, g, xg, rstd, rows, d, eps, zero_words, nz);
+    hipLaunchKernelGGL(norm_prep_kernel<1>, dim3(up.blocks + (rows + 3) / 4), dim3(256), 0, stream, x, g, xg, rstd, rows, d, eps, zero_words, nz, up);
+  return hipGetLastError();
+}
+
+hipError_t launch_upload(const Upload &up, hipStream_t stream) {
+  if (up.blocks <= 0) return hipSuccess;
+  hipLaunchKernelGGL(upload_kernel, dim3(up.blocks), dim3(256), 0, stream, up);
   return hipGetLastError();
 }
 

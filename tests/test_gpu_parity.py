@@ -672,3 +672,27 @@ def test_builder_batch_through_the_layer(lib):
                     node_seq_count=d["node_seq_count"], seq_leaf_node=d["seq_leaf_node"], n_pages=d["n_pages"] + 3)
     tens = W.make_tensors(W.TINY, batch, 5)
     check_step(lib, W.TINY, batch, tens)
+
+
+def test_descriptors_of_calls_in_flight_do_not_overwrite_one_another(lib):
+    # both halves of the staging buffer are filled several times over, and one descriptor is larger than either,
+    # with no synchronisation between the calls
+    import torch
+    shape = W.LayerShape(256, 8, 2, 64, 256)
+    rng = np.random.default_rng(3)
+    batches = [W.assemble_batch(16, [(1, 16 * pages + 5 + i % 40, 0) for i in range(n)], 0, [(-1, pages)], rng)
+               for n, pages in ((300, 700), (3, 2), (900, 333), (700, 1000), (301, 450), (40, 90))]
+    assert max(4 * len(b.page_ids) for b in batches) > 2 << 20 > 4 * len(batches[2].page_ids) > 1 << 20
+    layer = lib.Layer(shape, device=0)
+    pages = max(b.n_pages for b in batches)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    pool = torch.randn(pages * (layer.page_bytes() // 2), generator=gen, device="cuda").to(torch.bfloat16)
+    qs = [torch.randn((b.n_rows, 512), generator=gen, device="cuda").to(torch.bfloat16) for b in batches]
+    alone = []
+    for b, q in zip(batches, qs):
+        alone.append(lib.Layer(shape, device=0).attention(b, q, pool, pages))
+        torch.cuda.synchronize()
+    order = [0, 1, 2, 4, 5, 2, 0, 3, 1, 2, 4, 0, 2, 5, 3, 0, 1]
+    outs = [layer.attention(batches[i], qs[i], pool, pages) for i in order]
+    for i, out in zip(order, outs):
+        assert torch.equal(out, alone[i]), i
