@@ -73,6 +73,18 @@ __device__ __forceinline__ void store_bf16x4(uint16_t *p, float a, float b, floa
   *reinterpret_cast<u32x2_t *>(p) = v;
 }
 
+// Columns of the fused projection enter the tiles in groups of 64: 32 features of a head and those dh/2 behind them, so
+// that rotation pairs meet in a lane.  Groups of value heads are dealt evenly between the others: the rows of
+// decode sequences store them two bytes at a time, one lane per clock, 28 us for a 256x256 tile of nothing else
+// (QKV of 1093 prefill and 487 decode rows 114 -> 108 us).
+struct QkvGroup { int head, i0; };  // features i0 .. i0 + 31 and i0 + dh/2 .. of the head; head >= all of them: beyond the last
+__device__ __forceinline__ QkvGroup qkv_group(int p, const GemmArgs &a, int dh) {
+  const int per_head = dh / 64, n_v = a.n_kv_heads * per_head, n_rot = (a.n_q_heads + a.n_kv_heads) * per_head, n = n_rot + n_v;
+  const int v = (int)((unsigned)(p * n_v) / (unsigned)n);
+  const int g = p >= n ? n : (int)((unsigned)((p + 1) * n_v) / (unsigned)n) > v ? n_rot + v : p - v;
+  return QkvGroup{g / per_head, g % per_head * 32};
+}
+
 // s_waitcnt immediate (gfx9 encoding): wait until at most `vm` vector-memory
 // operations are outstanding and, if lgkm0, until all LDS reads have returned
 constexpr int waitcnt_imm(int vm, bool lgkm0) {
@@ -144,7 +156,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int bid, cons
   static_assert(BK == 64, "swizzle and fragment addressing assume 128-byte tile rows");
   static_assert(WTM % 16 == 0 && WTN % 16 == 0, "tiles are made of 16x16 MFMA blocks");
   static_assert(EPI != EPI_SWIGLU || WTN % 64 == 0, "32 gate rows and their 32 up rows pair up inside a wave");
-  static_assert(EPI != EPI_QKV || (WTN % DH == 0 && DH % 64 == 0), "a wave covers whole heads");
+  static_assert(EPI != EPI_QKV || (WTN % 64 == 0 && BN % DH == 0), "32 pairs of a head's features meet inside a wave");
   static_assert(2 * LA + 2 * LB < 64, "outstanding loads must fit the vmcnt field");
 
   extern __shared__ __align__(16) unsigned char smem[];
@@ -201,6 +213,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int bid, cons
       int col = n0 + (blk >> 1) * 32 + (wr & 31);
       col = col < a.N ? col : a.N - 1;
       gn = col + ((blk & 1) ? a.N : 0);
+    } else if (EPI == EPI_QKV) {
+      const QkvGroup q = qkv_group((n0 + wr) >> 6, a, DH);
+      gn = q.head * DH + q.i0 + (wr & 31) + ((wr & 32) ? DH / 2 : 0);
+      gn = gn < a.N ? gn : a.N - 1;
     } else {
       gn = n0 + wr;
       gn = gn < a.N ? gn : a.N - 1;
@@ -398,9 +414,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int bid, cons
   }
   // drain the look-ahead loads (zeros or clamped rows) before the LDS is released
   __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, true));
-  // the value heads of the fused projection pass through LDS on their way out: nobody may
-  // still be reading panels there
-  if (EPI == EPI_QKV) __syncthreads();
+  if (EPI != EPI_SWIGLU) __syncthreads();  // results pass through LDS on their way out: nobody may still be reading panels there
 
   if constexpr (SK) {
     if (seg.parts > 1) {
@@ -462,243 +476,260 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int bid, cons
   }
 
   // ---- epilogues ---------------------------------------------------------------
-  // accumulator element e of block (ni, mi): m = m0 + wm0 + mi*16 + lr,
-  // n = n_tile + wn0 + ni*16 + 4*lg + e
-  // A tile that lies wholly inside the matrix takes a copy of the epilogue without bounds
-  // checks: straight-line code whose loads all go out together; with the checks every
-  // block is a basic block of its own and the epilogue becomes a chain of memory round trips.
-  auto epilogue = [&](auto checked) {
-    constexpr bool CK = decltype(checked)::value;
-    float rstd[MI];
-    if (EPI == EPI_QKV || EPI == EPI_SWIGLU) {
-  #pragma unroll
-      for (int mi = 0; mi < MI; ++mi) {
-        const int m = m0 + wm0 + mi * 16 + lr;
-        rstd[mi] = (!CK || m < a.M) ? a.rstd[m] : 0.f;
-      }
-    }
-
-    if (EPI == EPI_PARTIAL) {
-      float *ws = a.sk_ws + (size_t)split * a.M * a.N;
-  #pragma unroll
-      for (int mi = 0; mi < MI; ++mi) {
-        const int m = m0 + wm0 + mi * 16 + lr;
-        if (CK && m >= a.M) continue;
-  #pragma unroll
-        for (int ni = 0; ni < NI; ++ni) {
-          const int n = n0 + wn0 + ni * 16 + 4 * lg;
-          if (CK && n >= a.N) continue;
-          *reinterpret_cast<f32x4_t *>(ws + (size_t)m * a.N + n) = acc[ni][mi];
-        }
-      }
-    }
-
-    if (EPI == EPI_PLAIN || EPI == EPI_RESID) {
-  #pragma unroll
-      for (int mi = 0; mi < MI; ++mi) {
-        const int m = m0 + wm0 + mi * 16 + lr;
-        if (CK && m >= a.M) continue;
-  #pragma unroll
-        for (int ni = 0; ni < NI; ++ni) {
-          const int n = n0 + wn0 + ni * 16 + 4 * lg;
-          if (CK && n >= n_lim) continue;
-          float v[4];
-  #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = acc[ni][mi][e];
-          if (EPI == EPI_RESID) {
-            if (a.resid32) {
-              const f32x4_t rr = *reinterpret_cast<const f32x4_t *>(a.resid32 + (size_t)m * a.ldr + n);
-  #pragma unroll
-              for (int e = 0; e < 4; ++e) v[e] += rr[e];
-            } else {
-              const u32x2_t rr = *reinterpret_cast<const u32x2_t *>(a.resid + (size_t)m * a.ldr + n);
-              v[0] += __uint_as_float(rr.x << 16);
-              v[1] += __uint_as_float(rr.x & 0xFFFF0000u);
-              v[2] += __uint_as_float(rr.y << 16);
-              v[3] += __uint_as_float(rr.y & 0xFFFF0000u);
-            }
-          }
-          store_bf16x4(a.C + (size_t)m * a.ldc + n, v[0], v[1], v[2], v[3]);
-        }
-      }
-    }
-
-    if (EPI == EPI_RESID_NORM) {
-  #pragma unroll
-      for (int mi = 0; mi < MI; ++mi) {
-        const int m = m0 + wm0 + mi * 16 + lr;
-        float ss = 0.f;
-        if (!CK || m < a.M) {
-  #pragma unroll
-          for (int ni = 0; ni < NI; ++ni) {
-            const int n = n0 + wn0 + ni * 16 + 4 * lg;
-            if (CK && n >= a.N) continue;
-            const u32x2_t rr = *reinterpret_cast<const u32x2_t *>(a.resid + (size_t)m * a.ldr + n);
-            const u32x2_t gg = *reinterpret_cast<const u32x2_t *>(a.gain + n);
-            float v[4], g[4];
-            v[0] = acc[ni][mi][0] + __uint_as_float(rr.x << 16);
-            v[1] = acc[ni][mi][1] + __uint_as_float(rr.x & 0xFFFF0000u);
-            v[2] = acc[ni][mi][2] + __uint_as_float(rr.y << 16);
-            v[3] = acc[ni][mi][3] + __uint_as_float(rr.y & 0xFFFF0000u);
-            g[0] = __uint_as_float(gg.x << 16);
-            g[1] = __uint_as_float(gg.x & 0xFFFF0000u);
-            g[2] = __uint_as_float(gg.y << 16);
-            g[3] = __uint_as_float(gg.y & 0xFFFF0000u);
-  #pragma unroll
-            for (int e = 0; e < 4; ++e) ss += v[e] * v[e];
-            // x1 stays in fp32 for the second residual add; the next GEMM reads bf16(x1 * gain)
-            *reinterpret_cast<f32x4_t *>(a.C32 + (size_t)m * a.ldc + n) = f32x4_t{v[0], v[1], v[2], v[3]};
-            store_bf16x4(a.C_gain + (size_t)m * a.ldc + n, v[0] * g[0], v[1] * g[1], v[2] * g[2], v[3] * g[3]);
-          }
-        }
-        // the four lanes that share the row (lg = 0..3) add up: one partial sum per wavefront column
-        ss += __shfl_xor(ss, 16, 64);
-        ss += __shfl_xor(ss, 32, 64);
-        if (lg == 0 && (!CK || m < a.M))
-          a.ss_out[(size_t)(tc.tn * WAVES_N + (wave % WAVES_N)) * a.ss_stride + m] = ss;
-      }
-    }
-
-    if (EPI == EPI_SWIGLU) {
-      // the weight tile interleaves 32 gate rows with the matching 32 up rows: blocks 4p, 4p+1 are
-      // gate features 32p .. 32p+31 of the wavefront, blocks 4p+2, 4p+3 their up features
-  #pragma unroll
-      for (int mi = 0; mi < MI; ++mi) {
-        const int m = m0 + wm0 + mi * 16 + lr;
-        if (CK && m >= a.M) continue;
-        const float s = rstd[mi];
-  #pragma unroll
-        for (int p = 0; p < NI / 4; ++p)
-  #pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const int n = n0 + (wn0 >> 1) + p * 32 + h * 16 + 4 * lg;
-            if (CK && n >= n_lim) continue;
-            float v[4];
-  #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float g = acc[4 * p + h][mi][e] * s;
-              const float u = acc[4 * p + 2 + h][mi][e] * s;
-              v[e] = g / (1.f + __expf(-g)) * u;
-            }
-            store_bf16x4(a.C + (size_t)m * a.ldc + n, v[0], v[1], v[2], v[3]);
-          }
-      }
-    }
-
-    if (EPI == EPI_QKV) {
-      constexpr int HB = DH / 16, PB = HB / 2, HALF = DH / 2;
-      constexpr int FS = (WTM + 4) * 2;  // bytes per feature of a wavefront's transposed block
-      static_assert(NW * WTN * FS <= NU * UNIT, "the transposed blocks fit the panel ring");
-      const size_t tile_elems = (size_t)16 * DH;  // one K or V tile of a (page, head)
-  #pragma unroll
-      for (int hh = 0; hh < WTN / DH; ++hh) {
-        const int nh = n0 + wn0 + hh * DH;
-        if (CK && nh >= a.N) continue;
-        const int head = nh / DH;
-        const bool is_q = head < a.n_q_heads;
-        const bool is_k = !is_q && head < a.n_q_heads + a.n_kv_heads;
-  #pragma unroll
-        for (int mi = 0; mi < MI; ++mi) {
-          const int m = m0 + wm0 + mi * 16 + lr;
-          if (CK && m >= a.M) continue;
-          const float s = rstd[mi];
-          if (is_q || is_k) {
-            const int pos = a.row_pos[m];
-            uint16_t *dst;
-            if (is_q) {
-              dst = a.q_out + (size_t)m * (a.n_q_heads * DH) + head * DH;
-            } else {
-              const size_t page = a.row_page[m];
-              dst = a.kv_pool + ((page * 2 + 0) * a.n_kv_heads + (head - a.n_q_heads)) * tile_elems +
-                    (size_t)a.row_slot[m] * DH;
-            }
-  #pragma unroll
-            for (int j = 0; j < PB; ++j) {
-              const int i = j * 16 + 4 * lg;
-              const f32x4_t c4 = *reinterpret_cast<const f32x4_t *>(a.rope_cos + (size_t)pos * HALF + i);
-              const f32x4_t s4 = *reinterpret_cast<const f32x4_t *>(a.rope_sin + (size_t)pos * HALF + i);
-              float lo[4], hi[4];
-  #pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                const float l = acc[hh * HB + j][mi][e] * s;
-                const float h = acc[hh * HB + PB + j][mi][e] * s;
-                lo[e] = l * c4[e] - h * s4[e];
-                hi[e] = h * c4[e] + l * s4[e];
-              }
-              store_bf16x4(dst + i, lo[0], lo[1], lo[2], lo[3]);
-              store_bf16x4(dst + HALF + i, hi[0], hi[1], hi[2], hi[3]);
-            }
-          } else {
-            // V^T tiles hold, per feature, the 16 slots of a page side by side, while a lane
-            // holds four features of one row: the wavefront turns its block round in LDS
-            // (feature-major, FS bytes per feature: the row count padded so that neither the
-            // 2-byte writes nor the 8-byte reads below collide on banks)
-            unsigned char *vt = smem + wave * (WTN * FS) + hh * (DH * FS);
-  #pragma unroll
-            for (int b = 0; b < HB; ++b)
-  #pragma unroll
-              for (int e = 0; e < 4; ++e)
-                *reinterpret_cast<uint16_t *>(vt + (b * 16 + 4 * lg + e) * FS + (mi * 16 + lr) * 2) =
-                    f32_to_bf16(acc[hh * HB + b][mi][e] * s);
-          }
-        }
-        if (!is_q && !is_k) {
-          // back out of LDS (written and read by this wavefront only): lane = 4 * feature + quad
-          // reads rows 4 quad .. 4 quad + 3 of a 16-row block for one feature.  Inside a prefill
-          // segment these are four adjacent slots of one page, and the 64 lanes then cover 512
-          // contiguous bytes of the page's V^T tile; they go out as one 8-byte store (or two
-          // 4-byte ones) where the address allows.  Rows of different sequences, or on either
-          // side of a page boundary, take a 2-byte store each.
-          __builtin_amdgcn_wave_barrier();  // the LDS operations of a wavefront complete in order
-          const unsigned char *vt = smem + wave * (WTN * FS) + hh * (DH * FS);
-          const int vh = head - a.n_q_heads - a.n_kv_heads;
-          const int fl = lane >> 2, rq = lane & 3;
-  #pragma unroll
-          for (int mi = 0; mi < MI; ++mi) {
-            const int ml = mi * 16 + rq * 4, mb = m0 + wm0 + ml;
-            size_t pg[4];
-            int sl[4];
-  #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int m = (!CK || mb + e < a.M) ? mb + e : a.M - 1;
-              pg[e] = a.row_page[m];
-              sl[e] = a.row_slot[m];
-            }
-            bool run = !CK || mb + 3 < a.M;
-  #pragma unroll
-            for (int e = 1; e < 4; ++e) run = run && pg[e] == pg[0] && sl[e] == sl[0] + e;
-  #pragma unroll
-            for (int b = 0; b < HB; ++b) {
-              const int ei = b * 16 + fl;
-              const u32x2_t v = *reinterpret_cast<const u32x2_t *>(vt + ei * FS + ml * 2);
-              uint16_t *d0 = a.kv_pool + ((pg[0] * 2 + 1) * a.n_kv_heads + vh) * tile_elems + ei * 16 + sl[0];
-              if (run && (reinterpret_cast<uintptr_t>(d0) & 7) == 0) {
-                *reinterpret_cast<u32x2_t *>(d0) = v;
-              } else if (run && (reinterpret_cast<uintptr_t>(d0) & 3) == 0) {
-                reinterpret_cast<uint32_t *>(d0)[0] = v.x;
-                reinterpret_cast<uint32_t *>(d0)[1] = v.y;
-              } else {
-                const uint16_t ve[4] = {(uint16_t)(v.x & 0xFFFFu), (uint16_t)(v.x >> 16), (uint16_t)(v.y & 0xFFFFu),
-                                        (uint16_t)(v.y >> 16)};
-  #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                  if (!CK || mb + e < a.M)
-                    a.kv_pool[((pg[e] * 2 + 1) * a.n_kv_heads + vh) * tile_elems + ei * 16 + sl[e]] = ve[e];
-              }
-            }
-          }
-        }
-      }
-    }
+  // accumulator element e of block (ni, mi): m = m0 + wm0 + mi*16 + lr, n = n_tile + wn0 + ni*16 + 4*lg + e.
+  // Neighbouring lanes hold neighbouring ROWS, and a CU serves loads and stores of such lanes at about one lane per
+  // clock.  The wavefront therefore turns its 64 columns round in LDS, CM blocks of 16 rows at a time, and comes back with
+  // sixteen lanes along a row: 16 tiles of 256x256 with K = 64, launch included, output projection 28 -> 17 us, down
+  // projection 15.8 -> 12.5, QKV 15.8 -> 12.7; 8192 rows of the 8B layer 287 -> 248, 756 -> 737, 353 -> 333.
+  static_assert(WTN == 64, "an epilogue hands 64 columns to 16 lanes");
+  constexpr int CM = MI <= 4 ? MI : (MI + 1) / 2;
+  constexpr int RS = 64 * 4 + 16;  // bytes of a row of 64 floats: rows four banks apart
+  constexpr int LDS_BYTES = DEEP ? 160 * 1024 : NU * UNIT;
+  static_assert(NW * CM * 16 * RS <= LDS_BYTES, "the turned blocks fit the panel ring");
+  unsigned char *turned = smem + wave * (CM * 16 * RS);
+  // blocks [c, c + CM) of rows into LDS (read and written by this wavefront alone, whose LDS operations complete in order)
+  auto turn = [&](int c) {
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int j = 0; j < CM; ++j)
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni)
+        if (c + j < MI) *reinterpret_cast<f32x4_t *>(turned + (j * 16 + lr) * RS + (ni * 16 + 4 * lg) * 4) = acc[ni][c + j];
+    __builtin_amdgcn_wave_barrier();
   };
-  if (m0 + BM <= a.M && n0 + OUT_BN <= n_lim && (EPI != EPI_QKV || n0 + BN <= a.N))
-    epilogue(No{});
-  else
-    epilogue(Yes{});
+  constexpr auto rows_in = [](int c) { return (MI - c < CM ? MI - c : CM) * 16; };
+  const int r16 = lane >> 4, c16 = 4 * (lane & 15);  // four rows of 64 columns per step
+
+  if constexpr (EPI == EPI_PARTIAL || EPI == EPI_PLAIN || EPI == EPI_RESID || EPI == EPI_RESID_NORM) {
+    const int n = n0 + wn0 + c16;
+    const bool n_ok = n < n_lim;
+    const int nc = min(n, a.N - 4);  // loads beyond an edge repeat the last column or row
+    constexpr int U = 4;             // steps of four rows whose residuals are in flight
+    float *ws = a.sk_ws + (size_t)split * a.M * a.N;
+    f32x4_t gain = {0.f, 0.f, 0.f, 0.f};
+    auto bf16x4 = [](u32x2_t v) {
+      return f32x4_t{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xFFFF0000u)};
+    };
+    if constexpr (EPI == EPI_RESID_NORM) gain = bf16x4(*reinterpret_cast<const u32x2_t *>(a.gain + nc));
+    auto resid = [&](int row) -> f32x4_t {
+      const size_t at = (size_t)min(m0 + wm0 + row, a.M - 1) * a.ldr + nc;
+      if (EPI == EPI_RESID && a.resid32) return *reinterpret_cast<const f32x4_t *>(a.resid32 + at);
+      return bf16x4(*reinterpret_cast<const u32x2_t *>(a.resid + at));
+    };
+    constexpr bool ADDS = EPI == EPI_RESID || EPI == EPI_RESID_NORM;
+    f32x4_t r[U];
+    if constexpr (ADDS) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) r[u] = resid(4 * u + r16);
+    }
+#pragma unroll
+    for (int c = 0; c < MI; c += CM) {
+      turn(c);
+#pragma unroll 1
+      for (int g = 0; g < rows_in(c); g += 4 * U) {
+        f32x4_t v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          v[u] = *reinterpret_cast<const f32x4_t *>(turned + (g + 4 * u + r16) * RS + c16 * 4);
+          if constexpr (ADDS) v[u] += r[u];
+        }
+        if constexpr (ADDS) {  // the next rows, ahead of the stores: a load does not pass a store that may write what it reads
+#pragma unroll
+          for (int u = 0; u < U; ++u) r[u] = resid(c * 16 + g + 4 * U + 4 * u + r16);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int m = m0 + wm0 + c * 16 + g + 4 * u + r16;
+          const bool ok = n_ok && m < a.M;
+          if constexpr (EPI == EPI_PARTIAL) {
+            if (ok) *reinterpret_cast<f32x4_t *>(ws + (size_t)m * a.N + n) = v[u];
+          } else if constexpr (EPI == EPI_RESID_NORM) {
+            float ss = ok ? v[u][0] * v[u][0] + v[u][1] * v[u][1] + v[u][2] * v[u][2] + v[u][3] * v[u][3] : 0.f;
+            if (ok) {
+              // x1 stays in fp32 for the second residual add; the next GEMM reads bf16(x1 * gain)
+              *reinterpret_cast<f32x4_t *>(a.C32 + (size_t)m * a.ldc + n) = v[u];
+              store_bf16x4(a.C_gain + (size_t)m * a.ldc + n, v[u][0] * gain[0], v[u][1] * gain[1], v[u][2] * gain[2], v[u][3] * gain[3]);
+            }
+            // the sixteen lanes of the row add up: one partial sum per wavefront column
+#pragma unroll
+            for (int o = 1; o < 16; o <<= 1) ss += __shfl_xor(ss, o, 64);
+            if (c16 == 0 && m < a.M) a.ss_out[(size_t)(tc.tn * WAVES_N + (wave % WAVES_N)) * a.ss_stride + m] = ss;
+          } else {
+            if (ok) store_bf16x4(a.C + (size_t)m * a.ldc + n, v[u][0], v[u][1], v[u][2], v[u][3]);
+          }
+        }
+      }
+    }
+  }
+
+  float rstd[MI];
+  if constexpr (EPI == EPI_QKV || EPI == EPI_SWIGLU) {
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) rstd[mi] = a.rstd[min(m0 + wm0 + mi * 16 + lr, a.M - 1)];
+  }
+
+  if constexpr (EPI == EPI_SWIGLU) {
+    // the weight tile interleaves 32 gate rows with the matching 32 up rows: blocks 0, 1 are gate
+    // features, blocks 2, 3 their up features.  A quarter of the output projection's bytes, straight from the
+    // registers (turned round in LDS as well: 1580 rows of the 8B layer 351 -> 357 us)
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) {
+      const int m = m0 + wm0 + mi * 16 + lr;
+      const float s = rstd[mi];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int n = n0 + (wn0 >> 1) + h * 16 + 4 * lg;
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float g = acc[h][mi][e] * s;
+          const float u = acc[2 + h][mi][e] * s;
+          v[e] = g / (1.f + __expf(-g)) * u;
+        }
+        if (m < a.M && n < n_lim) store_bf16x4(a.C + (size_t)m * a.ldc + n, v[0], v[1], v[2], v[3]);
+      }
+    }
+  }
+
+  if constexpr (EPI == EPI_QKV) {
+    // the 64 tile columns of a wavefront: features i0 .. i0 + 31 of a head (blocks 0, 1) and i0 + dh/2 .. (blocks 2, 3)
+    constexpr int HALF = DH / 2;
+    const size_t tile_elems = (size_t)16 * DH;  // one K or V tile of a (page, head)
+    const QkvGroup group = qkv_group((n0 + wn0) >> 6, a, DH);
+    const int head = group.head, i0 = group.i0;
+    const bool is_q = head < a.n_q_heads;
+    const bool is_k = !is_q && head < a.n_q_heads + a.n_kv_heads;
+    if (head >= a.n_q_heads + 2 * a.n_kv_heads) {
+      // a wavefront beyond the last head
+    } else if (is_q || is_k) {
+      // eight rows per step, eight lanes with four rotation pairs each along a row
+      const int r8 = lane >> 3, p8 = 4 * (lane & 7), i = i0 + p8;
+      constexpr int U = 2;  // steps at a time; the angles of the next ones and the positions of those behind are under way
+      int pos[U], page[U], slot[U], page_n[U] = {}, slot_n[U] = {};
+      float s[U], s_n[U];
+      f32x4_t cs[U], sn[U];
+      auto ask_rows = [&](int row) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int m = min(m0 + wm0 + row + 8 * u + r8, a.M - 1);
+          pos[u] = a.row_pos[m];
+          s_n[u] = a.rstd[m];
+          if (is_k) {
+            page_n[u] = a.row_page[m];
+            slot_n[u] = a.row_slot[m];
+          }
+        }
+      };
+      auto ask_angles = [&]() {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          cs[u] = *reinterpret_cast<const f32x4_t *>(a.rope_cos + (size_t)pos[u] * HALF + i);
+          sn[u] = *reinterpret_cast<const f32x4_t *>(a.rope_sin + (size_t)pos[u] * HALF + i);
+          s[u] = s_n[u];
+          page[u] = page_n[u];
+          slot[u] = slot_n[u];
+        }
+      };
+      ask_rows(0);
+      ask_angles();
+      ask_rows(8 * U);
+#pragma unroll
+      for (int c = 0; c < MI; c += CM) {
+        turn(c);
+#pragma unroll 1
+        for (int g = 0; g < rows_in(c); g += 8 * U) {
+          f32x4_t lo[U], hi[U];
+          uint16_t *dst[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const unsigned char *row = turned + (g + 8 * u + r8) * RS;
+            const f32x4_t l = *reinterpret_cast<const f32x4_t *>(row + p8 * 4) * s[u];
+            const f32x4_t h = *reinterpret_cast<const f32x4_t *>(row + (32 + p8) * 4) * s[u];
+            lo[u] = l * cs[u] - h * sn[u];
+            hi[u] = h * cs[u] + l * sn[u];
+            const int m = m0 + wm0 + c * 16 + g + 8 * u + r8;
+            dst[u] = is_q ? a.q_out + (size_t)m * (a.n_q_heads * DH) + head * DH + i
+                          : a.kv_pool + (((size_t)page[u] * 2 + 0) * a.n_kv_heads + (head - a.n_q_heads)) * tile_elems +
+                                (size_t)slot[u] * DH + i;
+          }
+          ask_angles();
+          ask_rows(c * 16 + g + 16 * U);
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            if (m0 + wm0 + c * 16 + g + 8 * u + r8 >= a.M) continue;
+            store_bf16x4(dst[u], lo[u][0], lo[u][1], lo[u][2], lo[u][3]);
+            store_bf16x4(dst[u] + HALF, hi[u][0], hi[u][1], hi[u][2], hi[u][3]);
+          }
+        }
+      }
+    } else {
+      // V^T tiles hold, per feature, the 16 slots of a page side by side, while a lane
+      // holds four features of one row: the wavefront turns its block round in LDS
+      // (feature-major, FS bytes per feature: the row count padded so that neither the
+      // 2-byte writes nor the 8-byte reads below collide on banks)
+      constexpr int FS = (WTM + 4) * 2;
+      static_assert(64 * FS <= CM * 16 * RS, "the features of a wavefront fit its part of the ring");
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            *reinterpret_cast<uint16_t *>(turned + (b * 16 + 4 * lg + e) * FS + (mi * 16 + lr) * 2) = f32_to_bf16(acc[b][mi][e] * rstd[mi]);
+      // Back out of LDS: lane = 4 * feature + quad reads rows 4 quad .. 4 quad + 3 of a 16-row block for one
+      // feature.  Inside a prefill segment these are four adjacent slots of one page, and the 64 lanes then
+      // cover 512 contiguous bytes of the page's V^T tile; they go out as one 8-byte store (or two
+      // 4-byte ones) where the address allows.  Rows of different sequences, or on either
+      // side of a page boundary, take a 2-byte store each.
+      __builtin_amdgcn_wave_barrier();
+      const int vh = head - a.n_q_heads - a.n_kv_heads;
+      const int fl = lane >> 2, rq = lane & 3;
+      int pg[4], sl[4], pn[4], ln[4];
+      auto ask = [&](int mi, int (&p)[4], int (&l)[4]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int m = min(m0 + wm0 + mi * 16 + rq * 4 + e, a.M - 1);
+          p[e] = a.row_page[m];
+          l[e] = a.row_slot[m];
+        }
+      };
+      ask(0, pg, sl);
+#pragma unroll 1
+      for (int mi = 0; mi < MI; ++mi) {
+        const int ml = mi * 16 + rq * 4, mb = m0 + wm0 + ml;
+        ask(mi + 1, pn, ln);
+        bool run = mb + 3 < a.M;
+#pragma unroll
+        for (int e = 1; e < 4; ++e) run = run && pg[e] == pg[0] && sl[e] == sl[0] + e;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const int ei = (b >> 1) * HALF + i0 + (b & 1) * 16 + fl;
+          const u32x2_t v = *reinterpret_cast<const u32x2_t *>(turned + (b * 16 + fl) * FS + ml * 2);
+          uint16_t *d0 = a.kv_pool + (((size_t)pg[0] * 2 + 1) * a.n_kv_heads + vh) * tile_elems + ei * 16 + sl[0];
+          if (run && (reinterpret_cast<uintptr_t>(d0) & 7) == 0) {
+            *reinterpret_cast<u32x2_t *>(d0) = v;
+          } else if (run && (reinterpret_cast<uintptr_t>(d0) & 3) == 0) {
+            reinterpret_cast<uint32_t *>(d0)[0] = v.x;
+            reinterpret_cast<uint32_t *>(d0)[1] = v.y;
+          } else {
+            const uint16_t ve[4] = {(uint16_t)(v.x & 0xFFFFu), (uint16_t)(v.x >> 16), (uint16_t)(v.y & 0xFFFFu), (uint16_t)(v.y >> 16)};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (mb + e < a.M) a.kv_pool[(((size_t)pg[e] * 2 + 1) * a.n_kv_heads + vh) * tile_elems + ei * 16 + sl[e]] = ve[e];
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          pg[e] = pn[e];
+          sl[e] = ln[e];
+        }
+      }
+    }
+  }
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int DH, int DEEP = 0>
-__global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_kernel(const GemmArgs a) {
+__global__ __launch_bounds__(WAVES_M *WAVES_N * 64, 2) void gemm_kernel(const GemmArgs a) {
   gemm_tile<BM, BN, WAVES_M, WAVES_N, EPI, DH, DEEP>(a, (int)blockIdx.x);
 }
 
@@ -1220,12 +1251,14 @@ hipError_t launch_gemm(const GemmArgs &a, int epilogue, int dh, hipStream_t stre
     case EPI_SWIGLU: return launch_variant<EPI_SWIGLU, 2, 4>(a, v, stream);
     case EPI_QKV:
       if (dh == 128)
-        return v == V_SHARED ? launch_sk<256, 256, 4, 2, EPI_QKV, 128>(a, stream)
-               : v == V_BIG  ? launch_one<256, 256, 4, 2, EPI_QKV, 128>(a, stream)
-                             : launch_one<128, 128, 4, 1, EPI_QKV, 128>(a, stream);
+        return v == V_SHARED ? launch_sk<256, 256, 2, 4, EPI_QKV, 128>(a, stream)
+               : v == V_BIG  ? launch_one<256, 256, 2, 4, EPI_QKV, 128>(a, stream)
+               : v == V_TALL ? launch_one<160, 256, 2, 4, EPI_QKV, 128>(a, stream)
+                             : launch_one<128, 128, 2, 2, EPI_QKV, 128>(a, stream);
       if (dh == 64)
         return v == V_SHARED ? launch_sk<256, 256, 2, 4, EPI_QKV, 64>(a, stream)
                : v == V_BIG  ? launch_one<256, 256, 2, 4, EPI_QKV, 64>(a, stream)
+               : v == V_TALL ? launch_one<160, 256, 2, 4, EPI_QKV, 64>(a, stream)
                              : launch_one<128, 128, 2, 2, EPI_QKV, 64>(a, stream);
       return hipErrorInvalidValue;
     default:
