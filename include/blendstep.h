@@ -300,7 +300,7 @@ int bs_attention_division(bs_ctx *ctx, const bs_batch *batch, int64_t n_pages, i
 
 /* Host-only: tile shape and number of ranges along K of a layer's QKV (product 0), output (1) or down (2)
  * projection over `rows` rows.  Shapes as in bs_set_gemm_tiles, and 4 = 128x256, 5 = 256x128 on the deep weight
- * ring (at most 128 / 256 rows). */
+ * ring (at most 128 / 256 rows), 7 = the few-row kernel, which cuts K among the wavefronts of a workgroup. */
 int bs_gemm_division(bs_ctx *ctx, int32_t product, int32_t rows, int32_t *tiles, int32_t *k_ranges);
 
 #ifdef __cplusplus

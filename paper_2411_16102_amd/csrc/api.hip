@@ -161,7 +161,8 @@ int ensure_rows(bs_ctx *c, int rows) {
   if ((rc = dev_alloc(c, &c->rstd1, (size_t)cap))) return rc;
   if ((rc = dev_alloc(c, &c->rstd2, (size_t)cap))) return rc;
   c->ss2_parts = ((g.d_model + 255) / 256) * 4;  // covers both tile shapes of the projection
-  if ((rc = dev_alloc(c, &c->ss2, (size_t)cap * c->ss2_parts))) return rc;
+  // (the few-row kernel: a part per 16 columns of at most 256 rows)
+  if ((rc = dev_alloc(c, &c->ss2, std::max((size_t)cap * c->ss2_parts, (size_t)256 * ((g.d_model + 15) / 16))))) return rc;
   c->cap_rows = cap;
   return BS_OK;
 }
@@ -819,13 +820,23 @@ int run_o_gate_up(bs_ctx *c, const bs_weights *w, const uint16_t *x, int r0, int
     o.rstd_out = c->rstd2 + r0;  // the reduction closes the second norm's statistics itself
     o.rstd_eps = g.rms_eps;
   }
+  GemmArgs u = gate_up_args(c, w, r0, r1);
   const int parts = gemm_ss_parts(o, EPI_RESID_NORM, g.head_dim);
+  if (gemm_streams_weights(o, EPI_RESID_NORM)) {
+    o.ss_out = c->ss2;  // many parts of few rows
+    o.ss_stride = rows;
+    if (gemm_streams_weights(u, EPI_SWIGLU)) {  // which adds the parts up itself
+      u.ss_in = c->ss2;
+      u.ss_in_parts = parts;
+      u.ss_stride = rows;
+      u.rstd_eps = g.rms_eps;
+    }
+  }
   SPAN(c, k_o, st, {
     HIP_TRY(c, launch_gemm(o, EPI_RESID_NORM, g.head_dim, st));
-    if (o.k_splits <= 1)
-      HIP_TRY(c, launch_rstd_finalize(c->ss2 + r0, parts, c->cap_rows, c->rstd2 + r0, rows, d, g.rms_eps, st));
+    if (o.k_splits <= 1 && !u.ss_in_parts)
+      HIP_TRY(c, launch_rstd_finalize(o.ss_out, parts, o.ss_stride, c->rstd2 + r0, rows, d, g.rms_eps, st));
   });
-  const GemmArgs u = gate_up_args(c, w, r0, r1);
   GemmArgs head, tail;
   if (gemm_round_split(u, EPI_SWIGLU, g.head_dim, &head, &tail)) {
     SPAN(c, k_gu, st, HIP_TRY(c, launch_gemm(head, EPI_SWIGLU, g.head_dim, st)));

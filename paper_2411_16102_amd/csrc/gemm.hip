@@ -28,6 +28,7 @@
 // (s_waitcnt vmcnt + s_barrier); the compiler does not track them.
 #include <algorithm>
 #include <numeric>
+#include <utility>
 #include "gemm.hpp"
 #include "attn_device.hpp"
 #include "common.hpp"
@@ -904,6 +905,270 @@ __global__ __launch_bounds__(256) void splitk_reduce_qkv_kernel(const GemmArgs a
   }
 }
 
+// Few rows: a product is the stream of its weights.  One workgroup of eight wavefronts per CU takes items, 16 NI weight
+// rows by 16 MI activation rows, in turn and cuts K among its wavefronts, k-tiles of 64 dealt round (together they walk
+// 1 KB of every weight row at a time).  A wavefront has a ring of S k-tiles of its own in LDS, both panels, filled by its
+// own requests and read by nobody else: no barrier while it streams, and the ring runs on across items.  At the end of
+// an item the eight partial sums of a value meet in LDS, one wavefront adds them in the order of the wavefronts and runs
+// the epilogue while the others stream on: no partial products in memory, no second kernel.
+// The 16 rows of a weight block are two units of eight where the epilogue pairs rows: gate and up rows, or the lower and
+// upper half of a head's rotation pairs.
+// Measured, cold weights, second kernels included, 8B layer at 8 rows: QKV 17.1 -> 12.9 us, output projection
+// 14.9 -> 9.1, gate/up 53.8 -> 39.5 (5.9 TB/s), down 27.9 -> 22.9; K = N = 256 7.7 -> 3.4.  Not depth but the order of
+// the requests makes the difference: 128x128 tiles with as many bytes in flight take 54 us for gate/up, every workgroup
+// at the same column of 128 rows 8 KB apart.  Loads straight into registers (a lane's operand: 16 bytes of a row
+// 8 KB from its neighbour's) reach 16 bytes per clock and CU: 56 us.
+constexpr int ROWS_MAX_M = 256;
+// blocks of 16 weight rows of a product (of pairs of eight where the epilogue pairs rows)
+constexpr long rows_blocks(int n, int epi) { return epi == EPI_QKV ? n / 16 : epi == EPI_SWIGLU ? n / 8 : (n + 15) / 16; }
+template <int MI, int NI>  // blocks of 16 activation rows, blocks of 16 weight rows
+struct RowsKernel {
+  static constexpr int L = 2 * (MI + NI), STAGE = L * 1024;  // loads and bytes of a k-tile
+  static constexpr int RED = 8 * MI * 1024, META = ROWS_MAX_M * 16;
+  static constexpr int S = (160 * 1024 - RED - META) / 8 / STAGE;
+  static constexpr int LDS = 8 * S * STAGE + RED + META;
+};
+
+// waits until at most J * L vector-memory operations are outstanding, for the J that equals `left`
+template <int L, int... J>
+__device__ __forceinline__ void wait_for_all_but(int left, std::integer_sequence<int, J...>) {
+  ((left == J ? __builtin_amdgcn_s_waitcnt(waitcnt_imm(J * L, false)) : (void)0), ...);
+}
+
+template <int MI, int NI>
+__global__ __launch_bounds__(512) void gemm_rows_kernel(const GemmArgs a, const int epi, const int dh, const int tiles_m, const int n_items) {
+  typedef RowsKernel<MI, NI> R;
+  constexpr int S = R::S, L = R::L;
+  static_assert(S >= 2 && (S - 1) * L < 64, "look-ahead, and the vmcnt field");
+  extern __shared__ __align__(16) unsigned char smem[];
+  f32x4_t *red = reinterpret_cast<f32x4_t *>(smem + 8 * S * R::STAGE);  // [8][MI][64]
+  float *meta_rs = reinterpret_cast<float *>(smem + 8 * S * R::STAGE + R::RED);  // [ROWS_MAX_M] per row: norm factor, position, page, slot
+  int *meta_pos = reinterpret_cast<int *>(meta_rs + ROWS_MAX_M), *meta_page = meta_pos + ROWS_MAX_M, *meta_slot = meta_page + ROWS_MAX_M;
+  const bool paired = epi == EPI_QKV || epi == EPI_SWIGLU;
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int lr = lane & 15, lg = lane >> 4;
+  unsigned char *ring = smem + wave * S * R::STAGE;
+
+  // requests: 8 lanes per row of 128 bytes, chunks swizzled as in gemm_tile
+  const int g_row = lane >> 3, g_slot = lane & 7;
+  const int chunk[2] = {g_slot ^ (g_row >> 1), g_slot ^ ((g_row + 8) >> 1)};  // rows g_row and g_row + 8 of a block
+  uint32_t off_x[2 * MI], off_w[2 * NI];
+  const int per_head = dh / 16;
+  auto first_row = [&](int blk) { return epi == EPI_QKV ? blk / per_head * dh + blk % per_head * 8 : paired ? blk * 8 : blk * 16; };
+  const int second = epi == EPI_QKV ? dh / 2 : a.N;  // from a paired unit's first eight rows to its second
+  // items: the row tiles of a weight block one after the other
+  auto set_item = [&](int item) {
+    const int blk = item / tiles_m, m0 = item % tiles_m * 16 * MI;
+#pragma unroll
+    for (int i = 0; i < 2 * MI; ++i) off_x[i] = (uint32_t)(((size_t)min(m0 + i * 8 + g_row, a.M - 1) * a.lda + chunk[i & 1] * 8) * 2);
+#pragma unroll
+    for (int i = 0; i < 2 * NI; ++i) {
+      // rows beyond the last repeat it (a unit of eight is whole or beyond it altogether)
+      const int row = min(first_row(blk * NI + i / 2) + (paired ? 0 : 8 * (i & 1)) + g_row, a.N - 1 - (epi == EPI_QKV ? second : 0)) +
+                      (paired ? (i & 1) * second : 0);
+      off_w[i] = (uint32_t)(((size_t)row * a.ldb + chunk[i & 1] * 8) * 2);
+    }
+  };
+  const int nk = (a.K + BK - 1) / BK;
+  const int n = nk > wave ? (nk - wave + 7) / 8 : 0;  // k-tiles of this wavefront per item
+  const int mine = (n_items - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
+  const int total = n * mine;                       // k-tiles it will see
+  int i_item = (int)blockIdx.x, i_k = 0, i_slot = 0, issued = 0;
+  auto dma = [](const void *p, unsigned char *lds) {
+    __builtin_amdgcn_global_load_lds(p, (__attribute__((address_space(3))) void *)lds, 16, 0, 0);
+  };
+  auto issue = [&]() __attribute__((always_inline)) {
+    const int kt = wave + 8 * i_k;
+    const unsigned char *bw = reinterpret_cast<const unsigned char *>(a.B) + (size_t)kt * 128;
+    const unsigned char *bx = reinterpret_cast<const unsigned char *>(a.A) + (size_t)kt * 128;
+    unsigned char *dst = ring + i_slot * R::STAGE;
+    const int beyond = (kt + 1) * BK > a.K ? a.K - kt * BK : BK;  // first element of the k-tile that lies beyond K
+    if (beyond == BK) {
+#pragma unroll
+      for (int i = 0; i < 2 * NI; ++i) dma(bw + off_w[i], dst + i * 1024);
+#pragma unroll
+      for (int i = 0; i < 2 * MI; ++i) dma(bx + off_x[i], dst + (2 * NI + i) * 1024);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 2 * NI; ++i) dma(chunk[i & 1] * 8 >= beyond ? (const void *)g_gemm_zero_chunk : bw + off_w[i], dst + i * 1024);
+#pragma unroll
+      for (int i = 0; i < 2 * MI; ++i) dma(chunk[i & 1] * 8 >= beyond ? (const void *)g_gemm_zero_chunk : bx + off_x[i], dst + (2 * NI + i) * 1024);
+    }
+    ++issued;
+    i_slot = i_slot + 1 == S ? 0 : i_slot + 1;
+    if (++i_k == n) {
+      i_k = 0;
+      i_item += (int)gridDim.x;
+      if (i_item < n_items) set_item(i_item);
+    }
+  };
+  if (total > 0) set_item(i_item);
+  for (int s = 0; s < S && issued < total; ++s) issue();
+
+  // what the epilogue asks per row
+  const int rows = tiles_m * 16 * MI;  // at most ROWS_MAX_M
+  if (t < rows) {
+    const int m = min(t, a.M - 1);
+    if (epi == EPI_QKV) {
+      meta_pos[t] = a.row_pos[m];
+      meta_page[t] = a.row_page[m];
+      meta_slot[t] = a.row_slot[m];
+    }
+    if (paired && !a.ss_in_parts) meta_rs[t] = a.rstd[m];
+  }
+  if (paired && a.ss_in_parts) {
+    // the second norm's factor from the output projection's partial row sums: 512 / rows threads per row
+    const int per_row = 512 / rows, r = t % rows, q = t / rows;
+    float s = 0.f;
+    if (q < per_row) {
+#pragma unroll 8
+      for (int p = q; p < a.ss_in_parts; p += per_row) s += a.ss_in[(size_t)p * a.ss_stride + min(r, a.M - 1)];
+    }
+    float *part = reinterpret_cast<float *>(red);
+    part[t] = s;
+    __syncthreads();
+    if (t < rows) {
+      s = 0.f;
+      for (int i = 0; i < per_row; ++i) s += part[t + rows * i];
+      meta_rs[t] = rsqrtf(s / (float)a.K + a.rstd_eps);
+    }
+    __syncthreads();
+  }
+
+  const int sw = (lr >> 1) & 7;
+  int slot = 0, left = total, turn = 0;
+  for (int item = (int)blockIdx.x; item < n_items; item += (int)gridDim.x, ++turn) {
+    const int blk = item / tiles_m, m0 = item % tiles_m * 16 * MI;
+    f32x4_t acc[NI][MI];
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < n; ++k) {
+      --left;  // k-tiles behind this one
+      if (left >= S - 1) {
+        __builtin_amdgcn_s_waitcnt(waitcnt_imm((S - 1) * L, false));
+      } else {
+        wait_for_all_but<L>(left, std::make_integer_sequence<int, S - 1>{});
+      }
+      const unsigned char *st = ring + slot * R::STAGE;
+      bf16x8_t w[2][NI], x[2][MI];
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const int ch = ((ks * 4 + lg) ^ sw) << 4;
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) w[ks][ni] = as_bf16x8(*reinterpret_cast<const u32x4_t *>(st + ni * 2048 + lr * 128 + ch));
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) x[ks][mi] = as_bf16x8(*reinterpret_cast<const u32x4_t *>(st + (NI + mi) * 2048 + lr * 128 + ch));
+      }
+      __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, true));  // the slot may be filled again
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+          for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][ni], x[ks][mi], acc[ni][mi], 0, 0, 0);
+      if (left >= S) issue();
+      slot = slot + 1 == S ? 0 : slot + 1;
+    }
+    // the partial sums of 16 weight rows at a time meet; the requests in flight are left alone
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni) {
+      __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, true));
+      __builtin_amdgcn_s_barrier();  // nobody reads the sums before these any more
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi) red[(wave * MI + mi) * 64 + lane] = acc[ni][mi];
+      __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, true));
+      __builtin_amdgcn_s_barrier();
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi) {
+        if (wave != ((turn * NI + ni) * MI + mi) % 8) continue;
+        auto total_of = [&](int l) {
+          f32x4_t s = red[mi * 64 + l];
+#pragma unroll
+          for (int v = 1; v < 8; ++v) s += red[(v * MI + mi) * 64 + l];
+          return s;
+        };
+        const int ml = m0 + 16 * mi + lr;  // (at most ROWS_MAX_M - 1)
+        const bool ok = ml < a.M;
+        if (paired) {
+          const int u = first_row(blk * NI + ni) + 4 * (lg & 1);  // first of this lane's four rows of the lower unit
+          const f32x4_t lo = total_of(lane & 31) * meta_rs[ml], hi = total_of((lane & 31) + 32) * meta_rs[ml];
+          if (!ok || lg > 1 || u >= a.N) continue;
+          if (epi == EPI_SWIGLU) {
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = lo[e] / (1.f + __expf(-lo[e])) * hi[e];
+            store_bf16x4(a.C + (size_t)ml * a.ldc + u, v[0], v[1], v[2], v[3]);
+          } else {
+            const int head = u / dh, i0 = u % dh, half = dh / 2;
+            const size_t tile_elems = (size_t)16 * dh, page = meta_page[ml];
+            const int slot_in = meta_slot[ml];
+            if (head < a.n_q_heads + a.n_kv_heads) {
+              const size_t at = (size_t)meta_pos[ml] * half + i0;
+              const f32x4_t cs = *reinterpret_cast<const f32x4_t *>(a.rope_cos + at), sn = *reinterpret_cast<const f32x4_t *>(a.rope_sin + at);
+              const f32x4_t l = lo * cs - hi * sn, h = hi * cs + lo * sn;
+              uint16_t *dst = head < a.n_q_heads
+                                  ? a.q_out + (size_t)ml * (a.n_q_heads * dh) + head * dh
+                                  : a.kv_pool + ((page * 2 + 0) * a.n_kv_heads + (head - a.n_q_heads)) * tile_elems + (size_t)slot_in * dh;
+              store_bf16x4(dst + i0, l[0], l[1], l[2], l[3]);
+              store_bf16x4(dst + half + i0, h[0], h[1], h[2], h[3]);
+            } else {
+              uint16_t *dst = a.kv_pool + ((page * 2 + 1) * a.n_kv_heads + (head - a.n_q_heads - a.n_kv_heads)) * tile_elems + slot_in;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                dst[(i0 + e) * 16] = f32_to_bf16(lo[e]);
+                dst[(i0 + half + e) * 16] = f32_to_bf16(hi[e]);
+              }
+            }
+          }
+        } else {
+          f32x4_t v = total_of(lane);
+          const int n0 = (blk * NI + ni) * 16 + 4 * lg;
+          const bool in = ok && n0 < a.N;
+          const size_t at = (size_t)ml * a.ldr + n0;
+          if (in && epi == EPI_RESID && a.resid32) {
+            v += *reinterpret_cast<const f32x4_t *>(a.resid32 + at);
+          } else if (in && epi != EPI_PLAIN) {
+            const u32x2_t rr = *reinterpret_cast<const u32x2_t *>(a.resid + at);
+            v += f32x4_t{__uint_as_float(rr.x << 16), __uint_as_float(rr.x & 0xFFFF0000u), __uint_as_float(rr.y << 16), __uint_as_float(rr.y & 0xFFFF0000u)};
+          }
+          if (epi == EPI_RESID_NORM) {
+            float ss = 0.f;
+            if (in) {
+              const u32x2_t gg = *reinterpret_cast<const u32x2_t *>(a.gain + n0);
+              ss = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+              *reinterpret_cast<f32x4_t *>(a.C32 + (size_t)ml * a.ldc + n0) = v;
+              store_bf16x4(a.C_gain + (size_t)ml * a.ldc + n0, v[0] * __uint_as_float(gg.x << 16), v[1] * __uint_as_float(gg.x & 0xFFFF0000u),
+                           v[2] * __uint_as_float(gg.y << 16), v[3] * __uint_as_float(gg.y & 0xFFFF0000u));
+            }
+            ss += __shfl_xor(ss, 16, 64);
+            ss += __shfl_xor(ss, 32, 64);
+            if (lg == 0 && in) a.ss_out[(size_t)(blk * NI + ni) * a.ss_stride + ml] = ss;
+          } else if (in) {
+            store_bf16x4(a.C + (size_t)ml * a.ldc + n0, v[0], v[1], v[2], v[3]);
+          }
+        }
+    }
+    }
+  }
+}
+
+template <int MI, int NI>
+hipError_t launch_rows_one(const GemmArgs &a, int epi, int dh, hipStream_t stream) {
+  typedef RowsKernel<MI, NI> R;
+  const int n_cu = a.n_cu > 0 ? a.n_cu : 256, tiles_m = (a.M + 16 * MI - 1) / (16 * MI);
+  if (tiles_m * 16 * MI > ROWS_MAX_M || a.N % 8) return hipErrorInvalidValue;
+  const long items = (long)tiles_m * ((rows_blocks(a.N, epi) + NI - 1) / NI), rounds = (items + n_cu - 1) / n_cu;
+  if (items <= 0 || items >= (1L << 30)) return hipErrorInvalidValue;
+  auto kern = gemm_rows_kernel<MI, NI>;
+  static OncePerDevice once;
+  if (const hipError_t e = allow_lds(once, reinterpret_cast<const void *>(kern), R::LDS)) return e;
+  // as many workgroups as give each the same number of items
+  hipLaunchKernelGGL(kern, dim3((unsigned)((items + rounds - 1) / rounds)), dim3(512), R::LDS, stream, a, epi, dh, tiles_m, (int)items);
+  return hipGetLastError();
+}
+
 template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int DH, int DEEP = 0>
 hipError_t launch_one(const GemmArgs &a, hipStream_t stream) {
   constexpr int OUT_BN = (EPI == EPI_SWIGLU) ? BN / 2 : BN;
@@ -977,7 +1242,7 @@ hipError_t launch_ride(const GemmArgs &a, const GemmRide &r, hipStream_t stream)
 // (256x128) or three of 32 KB (128x256); measured against two slots (six / four weight slots) on the
 // 256-row gate/up GEMM of the 8B layer: 0.075 against 0.078 ms, the other GEMMs the same
 constexpr int DEEP_X = 2;
-enum { V_AUTO = 0, V_BIG = 1, V_TALL = 2, V_SMALL = 3, V_S128 = 4, V_S256 = 5, V_SHARED = 6 };
+enum { V_AUTO = 0, V_BIG = 1, V_TALL = 2, V_SMALL = 3, V_S128 = 4, V_S256 = 5, V_SHARED = 6, V_ROWS = 7 };
 constexpr int N_CU = 256;
 
 thread_local int g_forced_variant = V_AUTO;  // set by the calling entry point from its context, for the launches of that call
@@ -988,6 +1253,25 @@ long n_tiles(int m, int n, int bm, int bn) { return (long)((m + bm - 1) / bm) * 
 int short_variant(int m) {
   if (g_forced_variant != V_AUTO || m > 256) return 0;
   return m <= 128 ? V_S128 : V_S256;
+}
+
+// The few-row kernel's item, as 10 MI + NI (0: the tiles are the better choice, or a shape is forced).  Up to 16 rows it is
+// ahead everywhere (70B down projection at 16 rows 88 against 86 us, the one exception).  Beyond, the activation rows of an
+// item outweigh its weights: it needs one round of items (gate/up two, which saves nothing else) over a short K, or its
+// eight wavefronts hold too little of K in flight.  Measured at 32 rows against the tiles, both with cold
+// weights: N = 3072, K = 2048 QKV 7.2 against 12.2 us, N = K = 4096 output projection 11.3 against 15.9, N = 2048,
+// K = 8192 down 16.3 against 17.7; N = 4096, K = 14336 31 against 28.5; gate/up of 2 x 8192 columns, K = 2048 17 against 24.8,
+// of 2 x 14336, K = 4096 51.5 against 54 for shallow tiles.  Above 64 rows only where a wavefront has one k-tile or two:
+// 136 rows, N = 512, K = 256 5 against 10.5 us; N = 256, K = 688 5 against 12.
+int rows_item(int m, int n, int k, int epilogue, int n_cu) {
+  if (g_forced_variant != V_AUTO || m > ROWS_MAX_M || n % 8) return 0;
+  const long nk = (k + BK - 1) / BK, blocks = rows_blocks(n, epilogue);
+  if (m <= 16) return 11;
+  const long tiles_m = (m + 31) / 32, longest = m <= 64 ? 128 : 12;
+  if (nk > longest) return 0;
+  if (tiles_m * blocks <= n_cu) return 21;
+  const long rounds = epilogue == EPI_SWIGLU && m <= 32 ? 2 : 1;
+  return tiles_m * ((blocks + 1) / 2) <= rounds * n_cu ? 22 : 0;
 }
 
 // Tile shape of a gate/up or plain product, or of any with a forced shape (QKV, output and down projection:
@@ -1053,9 +1337,14 @@ void gemm_force_variant(int v) { g_forced_variant = v; }
 size_t gemm_sk_workspace_floats() { return (size_t)2 * SK_MAX_G * 256 * 256; }
 int gemm_sk_counters() { return 2 * SK_MAX_G; }
 
+bool gemm_streams_weights(const GemmArgs &a, int epilogue) {
+  return !a.n_count && a.k_splits <= 1 && rows_item(a.M, a.N, a.K, epilogue, a.n_cu > 0 ? a.n_cu : N_CU) != 0;
+}
+
 bool gemm_round_split(const GemmArgs &a, int epilogue, int dh, GemmArgs *head, GemmArgs *tail) {
   if (epilogue != EPI_SWIGLU || g_forced_variant != V_AUTO || a.k_splits > 1) return false;
   const int n_cols = a.n_count ? a.n_count : a.N;
+  if (gemm_streams_weights(a, epilogue)) return false;
   if (choose_variant(a.M, 2 * n_cols, epilogue, dh, a.n_cu) != V_BIG) return false;
   const int n_cu = a.n_cu > 0 ? a.n_cu : N_CU;
   const long tm = (a.M + 255) / 256, tn = (n_cols + 127) / 128;  // a 256x256 tile yields 128 output columns
@@ -1075,6 +1364,10 @@ bool gemm_round_split(const GemmArgs &a, int epilogue, int dh, GemmArgs *head, G
 void gemm_plan(GemmArgs &a, int epilogue) {
   a.k_splits = 1;
   const int n_cu = std::min(a.n_cu > 0 ? a.n_cu : N_CU, N_CU);
+  if (gemm_streams_weights(a, epilogue)) {
+    a.tile_variant = V_ROWS;
+    return;
+  }
   const long nk = (a.K + BK - 1) / BK;
   const size_t room = a.sk_ws && a.N % 4 == 0 ? gemm_sk_workspace_floats() : 0;
   // k-ranges of at least eight k-tiles, one round of workgroups, partial products that fit the workspace
@@ -1157,6 +1450,7 @@ int gemm_ss_parts(const GemmArgs &a, int epilogue, int dh) {
   if (a.k_splits > 1) return 1;  // the split-K reduction leaves whole row sums
   const int v = a.tile_variant ? a.tile_variant
                                : choose_variant(a.M, a.N, epilogue, dh, a.n_cu, a.sk_ws && a.sk_cnt && !a.n_count ? a.K : 0);
+  if (v == V_ROWS) return (a.N + 15) / 16;  // one per block of 16 columns
   // partial row sums: one per (column tile, wavefront column)
   return v == V_SMALL ? ((a.N + 127) / 128) * 2 : ((a.N + 255) / 256) * 4;
 }
@@ -1241,6 +1535,15 @@ hipError_t launch_gemm(const GemmArgs &a, int epilogue, int dh, hipStream_t stre
   }
   if (a.n_count && epilogue != EPI_SWIGLU && epilogue != EPI_PLAIN) return hipErrorInvalidValue;
   const int n_cols = a.n_count ? a.n_count : a.N;
+  const bool streams = a.tile_variant ? a.tile_variant == V_ROWS : (epilogue == EPI_SWIGLU || epilogue == EPI_PLAIN) && gemm_streams_weights(a, epilogue);
+  if (streams) {
+    switch (rows_item(a.M, a.N, a.K, epilogue, a.n_cu > 0 ? a.n_cu : N_CU)) {
+      case 11: return launch_rows_one<1, 1>(a, epilogue, dh, stream);
+      case 21: return launch_rows_one<2, 1>(a, epilogue, dh, stream);
+      case 22: return launch_rows_one<2, 2>(a, epilogue, dh, stream);
+      default: return hipErrorInvalidValue;
+    }
+  }
   const int v = a.tile_variant ? a.tile_variant
                                : choose_variant(a.M, (epilogue == EPI_SWIGLU) ? 2 * n_cols : n_cols, epilogue, dh, a.n_cu,
                                                 a.sk_ws && a.sk_cnt && !a.n_count ? a.K : 0);

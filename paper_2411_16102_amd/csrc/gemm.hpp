@@ -33,14 +33,17 @@ struct GemmArgs {
   int ldr;
   // RMSNorm of the A rows, applied as a per-row factor after the contraction
   const float *rstd;     // [M] 1 / sqrt(mean(x^2) + eps) of each row (QKV, SWIGLU)
-  int ss_stride;         // row stride of ss_out
+  int ss_stride;         // row stride of ss_out (and of ss_in)
   // RESID_NORM extras
   const uint16_t *gain;  // [N] bf16 gain of the next norm
   float *C32;            // [M, ldc] x1 in fp32
   uint16_t *C_gain;      // [M, ldc] bf16(x1 * gain)
-  float *ss_out;         // [tiles_n * waves_n][ss_stride] partial row sums of x1^2
+  float *ss_out;         // [gemm_ss_parts][ss_stride] partial row sums of x1^2
   float *rstd_out;       // split-K only (may be NULL): the reduction, which sees whole rows, leaves
-  float rstd_eps;        //   1 / sqrt(mean(x1^2) + rstd_eps) of each row here, and no pass over ss_out is needed
+  float rstd_eps;        //   1 / sqrt(mean(x1^2) + rstd_eps) of each row here, and no pass over ss_out is needed (also for ss_in)
+  // SWIGLU on the few-row kernel: the partial row sums of the second norm in place of rstd (0 parts: rstd is complete)
+  const float *ss_in;    // [ss_in_parts][ss_stride]
+  int ss_in_parts;
   // Split-K (QKV, RESID and RESID_NORM where whole tiles leave CUs idle): k_splits > 1 cuts K into
   // that many ranges, each (tile, range) is one workgroup that leaves fp32 partial products in sk_ws
   // [k_splits][M][N]; a second kernel adds them up in a fixed order and applies the epilogue.
@@ -83,6 +86,8 @@ int gemm_ride_tiles(const GemmArgs &a, int epilogue);
 hipError_t launch_gemm(const GemmArgs &a, int epilogue, int dh, hipStream_t stream);
 // partial-sum slots a RESID_NORM launch over N columns writes
 int gemm_ss_parts(const GemmArgs &a, int epilogue, int dh);
+// Whether a product of these sizes goes to the few-row kernel (with the forced shapes in mind; GemmArgs::ss_in is for it).
+bool gemm_streams_weights(const GemmArgs &a, int epilogue);
 // Whole rounds first: when a gate/up GEMM on 256x256 tiles would end with a round that leaves
 // more than a quarter of the chip idle, returns true and the two column ranges to launch
 // instead: `head` = the tile columns of the whole rounds, `tail` = the rest (whatever tile

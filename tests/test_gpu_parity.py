@@ -696,3 +696,20 @@ def test_descriptors_of_calls_in_flight_do_not_overwrite_one_another(lib):
     outs = [layer.attention(batches[i], qs[i], pool, pages) for i in order]
     for i, out in zip(order, outs):
         assert torch.equal(out, alone[i]), i
+
+
+@pytest.mark.parametrize("shape,rows,division", [
+    # one and two blocks of rows; columns in half a block, contractions with a partial last k-tile or less than one per
+    # wavefront; several items per workgroup (gate/up of 513 units)
+    (W.LayerShape(264, 3, 1, 64, 344), 1, (7, 7, 7)), (W.LayerShape(520, 20, 2, 128, 4104), 7, (7, 7, 7)),
+    (W.LayerShape(4104, 5, 1, 128, 4104), 16, (7, 7, 7)), (W.LayerShape(264, 3, 1, 64, 344), 17, (7, 7, 7)),
+    (W.LayerShape(520, 20, 2, 128, 4104), 32, (7, 7, 7)), (W.LayerShape(520, 20, 2, 128, 4104), 33, (7, 7, 7)),
+    (W.LayerShape(1032, 8, 8, 64, 8200), 64, (7, 7, 3)), (W.LayerShape(264, 3, 1, 64, 344), 136, (7, 7, 7)),
+    (W.LayerShape(256, 4, 4, 64, 760), 256, (7, 7, 7)), (W.LayerShape(4096, 32, 8, 128, 1024), 32, (7, 7, 7))])
+def test_few_rows_stream_the_weights(lib, shape, rows, division):
+    layer = lib.Layer(shape, device=-1)
+    assert tuple(layer.gemm_division(p, rows)[0] for p in ("qkv", "o", "down")) == division
+    n = max(1, rows // 2)
+    seqs = ([(rows - n, rows - n + 21, -1)] if rows > n else []) + [(1, 20 + 9 * i, -1) for i in range(n)]
+    batch = W.assemble_batch(16, seqs, 1 if rows > n else 0, [], np.random.default_rng(rows))
+    check_step(lib, shape, batch, W.make_tensors(shape, batch, rows, gains="random"))
