@@ -224,8 +224,20 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int bid, cons
     }
     off_b[i] = (uint32_t)(((size_t)gn * a.ldb + chunk * 8) * 2);
   }
+  // Products of few rows on whole tiles, weight rows a multiple of 4 KB apart: every tile begins 16 k-tiles further along
+  // K than the one before and comes round.  All of them at the same column would ask for lines on few of the memory
+  // channels at any moment (the activation panel, read by all, stays in the caches anyway).  64 rows, 64x128 tiles:
+  // 2 x 14336 columns, K = 4096 53.5 -> 44.1 us, K = 8192 164 -> 162; rows of other lengths lose up to 4 % by it.
+  constexpr bool TURNED = DEEP && EPI != EPI_PARTIAL && BM <= 128;
+  const int nk_whole = (a.K + BK - 1) / BK;
+  const int first_kt = TURNED && a.ldb % 2048 == 0 && a.K % BK == 0 ? tile_id * 16 % nk_whole : 0;
+  auto turned_kt = [&](int kt) {
+    if (!TURNED || kt >= nk_whole) return kt;
+    return kt + first_kt >= nk_whole ? kt + first_kt - nk_whole : kt + first_kt;
+  };
   // load number i of panel X(kt) / W(kt) into ring slot `slot`; `checked` handles chunks past K
   auto dma_a = [&](int kt, int lds_off, int i, auto checked) {
+    kt = turned_kt(kt);
     const unsigned char *base = reinterpret_cast<const unsigned char *>(a.A) + (size_t)kt * ROWB;
     const void *p = base + off_a[i];
     if constexpr (decltype(checked)::value)
@@ -233,6 +245,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int bid, cons
     __builtin_amdgcn_global_load_lds(p, (__attribute__((address_space(3))) void *)(smem + lds_off + dst_a[i]), 16, 0, 0);
   };
   auto dma_b = [&](int kt, int lds_off, int i, auto checked) {
+    kt = turned_kt(kt);
     const unsigned char *base = reinterpret_cast<const unsigned char *>(a.B) + (size_t)kt * ROWB;
     const void *p = base + off_b[i];
     if constexpr (decltype(checked)::value)
@@ -1237,12 +1250,13 @@ hipError_t launch_ride(const GemmArgs &a, const GemmRide &r, hipStream_t stream)
 // Tile shapes.  BIG: 256x256, 8 wavefronts.  TALL: 160x256, 8 wavefronts of 80x64: 2560 (and
 // 5120) rows by 4096 (8192) columns then make exactly one (four) full rounds of 256
 // workgroups where 256x256 tiles leave 38 % (17 %) of the CUs idle.  SMALL: 128x128.
-// S128 / S256: 128x256 and 256x128 tiles on the deep weight ring, for at most 128 / 256 rows.
+// S128 / S256: 128x256 and 256x128 tiles on the deep weight ring, for at most 128 / 256 rows; D64 / D128: 64x128 and
+// 128x128 tiles on it, for whole products of at most 64 / 128 rows.
 // activation slots of the short-row pipeline, minus one: three slots leave four weight slots of 16 KB
 // (256x128) or three of 32 KB (128x256); measured against two slots (six / four weight slots) on the
 // 256-row gate/up GEMM of the 8B layer: 0.075 against 0.078 ms, the other GEMMs the same
 constexpr int DEEP_X = 2;
-enum { V_AUTO = 0, V_BIG = 1, V_TALL = 2, V_SMALL = 3, V_S128 = 4, V_S256 = 5, V_SHARED = 6, V_ROWS = 7 };
+enum { V_AUTO = 0, V_BIG = 1, V_TALL = 2, V_SMALL = 3, V_S128 = 4, V_S256 = 5, V_SHARED = 6, V_ROWS = 7, V_D64 = 8, V_D128 = 9 };
 constexpr int N_CU = 256;
 
 thread_local int g_forced_variant = V_AUTO;  // set by the calling entry point from its context, for the launches of that call
@@ -1288,6 +1302,15 @@ int choose_variant(int m, int n_b_rows, int epilogue, int dh, int n_cu, int shar
   if (n_cu <= 0) n_cu = N_CU;
   if (g_forced_variant != V_AUTO && !(g_forced_variant == V_TALL && epilogue == EPI_QKV)) return g_forced_variant;
   (void)dh;
+  // Few rows that the few-row kernel leaves: measured, cold weights, against 128x128 tiles on the shallow ring, 64 (90, 128)
+  // rows: 2 x 14336 columns, K = 4096 54.9 -> 44.1 (55.9 -> 48.9, 57.2 -> 52.4) us; 2 x 8192, K = 3072 34.9 -> 31.0
+  // (35.9 -> 35.0, 37.8 -> 37.5); 2 x 13824, K = 5120 60.9 -> 55.7 (62.5 -> 61.5, 66.3 -> 66.1); 2 x 4096, K = 1024
+  // 13.7 -> 11.8 (14.0 -> 13.5, 14.4 -> 14.3); of more than one round only at 64 rows: 2 x 28672, K = 8192 165 -> 162
+  // (128x128 tiles 179 against 162 of 128x256).
+  if (g_forced_variant == V_AUTO && m <= 128 && (epilogue == EPI_SWIGLU || epilogue == EPI_PLAIN)) {
+    if (m <= 64) return V_D64;
+    if (n_tiles(m, n_b_rows, 128, 128) <= n_cu) return V_D128;
+  }
   if (const int sv = short_variant(m); sv && (epilogue == EPI_SWIGLU || epilogue == EPI_PLAIN)) {
     // worth it once the single row of tiles fills at least half the chip
     if (2 * n_tiles(m, n_b_rows, sv == V_S128 ? 128 : 256, sv == V_S128 ? 256 : 128) >= n_cu) return sv;
@@ -1325,6 +1348,8 @@ hipError_t launch_variant(const GemmArgs &a, int v, hipStream_t stream) {
   if (v == V_SHARED) return launch_sk<256, 256, DH_BIG_M, DH_BIG_N, EPI, (DH_BIG_M == 4 ? 128 : 64)>(a, stream);
   if (v == V_TALL) return launch_one<160, 256, 2, 4, EPI, 64>(a, stream);
   if constexpr (EPI == EPI_SWIGLU || EPI == EPI_PLAIN) {
+    if (v == V_D64) return launch_one<64, 128, 4, 2, EPI, 64, DEEP_X>(a, stream);
+    if (v == V_D128) return launch_one<128, 128, 4, 2, EPI, 64, DEEP_X>(a, stream);
     if (v == V_S128) return launch_one<128, 256, 2, 4, EPI, 64, DEEP_X>(a, stream);
     if (v == V_S256) return launch_one<256, 128, 4, 2, EPI, 64, DEEP_X>(a, stream);
   }

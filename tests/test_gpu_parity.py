@@ -713,3 +713,13 @@ def test_few_rows_stream_the_weights(lib, shape, rows, division):
     seqs = ([(rows - n, rows - n + 21, -1)] if rows > n else []) + [(1, 20 + 9 * i, -1) for i in range(n)]
     batch = W.assemble_batch(16, seqs, 1 if rows > n else 0, [], np.random.default_rng(rows))
     check_step(lib, shape, batch, W.make_tensors(shape, batch, rows, gains="random"))
+
+
+@pytest.mark.parametrize("d_model,d_ffn,rows", [
+    (2048, 4104, 50), (2048, 4104, 100), (2048, 16648, 97),  # 64x128, 128x128 and 128x256 tiles, begun at shifted k-tiles
+    (1048, 4104, 64), (1048, 4104, 65)])                     # begun at the first, with a partial last one
+def test_gate_up_of_few_rows(lib, d_model, d_ffn, rows):
+    shape = W.LayerShape(d_model, 4, 2, 64, d_ffn)
+    seqs = [(rows - 13, rows - 3, -1)] + [(1, 20 + 9 * i, -1) for i in range(13)]
+    batch = W.assemble_batch(16, seqs, 1, [], np.random.default_rng(rows))
+    check_step(lib, shape, batch, W.make_tensors(shape, batch, rows, gains="random"))
