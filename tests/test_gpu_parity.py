@@ -723,3 +723,15 @@ def test_gate_up_of_few_rows(lib, d_model, d_ffn, rows):
     seqs = [(rows - 13, rows - 3, -1)] + [(1, 20 + 9 * i, -1) for i in range(13)]
     batch = W.assemble_batch(16, seqs, 1, [], np.random.default_rng(rows))
     check_step(lib, shape, batch, W.make_tensors(shape, batch, rows, gains="random"))
+
+
+@pytest.mark.parametrize("d_model,d_ffn,rows", [
+    (1024, 14336, 384),   # one round of 192x256 tiles, all whole
+    (136, 14280, 359),    # ragged rows, columns and K
+    (256, 8192, 577),     # a last row of tiles with one row
+    (256, 8192, 1344)])   # more than one round
+def test_gate_up_on_192_row_tiles(lib, d_model, d_ffn, rows):
+    shape = W.LayerShape(d_model, 4, 2, 64, d_ffn)
+    seqs = [(rows - 13, rows - 3, -1)] + [(1, 20 + 9 * i, -1) for i in range(13)]
+    batch = W.assemble_batch(16, seqs, 1, [], np.random.default_rng(rows))
+    check_step(lib, shape, batch, W.make_tensors(shape, batch, rows, gains="random"))
