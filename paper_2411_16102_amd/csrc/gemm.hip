@@ -10,7 +10,7 @@
 // a run of four consecutive output features (n = 4 * (lane / 16) ..).  Every fused epilogue is then
 // lane-local: the RMSNorm factor of a row is one scalar per lane, a RoPE pair
 // (i, i + dh/2) and a SwiGLU (gate, up) pair sit in two accumulator blocks of the
-// same lane, and results leave as 8-byte bf16x4 stores.
+// same lane; all but gate/up then turn round in LDS on their way out.
 //
 // Tiles travel global -> LDS directly (global_load_lds_dwordx4), so no VGPRs are spent
 // on staging.  A k-tile is BK = 64 wide: a tile row is then one whole 128-byte cache
@@ -1251,7 +1251,7 @@ hipError_t launch_ride(const GemmArgs &a, const GemmRide &r, hipStream_t stream)
 // 5120) rows by 4096 (8192) columns then make exactly one (four) full rounds of 256
 // workgroups where 256x256 tiles leave 38 % (17 %) of the CUs idle.  SMALL: 128x128.
 // S128 / S256: 128x256 and 256x128 tiles on the deep weight ring, for at most 128 / 256 rows; D64 / D128: 64x128 and
-// 128x128 tiles on it, for whole products of at most 64 / 128 rows.
+// 128x128 tiles on it, for whole products of at most 64 / 128 rows.  MID: 192x256, 8 wavefronts of 96x64, gate/up only.
 // activation slots of the short-row pipeline, minus one: three slots leave four weight slots of 16 KB
 // (256x128) or three of 32 KB (128x256); measured against two slots (six / four weight slots) on the
 // 256-row gate/up GEMM of the 8B layer: 0.075 against 0.078 ms, the other GEMMs the same
