@@ -19,6 +19,7 @@
 #include "attn.hpp"
 #include "gemm.hpp"
 #include "misc.hpp"
+#include "staging.hpp"
 
 using namespace bs;
 
@@ -38,6 +39,21 @@ unsigned char *g_scratch_ptr[MAX_DEVICES] = {nullptr};
 std::mutex g_scratch_mutex;
 
 constexpr long STAGE_HALF = 2 * BS_NOALLOC_BLOB_BYTES / 4;  // 32-bit words of either half of the staging buffer, at first
+
+struct HipRuntime {  // what Staging asks of the runtime
+  typedef hipStream_t Stream;
+  typedef hipEvent_t Event;
+  int create(Event *e) { return hipEventCreateWithFlags(e, hipEventDisableTiming); }
+  int destroy(Event e) { return hipEventDestroy(e); }
+  int alloc(int32_t **p, long words) {
+    return hipHostMalloc(reinterpret_cast<void **>(p), (size_t)words * sizeof(int32_t), hipHostMallocDefault);
+  }
+  int release(int32_t *p) { return hipHostFree(p); }
+  int record(Event e, Stream s) { return hipEventRecord(e, s); }
+  int wait(Event e) { return hipEventSynchronize(e); }
+  int wait_all() { return hipDeviceSynchronize(); }
+};
+
 constexpr long TRACE_CAP = 8192;  // workgroups per launch that a timeline can hold
 std::string g_create_error;
 
@@ -65,14 +81,10 @@ struct bs_ctx {
   long cap_slots = 0;
   float *part_acc = nullptr, *part_m = nullptr, *part_l = nullptr;
   uint16_t *hid[2] = {nullptr, nullptr};  // activations between the layers of bs_blend_layers
-  // descriptor blob: pinned staging buffer and one device copy
+  // descriptor blob: pinned staging memory and one device copy
   long cap_blob = 0;
   int32_t *d_blob = nullptr;
-  int32_t *h_stage = nullptr;      // two halves, filled in turn, descriptor behind descriptor
-  long stage_half = 0, stage_at = 0;  // words of a half; place of the next descriptor in the one being filled
-  int stage_cur = 0;
-  hipEvent_t h_ev[2];              // behind every copy out of a half, recorded when the other half is turned to
-  bool h_ev_live[2] = {};
+  Staging<HipRuntime> stage;
   // host scratch reused across calls
   std::vector<int32_t> refcount, path_pages, path_chunks, members, tail_pages, blob;
   std::vector<DecodeItem> items, items_wide;
@@ -191,17 +203,9 @@ int ensure_blob(bs_ctx *c, long ints) {
   return BS_OK;
 }
 
-// both halves of the staging buffer with room for `ints` words each (nothing may still be read from them)
-int alloc_stage(bs_ctx *c, long ints) {
-  if (c->h_stage) HIP_TRY(c, hipHostFree(c->h_stage));
-  c->h_stage = nullptr;
-  c->stage_half = c->stage_at = 0;
-  c->stage_cur = 0;
-  c->h_ev_live[0] = c->h_ev_live[1] = false;
-  hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&c->h_stage), (size_t)ints * 2 * sizeof(int32_t), hipHostMallocDefault);
-  if (e != hipSuccess) return fail(c, BS_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(e));
-  c->stage_half = ints;
-  return BS_OK;
+// the code of a call that could not get, or not hand on, staging memory
+int staging_failed(bs_ctx *c, int e) {
+  return fail(c, e == hipErrorOutOfMemory ? BS_ENOMEM : BS_EHIP, "staging memory: %s", hipGetErrorString((hipError_t)e));
 }
 
 // ---------------------------------------------------------------------------------
@@ -647,34 +651,19 @@ int plan_noalloc(bs_ctx *c, const bs_batch *b, Plan &p) {
 // Puts the plan into pinned memory, bound for the context's descriptor buffer, grown on demand, or for `dst`, a
 // buffer of `room` words of the caller's (nothing grows then).  The first kernel of the step brings it over, or
 // launch_upload.
-// Descriptors stand one behind the other in a half of the staging buffer; when one does not fit any more an
-// event is recorded behind the copies out of this half (calls of a context follow one another), and the other
-// half is taken once its own event has passed.  An event for every call would cost the stream 5.5 us each.
 int stage_plan(bs_ctx *c, const Plan &p, hipStream_t stream, Upload &up, int32_t *dst = nullptr, long room = 0) {
-  const long units = (p.total_ints + 3) / 4, words = 4 * units;  // whole 16-byte units on both sides
+  const long words = whole_units(p.total_ints), units = words / 4;
   if (dst) {
-    if (words > std::min(room, c->stage_half))
+    if (words > std::min(room, STAGE_HALF))
       return fail(c, BS_EINVAL, "descriptor of %ld words exceeds its buffer of %ld", p.total_ints, room);
   } else if (int rc = ensure_blob(c, words)) {
     return rc;
   }
   if (p.total_ints == 0) return BS_OK;
   if (units > std::numeric_limits<int>::max() - 256) return fail(c, BS_EINVAL, "descriptor of %ld words", p.total_ints);
-  if (words > c->stage_half) {
-    HIP_TRY(c, hipDeviceSynchronize());
-    if (int rc = alloc_stage(c, words + words / 4 + 1024)) return rc;
-  } else if (c->stage_at + words > c->stage_half) {
-    HIP_TRY(c, hipEventRecord(c->h_ev[c->stage_cur], stream));
-    c->h_ev_live[c->stage_cur] = true;
-    const int other = c->stage_cur ^ 1;
-    if (c->h_ev_live[other]) HIP_TRY(c, hipEventSynchronize(c->h_ev[other]));
-    c->h_ev_live[other] = false;
-    c->stage_cur = other;
-    c->stage_at = 0;
-  }
-  int32_t *src = c->h_stage + c->stage_cur * c->stage_half + c->stage_at;
+  int32_t *src = nullptr;
+  if (const int e = c->stage.place(words, stream, &src)) return staging_failed(c, e);
   std::memcpy(src, c->blob.data(), sizeof(int32_t) * p.total_ints);
-  c->stage_at += words;
   up.src = reinterpret_cast<const uint4 *>(src);
   up.dst = reinterpret_cast<uint4 *>(dst ? dst : c->d_blob);
   up.n16 = (int)units;
@@ -1093,8 +1082,6 @@ int bs_create(const bs_layer_cfg *cfg, int device, bs_ctx **out) {
   hipError_t e = launch_rope_table(c->rope_cos, c->rope_sin, c->cfg.max_positions, half, (double)c->cfg.rope_theta, nullptr);
   if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
   if (e != hipSuccess) { c->err = std::string("rope table: ") + hipGetErrorString(e); return bail(BS_EHIP); }
-  for (hipEvent_t &ev : c->h_ev)
-    if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) { c->err = "hipEventCreate failed"; return bail(BS_EHIP); }
   {  // this device's copy of the static scratch array (each GPU holds its own, at its own address)
     std::lock_guard<std::mutex> lock(g_scratch_mutex);
     if (device < MAX_DEVICES && !g_scratch_ptr[device]) {
@@ -1107,7 +1094,7 @@ int bs_create(const bs_layer_cfg *cfg, int device, bs_ctx **out) {
   }
   // pinned staging for descriptors up to the size bs_attention_noalloc accepts and more, and host vectors that
   // such a call then never has to grow
-  if ((rc = alloc_stage(c, STAGE_HALF))) return bail(rc);
+  if (const int e = c->stage.open(STAGE_HALF)) return bail(staging_failed(c, e));
   try {
     c->blob.reserve(BS_NOALLOC_BLOB_BYTES / sizeof(int32_t));
     c->items.reserve(BS_NOALLOC_BLOB_BYTES / sizeof(DecodeItem));
@@ -1140,8 +1127,7 @@ void bs_destroy(bs_ctx *c) {
                   (void *)c->xg2, (void *)c->act, (void *)c->rstd1, (void *)c->rstd2, (void *)c->ss2, (void *)c->part_acc, (void *)c->part_m,
                   (void *)c->part_l, (void *)c->d_blob, (void *)c->hid[0], (void *)c->hid[1], (void *)c->sync_words, (void *)c->trace_buf, (void *)c->sk_ws, (void *)c->sk_cnt})
     if (p) (void)hipFree(p);
-  if (c->h_stage) (void)hipHostFree(c->h_stage);
-  for (hipEvent_t ev : c->h_ev) (void)hipEventDestroy(ev);
+  c->stage.close();
   for (auto &v : c->spans) for (auto &s : v) { (void)hipEventDestroy(s.a); (void)hipEventDestroy(s.b); }
   for (auto e : c->free_events) (void)hipEventDestroy(e);
   delete c;
