@@ -26,6 +26,10 @@
  *     buffer that is being filled (2 MiB, more after larger descriptors) waits on
  *     the host for the copies out of the other half.  Calls on one context must not overlap in time on
  *     different streams (they share the workspace).
+ *   - Under stream capture the descriptor of a call is kept in pinned memory of the context apart from
+ *     the staging buffer: every replay reads it again.  The last four captured calls of a context can be
+ *     replayed, and of calls with short descriptors as many as 5 MiB hold, until a call grows the
+ *     workspace that they run in (bs_attention_noalloc has none that grows).
  */
 #ifndef BLENDSTEP_H
 #define BLENDSTEP_H

@@ -39,6 +39,7 @@ unsigned char *g_scratch_ptr[MAX_DEVICES] = {nullptr};
 std::mutex g_scratch_mutex;
 
 constexpr long STAGE_HALF = 2 * BS_NOALLOC_BLOB_BYTES / 4;  // 32-bit words of either half of the staging buffer, at first
+constexpr long STAGE_RING = 5 * BS_NOALLOC_BLOB_BYTES / 4;  // and of the ring for captured calls: bs_attention_noalloc never has to grow it
 
 struct HipRuntime {  // what Staging asks of the runtime
   typedef hipStream_t Stream;
@@ -52,6 +53,12 @@ struct HipRuntime {  // what Staging asks of the runtime
   int record(Event e, Stream s) { return hipEventRecord(e, s); }
   int wait(Event e) { return hipEventSynchronize(e); }
   int wait_all() { return hipDeviceSynchronize(); }
+  int capturing(Stream s, bool *yes) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(s, &status);
+    *yes = status == hipStreamCaptureStatusActive;
+    return e;
+  }
 };
 
 constexpr long TRACE_CAP = 8192;  // workgroups per launch that a timeline can hold
@@ -1094,7 +1101,7 @@ int bs_create(const bs_layer_cfg *cfg, int device, bs_ctx **out) {
   }
   // pinned staging for descriptors up to the size bs_attention_noalloc accepts and more, and host vectors that
   // such a call then never has to grow
-  if (const int e = c->stage.open(STAGE_HALF)) return bail(staging_failed(c, e));
+  if (const int e = c->stage.open(STAGE_HALF, STAGE_RING)) return bail(staging_failed(c, e));
   try {
     c->blob.reserve(BS_NOALLOC_BLOB_BYTES / sizeof(int32_t));
     c->items.reserve(BS_NOALLOC_BLOB_BYTES / sizeof(DecodeItem));

@@ -68,3 +68,45 @@ def test_noalloc_attention_refuses_what_does_not_fit(lib):
     assert bool((out == 3.0).all())
     # the allocating entry point takes the same batch
     assert bool(torch.isfinite(layer.attention(batch, q, pool, batch.n_pages).float()).all())
+
+
+def test_captured_calls_replay_behind_other_calls(lib):
+    # a captured call of either kind reads its own descriptor with every replay, whatever was called since: calls that
+    # turn to both halves of the staging buffer again, and one whose descriptor takes a larger buffer
+    import torch
+    shape = W.LayerShape(256, 8, 2, 64, 256)
+    layer = lib.Layer(shape, device=0)
+    rng = np.random.default_rng(5)
+    mine = W.batch_random(61, n_prefill=3, n_decode=30, max_q=90, max_ctx=500, n_roots=2)
+    others = [W.assemble_batch(16, [(1, 16 * pages + 5 + i % 40, 0) for i in range(n)], 0, [(-1, pages)], rng)
+              for n, pages in ((900, 333), (900, 333), (900, 333), (900, 333), (700, 1000), (20, 9))]
+    assert max(4 * len(b.page_ids) for b in others) > 2 << 20 and 4 * len(others[0].page_ids) > 1 << 20
+    pages = max(b.n_pages for b in others + [mine])
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    pool = torch.randn(pages * (layer.page_bytes() // 2), generator=gen, device="cuda").to(torch.bfloat16)
+    qs = [torch.randn((b.n_rows, 512), generator=gen, device="cuda").to(torch.bfloat16) for b in others + [mine]]
+    dev = layer.upload(W.make_tensors(shape, mine, 3), mine)
+    # every workspace has its size, every kernel has run
+    want_o = layer.attention(mine, qs[-1], pool, pages)
+    want_y = layer.blend_step(dev, mine)
+    for b, q in zip(others, qs):
+        layer.attention(b, q, pool, pages)
+    fresh = lib.Layer(shape, device=0)   # its staging buffer has not grown yet, and its workspace is not captured
+    o, y = torch.zeros_like(want_o), torch.zeros_like(want_y)
+    torch.cuda.synchronize()
+    one, two = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(one):
+        fresh.attention_noalloc(mine, qs[-1], pool, pages, o)
+    with torch.cuda.graph(two):
+        layer.blend_step(dev, mine, y=y)
+    for i in range(len(others) + 1):
+        o.zero_()
+        y.zero_()
+        one.replay()
+        two.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(o, want_o), "attention, replay %d" % i
+        assert torch.equal(y, want_y), "step, replay %d" % i
+        if i < len(others):
+            for l in (layer, fresh):
+                l.attention(others[i], qs[i], pool, pages)
