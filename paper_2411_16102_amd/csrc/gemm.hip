@@ -31,6 +31,7 @@
 #include <utility>
 #include "gemm.hpp"
 #include "attn_device.hpp"
+#include "k_order.hpp"
 #include "common.hpp"
 
 namespace bs {
@@ -40,7 +41,7 @@ __device__ __align__(16) uint16_t g_gemm_zero_chunk[8];
 
 namespace {
 
-constexpr int BK = 64;      // k-extent of one k-tile: rows of 128 bytes
+constexpr int BK = K_TILE;  // k-extent of one k-tile: rows of 128 bytes
 constexpr int NU = 5;       // LDS ring, in units of one operand panel of one k-tile
 constexpr int XCDS = 8;
 
@@ -224,13 +225,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int bid, cons
     }
     off_b[i] = (uint32_t)(((size_t)gn * a.ldb + chunk * 8) * 2);
   }
-  // Products of few rows on whole tiles, weight rows a multiple of 4 KB apart: every tile begins 16 k-tiles further along
-  // K than the one before and comes round.  All of them at the same column would ask for lines on few of the memory
-  // channels at any moment (the activation panel, read by all, stays in the caches anyway).  64 rows, 64x128 tiles:
-  // 2 x 14336 columns, K = 4096 53.5 -> 44.1 us, K = 8192 164 -> 162; rows of other lengths lose up to 4 % by it.
   constexpr bool TURNED = DEEP && EPI != EPI_PARTIAL && BM <= 128;
   const int nk_whole = (a.K + BK - 1) / BK;
-  const int first_kt = TURNED && a.ldb % 2048 == 0 && a.K % BK == 0 ? tile_id * 16 % nk_whole : 0;
+  const int first_kt = TURNED ? first_k_tile(tile_id, a.K, a.ldb) : 0;
   auto turned_kt = [&](int kt) {
     if (!TURNED || kt >= nk_whole) return kt;
     return kt + first_kt >= nk_whole ? kt + first_kt - nk_whole : kt + first_kt;

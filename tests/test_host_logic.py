@@ -342,3 +342,26 @@ int main() {
     csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2411_16102_amd", "csrc")
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-pthread", "-I", csrc, "-o", str(tmp_path / "once"), str(src)])
     assert subprocess.call([str(tmp_path / "once")]) == 0
+
+
+def test_first_k_tile_of_a_tile(tmp_path):
+    # evaluated by the compiler, which refuses what is undefined: within the k-tiles there are, and 0 where K is empty
+    import subprocess
+    src = tmp_path / "k.cpp"
+    src.write_text("""
+#include "k_order.hpp"
+using bs::first_k_tile;
+constexpr bool inside(int k, int ldb) {
+  for (int tile = 0; tile < 600; ++tile)
+    if (first_k_tile(tile, k, ldb) < 0 || first_k_tile(tile, k, ldb) >= (k + 63) / 64) return false;
+  return true;
+}
+static_assert(inside(4096, 4096) && inside(2048, 2048) && inside(64, 2048) && inside(14336, 14336) && inside(8, 8), "");
+static_assert(first_k_tile(1, 4096, 4096) == 16 && first_k_tile(5, 4096, 4096) == 16 && first_k_tile(3, 2048, 2048) == 16, "");
+static_assert(first_k_tile(3, 4160, 4160) == 0 && first_k_tile(3, 2000, 2048) == 0, "");
+static_assert(first_k_tile(0, 0, 0) == 0 && first_k_tile(3, 0, 0) == 0 && first_k_tile(3, 0, 2048) == 0, "");
+int main() {}
+""")
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2411_16102_amd", "csrc")
+    r = subprocess.run(["g++", "-std=c++17", "-fsyntax-only", "-I", csrc, str(src)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout
