@@ -1324,7 +1324,7 @@ int choose_variant(int m, int n_b_rows, int epilogue, int dh, int n_cu, int shar
   int best = V_SMALL;
   double best_t = 1e300;
   for (const Cand &c : cands) {
-    if (c.v == V_TALL && epilogue == EPI_QKV) continue;  // a wavefront must cover whole heads
+    if (c.v == V_TALL && epilogue == EPI_QKV) continue;  // not built for it
     if (c.v == V_MID && epilogue != EPI_SWIGLU) continue;
     const long tiles = n_tiles(m, n_b_rows, c.bm, c.bn);
     const long slots = (long)n_cu * c.per_cu;
@@ -1347,10 +1347,10 @@ int choose_variant(int m, int n_b_rows, int epilogue, int dh, int n_cu, int shar
   return best;
 }
 
-template <int EPI, int DH_BIG_M, int DH_BIG_N>
+template <int EPI>
 hipError_t launch_variant(const GemmArgs &a, int v, hipStream_t stream) {
-  if (v == V_BIG) return launch_one<256, 256, DH_BIG_M, DH_BIG_N, EPI, (DH_BIG_M == 4 ? 128 : 64)>(a, stream);
-  if (v == V_SHARED) return launch_sk<256, 256, DH_BIG_M, DH_BIG_N, EPI, (DH_BIG_M == 4 ? 128 : 64)>(a, stream);
+  if (v == V_BIG) return launch_one<256, 256, 2, 4, EPI, 64>(a, stream);
+  if (v == V_SHARED) return launch_sk<256, 256, 2, 4, EPI, 64>(a, stream);
   if (v == V_TALL) return launch_one<160, 256, 2, 4, EPI, 64>(a, stream);
   if constexpr (EPI == EPI_SWIGLU || EPI == EPI_PLAIN) {
     if (v == V_D64) return launch_one<64, 128, 4, 2, EPI, 64, DEEP_X>(a, stream);
@@ -1456,7 +1456,7 @@ void gemm_plan(GemmArgs &a, int epilogue) {
   for (const Cand &c : cands) {
     const long tiles = n_tiles(a.M, a.N, c.bm, c.bn), slots = (long)n_cu * c.per_cu;
     for (long s = 1; s <= max_splits(tiles, slots); ++s) {
-      if (s == 1 && c.v == V_TALL && epilogue == EPI_QKV) continue;  // a wavefront must cover whole heads
+      if (s == 1 && c.v == V_TALL && epilogue == EPI_QKV) continue;  // not built for it
       const long full = tiles * s / slots, rem = tiles * s % slots;
       double part = 0.0;
       if (rem && c.per_cu == 1) part = c.lo + (c.hi - c.lo) * (double)rem / (double)slots;
@@ -1581,20 +1581,18 @@ hipError_t launch_gemm(const GemmArgs &a, int epilogue, int dh, hipStream_t stre
                                : choose_variant(a.M, (epilogue == EPI_SWIGLU) ? 2 * n_cols : n_cols, epilogue, dh, a.n_cu,
                                                 a.sk_ws && a.sk_cnt && !a.n_count ? a.K : 0);
   switch (epilogue) {
-    case EPI_PLAIN: return launch_variant<EPI_PLAIN, 2, 4>(a, v, stream);
-    case EPI_RESID: return launch_variant<EPI_RESID, 2, 4>(a, v, stream);
-    case EPI_RESID_NORM: return launch_variant<EPI_RESID_NORM, 2, 4>(a, v, stream);
-    case EPI_SWIGLU: return launch_variant<EPI_SWIGLU, 2, 4>(a, v, stream);
+    case EPI_PLAIN: return launch_variant<EPI_PLAIN>(a, v, stream);
+    case EPI_RESID: return launch_variant<EPI_RESID>(a, v, stream);
+    case EPI_RESID_NORM: return launch_variant<EPI_RESID_NORM>(a, v, stream);
+    case EPI_SWIGLU: return launch_variant<EPI_SWIGLU>(a, v, stream);
     case EPI_QKV:
       if (dh == 128)
         return v == V_SHARED ? launch_sk<256, 256, 2, 4, EPI_QKV, 128>(a, stream)
                : v == V_BIG  ? launch_one<256, 256, 2, 4, EPI_QKV, 128>(a, stream)
-               : v == V_TALL ? launch_one<160, 256, 2, 4, EPI_QKV, 128>(a, stream)
                              : launch_one<128, 128, 2, 2, EPI_QKV, 128>(a, stream);
       if (dh == 64)
         return v == V_SHARED ? launch_sk<256, 256, 2, 4, EPI_QKV, 64>(a, stream)
                : v == V_BIG  ? launch_one<256, 256, 2, 4, EPI_QKV, 64>(a, stream)
-               : v == V_TALL ? launch_one<160, 256, 2, 4, EPI_QKV, 64>(a, stream)
                              : launch_one<128, 128, 2, 2, EPI_QKV, 64>(a, stream);
       return hipErrorInvalidValue;
     default:
