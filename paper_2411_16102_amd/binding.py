@@ -344,9 +344,9 @@ class Layer:
         return out
 
     def gemm_division(self, product: str, rows: int):
-        """(tile shape, ranges along K) of the "qkv", "o" or "down" projection over `rows` rows; host only."""
+        """(tile shape, ranges along K) of the "qkv", "o" or "down" projection or of "gate_up" over `rows` rows; host only."""
         tiles, ranges = C.c_int32(), C.c_int32()
-        self._check(self.lib.bs_gemm_division(self.h, ("qkv", "o", "down").index(product), rows, C.byref(tiles), C.byref(ranges)))
+        self._check(self.lib.bs_gemm_division(self.h, ("qkv", "o", "down", "gate_up").index(product), rows, C.byref(tiles), C.byref(ranges)))
         return tiles.value, ranges.value
 
     def gemm_nt(self, a, b, stream=None):

@@ -1229,7 +1229,7 @@ int bs_attention_division(bs_ctx *c, const bs_batch *b, int64_t n_pages, int32_t
 int bs_gemm_division(bs_ctx *c, int32_t product, int32_t rows, int32_t *tiles, int32_t *k_ranges) {
   return guarded(c, [&]() -> int {
   if (!c) return BS_EINVAL;
-  if (product < 0 || product > 2 || rows < 1 || !tiles || !k_ranges) return fail(c, BS_EINVAL, "bs_gemm_division: bad argument");
+  if (product < 0 || product > 3 || rows < 1 || !tiles || !k_ranges) return fail(c, BS_EINVAL, "bs_gemm_division: bad argument");
   const bs_layer_cfg &g = c->cfg;
   const int hd = g.n_q_heads * g.head_dim;
   float workspace;  // (a context with a device has one; planning reads neither)
@@ -1240,6 +1240,14 @@ int bs_gemm_division(bs_ctx *c, int32_t product, int32_t rows, int32_t *tiles, i
   a.K = product == 0 ? g.d_model : product == 1 ? hd : g.d_ffn;
   a.sk_ws = &workspace; a.sk_cnt = &counter;
   gemm_force_variant(c->forced_tiles);
+  if (product == 3) {
+    a.N = g.d_ffn; a.K = g.d_model;
+    GemmArgs first, rest;
+    const bool split = gemm_round_split(a, EPI_SWIGLU, g.head_dim, &first, &rest);
+    *tiles = gemm_shape(split ? first : a, EPI_SWIGLU, g.head_dim);
+    *k_ranges = 1;
+    return BS_OK;
+  }
   gemm_plan(a, product == 0 ? EPI_QKV : product == 1 ? EPI_RESID_NORM : EPI_RESID);
   *tiles = a.tile_variant;
   *k_ranges = a.k_splits;

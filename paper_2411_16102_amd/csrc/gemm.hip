@@ -1479,6 +1479,13 @@ void gemm_plan(GemmArgs &a, int epilogue) {
   }
 }
 
+int gemm_shape(const GemmArgs &a, int epilogue, int dh) {
+  if (a.tile_variant) return a.tile_variant;
+  if ((epilogue == EPI_SWIGLU || epilogue == EPI_PLAIN) && gemm_streams_weights(a, epilogue)) return V_ROWS;
+  const int n_cols = a.n_count ? a.n_count : a.N;
+  return choose_variant(a.M, epilogue == EPI_SWIGLU ? 2 * n_cols : n_cols, epilogue, dh, a.n_cu, a.sk_ws && a.sk_cnt && !a.n_count ? a.K : 0);
+}
+
 int gemm_ss_parts(const GemmArgs &a, int epilogue, int dh) {
   if (a.k_splits > 1) return 1;  // the split-K reduction leaves whole row sums
   const int v = a.tile_variant ? a.tile_variant
@@ -1567,9 +1574,8 @@ hipError_t launch_gemm(const GemmArgs &a, int epilogue, int dh, hipStream_t stre
     return hipGetLastError();
   }
   if (a.n_count && epilogue != EPI_SWIGLU && epilogue != EPI_PLAIN) return hipErrorInvalidValue;
-  const int n_cols = a.n_count ? a.n_count : a.N;
-  const bool streams = a.tile_variant ? a.tile_variant == V_ROWS : (epilogue == EPI_SWIGLU || epilogue == EPI_PLAIN) && gemm_streams_weights(a, epilogue);
-  if (streams) {
+  const int v = gemm_shape(a, epilogue, dh);
+  if (v == V_ROWS) {
     switch (rows_item(a.M, a.N, a.K, epilogue, a.n_cu > 0 ? a.n_cu : N_CU)) {
       case 11: return launch_rows_one<1, 1>(a, epilogue, dh, stream);
       case 21: return launch_rows_one<2, 1>(a, epilogue, dh, stream);
@@ -1577,9 +1583,6 @@ hipError_t launch_gemm(const GemmArgs &a, int epilogue, int dh, hipStream_t stre
       default: return hipErrorInvalidValue;
     }
   }
-  const int v = a.tile_variant ? a.tile_variant
-                               : choose_variant(a.M, (epilogue == EPI_SWIGLU) ? 2 * n_cols : n_cols, epilogue, dh, a.n_cu,
-                                                a.sk_ws && a.sk_cnt && !a.n_count ? a.K : 0);
   switch (epilogue) {
     case EPI_PLAIN: return launch_variant<EPI_PLAIN>(a, v, stream);
     case EPI_RESID: return launch_variant<EPI_RESID>(a, v, stream);

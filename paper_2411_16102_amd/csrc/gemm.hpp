@@ -84,6 +84,8 @@ int gemm_ride_tiles(const GemmArgs &a, int epilogue);
 // Picks a tile shape for the problem and launches on `stream`.  dh is the head
 // dimension (used by EPI_QKV only).  Returns hipSuccess or the launch error.
 hipError_t launch_gemm(const GemmArgs &a, int epilogue, int dh, hipStream_t stream);
+// The tile shape that launch_gemm takes for a product that is not cut along K.
+int gemm_shape(const GemmArgs &a, int epilogue, int dh);
 // partial-sum slots a RESID_NORM launch over N columns writes
 int gemm_ss_parts(const GemmArgs &a, int epilogue, int dh);
 // Whether a product of these sizes goes to the few-row kernel (with the forced shapes in mind; GemmArgs::ss_in is for it).

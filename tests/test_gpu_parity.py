@@ -57,7 +57,12 @@ def check_step(lib, shape, batch, tens, flags=0, tiles=0):
 # ---------------------------------------------------------------------------
 @pytest.mark.parametrize("m,n,k", [(136, 512, 256), (300, 264, 688), (1, 8, 8), (1030, 1544, 520), (2048, 1024, 512),
                                    # at most 256 / 128 rows and a row of tiles that fills the chip: the deep weight ring
-                                   (200, 16512, 520), (256, 16384, 192), (100, 33000, 328), (128, 32768, 1024)])
+                                   (200, 16512, 520), (256, 16384, 192), (100, 33000, 328), (128, 32768, 1024),
+                                   # the few-row kernel: one and two blocks of rows and of columns, several items per
+                                   # workgroup, a partial last k-tile, eight and more k-tiles per wavefront
+                                   (7, 520, 1032), (16, 4104, 4096), (17, 264, 8), (33, 2056, 2048), (64, 520, 4096), (256, 512, 256),
+                                   # 64x128 and 128x128 tiles on the deep ring, begun at shifted k-tiles and at the first
+                                   (50, 9000, 2048), (64, 9000, 1000), (100, 9000, 2048), (65, 9000, 1000)])
 def test_gemm_nt(lib, m, n, k):
     import torch
     rng = np.random.default_rng(m + n + k)
@@ -398,6 +403,7 @@ def test_rounds_of_full_tiles_in_gate_up(lib, d_model, d_ffn):
     batch = W.assemble_batch(16, [(300, 300, -1), (150, 180, -1)] + [(1, 20 + 3 * i, -1) for i in range(62)], 2,
                              [], np.random.default_rng(9))
     assert batch.n_rows == 512
+    assert lib.Layer(shape, device=-1).gemm_division("gate_up", 512) == (1, 1)
     tens = W.make_tensors(shape, batch, 9)
     check_step(lib, shape, batch, tens)
 
@@ -698,40 +704,86 @@ def test_descriptors_of_calls_in_flight_do_not_overwrite_one_another(lib):
         assert torch.equal(out, alone[i]), i
 
 
+def test_a_half_of_the_staging_buffer_is_refilled_behind_its_copies(lib):
+    # calls whose descriptors fill more than half of a half each, enqueued behind ordinary work that takes longer than
+    # the host needs for all of them: the first turns to the other half at once, one of the next has to wait on the host
+    # for copies that stand behind that work, so that it has passed when the last one returns
+    import time
+    import torch
+    shape = W.LayerShape(256, 8, 2, 64, 256)
+    rng = np.random.default_rng(4)
+    batches = [W.assemble_batch(16, [(1, 16 * pages + 5 + i % 40, 0) for i in range(n)], 0, [(-1, pages)], rng)
+               for n, pages in ((900, 333), (800, 400), (1000, 310), (700, 450))]
+    layer = lib.Layer(shape, device=0)
+    for b in batches:
+        assert 1 << 20 < 4 * layer.attention_division(b).descriptor_words < 2 << 20
+    pages = max(b.n_pages for b in batches)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    pool = torch.randn(pages * (layer.page_bytes() // 2), generator=gen, device="cuda").to(torch.bfloat16)
+    qs = [torch.randn((b.n_rows, 512), generator=gen, device="cuda").to(torch.bfloat16) for b in batches]
+    outs = [torch.zeros_like(q) for q in qs]
+    work = torch.randn((8192, 8192), generator=gen, device="cuda").to(torch.bfloat16)
+    product = work @ work
+    alone = [layer.attention(b, q, pool, pages) for b, q in zip(batches, qs)]   # every workspace has its size
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    for b, q in zip(batches, qs):
+        layer.attention(b, q, pool, pages)
+    host_s = time.perf_counter() - t0
+    torch.cuda.synchronize()
+    begun, passed = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    begun.record()
+    for _ in range(200):   # 0.1 s and more: 1.1 TFLOP each
+        torch.mm(work, work, out=product)
+    passed.record()
+    outs[0] = layer.attention(batches[0], qs[0], pool, pages)
+    assert not passed.query(), "the work ended too early to show anything"
+    for i in (1, 2, 3):
+        outs[i] = layer.attention(batches[i], qs[i], pool, pages)
+    assert passed.query(), "a half was refilled while a copy out of it was still to come"
+    torch.cuda.synchronize()
+    assert begun.elapsed_time(passed) * 1e-3 > 2 * host_s
+    for i in range(4):
+        assert torch.equal(outs[i], alone[i]), i
+
+
 @pytest.mark.parametrize("shape,rows,division", [
     # one and two blocks of rows; columns in half a block, contractions with a partial last k-tile or less than one per
     # wavefront; several items per workgroup (gate/up of 513 units)
-    (W.LayerShape(264, 3, 1, 64, 344), 1, (7, 7, 7)), (W.LayerShape(520, 20, 2, 128, 4104), 7, (7, 7, 7)),
-    (W.LayerShape(4104, 5, 1, 128, 4104), 16, (7, 7, 7)), (W.LayerShape(264, 3, 1, 64, 344), 17, (7, 7, 7)),
-    (W.LayerShape(520, 20, 2, 128, 4104), 32, (7, 7, 7)), (W.LayerShape(520, 20, 2, 128, 4104), 33, (7, 7, 7)),
-    (W.LayerShape(1032, 8, 8, 64, 8200), 64, (7, 7, 3)), (W.LayerShape(264, 3, 1, 64, 344), 136, (7, 7, 7)),
-    (W.LayerShape(256, 4, 4, 64, 760), 256, (7, 7, 7)), (W.LayerShape(4096, 32, 8, 128, 1024), 32, (7, 7, 7))])
+    (W.LayerShape(264, 3, 1, 64, 344), 1, (7, 7, 7, 7)), (W.LayerShape(520, 20, 2, 128, 4104), 7, (7, 7, 7, 7)),
+    (W.LayerShape(4104, 5, 1, 128, 4104), 16, (7, 7, 7, 7)), (W.LayerShape(264, 3, 1, 64, 344), 17, (7, 7, 7, 7)),
+    (W.LayerShape(520, 20, 2, 128, 4104), 32, (7, 7, 7, 7)), (W.LayerShape(520, 20, 2, 128, 4104), 33, (7, 7, 7, 8)),
+    (W.LayerShape(1032, 8, 8, 64, 8200), 64, (7, 7, 3, 8)), (W.LayerShape(264, 3, 1, 64, 344), 136, (7, 7, 7, 7)),
+    (W.LayerShape(256, 4, 4, 64, 760), 256, (7, 7, 7, 3)), (W.LayerShape(4096, 32, 8, 128, 1024), 32, (7, 7, 7, 7))])
 def test_few_rows_stream_the_weights(lib, shape, rows, division):
     layer = lib.Layer(shape, device=-1)
-    assert tuple(layer.gemm_division(p, rows)[0] for p in ("qkv", "o", "down")) == division
+    assert tuple(layer.gemm_division(p, rows)[0] for p in ("qkv", "o", "down", "gate_up")) == division
     n = max(1, rows // 2)
     seqs = ([(rows - n, rows - n + 21, -1)] if rows > n else []) + [(1, 20 + 9 * i, -1) for i in range(n)]
     batch = W.assemble_batch(16, seqs, 1 if rows > n else 0, [], np.random.default_rng(rows))
     check_step(lib, shape, batch, W.make_tensors(shape, batch, rows, gains="random"))
 
 
-@pytest.mark.parametrize("d_model,d_ffn,rows", [
-    (2048, 4104, 50), (2048, 4104, 100), (2048, 16648, 97),  # 64x128, 128x128 and 128x256 tiles, begun at shifted k-tiles
-    (1048, 4104, 64), (1048, 4104, 65)])                     # begun at the first, with a partial last one
-def test_gate_up_of_few_rows(lib, d_model, d_ffn, rows):
+@pytest.mark.parametrize("d_model,d_ffn,rows,tiles", [
+    (2048, 4104, 50, 8), (2048, 4104, 100, 9), (2048, 16648, 97, 4),  # 64x128, 128x128 and 128x256 tiles, begun at shifted k-tiles
+    (1048, 4104, 64, 8), (1048, 4104, 65, 9)])                        # begun at the first, with a partial last one
+def test_gate_up_of_few_rows(lib, d_model, d_ffn, rows, tiles):
     shape = W.LayerShape(d_model, 4, 2, 64, d_ffn)
+    assert lib.Layer(shape, device=-1).gemm_division("gate_up", rows) == (tiles, 1)
     seqs = [(rows - 13, rows - 3, -1)] + [(1, 20 + 9 * i, -1) for i in range(13)]
     batch = W.assemble_batch(16, seqs, 1, [], np.random.default_rng(rows))
     check_step(lib, shape, batch, W.make_tensors(shape, batch, rows, gains="random"))
 
 
-@pytest.mark.parametrize("d_model,d_ffn,rows", [
-    (1024, 14336, 384),   # one round of 192x256 tiles, all whole
-    (136, 14280, 359),    # ragged rows, columns and K
-    (256, 8192, 577),     # a last row of tiles with one row
-    (256, 8192, 1344)])   # more than one round
-def test_gate_up_on_192_row_tiles(lib, d_model, d_ffn, rows):
+@pytest.mark.parametrize("d_model,d_ffn,rows,tiles", [
+    (1024, 14336, 384, 10),  # one round of 192x256 tiles, all whole
+    (136, 14280, 359, 10),   # ragged rows, columns and K
+    (256, 8448, 1153, 10),   # a last row of tiles with one row
+    (256, 8192, 1344, 10),   # more than one round
+    (256, 8192, 577, 2)])    # (so few tiles that 160x256 ones are taken)
+def test_gate_up_on_192_row_tiles(lib, d_model, d_ffn, rows, tiles):
     shape = W.LayerShape(d_model, 4, 2, 64, d_ffn)
+    assert lib.Layer(shape, device=-1).gemm_division("gate_up", rows) == (tiles, 1)
     seqs = [(rows - 13, rows - 3, -1)] + [(1, 20 + 9 * i, -1) for i in range(13)]
     batch = W.assemble_batch(16, seqs, 1, [], np.random.default_rng(rows))
     check_step(lib, shape, batch, W.make_tensors(shape, batch, rows, gains="random"))
