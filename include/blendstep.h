@@ -260,9 +260,10 @@ int bs_overlap_trace_read(bs_ctx *ctx, int32_t launch, uint64_t *out, int64_t ca
 
 /* Tuning knob: GEMM tile shape for the calls on this context: 0 = chosen per problem (default), 1 = 256x256,
  * 2 = 160x256 (not for the QKV GEMM), 3 = 128x128, 6 = 256x256 tiles shared between workgroups (one persistent
- * workgroup per CU; the tiles that do not fill a whole round are cut along K into equal ranges).  With 0, GEMMs of at most 256 rows run as one
- * row of 128x256 or 256x128 tiles on a pipeline with its own look-ahead for the weight panel; a
- * forced shape switches that off. */
+ * workgroup per CU; the tiles that do not fill a whole round are cut along K into equal ranges).  With 0, products of few
+ * rows (up to 16; up to 64, or 256 where K is short, where one round covers the product) run on a kernel of their own, and
+ * others of at most 256 rows mostly as one row of tiles on a pipeline with its own look-ahead for the weight panel; a
+ * forced shape switches both off. */
 int bs_set_gemm_tiles(bs_ctx *ctx, int32_t variant);
 
 /* Stand-alone entry points of the individual operators (the same kernels the

@@ -865,11 +865,11 @@ int run_down(bs_ctx *c, const bs_weights *w, uint16_t *y, int r0, int r1, hipStr
 // Estimated duration of a GEMM launch of M rows on n_cu CUs by whole rounds of tiles, for the decision between the
 // two schedules alone (the tiles that run are chosen by gemm_plan and, gate/up, by launch_gemm): a 256x256
 // tile sustains 5.8 TFLOP/s per CU, a 160x256 tile 4.5, and 128x128 tiles, two per CU, take three
-// quarters of a 256x256 round for half its work.  It does not know products cut along K, which makes the serial
-// schedule look up to a few per cent longer than it is at 600 to 1700 prefill rows; over 180 blended steps (8B,
-// 70B and a layer of 2048; 256 to 4096 prefill rows, 8 to 1024 decode rows) timed both ways the decision loses
-// 0.1 % on average and 4.4 % at worst.  With gemm_plan's own estimates of the serial and the decode rows' products
-// (and 75 us instead of 30 beside them, fitted to half of these steps) it lost as much on average and 4.9 % at worst.
+// quarters of a 256x256 round for half its work.  It knows neither the 192x256 tiles of gate/up nor products cut
+// along K, which makes the serial schedule look up to a few per cent longer than it is at 600 to 1700 prefill rows; over
+// 200 blended steps (8B, 70B and a layer of 2048; 150 to 6000 prefill rows, 8 to 1024 decode rows) timed both ways with
+// the present kernels the decision loses 0.2 % on average and 6.3 % at worst (5337 + 45 rows of the layer of 2048,
+// kept serial; co-scheduled in error: at most 4.4 %, 1111 + 540 rows of the 8B layer).
 double est_gemm_s(int M, int b_rows, int K, int n_cu) {
   if (M <= 0) return 0.0;
   const double big = 2.0 * 256 * 256 * K / 5.8e12, tall = 2.0 * 160 * 256 * K / 4.5e12, small = 0.75 * big;
@@ -913,7 +913,8 @@ void plan_coscheduled(bs_ctx *c, const Plan &p, const bs_weights *w, const uint1
   // long as the tiles still fill whole rounds on the CUs that remain: the choice minimises
   //   rounds(tiles, CUs - head) * tile time  -  head * 36 GB/s * that time / 5.3 TB/s
   // over both tile shapes and head = head_cus_min, +8, ... (a 256x256 tile sustains 5.8 TFLOP/s
-  // per CU, a 160x256 tile 4.5), never hiding more than the queue still holds.
+  // per CU, a 160x256 tile 4.5: with the epilogues before results turned round in LDS; the output projection's launch
+  // has since become shorter than this expects and hides less), never hiding more than the queue still holds.
   ga[0] = o_proj_args(c, w, x, 0, Tp); ga[1] = gate_up_args(c, w, 0, Tp); ga[2] = down_args(c, w, y, 0, Tp);
   const int epi[3] = {EPI_RESID_NORM, EPI_SWIGLU, EPI_RESID};
   const size_t per_token = (size_t)2 * g.head_dim * 2 * g.n_kv_heads;

@@ -19,7 +19,8 @@
 // of five 32 KB units, one unit holding the activation panel or the weight panel of one
 // k-tile, so two and a half k-tiles fit in the 160 KB: while tile kt is multiplied,
 // tile kt+1 has landed or is landing and the weight panel of tile kt+2 is in flight.
-// (GEMMs of at most 256 rows use a second pipeline, DEEP in the kernel below: one row
+// (Of at most 256 rows, what the few-row kernel leaves, gate/up and plain products and the
+// k-ranges of the others, uses a second pipeline where it pays, DEEP in the kernel below: one row
 // of tiles, a few slots for the activation panel and all other LDS for the weight
 // panel, the two kinds of panel requested by different wavefronts.)  Rows are 128 B whose eight 16-byte chunks are XOR-swizzled with
 // ((row >> 1) & 7): two consecutive rows fill the 256-byte bank row, so the swizzle
@@ -78,7 +79,7 @@ __device__ __forceinline__ void store_bf16x4(uint16_t *p, float a, float b, floa
 // Columns of the fused projection enter the tiles in groups of 64: 32 features of a head and those dh/2 behind them, so
 // that rotation pairs meet in a lane.  Groups of value heads are dealt evenly between the others: the rows of
 // decode sequences store them two bytes at a time, one lane per clock, 28 us for a 256x256 tile of nothing else
-// (QKV of 1093 prefill and 487 decode rows 114 -> 108 us).
+// (QKV of 1093 prefill and 487 decode rows 111 -> 106 us against the columns in their own order).
 struct QkvGroup { int head, i0; };  // features i0 .. i0 + 31 and i0 + dh/2 .. of the head; head >= all of them: beyond the last
 __device__ __forceinline__ QkvGroup qkv_group(int p, const GemmArgs &a, int dh) {
   const int per_head = dh / 64, n_v = a.n_kv_heads * per_head, n_rot = (a.n_q_heads + a.n_kv_heads) * per_head, n = n_rot + n_v;
@@ -744,6 +745,8 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, 2) void gemm_kernel(const Ge
   gemm_tile<BM, BN, WAVES_M, WAVES_N, EPI, DH, DEEP>(a, (int)blockIdx.x);
 }
 
+// (All 256 registers are in use: 36 to 66 spill, around the loop over k-tiles and never in it, as do 4 to 7 of the whole
+// 256x256 tiles of the QKV projection.)
 template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int DH>
 __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_sk_kernel(const GemmArgs a, const SkPlan p) {
   const int w = (int)blockIdx.x, G = (int)gridDim.x;
@@ -1324,7 +1327,7 @@ int choose_variant(int m, int n_b_rows, int epilogue, int dh, int n_cu, int shar
   int best = V_SMALL;
   double best_t = 1e300;
   for (const Cand &c : cands) {
-    if (c.v == V_TALL && epilogue == EPI_QKV) continue;  // not built for it
+    if (c.v == V_TALL && epilogue == EPI_QKV) continue;  // not built for it (see gemm_plan)
     if (c.v == V_MID && epilogue != EPI_SWIGLU) continue;
     const long tiles = n_tiles(m, n_b_rows, c.bm, c.bn);
     const long slots = (long)n_cu * c.per_cu;
@@ -1440,13 +1443,15 @@ void gemm_plan(GemmArgs &a, int epilogue) {
   // between `lo` (few workgroups on the chip) and `hi` (all of them: the clock falls under matrix load); 128x128
   // tiles, two to a CU, cost `lo` up to one per CU.  A round of whole tiles has its start and its epilogue, a
   // cut product the second kernel and the partial products once out and once back in (6.4 TB/s, most of it the
-  // last-level cache); the output projection whole needs the pass that closes the second norm.  Fitted on
-  // MI355X to the three products of twelve layers (256 to 12288 columns, K 256 to 28672) at 40 row counts from
-  // 257 to 5120, weights cold, every shape and cut timed: within 0.5 % of the best on average, and of 1314
-  // products nine are more than 3 % (at most 11 %) slower than with whole tiles and cuts of 128x128 ones only,
-  // which are 15 % off the best.  One cost for every epilogue, fitted to 4096 columns and more, was 1.5 % off
-  // and up to 28 % slower than those where the product is narrow or short: N = K = 1024 at 359 rows 17.6 against
-  // 14.3 us, QKV of N = 10240, K = 8192 at 359 rows 103 against 90 (now 84).
+  // last-level cache); the output projection whole needs the pass that closes the second norm.  One cost for every
+  // epilogue, fitted to 4096 columns and more, was 1.5 % off and up to 28 % slower than whole tiles and cuts of 128x128
+  // ones only where the product is narrow or short.
+  // Fitted on MI355X to the three products of twelve layers (256 to 12288 columns, K 256 to 28672) at 40 row counts from
+  // 257 to 5120, weights cold, every shape and cut timed, with the kernels before results turned round in LDS: a round
+  // now ends up to 11 us sooner.  Of 1274 products timed with the present ones the choice is 0.8 % off the best on
+  // average (whole tiles alone: 22 %), 74 are more than 5 % off and the worst 22 %.  Of these 26 are QKV products on whole,
+  // cut or shared 256x256 tiles where whole 128x128 ones are now ahead (N = 7168, K = 5120 at 2560 rows 230 against
+  // 189 us), 20 are 128x128 tiles in too many ranges (down, N = 1024, K = 4096 at 420 rows 18.8 us in eight, 15.5 in seven).
   struct Epi { double round, second, closing; };
   const Epi ep = epilogue == EPI_QKV ? Epi{7.1, 5.2, 0.0} : epilogue == EPI_RESID_NORM ? Epi{6.7, 7.4, 4.0} : Epi{5.7, 4.0, 0.0};
   constexpr double PARTIAL_ROUND = 5.0, PARTIAL_BYTES_PER_US = 6.4e6;
@@ -1456,7 +1461,9 @@ void gemm_plan(GemmArgs &a, int epilogue) {
   for (const Cand &c : cands) {
     const long tiles = n_tiles(a.M, a.N, c.bm, c.bn), slots = (long)n_cu * c.per_cu;
     for (long s = 1; s <= max_splits(tiles, slots); ++s) {
-      if (s == 1 && c.v == V_TALL && epilogue == EPI_QKV) continue;  // not built for it
+      // whole 160x256 tiles are not built for QKV (they would be the fastest for 45 of 438 products, by up to 20 %:
+      // N = 6144, K = 4096 at 1580 rows 77 against 92 us)
+      if (s == 1 && c.v == V_TALL && epilogue == EPI_QKV) continue;
       const long full = tiles * s / slots, rem = tiles * s % slots;
       double part = 0.0;
       if (rem && c.per_cu == 1) part = c.lo + (c.hi - c.lo) * (double)rem / (double)slots;
