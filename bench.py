@@ -307,7 +307,7 @@ def main():
         if ms <= 0:
             return None
         r = {"bound": "mfma", "kernel": name, "ms": ms, "achieved": flops / (ms * 1e-3) / 1e12, "peak": PEAK_MFMA_BF16 / 1e12,
-             "unit": "TFLOP/s", "traffic": (measured_traffic(traffic_file, ["gemm.hip", "gemm.hpp", "common.hpp", "attn_device.hpp"])
+             "unit": "TFLOP/s", "traffic": (measured_traffic(traffic_file, ["gemm.hip", "gemm.hpp", "k_order.hpp", "common.hpp", "attn_device.hpp"])
                                             if traffic_file else None)}
         r["frac"] = r["achieved"] / r["peak"]
         if extra:
