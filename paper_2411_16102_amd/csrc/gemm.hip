@@ -15,10 +15,10 @@
 // Tiles travel global -> LDS directly (global_load_lds_dwordx4), so no VGPRs are spent
 // on staging.  A k-tile is BK = 64 wide: a tile row is then one whole 128-byte cache
 // line, which the memory pipeline delivers about 1.5 times faster than the two 64-byte
-// halves fetched separately (measured: 41 against 26 B/clk/CU into LDS).  LDS is a ring
-// of five 32 KB units, one unit holding the activation panel or the weight panel of one
-// k-tile, so two and a half k-tiles fit in the 160 KB: while tile kt is multiplied,
-// tile kt+1 has landed or is landing and the weight panel of tile kt+2 is in flight.
+// halves fetched separately (measured: 41 against 26 B/clk/CU into LDS).  LDS holds two
+// rings of panels, three weight panels and two activation panels of one k-tile each for a 256x256
+// tile: while tile kt is multiplied, tile kt+1 has landed or is landing and the weight panel of
+// tile kt+2 is in flight; 160x256 tiles have room for a third activation panel.
 // (Of at most 256 rows, what the few-row kernel leaves, gate/up and plain products and the
 // k-ranges of the others, uses a second pipeline where it pays, DEEP in the kernel below: one row
 // of tiles, a few slots for the activation panel and all other LDS for the weight
@@ -43,7 +43,15 @@ __device__ __align__(16) uint16_t g_gemm_zero_chunk[8];
 namespace {
 
 constexpr int BK = K_TILE;  // k-extent of one k-tile: rows of 128 bytes
-constexpr int NU = 5;       // LDS ring, in units of one operand panel of one k-tile
+constexpr int LDS_CU = 160 * 1024;
+// the panel ring of a workgroup: all of a CU's LDS, or half where two workgroups of four wavefronts share a CU; three
+// weight panels, as many activation panels as fit beside them (three are enough), and what is left to weights again
+constexpr int ring_bytes(int waves) { return waves > 4 ? LDS_CU : LDS_CU / 2; }
+constexpr int ring_x_slots(int bm, int bn, int waves) {
+  const int n = (ring_bytes(waves) - 3 * bn * BK * 2) / (bm * BK * 2);
+  return n < 3 ? n : 3;
+}
+constexpr int ring_w_slots(int bm, int bn, int waves) { return (ring_bytes(waves) - ring_x_slots(bm, bn, waves) * bm * BK * 2) / (bn * BK * 2); }
 constexpr int XCDS = 8;
 
 struct TileCoord { int tm, tn; };
@@ -152,7 +160,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int bid, cons
   constexpr int MI = WTM / 16, NI = WTN / 16;  // 16x16 accumulator blocks of a wavefront's tile
   constexpr int OUT_BN = (EPI == EPI_SWIGLU) ? BN / 2 : BN;
   constexpr int ROWB = BK * 2;                       // bytes of one tile row
-  constexpr int UNIT = (BM > BN ? BM : BN) * ROWB;   // one ring unit holds either panel
+  constexpr int LDS_BYTES = DEEP ? LDS_CU : ring_bytes(NW);
   constexpr int GA = BM / 8, GB = BN / 8;            // 8-row groups = one 1 KB wavefront load each
   constexpr int LA = (GA + XW - 1) / XW, LB = (GB + WW - 1) / WW;  // loads per thread per panel
   static_assert(!DEEP || NW % 2 == 0, "two halves of the workgroup share the loads");
@@ -233,23 +241,29 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int bid, cons
     if (!TURNED || kt >= nk_whole) return kt;
     return kt + first_kt >= nk_whole ? kt + first_kt - nk_whole : kt + first_kt;
   };
-  // load number i of panel X(kt) / W(kt) into ring slot `slot`; `checked` handles chunks past K
-  auto dma_a = [&](int kt, int lds_off, int i, auto checked) {
+  // load number i of panel X(kt) / W(kt) to LDS byte offset `lds_off`; `checked` handles chunks past K.  Buffer loads take the
+  // k-tile as a scalar offset: no address arithmetic per load, and 16 registers less than 64-bit addresses.
+#ifdef __HIP_DEVICE_COMPILE__
+  const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.A), 0, 0xffffffff, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsrc_b = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.B), 0, 0xffffffff, 0x00020000);
+#else
+  const int rsrc_a = 0, rsrc_b = 0;
+#endif
+  auto dma = [&](const uint16_t *mat, auto rsrc, int kt, uint32_t off, int ke, int lds_off, auto checked) {
     kt = turned_kt(kt);
-    const unsigned char *base = reinterpret_cast<const unsigned char *>(a.A) + (size_t)kt * ROWB;
-    const void *p = base + off_a[i];
-    if constexpr (decltype(checked)::value)
-      if (kt * BK + ka[i] >= a.K) p = g_gemm_zero_chunk;
-    __builtin_amdgcn_global_load_lds(p, (__attribute__((address_space(3))) void *)(smem + lds_off + dst_a[i]), 16, 0, 0);
+#ifdef __HIP_DEVICE_COMPILE__
+    auto *dst = (__attribute__((address_space(3))) void *)(smem + lds_off);
+    if constexpr (decltype(checked)::value) {
+      const void *p = reinterpret_cast<const unsigned char *>(mat) + (size_t)kt * ROWB + off;
+      if (kt * BK + ke >= a.K) p = g_gemm_zero_chunk;
+      __builtin_amdgcn_global_load_lds(p, dst, 16, 0, 0);
+    } else {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, dst, 16, off, kt * ROWB, 0, 0);
+    }
+#endif
   };
-  auto dma_b = [&](int kt, int lds_off, int i, auto checked) {
-    kt = turned_kt(kt);
-    const unsigned char *base = reinterpret_cast<const unsigned char *>(a.B) + (size_t)kt * ROWB;
-    const void *p = base + off_b[i];
-    if constexpr (decltype(checked)::value)
-      if (kt * BK + kb[i] >= a.K) p = g_gemm_zero_chunk;
-    __builtin_amdgcn_global_load_lds(p, (__attribute__((address_space(3))) void *)(smem + lds_off + dst_b[i]), 16, 0, 0);
-  };
+  auto dma_a = [&](int kt, int lds_off, int i, auto checked) { dma(a.A, rsrc_a, kt, off_a[i], ka[i], lds_off + dst_a[i], checked); };
+  auto dma_b = [&](int kt, int lds_off, int i, auto checked) { dma(a.B, rsrc_b, kt, off_b[i], kb[i], lds_off + dst_b[i], checked); };
 
   f32x4_t acc[NI][MI];
 #pragma unroll
@@ -277,80 +291,87 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int bid, cons
     else
       wf[o - MI] = as_bf16x8(*reinterpret_cast<const u32x4_t *>(smem + wo + wfrag + (o - MI) * 16 * ROWB + ch));
   };
-  // One k-step: its NMF MFMAs in program order, with the `n_ops` side operations (LDS
-  // reads of the next k-step, DMA requests) dealt out behind the first MFMAs, `per` at a
-  // time, so that the matrix pipe is never left idle behind a run of memory instructions.
-  auto step = [&](const bf16x8_t (&xf)[MI], const bf16x8_t (&wf)[NI], int n_ops, int per, auto &&op) {
+  // One k-step: its NMF MFMAs in program order, with `n_ops` side operations (LDS reads of the next k-step, DMA
+  // requests) dealt out between them, operation o behind MFMA at(o), so that the matrix pipe is never left idle
+  // behind a run of memory instructions.
+  auto step = [&](const bf16x8_t (&xf)[MI], const bf16x8_t (&wf)[NI], int n_ops, auto &&at, auto &&op) {
 #pragma unroll
     for (int j = 0; j < NMF; ++j) {
       const int ni = j / MI, mi = j % MI;
       acc[ni][mi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[ni], xf[mi], acc[ni][mi], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int q = 0; q < per; ++q)
-        if (j * per + q < n_ops) op(j * per + q);
+      for (int o = 0; o < n_ops; ++o)
+        if (at(o) == j) op(o);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  auto next_slot = [](int s, int by) { s += by; return s >= NU ? s - NU : s; };
-  static_assert(NU == 5, "the pipeline below is written for a ring of five panels");
-  // Software pipeline.  Panels are numbered in issue order, W(0) X(0) W(1) X(1) ..., and
-  // panel u lives in ring slot u % 5.  Once the last fragments of tile kt are in
-  // registers, at the one barrier of the iteration, X(kt+2) and W(kt+3) are requested
-  // into the two slots that tile kt frees: the weight panel, which in a layer streams from
-  // HBM, gets the two k-tiles of look-ahead, and the activation panel, which the previous
-  // kernel has just left in the caches, gets one.  LDS -> registers: the fragments of the next
-  // 32-wide k-step are requested while the MFMAs of the current one are issued, across
-  // tile boundaries too, so the matrix pipe never waits for a whole LDS read phase.
+  // Where the operations of a k-step go: NF reads, then `n_dma` requests.  A request keeps the CU's address unit busy for
+  // 16 to 24 clocks, and eight wavefronts that ask for eight KB each without a pause stand still behind one another, MFMAs
+  // and all: a request every third MFMA (every second where a step is short), reads in between.
+  // (The deep ring, bound by its weight stream, asks as early as it can: 256 rows, N = 4096, K = 14336 43.4 against 44.8 us.)
+  constexpr auto place = [](int o, int n_dma) {
+    if (DEEP) return o * NMF / (NF + n_dma > NMF ? NF + n_dma : NMF);
+    const int pitch = 3 * n_dma - 1 <= NMF ? 3 : 2;
+    const int j = o >= NF ? pitch - 1 + pitch * (o - NF) : pitch == 3 ? o + o / 2 : o;
+    return j < NMF ? j : NMF - 1;
+  };
+  // LDS -> registers: the fragments of the next 32-wide k-step are requested while the MFMAs of the current one are
+  // issued, across tile boundaries too, so the matrix pipe never waits for a whole LDS read phase.
   // The compiler counts an LDS-DMA load as a pending LDS operation of unknown order, so
   // every wait it places before an MFMA is lgkmcnt(0); waiting explicitly at the start of
   // a k-step, for reads issued during the first MFMAs of the previous one, keeps those
   // waits from covering reads that were only just issued.
   constexpr int LGKM0 = waitcnt_imm(63, true);
-  constexpr int PER_F = (NF + NMF - 1) / NMF;  // side operations per MFMA: one is enough where a step has 32 MFMAs
-  constexpr int N_P = NF + LB + LA;
-  constexpr int PER_P = (N_P + NMF - 1) / NMF;
-  (void)N_P; (void)PER_P;
+  constexpr int UX = BM * ROWB, UW = BN * ROWB;  // bytes of a panel
   bf16x8_t xa[MI], wa[NI], xb[MI], wb[NI];
   if constexpr (!DEEP) {
+    // Panel X(kt) lives in activation slot kt % NXS, W(kt) in weight slot kt % NWS.  Once the last fragments of tile kt
+    // are in registers, at the one barrier of the iteration, X(kt+NXS) and W(kt+NWS) are requested into the two slots
+    // that tile kt frees: the weight panel, which in a layer streams from HBM, has two k-tiles of look-ahead, and the
+    // activation panel, which the previous kernel has just left in the caches, one, or two where three slots fit.
+    constexpr int NXS = ring_x_slots(BM, BN, NW), NWS = ring_w_slots(BM, BN, NW), W_BASE = NXS * UX;
+    constexpr int AHEAD = NXS > NWS ? NXS : NWS;
+    // loads requested after both panels of the next tile, and so still in flight when these have landed
+    constexpr int YOUNG = NXS < NWS ? (NXS - 2) * (LA + LB) + LB : (NWS - 2) * (LA + LB);
+    static_assert(NXS >= 2 && NWS >= 2 && W_BASE + NWS * UW <= LDS_BYTES && NXS * LA + NWS * LB < 64, "slots and the vmcnt field");
 #pragma unroll
-    for (int i = 0; i < LB; ++i) dma_b(kt0, 0 * UNIT, i, Yes{});
+    for (int r = -AHEAD; r < 0; ++r) {
+      if (r + NXS >= 0)
 #pragma unroll
-    for (int i = 0; i < LA; ++i) dma_a(kt0, 1 * UNIT, i, Yes{});
+        for (int i = 0; i < LA; ++i) dma_a(kt0 + r + NXS, (r + NXS) * UX, i, Yes{});
+      if (r + NWS >= 0)
 #pragma unroll
-    for (int i = 0; i < LB; ++i) dma_b(kt0 + 1, 2 * UNIT, i, Yes{});
-#pragma unroll
-    for (int i = 0; i < LA; ++i) dma_a(kt0 + 1, 3 * UNIT, i, Yes{});
-#pragma unroll
-    for (int i = 0; i < LB; ++i) dma_b(kt0 + 2, 4 * UNIT, i, Yes{});
-    __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * LB + LA, true));  // tile 0 has landed
+        for (int i = 0; i < LB; ++i) dma_b(kt0 + r + NWS, W_BASE + (r + NWS) * UW, i, Yes{});
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_imm(YOUNG + LA + LB, true));  // tile 0 has landed
     __builtin_amdgcn_s_barrier();
-    int sb = 0, sa = 1;  // slots of the tile being multiplied: weights, activations
+    int xo = 0, wo = W_BASE;  // slots of the tile being multiplied
 #pragma unroll
-    for (int o = 0; o < NF; ++o) frag(sa * UNIT, sb * UNIT, 0, o, xa, wa);
+    for (int o = 0; o < NF; ++o) frag(xo, wo, 0, o, xa, wa);
     auto tile = [&](int kt, auto checked) {
       __builtin_amdgcn_s_waitcnt(LGKM0);
-      step(xa, wa, NF, PER_F, [&](int o) { frag(sa * UNIT, sb * UNIT, 1, o, xb, wb); });
+      step(xa, wa, NF, [&](int o) { return place(o, 0); }, [&](int o) { frag(xo, wo, 1, o, xb, wb); });
       // Every fragment of tile kt is in registers once the LDS reads have returned, and
-      // tile kt+1 has landed once this wavefront's loads other than the youngest panel,
-      // W(kt+2), are done; after the barrier both hold for every wavefront, so the two
+      // tile kt+1 has landed once this wavefront's loads other than the YOUNG last ones
+      // are done; after the barrier both hold for every wavefront, so the two
       // slots of tile kt can be refilled and tile kt+1 can be read.
-      __builtin_amdgcn_s_waitcnt(waitcnt_imm(LB, true));
+      __builtin_amdgcn_s_waitcnt(waitcnt_imm(YOUNG, true));
       __builtin_amdgcn_s_barrier();
-      const int na = next_slot(sa, 2), nb = next_slot(sb, 2);
-      step(xb, wb, N_P, PER_P, [&](int o) {
+      const int nx = xo == (NXS - 1) * UX ? 0 : xo + UX, nw = wo == W_BASE + (NWS - 1) * UW ? W_BASE : wo + UW;
+      step(xb, wb, NF + LA + LB, [&](int o) { return place(o, LA + LB); }, [&](int o) {
         if (o < NF)
-          frag(na * UNIT, nb * UNIT, 0, o, xa, wa);
+          frag(nx, nw, 0, o, xa, wa);
         else if (o < NF + LA)
-          dma_a(kt + 2, sb * UNIT, o - NF, checked);
+          dma_a(kt + NXS, xo, o - NF, checked);
         else
-          dma_b(kt + 3, sa * UNIT, o - NF - LA, checked);
+          dma_b(kt + NWS, wo, o - NF - LA, checked);
       });
-      sa = na;
-      sb = nb;
+      xo = nx;
+      wo = nw;
     };
     int kt = kt0;
-    const int n_plain = a.K / BK - 3;  // tiles kt for which X(kt+2) and W(kt+3) lie wholly inside K
+    const int n_plain = a.K / BK - AHEAD;  // tiles kt for which X(kt+NXS) and W(kt+NWS) lie wholly inside K
     for (; kt < n_plain && kt < kt1; ++kt) tile(kt, No{});
     for (; kt < kt1; ++kt) tile(kt, Yes{});
   } else {
@@ -364,8 +385,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int bid, cons
     // the first half of the workgroup loads activations and waits until its NXS - 2 youngest
     // panels remain, the second half loads weights and waits until its NWS - 2 youngest remain.
     constexpr int NXS = DEEP + 1;  // activation slots
-    constexpr int UX = BM * ROWB, UW = BN * ROWB, W_BASE = NXS * UX;
-    constexpr int NWS = (160 * 1024 - W_BASE) / UW;
+    constexpr int W_BASE = NXS * UX;
+    constexpr int NWS = (LDS_BYTES - W_BASE) / UW;
     static_assert(NWS >= 3 && (NWS - 1) * LB < 64 && (NXS - 1) * LA < 64, "slots and the vmcnt field");
     const bool loads_x = wave < XW;  // uniform
     if (loads_x) {
@@ -385,12 +406,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int bid, cons
     int xs = 0, ws = 0;            // activation and weight slot numbers of the tile being multiplied
 #pragma unroll
     for (int o = 0; o < NF; ++o) frag(xs * UX, W_BASE + ws * UW, 0, o, xa, wa);
-    constexpr int N_X = NF + LA, N_W = NF + LB;
-    constexpr int PER_X = (N_X + NMF - 1) / NMF, PER_W = (N_W + NMF - 1) / NMF;
     auto tile = [&](int kt, auto checked) {
       const int wo = W_BASE + ws * UW, xo = xs * UX;
       __builtin_amdgcn_s_waitcnt(LGKM0);
-      step(xa, wa, NF, PER_F, [&](int o) { frag(xo, wo, 1, o, xb, wb); });
+      step(xa, wa, NF, [&](int o) { return place(o, 0); }, [&](int o) { frag(xo, wo, 1, o, xb, wb); });
       // after the barrier: every wavefront holds all fragments of tile kt, X(kt+1) has landed
       // (the activation half waited until only X(kt+2) .. X(kt+NXS-1) were outstanding) and so
       // has W(kt+1) (the weight half: only W(kt+2) .. W(kt+NWS-1))
@@ -403,14 +422,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int bid, cons
       const int nxo = nxs * UX;
       const int nwo = W_BASE + nws * UW;
       if (loads_x)
-        step(xb, wb, N_X, PER_X, [&](int o) {
+        step(xb, wb, NF + LA, [&](int o) { return place(o, LA); }, [&](int o) {
           if (o < NF)
             frag(nxo, nwo, 0, o, xa, wa);
           else
             dma_a(kt + NXS, xo, o - NF, checked);
         });
       else
-        step(xb, wb, N_W, PER_W, [&](int o) {
+        step(xb, wb, NF + LB, [&](int o) { return place(o, LB); }, [&](int o) {
           if (o < NF)
             frag(nxo, nwo, 0, o, xa, wa);
           else
@@ -455,7 +474,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int bid, cons
       }
       __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, true));  // the part has arrived there before the workgroup counts itself in
       __syncthreads();
-      volatile unsigned *flag = reinterpret_cast<volatile unsigned *>(smem + NU * UNIT - 16);
+      volatile unsigned *flag = reinterpret_cast<volatile unsigned *>(smem + LDS_BYTES - 16);
       if (t == 0) *flag = atomicAdd(sp->cnt + seg.j, 1u);
       __syncthreads();
       if (*flag + 1u != (unsigned)seg.parts) return;
@@ -496,7 +515,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int bid, cons
   static_assert(WTN == 64, "an epilogue hands 64 columns to 16 lanes");
   constexpr int CM = MI <= 4 ? MI : (MI + 1) / 2;
   constexpr int RS = 64 * 4 + 16;  // bytes of a row of 64 floats: rows four banks apart
-  constexpr int LDS_BYTES = DEEP ? 160 * 1024 : NU * UNIT;
   static_assert(NW * CM * 16 * RS <= LDS_BYTES, "the turned blocks fit the panel ring");
   unsigned char *turned = smem + wave * (CM * 16 * RS);
   // blocks [c, c + CM) of rows into LDS (read and written by this wavefront alone, whose LDS operations complete in order)
@@ -1185,7 +1203,7 @@ hipError_t launch_rows_one(const GemmArgs &a, int epi, int dh, hipStream_t strea
 template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int DH, int DEEP = 0>
 hipError_t launch_one(const GemmArgs &a, hipStream_t stream) {
   constexpr int OUT_BN = (EPI == EPI_SWIGLU) ? BN / 2 : BN;
-  constexpr int LDS = DEEP ? 160 * 1024 : NU * (BM > BN ? BM : BN) * BK * 2;
+  constexpr int LDS = DEEP ? LDS_CU : ring_bytes(WAVES_M * WAVES_N);
   auto kern = gemm_kernel<BM, BN, WAVES_M, WAVES_N, EPI, DH, DEEP>;
   static OncePerDevice once;
   if (const hipError_t e = allow_lds(once, reinterpret_cast<const void *>(kern), LDS)) return e;
@@ -1201,7 +1219,7 @@ constexpr int SK_MAX_G = 256;  // workgroups of a shared-tile launch at most: on
 template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int DH>
 hipError_t launch_sk(const GemmArgs &a, hipStream_t stream) {
   constexpr int OUT_BN = (EPI == EPI_SWIGLU) ? BN / 2 : BN;
-  constexpr int LDS = NU * (BM > BN ? BM : BN) * BK * 2;
+  constexpr int LDS = ring_bytes(WAVES_M * WAVES_N);
   static_assert(BM == 256 && BN == 256, "the workspace slots are sized for 256x256 tiles");
   if (!a.sk_ws || !a.sk_cnt || a.n_count || a.k_splits > 1) return hipErrorInvalidValue;
   auto kern = gemm_sk_kernel<BM, BN, WAVES_M, WAVES_N, EPI, DH>;
@@ -1233,8 +1251,8 @@ hipError_t launch_sk(const GemmArgs &a, hipStream_t stream) {
 template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int ADH>
 hipError_t launch_ride(const GemmArgs &a, const GemmRide &r, hipStream_t stream) {
   constexpr int OUT_BN = (EPI == EPI_SWIGLU) ? BN / 2 : BN;
-  constexpr int LDS = NU * (BM > BN ? BM : BN) * BK * 2;
-  static_assert(LDS == 160 * 1024, "a workgroup of either kind must take the whole LDS of its CU");
+  constexpr int LDS = ring_bytes(WAVES_M * WAVES_N);
+  static_assert(LDS == LDS_CU, "a workgroup of either kind must take the whole LDS of its CU");
   auto kern = gemm_attn_kernel<BM, BN, WAVES_M, WAVES_N, EPI, 64, ADH>;
   static OncePerDevice once;
   if (const hipError_t e = allow_lds(once, reinterpret_cast<const void *>(kern), LDS)) return e;

@@ -79,6 +79,23 @@ def test_gemm_nt(lib, m, n, k):
     assert maxrel < 4e-3
 
 
+@pytest.mark.parametrize("tiles,m", [(1, 300), (2, 330), (3, 130)])
+@pytest.mark.parametrize("k", [8, 64, 72, 128, 192, 200, 256, 320, 456])
+def test_gemm_nt_around_the_look_ahead(lib, tiles, m, k):
+    # one to eight k-tiles, whole and ragged: fewer than the panel rings hold, as many, and more (two or three panels
+    # requested ahead, by the tile shape; chunks beyond K among the first, the refilled and the last)
+    import torch
+    rng = np.random.default_rng(m + k)
+    a = W.round_to_bf16(rng.standard_normal((m, k), dtype=np.float32))
+    b = W.round_to_bf16(rng.standard_normal((264, k), dtype=np.float32) * 0.05)
+    layer = lib.Layer(W.TINY, device=0)
+    layer.set_gemm_tiles(tiles)
+    c = to_np(layer.gemm_nt(torch.from_numpy(a).cuda().to(torch.bfloat16), torch.from_numpy(b).cuda().to(torch.bfloat16)))
+    ref = a.astype(np.float64) @ b.astype(np.float64).T
+    assert np.max(np.abs(c - ref) / (np.abs(ref) + 1e-3 * np.max(np.abs(ref)))) < 6e-3
+    assert errs(c, ref)[0] < 4e-3
+
+
 @pytest.mark.parametrize("m,n,k", [(2600, 4104, 520),    # 187 tiles for 256 workgroups: every tile cut along K
                                    (4096, 4096, 192),    # 256 tiles: one whole round, nothing shared
                                    (4100, 5000, 328),    # 340 tiles: all shared, more than a tile's worth each
