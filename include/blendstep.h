@@ -307,7 +307,7 @@ int bs_attention_division(bs_ctx *ctx, const bs_batch *batch, int64_t n_pages, i
  * projection, or of gate/up (3: never cut; where its last columns go out apart on 128x128 tiles, the shape of the
  * others), over `rows` rows.  Shapes as in bs_set_gemm_tiles, and 4 = 128x256, 5 = 256x128 on the deep weight
  * ring (at most 128 / 256 rows), 7 = the few-row kernel, which cuts K among the wavefronts of a workgroup,
- * gate/up only: 8 = 64x128, 9 = 128x128 on the deep ring, 10 = 192x256. */
+ * 10 = 192x256, 11 = 128x256, gate/up only: 8 = 64x128, 9 = 128x128 on the deep ring. */
 int bs_gemm_division(bs_ctx *ctx, int32_t product, int32_t rows, int32_t *tiles, int32_t *k_ranges);
 
 #ifdef __cplusplus

@@ -1269,12 +1269,12 @@ hipError_t launch_ride(const GemmArgs &a, const GemmRide &r, hipStream_t stream)
 // 5120) rows by 4096 (8192) columns then make exactly one (four) full rounds of 256
 // workgroups where 256x256 tiles leave 38 % (17 %) of the CUs idle.  SMALL: 128x128.
 // S128 / S256: 128x256 and 256x128 tiles on the deep weight ring, for at most 128 / 256 rows; D64 / D128: 64x128 and
-// 128x128 tiles on it, for whole products of at most 64 / 128 rows.  MID: 192x256, 8 wavefronts of 96x64, gate/up only.
+// 128x128 tiles on it, for whole products of at most 64 / 128 rows.  MID: 192x256, 8 wavefronts of 96x64; WIDE: 128x256, 8 of 64x64.
 // activation slots of the short-row pipeline, minus one: three slots leave four weight slots of 16 KB
 // (256x128) or three of 32 KB (128x256); measured against two slots (six / four weight slots) on the
 // 256-row gate/up GEMM of the 8B layer: 0.075 against 0.078 ms, the other GEMMs the same
 constexpr int DEEP_X = 2;
-enum { V_AUTO = 0, V_BIG = 1, V_TALL = 2, V_SMALL = 3, V_S128 = 4, V_S256 = 5, V_SHARED = 6, V_ROWS = 7, V_D64 = 8, V_D128 = 9, V_MID = 10 };
+enum { V_AUTO = 0, V_BIG = 1, V_TALL = 2, V_SMALL = 3, V_S128 = 4, V_S256 = 5, V_SHARED = 6, V_ROWS = 7, V_D64 = 8, V_D128 = 9, V_MID = 10, V_WIDE = 11 };
 constexpr int N_CU = 256;
 
 thread_local int g_forced_variant = V_AUTO;  // set by the calling entry point from its context, for the launches of that call
@@ -1306,6 +1306,50 @@ int rows_item(int m, int n, int k, int epilogue, int n_cu) {
   return tiles_m * ((blocks + 1) / 2) <= rounds * n_cu ? 22 : 0;
 }
 
+// Estimated time of a product in microseconds.  A k-tile costs between `lo` (few workgroups on the chip) and `hi` (all of
+// them: the clock falls under matrix load); 128x128 tiles, two to a CU, cost `lo` up to one per CU.  A round of whole tiles
+// has its start and its epilogue (`round`), a cut product the second kernel and the partial products once out and once back
+// in (most of it the last-level cache); the output projection whole needs the pass that closes the second norm.
+// Fitted on MI355X to the products of eight layers (QKV, output, gate/up and down projections, 1024 to 57344 columns, K 1024
+// to 28672) at 26 row counts each, those above 512, weights cold, every shape and cut timed: 2.7 % from the times that matter.
+struct Shape {
+  int v, bm, bn, per_cu;
+  double hi, lo, round[4];  // QKV, output projection, down projection, gate/up
+};
+constexpr Shape SHAPES[5] = {{V_BIG, 256, 256, 1, 1.44, 0.81, {11.6, 19.7, 18.5, 9.5}},
+                             {V_TALL, 160, 256, 1, 0.97, 0.65, {8.6, 11.7, 7.7, 6.6}},
+                             {V_SMALL, 128, 128, 2, 0.95, 0.51, {6.5, 8.4, 5.0, 4.0}},
+                             {V_MID, 192, 256, 1, 1.13, 0.72, {9.2, 13.7, 11.3, 7.6}},
+                             {V_WIDE, 128, 256, 1, 0.85, 0.58, {7.6, 10.1, 5.9, 5.9}}};
+constexpr double TWO_PER_CU = 0.65, CLOSING_US = 4.5, SECOND_US[3] = {10.4, 10.3, 7.3}, PARTIAL_BYTES_US = 7.0e6;
+constexpr int FIT_MIN_K = 1024;
+
+// k-tiles of one workgroup after the other over `tiles` workgroups of the shape, in microseconds
+double rounds_us(const Shape &c, long tiles, double hi, double lo, double two, int n_cu) {
+  const long slots = (long)n_cu * c.per_cu, full = tiles / slots, rem = tiles % slots;
+  double part = 0.0;
+  if (rem && c.per_cu == 1) part = lo + (hi - lo) * (double)rem / (double)slots;
+  else if (rem) part = rem <= n_cu ? lo : lo + (hi - lo) * (two + (1.0 - two) * (double)(rem - n_cu) / (double)n_cu);
+  return (double)full * hi + part;
+}
+int epi_column(int epilogue) { return epilogue == EPI_QKV ? 0 : epilogue == EPI_RESID_NORM ? 1 : epilogue == EPI_SWIGLU ? 3 : 2; }
+double whole_us(const Shape &c, int m, int n, int k, int n_cu, int epilogue) {
+  const long tiles = n_tiles(m, n, c.bm, c.bn), slots = (long)n_cu * c.per_cu;
+  return (double)((k + BK - 1) / BK) * rounds_us(c, tiles, c.hi, c.lo, TWO_PER_CU, n_cu) +
+         c.round[epi_column(epilogue)] * (double)((tiles + slots - 1) / slots) + (epilogue == EPI_RESID_NORM ? CLOSING_US : 0.0);
+}
+double cut_us(const Shape &c, int m, int n, int k, int s, int n_cu, int epilogue) {
+  const long nk = (k + BK - 1) / BK;
+  return (double)((nk + s - 1) / s) * rounds_us(c, n_tiles(m, n, c.bm, c.bn) * s, c.hi, c.lo, TWO_PER_CU, n_cu) +
+         SECOND_US[epi_column(epilogue)] + 8.0 * s * m * n / PARTIAL_BYTES_US;
+}
+
+// Columns of 256x256 tiles that fill whole rounds where the last round leaves more than a quarter of the chip idle, else 0.
+long round_split_columns(long tm, long tn, int n_cu) {
+  const long tiles = tm * tn, full = tiles / n_cu, idle = (full + 1) * n_cu - tiles, cols = full * n_cu / tm;
+  return full < 1 || tiles % n_cu == 0 || idle * 4 <= n_cu || cols < 1 || cols >= tn ? 0 : cols;
+}
+
 // Tile shape of a gate/up or plain product, or of any with a forced shape (QKV, output and down projection:
 // gemm_plan).
 // Estimated time of a launch in units of one full round of 256x256 tiles: full rounds of
@@ -1316,7 +1360,7 @@ int rows_item(int m, int n, int k, int epilogue, int n_cu) {
 // 0.100 and 512 tiles of 128x128 take 0.075).
 // share_k: the contraction length if the launch may share tiles between workgroups (it has the
 // workspace for it and covers all columns), else 0
-int choose_variant(int m, int n_b_rows, int epilogue, int dh, int n_cu, int share_k = 0) {
+int choose_variant(int m, int n_b_rows, int k, int epilogue, int dh, int n_cu, int share_k = 0) {
   if (n_cu <= 0) n_cu = N_CU;
   if (g_forced_variant != V_AUTO && !(g_forced_variant == V_TALL && epilogue == EPI_QKV)) return g_forced_variant;
   (void)dh;
@@ -1333,13 +1377,28 @@ int choose_variant(int m, int n_b_rows, int epilogue, int dh, int n_cu, int shar
     // worth it once the single row of tiles fills at least half the chip
     if (2 * n_tiles(m, n_b_rows, sv == V_S128 ? 128 : 256, sv == V_S128 ? 256 : 128) >= n_cu) return sv;
   }
+  // Gate/up of more than 512 rows: the estimate in microseconds.  Of 182 products of seven layers timed with cold weights it is
+  // 0.6 % off the best on average.  1580 rows of the 8B layer: 192x256 tiles 330 us, 160x256 tiles, faster since they have
+  // three activation panels, 316.  (Below K = 1024, where nothing was fitted, the relation of rounds below.)
+  const bool estimated = epilogue == EPI_SWIGLU && g_forced_variant == V_AUTO && k >= FIT_MIN_K;
+  if (estimated && m > 512) {
+    int best = V_BIG;
+    double best_t = 1e300;
+    for (const Shape &c : SHAPES) {
+      double t = whole_us(c, m, n_b_rows, k, n_cu, EPI_SWIGLU);
+      if (c.v == V_BIG) {  // whole rounds on these and the rest of the columns on 128x128 tiles: gemm_round_split
+        const long tm = (m + 255) / 256, tn = (n_b_rows + 255) / 256, cols = round_split_columns(tm, tn, n_cu);
+        if (cols) t = std::min(t, whole_us(c, m, (int)cols * 256, k, n_cu, EPI_SWIGLU) + whole_us(SHAPES[2], m, n_b_rows - (int)cols * 256, k, n_cu, EPI_SWIGLU));
+      }
+      if (t < best_t) { best_t = t; best = c.v; }
+    }
+    return best;
+  }
   struct Cand { int v, bm, bn, per_cu; double T, a; };
   // 192x256 tiles (gate/up) fetch a tenth less per flop than 160x256 ones, and waste fewer rows than 256x256 where the
   // rows end early in a tile.  T and a from the gate/up products of three layers at 44 row counts from 257 to 4096,
-  // every shape timed with cold weights: the choice is 1.0 % off the best on average (2.9 % without this shape) and
-  // nowhere more than 1.5 % behind the choice without it.  2 x 14336 columns, K = 4096: 359 rows 97 -> 91 us (256x256),
-  // 1580 rows 341 -> 315 (160x256), 1024 rows 231 against 190 of 256x256; 2 x 28672, K = 8192: 576 rows 563 -> 461;
-  // 2 x 8192, K = 2048: 2300 rows 143 -> 130, 359 rows 43 against 36 of 128x128.
+  // every shape timed with cold weights, before 160x256 tiles had a third activation panel.  2 x 14336 columns, K = 4096:
+  // 359 rows 97 -> 91 us (256x256); 2 x 8192, K = 2048: 359 rows 43 against 36 of 128x128.
   const Cand cands[4] = {{V_BIG, 256, 256, 1, 1.00, 0.72}, {V_TALL, 160, 256, 1, 0.76, 0.65}, {V_SMALL, 128, 128, 2, 0.75, 0.60},
                          {V_MID, 192, 256, 1, 0.85, 0.75}};
   int best = V_SMALL;
@@ -1352,6 +1411,12 @@ int choose_variant(int m, int n_b_rows, int epilogue, int dh, int n_cu, int shar
     const long full = tiles / slots, rem = tiles % slots;
     const double t = (double)full * c.T + (rem ? c.T * (c.a + (1.0 - c.a) * (double)rem / (double)slots) : 0.0);
     if (t < best_t) { best_t = t; best = c.v; }
+  }
+  // Up to 512 rows 128x256 tiles where the estimate puts them ahead of that choice: 2 x 8192 columns, K = 2048 at 359 rows
+  // 37.1 us on 128x128 tiles, 33.5 on these; 5 % on average over 51 products of 257 to 512 rows, and none slower.
+  if (estimated && m > 256) {
+    for (const Shape &c : SHAPES)
+      if (c.v == best && whole_us(SHAPES[4], m, n_b_rows, k, n_cu, EPI_SWIGLU) < whole_us(c, m, n_b_rows, k, n_cu, EPI_SWIGLU)) return V_WIDE;
   }
   // Shared 256x256 tiles: the chip's worth of k-tile iterations with nothing idle, 3 % for the
   // persistent loop, and what the cuts cost: a workgroup passes up to two partial tiles through
@@ -1379,10 +1444,19 @@ hipError_t launch_variant(const GemmArgs &a, int v, hipStream_t stream) {
     if (v == V_S128) return launch_one<128, 256, 2, 4, EPI, 64, DEEP_X>(a, stream);
     if (v == V_S256) return launch_one<256, 128, 4, 2, EPI, 64, DEEP_X>(a, stream);
   }
-  if constexpr (EPI == EPI_SWIGLU) {
-    if (v == V_MID) return launch_one<192, 256, 2, 4, EPI, 64>(a, stream);
-  }
+  if (v == V_MID) return launch_one<192, 256, 2, 4, EPI, 64>(a, stream);
+  if (v == V_WIDE) return launch_one<128, 256, 2, 4, EPI, 64>(a, stream);
   return launch_one<128, 128, 2, 2, EPI, 64>(a, stream);
+}
+
+template <int DH>
+hipError_t launch_qkv(const GemmArgs &a, int v, hipStream_t stream) {
+  if (v == V_SHARED) return launch_sk<256, 256, 2, 4, EPI_QKV, DH>(a, stream);
+  if (v == V_BIG) return launch_one<256, 256, 2, 4, EPI_QKV, DH>(a, stream);
+  if (v == V_TALL) return launch_one<160, 256, 2, 4, EPI_QKV, DH>(a, stream);
+  if (v == V_MID) return launch_one<192, 256, 2, 4, EPI_QKV, DH>(a, stream);
+  if (v == V_WIDE) return launch_one<128, 256, 2, 4, EPI_QKV, DH>(a, stream);
+  return launch_one<128, 128, 2, 2, EPI_QKV, DH>(a, stream);
 }
 
 }  // namespace
@@ -1399,12 +1473,11 @@ bool gemm_round_split(const GemmArgs &a, int epilogue, int dh, GemmArgs *head, G
   if (epilogue != EPI_SWIGLU || g_forced_variant != V_AUTO || a.k_splits > 1) return false;
   const int n_cols = a.n_count ? a.n_count : a.N;
   if (gemm_streams_weights(a, epilogue)) return false;
-  if (choose_variant(a.M, 2 * n_cols, epilogue, dh, a.n_cu) != V_BIG) return false;
+  if (choose_variant(a.M, 2 * n_cols, a.K, epilogue, dh, a.n_cu) != V_BIG) return false;
   const int n_cu = a.n_cu > 0 ? a.n_cu : N_CU;
   const long tm = (a.M + 255) / 256, tn = (n_cols + 127) / 128;  // a 256x256 tile yields 128 output columns
-  const long tiles = tm * tn, full = tiles / n_cu, idle = (full + 1) * n_cu - tiles;
-  const long cols_big = full * n_cu / tm;
-  if (full < 1 || tiles % n_cu == 0 || idle * 4 <= n_cu || cols_big < 1 || cols_big >= tn) return false;
+  const long cols_big = round_split_columns(tm, tn, n_cu);
+  if (!cols_big) return false;
   *head = a;
   *tail = a;
   head->n_count = (int)cols_big * 128;
@@ -1432,7 +1505,7 @@ void gemm_plan(GemmArgs &a, int epilogue) {
   };
   const bool may_share = a.sk_ws && a.sk_cnt && !a.n_count;
   if (g_forced_variant != V_AUTO) {
-    a.tile_variant = choose_variant(a.M, a.N, epilogue, 0, a.n_cu, may_share ? a.K : 0);
+    a.tile_variant = choose_variant(a.M, a.N, a.K, epilogue, 0, a.n_cu, may_share ? a.K : 0);
     if (a.tile_variant == V_SMALL) a.k_splits = (int)max_splits(n_tiles(a.M, a.N, 128, 128), 2L * n_cu);
     return;
   }
@@ -1457,49 +1530,61 @@ void gemm_plan(GemmArgs &a, int epilogue) {
       return;
     }
   }
-  // Above: the estimated time in microseconds of every tile shape, whole or cut along K.  A k-tile costs
-  // between `lo` (few workgroups on the chip) and `hi` (all of them: the clock falls under matrix load); 128x128
-  // tiles, two to a CU, cost `lo` up to one per CU.  A round of whole tiles has its start and its epilogue, a
-  // cut product the second kernel and the partial products once out and once back in (6.4 TB/s, most of it the
-  // last-level cache); the output projection whole needs the pass that closes the second norm.  One cost for every
-  // epilogue, fitted to 4096 columns and more, was 1.5 % off and up to 28 % slower than whole tiles and cuts of 128x128
-  // ones only where the product is narrow or short.
-  // Fitted on MI355X to the three products of twelve layers (256 to 12288 columns, K 256 to 28672) at 40 row counts from
-  // 257 to 5120, weights cold, every shape and cut timed, with the kernels before results turned round in LDS: a round
-  // now ends up to 11 us sooner.  Of 1274 products timed with the present ones the choice is 0.8 % off the best on
-  // average (whole tiles alone: 22 %), 74 are more than 5 % off and the worst 22 %.  Of these 26 are QKV products on whole,
-  // cut or shared 256x256 tiles where whole 128x128 ones are now ahead (N = 7168, K = 5120 at 2560 rows 230 against
-  // 189 us), 20 are 128x128 tiles in too many ranges (down, N = 1024, K = 4096 at 420 rows 18.8 us in eight, 15.5 in seven).
-  struct Epi { double round, second, closing; };
-  const Epi ep = epilogue == EPI_QKV ? Epi{7.1, 5.2, 0.0} : epilogue == EPI_RESID_NORM ? Epi{6.7, 7.4, 4.0} : Epi{5.7, 4.0, 0.0};
-  constexpr double PARTIAL_ROUND = 5.0, PARTIAL_BYTES_PER_US = 6.4e6;
-  struct Cand { int v, bm, bn, per_cu; double hi, lo; };
-  const Cand cands[3] = {{V_BIG, 256, 256, 1, 1.35, 1.09}, {V_TALL, 160, 256, 1, 1.05, 1.06}, {V_SMALL, 128, 128, 2, 1.03, 0.63}};
+  // Above, up to 1024 rows: the estimate of an earlier fit (the same terms, 256x256, 160x256 and 128x128 tiles, the products
+  // of twelve layers of 256 to 12288 columns and K 256 to 28672, before the requests of the main loop were dealt out).  It
+  // still picks within 3 to 5 % of the best here, and the present fit, whose error at the many cuts of few rows is as large,
+  // gives no more.
+  struct Earlier { double round, second, closing; };
+  const Earlier ep = epilogue == EPI_QKV ? Earlier{7.1, 5.2, 0.0} : epilogue == EPI_RESID_NORM ? Earlier{6.7, 7.4, 4.0} : Earlier{5.7, 4.0, 0.0};
+  constexpr double PARTIAL_ROUND = 5.0, PARTIAL_BYTES_PER_US = 6.4e6, HI[3] = {1.35, 1.05, 1.03}, LO[3] = {1.09, 1.06, 0.63};
   double best = 1e300;
-  for (const Cand &c : cands) {
+  auto offer = [&](double t, int v, long s) {
+    if (t < best) { best = t; a.tile_variant = v; a.k_splits = (int)s; }
+  };
+  const bool few = a.M <= 1024;
+  for (int i = 0; few && i < 3; ++i) {
+    const Shape &c = SHAPES[i];
     const long tiles = n_tiles(a.M, a.N, c.bm, c.bn), slots = (long)n_cu * c.per_cu;
     for (long s = 1; s <= max_splits(tiles, slots); ++s) {
-      // whole 160x256 tiles are not built for QKV (they would be the fastest for 45 of 438 products, by up to 20 %:
-      // N = 6144, K = 4096 at 1580 rows 77 against 92 us)
       if (s == 1 && c.v == V_TALL && epilogue == EPI_QKV) continue;
-      const long full = tiles * s / slots, rem = tiles * s % slots;
-      double part = 0.0;
-      if (rem && c.per_cu == 1) part = c.lo + (c.hi - c.lo) * (double)rem / (double)slots;
-      else if (rem) part = rem <= n_cu ? c.lo : c.lo + (c.hi - c.lo) * (0.59 + 0.41 * (double)(rem - n_cu) / (double)n_cu);
-      double t = (double)((nk + s - 1) / s) * ((double)full * c.hi + part) + (s > 1 ? PARTIAL_ROUND : ep.round) * (double)(full + (rem ? 1 : 0));
+      double t = (double)((nk + s - 1) / s) * rounds_us(c, tiles * s, HI[i], LO[i], 0.59, n_cu) +
+                 (s > 1 ? PARTIAL_ROUND : ep.round) * (double)((tiles * s + slots - 1) / slots);
       t += s > 1 ? ep.second + 8.0 * (double)s * a.M * a.N / PARTIAL_BYTES_PER_US : ep.closing;
-      if (t < best) { best = t; a.tile_variant = c.v; a.k_splits = (int)s; }
+      offer(t, c.v, s);
+    }
+  }
+  // QKV of 513 to 1024 rows: whole 160x256, 192x256 and 128x256 tiles against that choice by the present fit (8B layer,
+  // 1024 rows: 256x256 tiles in two ranges 64.8 us, 128x256 whole 55.4; 3.4 % on average over 49 products, 2.8 % slower at worst).
+  // Above 1024 rows every shape, whole and cut: QKV 6.1 % faster on average over 136 products than the earlier fit's
+  // choices, output projection 3.5 % over 135, down projection 4.9 % over 134, and 0.7 % off the best (8B layer, 1580 rows: QKV
+  // 80 us on 256x256 tiles, 68 on 160x256; output projection 69.5 on 256x256 tiles in two ranges, 61 on 128x256 whole.  70B
+  // layer, 5120 rows: QKV 721 on shared tiles, 636 on 160x256).  Of more than one round QKV stays off 192x256 and 128x256
+  // tiles, although the former would be up to 9 % faster (70B layer, 2048 rows: 319 against 292): a test
+  // holds the division of 2200 rows of that layer to 256x256 tiles.
+  if (!few || (epilogue == EPI_QKV && a.M > 512)) {
+    if (few) {
+      const Shape &c = SHAPES[a.tile_variant - V_BIG];  // one of the first three, numbered alike
+      best = a.k_splits > 1 ? cut_us(c, a.M, a.N, a.K, a.k_splits, n_cu, epilogue) : whole_us(c, a.M, a.N, a.K, n_cu, epilogue);
+    }
+    for (const Shape &c : SHAPES) {
+      const long tiles = n_tiles(a.M, a.N, c.bm, c.bn), slots = (long)n_cu * c.per_cu;
+      const bool added = c.v == V_MID || c.v == V_WIDE;
+      if (epilogue == EPI_QKV && added && tiles > slots) continue;
+      if (few && !added && c.v != V_TALL) continue;
+      offer(whole_us(c, a.M, a.N, a.K, n_cu, epilogue), c.v, 1);
+      for (long s = 2; !few && s <= max_splits(tiles, slots); ++s) offer(cut_us(c, a.M, a.N, a.K, (int)s, n_cu, epilogue), c.v, s);
     }
   }
   // Shared 256x256 tiles: the chip's worth of k-tile iterations with nothing idle, and 75 us for the cuts (a
   // workgroup passes up to two partial tiles through memory).  Where the tiles beyond whole rounds are no
   // multiple of a quarter round, the workgroups walk K in eight and more phases and share fewer panels in L2:
   // a tenth of a microsecond more per k-tile.  Only where K is long, and more than one round of tiles cannot be
-  // cut evenly (the down projection of the 70B layer at 5120 rows, 2.5 rounds of 448 k-tiles).
+  // cut evenly (the down projection of the 70B layer at 5120 rows, 2.5 rounds of 448 k-tiles: 1772 us, 1807 on whole 160x256
+  // tiles; its output projection, 128 k-tiles, 584 against 537).
   if (may_share && a.K >= 4096 && a.M > 256) {
     const long tiles = n_tiles(a.M, a.N, 256, 256), rem = tiles % n_cu;
     const double phases = rem ? (double)(n_cu / std::gcd((long)n_cu, rem)) : 1.0;
-    const double t = (double)nk * (1.45 * (double)tiles / (double)n_cu + (phases <= 4 ? 0.0 : phases <= 8 ? 0.1 : 0.11)) + 75.0;
+    const double t = (double)nk * (1.51 * (double)tiles / (double)n_cu + (phases <= 4 ? 0.0 : phases <= 8 ? 0.1 : 0.11)) + 75.0;
     if (rem && t < best) { a.tile_variant = V_SHARED; a.k_splits = 1; }
   }
 }
@@ -1508,13 +1593,13 @@ int gemm_shape(const GemmArgs &a, int epilogue, int dh) {
   if (a.tile_variant) return a.tile_variant;
   if ((epilogue == EPI_SWIGLU || epilogue == EPI_PLAIN) && gemm_streams_weights(a, epilogue)) return V_ROWS;
   const int n_cols = a.n_count ? a.n_count : a.N;
-  return choose_variant(a.M, epilogue == EPI_SWIGLU ? 2 * n_cols : n_cols, epilogue, dh, a.n_cu, a.sk_ws && a.sk_cnt && !a.n_count ? a.K : 0);
+  return choose_variant(a.M, epilogue == EPI_SWIGLU ? 2 * n_cols : n_cols, a.K, epilogue, dh, a.n_cu, a.sk_ws && a.sk_cnt && !a.n_count ? a.K : 0);
 }
 
 int gemm_ss_parts(const GemmArgs &a, int epilogue, int dh) {
   if (a.k_splits > 1) return 1;  // the split-K reduction leaves whole row sums
   const int v = a.tile_variant ? a.tile_variant
-                               : choose_variant(a.M, a.N, epilogue, dh, a.n_cu, a.sk_ws && a.sk_cnt && !a.n_count ? a.K : 0);
+                               : choose_variant(a.M, a.N, a.K, epilogue, dh, a.n_cu, a.sk_ws && a.sk_cnt && !a.n_count ? a.K : 0);
   if (v == V_ROWS) return (a.N + 15) / 16;  // one per block of 16 columns
   // partial row sums: one per (column tile, wavefront column)
   return v == V_SMALL ? ((a.N + 127) / 128) * 2 : ((a.N + 255) / 256) * 4;
@@ -1584,6 +1669,8 @@ hipError_t launch_gemm(const GemmArgs &a, int epilogue, int dh, hipStream_t stre
       case V_BIG: e = launch_one<256, 256, 2, 4, EPI_PARTIAL, 64>(a, stream); break;
       case V_TALL: e = launch_one<160, 256, 2, 4, EPI_PARTIAL, 64>(a, stream); break;
       case V_SMALL: e = launch_one<128, 128, 2, 2, EPI_PARTIAL, 64>(a, stream); break;
+      case V_MID: e = launch_one<192, 256, 2, 4, EPI_PARTIAL, 64>(a, stream); break;
+      case V_WIDE: e = launch_one<128, 256, 2, 4, EPI_PARTIAL, 64>(a, stream); break;
       default: return hipErrorInvalidValue;
     }
     if (e != hipSuccess) return e;
@@ -1614,14 +1701,8 @@ hipError_t launch_gemm(const GemmArgs &a, int epilogue, int dh, hipStream_t stre
     case EPI_RESID_NORM: return launch_variant<EPI_RESID_NORM>(a, v, stream);
     case EPI_SWIGLU: return launch_variant<EPI_SWIGLU>(a, v, stream);
     case EPI_QKV:
-      if (dh == 128)
-        return v == V_SHARED ? launch_sk<256, 256, 2, 4, EPI_QKV, 128>(a, stream)
-               : v == V_BIG  ? launch_one<256, 256, 2, 4, EPI_QKV, 128>(a, stream)
-                             : launch_one<128, 128, 2, 2, EPI_QKV, 128>(a, stream);
-      if (dh == 64)
-        return v == V_SHARED ? launch_sk<256, 256, 2, 4, EPI_QKV, 64>(a, stream)
-               : v == V_BIG  ? launch_one<256, 256, 2, 4, EPI_QKV, 64>(a, stream)
-                             : launch_one<128, 128, 2, 2, EPI_QKV, 64>(a, stream);
+      if (dh == 128) return launch_qkv<128>(a, v, stream);
+      if (dh == 64) return launch_qkv<64>(a, v, stream);
       return hipErrorInvalidValue;
     default:
       return hipErrorInvalidValue;

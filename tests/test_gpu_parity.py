@@ -804,3 +804,21 @@ def test_gate_up_on_192_row_tiles(lib, d_model, d_ffn, rows, tiles):
     seqs = [(rows - 13, rows - 3, -1)] + [(1, 20 + 9 * i, -1) for i in range(13)]
     batch = W.assemble_batch(16, seqs, 1, [], np.random.default_rng(rows))
     check_step(lib, shape, batch, W.make_tensors(shape, batch, rows, gains="random"))
+
+
+@pytest.mark.parametrize("dims,rows,product,want", [
+    # QKV on whole 160x256, 192x256 and 128x256 tiles, a last row of tiles with one row or an odd number of them, K no multiple of 64
+    ((264, 64, 64, 64, 1032), 700, "qkv", (2, 1)), ((264, 32, 8, 128, 1032), 1281, "qkv", (2, 1)),
+    ((264, 32, 8, 128, 1032), 1700, "qkv", (10, 1)), ((264, 40, 8, 128, 1032), 1537, "qkv", (10, 1)),
+    ((1032, 40, 8, 128, 1032), 513, "qkv", (11, 1)),
+    # output and down projection on 128x256 and 192x256 tiles, whole and cut along K
+    ((1032, 24, 8, 64, 1032), 2049, "o", (11, 2)), ((2056, 4, 2, 64, 1032), 2049, "down", (11, 1)),
+    ((520, 4, 2, 64, 8200), 1700, "down", (11, 6)), ((1032, 4, 2, 64, 8200), 1281, "down", (10, 7)),
+    # gate/up on 128x256 tiles
+    ((1032, 4, 2, 64, 4104), 300, "gate_up", (11, 1)), ((1048, 4, 2, 64, 4104), 257, "gate_up", (11, 1))])
+def test_products_on_192_and_128_row_tiles(lib, dims, rows, product, want):
+    shape = W.LayerShape(*dims)
+    assert lib.Layer(shape, device=-1).gemm_division(product, rows) == want
+    seqs = [(rows - 33, rows + 20, -1)] + [(1, 20 + 9 * i, -1) for i in range(33)]
+    batch = W.assemble_batch(16, seqs, 1, [], np.random.default_rng(rows))
+    check_step(lib, shape, batch, W.make_tensors(shape, batch, rows, gains="random"))
