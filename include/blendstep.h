@@ -201,7 +201,8 @@ int bs_profile_reset(bs_ctx *ctx);
 /* Tuning knob: pages per chunk of decode-attention work (even, 2..64).  Smaller chunks give more
  * workgroups, larger ones fewer partial states.  Without it the chunk is chosen for each step: 64
  * pages where the step has enough work for the whole chip, down to 8 where it has not, apart for
- * prefix nodes whose work items carry more than 16 query rows and for the rest. */
+ * prefix nodes whose work items carry more than 16 query rows and for the rest, and a prefill context that
+ * would outlast the rest of the launch is cut into ranges; with it prefill contexts stay whole. */
 int bs_set_chunk_pages(bs_ctx *ctx, int32_t pages);
 
 /* Tuning knobs of the BS_FLAG_OVERLAP schedule. */
@@ -298,7 +299,7 @@ typedef struct bs_division {
   int32_t items, wide_items;       /* decode work items; those with more than 16 query rows */
   int32_t longest_item_tokens[2];  /* of the items with up to / with more than 16 query rows (0: none) */
   int32_t prefill_rows;            /* query rows that a prefill workgroup covers: 64, 128 or 256 (0: no prefill rows) */
-  int64_t states;                  /* partial softmax states */
+  int64_t states;                  /* partial softmax states: of decode sequences, and a row each of prefill workgroups whose context is cut */
   int64_t descriptor_words;        /* 32-bit words of the planned descriptor */
 } bs_division;
 int bs_attention_division(bs_ctx *ctx, const bs_batch *batch, int64_t n_pages, int32_t noalloc, bs_division *out);

@@ -13,6 +13,7 @@
 #include <new>
 #include <string>
 #include <utility>
+#include <climits>
 #include <vector>
 
 #include "../../include/blendstep.h"
@@ -68,9 +69,11 @@ struct Plan {
   int n_seq = 0, n_prefill = 0, n_rows = 0, n_decode = 0, n_prefill_rows = 0;
   long off_row_start = 0, off_kv_len = 0, off_page_start = 0, off_row_pos = 0, off_row_page = 0, off_row_slot = 0,
        off_part_start = 0, off_pf_work = 0, off_items = 0, off_pages = 0, total_ints = 0;
-  long total_node_pages = 0, n_slots = 0;
+  long total_node_pages = 0, n_slots = 0;  // (partial states, in units of one row's: those of decode sequences, then those of cut prefill work)
   int n_pf_work = 0;
   PrefillRoute pf_route{false, 4, 64};
+  long off_pf_cut = 0, n_decode_slots = 0;
+  int n_pf_cut = 0;  // blocks of query rows whose context is cut (0: the work list has two words an item, else four)
   int n_wide = 0, n_narrow = 0;  // decode items with up to 64 / up to 16 query rows (wide ones first)
 };
 
@@ -95,8 +98,9 @@ struct bs_ctx {
   // host scratch reused across calls
   std::vector<int32_t> refcount, path_pages, path_chunks, members, tail_pages, blob;
   std::vector<DecodeItem> items, items_wide;
-  std::vector<int32_t> pf_work;
-  std::vector<std::pair<int, std::pair<int, int>>> pf_order;
+  struct PrefillItem { int blocks, seq, block, t0, t1, state; };
+  std::vector<PrefillItem> pf_order;
+  std::vector<int32_t> pf_cut;
   unsigned char *scratch_ptr = nullptr;  // this device's copy of the static scratch array
   // co-scheduling of decode attention with the prefill rows' GEMMs (BS_FLAG_OVERLAP)
   float *sk_ws = nullptr;       // partial tiles of the GEMM launches whose workgroups share tiles, partial products of split-K
@@ -197,6 +201,13 @@ int ensure_slots(bs_ctx *c, long slots) {
   if ((rc = dev_alloc(c, &c->part_l, (size_t)cap * hq))) return rc;
   c->cap_slots = cap;
   return BS_OK;
+}
+
+// Partial states that a step may use: any number, or, while the stream is being captured and nothing may be allocated,
+// what the context has.
+long step_slots(const bs_ctx *c, hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(st, &status) == hipSuccess && status == hipStreamCaptureStatusNone ? LONG_MAX : c->cap_slots;
 }
 
 int ensure_blob(bs_ctx *c, long ints) {
@@ -475,7 +486,88 @@ PlanSize plan_size(bs_ctx *c, const bs_batch *b, Chunks chunks) {
   return z;
 }
 
-int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chunks) {
+// How a block of query rows of a ring workgroup divides its context of `blocks` blocks of 32 tokens: ranges of nearly equal
+// length, at most `longest` blocks, none begun behind block `last_start`, the last whose first token every row may see.
+int prefill_ranges(int blocks, int longest, int last_start) {
+  int n = (blocks + longest - 1) / longest;
+  while (n > 1 && (long)blocks * (n - 1) / n > last_start) --n;
+  return n;
+}
+// calls f(seq, block of rows, blocks of 32 tokens it walks, last block a range may begin at)
+template <class F>
+void each_prefill_block(const bs_batch *b, int wg_rows, F &&f) {
+  for (int s = 0; s < b->n_prefill; ++s) {
+    const int q = b->row_start[s + 1] - b->row_start[s], before = b->kv_len[s] - q;
+    for (int k = 0; k * wg_rows < q; ++k) f(s, k, (before + std::min(q, (k + 1) * wg_rows) - 1) / 32 + 1, (before + k * wg_rows) / 32);
+  }
+}
+
+// What the launch has to hold beside the prefill work, and the room for the division
+struct CutLimits {
+  double decode_us;  // its decode items, on the whole chip
+  long slots, words; // partial states (rows) and descriptor words that may be added
+};
+
+// Longest range of a prefill workgroup's context in blocks of 32 tokens (0: contexts stay whole).  A block takes a
+// workgroup a microsecond whatever else runs, so a chunk of few rows behind a long context keeps a handful of CUs
+// busy for as long as that context is (8B heads, 32 rows behind 8000 tokens: 8 workgroups, 216 us); cut, the same work is
+// spread over the chip and a merge follows.  The length is the one with the smallest estimate in microseconds: the launch is
+// as long as its longest workgroup, as all its work on the CUs (decode items of the same launch included), or as the
+// rounds of workgroups that it makes, whichever is most; a state costs its way out and back.  Measured, 8B heads, launch and
+// merge: 32 rows behind 8000 tokens 221 -> 34 us, 1024 behind 2000 97 -> 71, 8 x 100 behind 6000 180 -> 114, 500 behind 5000
+// beside 200 decode sequences of 1000 240 -> 207; 2 x 1024 behind 9000 (224 workgroups of one length) stay whole, 305.
+int prefill_cut(bs_ctx *c, const bs_batch *b, const PrefillRoute &route, const CutLimits &lim) {
+  constexpr int SHORTEST = 16;  // blocks of a context that is not worth a cut
+  // (a caller that has fixed the length of decode chunks has the division in hand: contexts stay whole)
+  if (route.direct || b->n_prefill == 0 || c->chunk_pages > 0 || c->cfg.max_positions > 32 * 0x7FFF) return 0;
+  const int wgs = c->cfg.n_q_heads / route.heads;
+  const bool wide = c->cfg.head_dim == 128;  // 64-wide heads: two workgroups to a CU, each at two thirds of its speed
+  const double start = 7.0, merge = 6.0, state_us = 8.0 * c->cfg.n_q_heads * route.rows * c->cfg.head_dim / 4.0e6;
+  int longest = 0;
+  double sum = 0.0;
+  each_prefill_block(b, route.rows, [&](int, int, int blocks, int) { longest = std::max(longest, blocks); sum += blocks; });
+  if (longest < SHORTEST || sum * wgs > 3.0 * 256.0 * longest) return 0;
+  const int lengths[] = {1 << 20, 384, 256, 192, 128, 96, 64, 48, 32, 24, 16, 12, 8};
+  int best = 0;
+  double whole_us = 0.0, best_us = 1e300;
+  std::vector<int> &count = c->members;  // workgroups by length (validate() is done with it)
+  for (const int length : lengths) {
+    if (length != lengths[0] && length >= longest) continue;
+    count.assign((size_t)longest + 1, 0);
+    long states = 0, items = 0, cuts = 0;
+    each_prefill_block(b, route.rows, [&](int, int, int blocks, int last_start) {
+      const int n = prefill_ranges(blocks, length, last_start);
+      count[(blocks + n - 1) / n] += n * wgs;
+      items += n;
+      if (n > 1) { states += n; ++cuts; }
+    });
+    if (states * route.rows > lim.slots || 4 * (items + cuts) > lim.words) break;
+    const int per_cu = !wide && items * wgs > 256 ? 2 : 1;
+    const double block = wide ? 1.0 : per_cu == 2 ? 0.95 : 0.65;
+    // CUs that the decode items leave, on average, while the longest workgroup runs
+    double work = 0.0, rounds = 0.0, first = 0.0;
+    long seen = 0, slots = 0;
+    for (int k = longest; k > 0; --k) {
+      if (!count[k]) continue;
+      const double us = start + block * k;
+      if (!seen) {
+        first = us;
+        slots = per_cu * std::max(64L, 256L - (long)std::ceil(256.0 * std::min(1.0, lim.decode_us / us)));
+      }
+      // of slots * j + 1 workgroups at least this long, j + 1 run one after the other somewhere
+      seen += count[k];
+      rounds = std::max(rounds, us * (double)((seen + slots - 1) / slots));
+      work += us * count[k];
+    }
+    const double all = work / (256.0 * per_cu) + lim.decode_us;
+    const double us = std::max(all, lim.decode_us > 0.5 * all ? first : rounds) + 0.1 * std::min(all, first) + (states ? merge + state_us * states : 0.0);
+    if (length == lengths[0]) whole_us = us;
+    if (us < best_us) { best_us = us; best = states ? length : 0; }
+  }
+  return best_us < 0.95 * whole_us ? best : 0;
+}
+
+int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chunks, long cut_slots, long max_words = LONG_MAX) {
   const int ch = chunks.other;
   const int ps = c->cfg.page_size;
   const int grp = c->cfg.n_q_heads / c->cfg.n_kv_heads;
@@ -565,19 +657,37 @@ int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chu
       }
     }
   }
-  // prefill work: (sequence, block of query rows of one workgroup), longest contexts first
+  // prefill work: (sequence, block of query rows of one workgroup), longest contexts first; a context that would outlast
+  // the rest of the launch is cut into ranges, workgroups of their own
   p.pf_route = prefill_route(attn_shape(c), b->n_prefill, b->row_start, b->kv_len);
-  const int wg_rows = p.pf_route.rows;
-  c->pf_work.clear();
-  std::vector<std::pair<int, std::pair<int, int>>> &order = c->pf_order;
+  std::vector<bs_ctx::PrefillItem> &order = c->pf_order;
   order.clear();
-  for (int s = 0; s < b->n_prefill; ++s) {
-    const int q = b->row_start[s + 1] - b->row_start[s];
-    for (int k = 0; k * wg_rows < q; ++k) order.push_back({-(b->kv_len[s] - q + std::min(q, (k + 1) * wg_rows)), {s, k}});
-  }
-  std::stable_sort(order.begin(), order.end(), [](const auto &x, const auto &y) { return x.first < y.first; });
+  c->pf_cut.clear();
+  double decode_us = 0.0;
+  for (const DecodeItem &it : c->items) decode_us += 2.9 + 0.97 / 16 * it.n_tokens;
+  for (const DecodeItem &it : c->items_wide) decode_us += 6.3 + 0.97 / 16 * it.n_tokens;
+  const long other_words = p.off_pf_work + 8L * (long)(c->items.size() + c->items_wide.size()) + p.total_node_pages + n_tab;
+  const CutLimits lim = {decode_us * c->cfg.n_kv_heads / 1024.0, cut_slots - p.n_slots, max_words - other_words};
+  const int cut = prefill_cut(c, b, p.pf_route, lim);
+  int n_states = 0;
+  each_prefill_block(b, p.pf_route.rows, [&](int seq, int k, int blocks, int last_start) {
+    const int n = cut ? prefill_ranges(blocks, cut, last_start) : 1;
+    for (int i = 0; i < n; ++i) {
+      const int t0 = (int)((long)blocks * i / n), t1 = (int)((long)blocks * (i + 1) / n);
+      order.push_back({t1 - t0, seq, k, t0, i + 1 < n ? t1 : 0, n > 1 ? n_states + i : -1});
+    }
+    if (n == 1) return;
+    c->pf_cut.insert(c->pf_cut.end(), {seq, k, n_states, n});
+    n_states += n;
+  });
+  std::stable_sort(order.begin(), order.end(), [](const auto &x, const auto &y) { return x.blocks > y.blocks; });
   p.n_pf_work = (int)order.size();
-  p.off_items = p.off_pf_work + 2L * p.n_pf_work;
+  p.n_pf_cut = (int)c->pf_cut.size() / 4;
+  p.n_decode_slots = p.n_slots;
+  p.n_slots += (long)n_states * p.pf_route.rows;
+  const int work_words = p.n_pf_cut ? 4 : 2;
+  p.off_pf_cut = p.off_pf_work + (long)work_words * p.n_pf_work;
+  p.off_items = p.off_pf_cut + 4L * p.n_pf_cut;
   // longest chunks first: the many short tail chunks then fill the gaps at the end of the launch
   auto longer = [](const DecodeItem &x, const DecodeItem &y) { return x.n_tokens > y.n_tokens; };
   std::stable_sort(c->items.begin(), c->items.end(), longer);
@@ -589,9 +699,14 @@ int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chu
   p.total_ints = p.off_pages + p.total_node_pages + n_tab;
   blob.resize((size_t)p.total_ints);
   for (int i = 0; i < p.n_pf_work; ++i) {
-    blob[p.off_pf_work + 2 * i] = order[i].second.first;
-    blob[p.off_pf_work + 2 * i + 1] = order[i].second.second;
+    int32_t *w = &blob[p.off_pf_work + (long)work_words * i];
+    w[0] = order[i].seq;
+    w[1] = order[i].block;
+    if (work_words == 2) continue;
+    w[2] = (int32_t)((uint32_t)order[i].t0 | (uint32_t)order[i].t1 << 16);
+    w[3] = order[i].state;
   }
+  if (p.n_pf_cut) std::memcpy(&blob[p.off_pf_cut], c->pf_cut.data(), sizeof(int32_t) * c->pf_cut.size());
   if (p.n_wide) std::memcpy(&blob[p.off_items], c->items_wide.data(), sizeof(DecodeItem) * p.n_wide);
   if (p.n_narrow) std::memcpy(&blob[p.off_items + 8L * p.n_wide], c->items.data(), sizeof(DecodeItem) * p.n_narrow);
   if (p.total_node_pages) std::memcpy(&blob[p.off_pages], b->node_page_ids, sizeof(int32_t) * p.total_node_pages);
@@ -640,6 +755,21 @@ Chunks attention_chunks(bs_ctx *c, const bs_batch *b) {
   return between;
 }
 
+// Partial states that the scratch array of bs_attention_noalloc holds, for a batch that it accepts; bs_attention keeps to them
+// too, so that the two cut the same contexts.
+long attention_slots(bs_ctx *c, const bs_batch *b, long *max_words) {
+  *max_words = LONG_MAX;
+  if (!noalloc_accepts(c, plan_size(c, b, NOALLOC_CHUNKS))) return LONG_MAX;
+  *max_words = BS_NOALLOC_BLOB_BYTES / sizeof(int32_t);
+  const long per = (long)c->cfg.n_q_heads * (c->cfg.head_dim + 2) * (long)sizeof(float);
+  return ((long)(BS_NOALLOC_SCRATCH_BYTES - BS_NOALLOC_BLOB_BYTES) - 32) / per;  // (32: m and l padded to whole 16-byte units)
+}
+int plan_attention(bs_ctx *c, const bs_batch *b, Plan &p) {
+  long words;
+  const long slots = attention_slots(c, b, &words);
+  return build_plan(c, b, p, false, attention_chunks(c, b), slots, words);
+}
+
 // The plan of bs_attention_noalloc.  What fits is decided by the fixed division of the contexts, so that it
 // does not depend on how finely chunk_choice would cut them.
 int plan_noalloc(bs_ctx *c, const bs_batch *b, Plan &p) {
@@ -649,7 +779,7 @@ int plan_noalloc(bs_ctx *c, const bs_batch *b, Plan &p) {
   if (!noalloc_accepts(c, z))
     return fail(c, BS_EINVAL, "bs_attention_noalloc: %ld partial softmax states (%zu bytes) exceed the limit of %u bytes",
                 z.slots, noalloc_state_bytes(c, z.slots), BS_NOALLOC_STATE_BYTES);
-  const int rc = build_plan(c, b, p, false, attention_chunks(c, b));
+  const int rc = plan_attention(c, b, p);
   if (!rc && noalloc_state_bytes(c, p.n_slots) > BS_NOALLOC_SCRATCH_BYTES - BS_NOALLOC_BLOB_BYTES)
     return fail(c, BS_EINVAL, "bs_attention_noalloc: %ld partial softmax states do not fit", p.n_slots);  // (attention_chunks keeps to what fits)
   return rc;
@@ -715,6 +845,9 @@ PrefillArgs prefill_args(const bs_ctx *c, const Plan &p, const uint16_t *q, uint
   a.row_start = c->d_blob + p.off_row_start; a.kv_len = c->d_blob + p.off_kv_len;
   a.page_start = c->d_blob + p.off_page_start; a.page_ids = c->d_blob + p.off_pages + p.total_node_pages;
   a.q = q; a.kv_pool = pool; a.out = out;
+  const size_t first = (size_t)p.n_decode_slots * c->cfg.n_q_heads;
+  a.cut = p.n_pf_cut > 0;
+  a.part_acc = c->part_acc + first * c->cfg.head_dim; a.part_m = c->part_m + first; a.part_l = c->part_l + first;
   return a;
 }
 
@@ -729,6 +862,21 @@ DecodeArgs decode_args(const bs_ctx *c, const Plan &p, const uint16_t *q, const 
   return a;
 }
 
+// The merge of the decode sequences, of the cut prefill work, or of both in one launch
+int run_merge(bs_ctx *c, const Plan &p, bool decode, bool prefill, uint16_t *out, hipStream_t st) {
+  if (!(decode && p.n_decode > 0) && !(prefill && p.n_pf_cut > 0)) return BS_OK;
+  MergeArgs m;
+  m.s = attn_shape(c); m.n_prefill = p.n_prefill; m.n_decode = decode ? p.n_decode : 0;
+  m.row_start = c->d_blob + p.off_row_start; m.part_start = c->d_blob + p.off_part_start;
+  m.part_acc = c->part_acc; m.part_m = c->part_m; m.part_l = c->part_l; m.out = out;
+  const size_t first = (size_t)p.n_decode_slots * c->cfg.n_q_heads;
+  m.cut = c->d_blob + p.off_pf_cut; m.n_cut = prefill ? p.n_pf_cut : 0;
+  m.cut_heads = p.pf_route.heads; m.cut_rows = p.pf_route.rows;
+  m.cut_acc = c->part_acc + first * c->cfg.head_dim; m.cut_m = c->part_m + first; m.cut_l = c->part_l + first;
+  SPAN(c, BS_K_ATTN_MERGE, st, HIP_TRY(c, launch_merge(m, st)));
+  return BS_OK;
+}
+
 int run_prefill_attn(bs_ctx *c, const Plan &p, const uint16_t *q, uint16_t *out, const uint16_t *pool, hipStream_t st) {
   if (p.n_pf_work == 0) return BS_OK;
   const PrefillArgs a = prefill_args(c, p, q, out, pool);
@@ -736,20 +884,11 @@ int run_prefill_attn(bs_ctx *c, const Plan &p, const uint16_t *q, uint16_t *out,
   return BS_OK;
 }
 
-int run_decode_merge(bs_ctx *c, const Plan &p, uint16_t *out, hipStream_t st) {
-  MergeArgs m;
-  m.s = attn_shape(c); m.n_prefill = p.n_prefill; m.n_decode = p.n_decode;
-  m.row_start = c->d_blob + p.off_row_start; m.part_start = c->d_blob + p.off_part_start;
-  m.part_acc = c->part_acc; m.part_m = c->part_m; m.part_l = c->part_l; m.out = out;
-  SPAN(c, BS_K_ATTN_MERGE, st, HIP_TRY(c, launch_decode_merge(m, st)));
-  return BS_OK;
-}
-
-int run_decode_attn(bs_ctx *c, const Plan &p, const uint16_t *q, uint16_t *out, const uint16_t *pool, hipStream_t st) {
+int run_decode_attn(bs_ctx *c, const Plan &p, const uint16_t *q, const uint16_t *pool, hipStream_t st) {
   if (p.n_decode == 0) return BS_OK;
   const DecodeArgs a = decode_args(c, p, q, pool);
   SPAN(c, BS_K_ATTN_DECODE, st, HIP_TRY(c, launch_decode_attn(a, p.n_wide, p.n_narrow, st)));
-  return run_decode_merge(c, p, out, st);
+  return BS_OK;
 }
 
 // Attention of a whole step on one stream: prefill and decode rows in one launch where the step
@@ -757,12 +896,13 @@ int run_decode_attn(bs_ctx *c, const Plan &p, const uint16_t *q, uint16_t *out, 
 int run_attention(bs_ctx *c, const Plan &p, const uint16_t *q, uint16_t *out, const uint16_t *pool, hipStream_t st) {
   if (p.n_pf_work == 0 || p.n_decode == 0 || !blended_attn_possible(attn_shape(c))) {
     int rc = run_prefill_attn(c, p, q, out, pool, st);
-    return rc ? rc : run_decode_attn(c, p, q, out, pool, st);
+    if (!rc) rc = run_decode_attn(c, p, q, pool, st);
+    return rc ? rc : run_merge(c, p, true, true, out, st);
   }
   const PrefillArgs pf = prefill_args(c, p, q, out, pool);
   const DecodeArgs d = decode_args(c, p, q, pool);
   SPAN(c, BS_K_ATTN_DECODE, st, HIP_TRY(c, launch_blended_attn(d, p.n_wide, p.n_narrow, pf, st)));
-  return run_decode_merge(c, p, out, st);
+  return run_merge(c, p, true, true, out, st);
 }
 
 // GEMM arguments of the output projection (+ first residual, second norm), of gate/up (+ SwiGLU)
@@ -1004,6 +1144,7 @@ int run_coscheduled(bs_ctx *c, const Plan &p, const bs_weights *w, const uint16_
     if (p.n_wide > 0 || n_first > 0)
       SPAN(c, BS_K_ATTN_DECODE, st, HIP_TRY(c, launch_decode_attn(dargs, p.n_wide, n_first, st)));
   }
+  if ((rc = run_merge(c, p, false, true, c->attn, st))) return rc;  // the prefill rows go on at once
 
   GemmRide ride{};
   ride.q.d = dargs;
@@ -1046,7 +1187,7 @@ int run_coscheduled(bs_ctx *c, const Plan &p, const bs_weights *w, const uint16_
     rest.trace = trace_of(3, c->n_cu);
     SPAN(c, BS_K_ATTN_QUEUE_REST, st, HIP_TRY(c, launch_decode_queue(rest, c->n_cu, st)));
   }
-  if ((rc = run_decode_merge(c, p, c->attn, st))) return rc;
+  if ((rc = run_merge(c, p, true, false, c->attn, st))) return rc;
   if ((rc = run_o_gate_up(c, w, x, Tp, T, st, BS_K_GEMM_DECODE_ROWS, BS_K_GEMM_DECODE_ROWS))) return rc;
   if (carry_down) return run_down(c, w, y, Tp, T, st, BS_K_GEMM_DECODE_ROWS);
   return run_down(c, w, y, 0, T, st);
@@ -1108,7 +1249,7 @@ int bs_create(const bs_layer_cfg *cfg, int device, bs_ctx **out) {
     c->items.reserve(BS_NOALLOC_BLOB_BYTES / sizeof(DecodeItem));
     c->items_wide.reserve(BS_NOALLOC_BLOB_BYTES / sizeof(DecodeItem));
     c->pf_order.reserve(1 << 15);
-    c->pf_work.reserve(1 << 16);
+    c->pf_cut.reserve(1 << 16);
     c->refcount.reserve(1 << 20);
     c->path_pages.reserve(1 << 15); c->tail_pages.reserve(1 << 15); c->path_chunks.reserve(1 << 15); c->members.reserve(1 << 15);
   } catch (const std::bad_alloc &) { c->err = "out of host memory"; return bail(BS_ENOMEM); }
@@ -1193,7 +1334,7 @@ int bs_resolve_rows(bs_ctx *c, const bs_batch *b, int32_t *page_out, int32_t *sl
   if (rc) return rc;
   if (b->n_rows == 0) return BS_OK;  // (the node arrays of a batch without sequences are not looked at)
   Plan p;
-  if ((rc = build_plan(c, b, p, true, chunk_choice(c, b)))) return rc;
+  if ((rc = build_plan(c, b, p, true, chunk_choice(c, b), 0))) return rc;
   for (int r = 0; r < b->n_rows; ++r) {
     page_out[r] = c->blob[p.off_row_page + r];
     slot_out[r] = c->blob[p.off_row_slot + r];
@@ -1213,7 +1354,7 @@ int bs_attention_division(bs_ctx *c, const bs_batch *b, int64_t n_pages, int32_t
   Plan p;
   if (noalloc) {
     if ((rc = check_noalloc_counts(c, b, n_pages)) || (rc = plan_noalloc(c, b, p))) return rc;
-  } else if ((rc = build_plan(c, b, p, false, attention_chunks(c, b)))) {
+  } else if ((rc = plan_attention(c, b, p))) {
     return rc;
   }
   bs_division d{};
@@ -1367,11 +1508,12 @@ int run_layers_pipelined(bs_ctx *c, const Plan &p, int n_layers, const bs_weight
       if (p.n_wide > 0 || cp.n_first > 0)
         SPAN(c, BS_K_ATTN_DECODE, st, HIP_TRY(c, launch_decode_attn(dargs, p.n_wide, cp.n_first, st)));
     }
+    if ((rc = run_merge(c, p, false, true, c->attn, st))) return rc;  // the prefill rows go on at once
     // (in a later layer launch 0 was the previous layer's down projection)
     const int s0 = l == 0 ? 0 : 1;
     if ((rc = carry(cp, s0, 0, o_proj_args(c, &w[l], in, 0, Tp), dargs, false))) return rc;
     if ((rc = carry(cp, s0 + 1, 1, gate_up_args(c, &w[l], 0, Tp), dargs, true))) return rc;
-    if ((rc = run_decode_merge(c, p, c->attn, st))) return rc;
+    if ((rc = run_merge(c, p, true, false, c->attn, st))) return rc;
     if ((rc = run_o_gate_up(c, &w[l], in, Tp, T, st, BS_K_GEMM_DECODE_ROWS, BS_K_GEMM_DECODE_ROWS))) return rc;
     if (l == n_layers - 1) return run_down(c, &w[l], out, 0, T, st);
     // the decode rows leave this layer and enter the next ...
@@ -1408,7 +1550,7 @@ int bs_blend_step(bs_ctx *c, const bs_weights *w, const bs_batch *b, const void 
   gemm_force_variant(c->forced_tiles);
   hipStream_t st = (hipStream_t)stream_;
   Plan p;
-  if ((rc = build_plan(c, b, p, true, chunk_choice(c, b)))) return rc;
+  if ((rc = build_plan(c, b, p, true, chunk_choice(c, b), step_slots(c, st)))) return rc;
   if ((rc = ensure_rows(c, p.n_rows))) return rc;
   if ((rc = ensure_slots(c, p.n_slots))) return rc;
   Upload up;
@@ -1433,7 +1575,7 @@ int bs_blend_layers(bs_ctx *c, int32_t n_layers, const bs_weights *w, const bs_b
   gemm_force_variant(c->forced_tiles);
   hipStream_t st = (hipStream_t)stream_;
   Plan p;
-  if ((rc = build_plan(c, b, p, true, chunk_choice(c, b)))) return rc;
+  if ((rc = build_plan(c, b, p, true, chunk_choice(c, b), step_slots(c, st)))) return rc;
   if ((rc = ensure_rows(c, p.n_rows))) return rc;
   if ((rc = ensure_slots(c, p.n_slots))) return rc;
   Upload up;
@@ -1471,7 +1613,7 @@ int bs_attention(bs_ctx *c, const bs_batch *b, const void *q, void *out, const v
   HIP_TRY(c, hipSetDevice(c->device));
   hipStream_t st = (hipStream_t)stream_;
   Plan p;
-  if ((rc = build_plan(c, b, p, false, attention_chunks(c, b)))) return rc;
+  if ((rc = plan_attention(c, b, p))) return rc;
   if ((rc = ensure_slots(c, p.n_slots))) return rc;
   Upload up;
   if ((rc = stage_plan(c, p, st, up))) return rc;

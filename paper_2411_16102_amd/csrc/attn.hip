@@ -97,15 +97,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 // 16 bytes per lane, and the partial states are added eight at a time with all their loads
 // issued together: the kernel is a chain of a few memory round trips, not bandwidth.
 template <int DH>
-__global__ __launch_bounds__(256) void decode_merge_kernel(const MergeArgs a) {
+__device__ __forceinline__ void merge_decode_unit(const MergeArgs &a, int unit, int lane) {
   constexpr int LPH = DH / 4;    // lanes per head
   constexpr int HPW = 64 / LPH;  // heads per wavefront
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
   const int hq = a.s.n_q_heads;
   const int units_per_seq = (hq + HPW - 1) / HPW;
-  const int unit = blockIdx.x * 4 + wave;
-  if (unit >= a.n_decode * units_per_seq) return;
   const int seq = a.n_prefill + unit / units_per_seq;
   const int sub = lane / LPH, li = lane % LPH;
   const int head_raw = (unit % units_per_seq) * HPW + sub;
@@ -150,6 +146,64 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(const MergeArgs a) {
   o2.x = pack_bf16x2(acc[0] * inv, acc[1] * inv);
   o2.y = pack_bf16x2(acc[2] * inv, acc[3] * inv);
   *reinterpret_cast<u32x2_t *>(a.out + (size_t)a.row_start[seq] * (hq * DH) + head * DH + li * 4) = o2;
+}
+
+// The same for prefill work whose context is cut: a wavefront merges, of 32 query rows and one head, the 8 output columns
+// that lie in one accumulator register group of the ring kernel's wavefront, in that kernel's layout.
+template <int DH>
+__device__ __forceinline__ void merge_prefill_unit(const MergeArgs &a, int unit, int lane) {
+  constexpr int GROUPS = DH / 8;  // register groups of a block of 32 rows
+  const int wg_per_work = a.s.n_q_heads / a.cut_heads;
+  const int group = unit % GROUPS, qb = unit / GROUPS % 2, region = unit / (2 * GROUPS);
+  const int wave = region % 4, wg = region / 4 % wg_per_work;
+  const int32_t *cut = a.cut + 4 * (region / (4 * wg_per_work));
+  const int r0 = a.row_start[cut[0]], q_len = a.row_start[cut[0] + 1] - r0;
+  const int row0 = cut[1] * a.cut_rows + 64 * (wave / a.cut_heads) + 32 * qb;  // of the segment
+  const int head = wg * a.cut_heads + wave % a.cut_heads, lr = lane & 31;
+  if (row0 >= q_len) return;
+  const int n = cut[3];
+  float mx = NEG_BIG, ls = 0.f;
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  constexpr int B = 8;
+  for (int p = 0; p < n; p += B) {
+    float m[B], l[B];
+    f32x4_t v[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const size_t at = ((size_t)(cut[2] + min(p + u, n - 1)) * wg_per_work + wg) * 4 + wave;
+      m[u] = a.cut_m[at * 64 + 32 * qb + lr];
+      l[u] = a.cut_l[at * 64 + 32 * qb + lr];
+      v[u] = *reinterpret_cast<const f32x4_t *>(a.cut_acc + at * (64 * DH) + qb * (32 * DH) + group * 256 + lane * 4);
+    }
+    float m_new = mx;
+#pragma unroll
+    for (int u = 0; u < B; ++u) m_new = fmaxf(m_new, m[u]);
+    const float alpha = fast_exp2(mx - m_new);
+    mx = m_new;
+    ls *= alpha;
+    acc *= alpha;
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const float w = p + u < n ? fast_exp2(m[u] - mx) : 0.f;
+      ls += w * l[u];
+      acc += w * v[u];
+    }
+  }
+  if (row0 + lr >= q_len) return;
+  const float inv = 1.f / ls;
+  u32x2_t o2;
+  o2.x = pack_bf16x2(acc[0] * inv, acc[1] * inv);
+  o2.y = pack_bf16x2(acc[2] * inv, acc[3] * inv);
+  *reinterpret_cast<u32x2_t *>(a.out + (size_t)(r0 + row0 + lr) * (a.s.n_q_heads * DH) + head * DH + group * 8 + 4 * (lane >> 5)) = o2;
+}
+
+template <int DH>
+__global__ __launch_bounds__(256) void merge_kernel(const MergeArgs a, int n_decode_units, int n_units) {
+  const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (unit < n_decode_units)
+    merge_decode_unit<DH>(a, unit, lane);
+  else if (unit < n_units)
+    merge_prefill_unit<DH>(a, unit - n_decode_units, lane);
 }
 
 // ------------------------------------------------------------------------------
@@ -223,6 +277,30 @@ __device__ __forceinline__ void store_prefill_rows(const PrefillArgs &a, const f
   }
 }
 
+// The partial softmax state of the same rows: the accumulators as the lanes hold them (1 KB per store; row by row a CU
+// would store one lane per clock), maxima and sums per row.  `at`: number of the wavefront's part of the state.
+template <int DH>
+__device__ __forceinline__ void store_prefill_state(const PrefillArgs &a, const f32x16_t (&o)[2][DH / 32], const float (&m)[2],
+                                                    const float (&l)[2], const int (&n_q)[2], size_t at, int lane) {
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    float ls = l[qb];
+    ls += __shfl_xor(ls, 32, 64);
+    if (n_q[qb] <= 0) continue;  // wave-uniform
+    float *acc = a.part_acc + at * (64 * DH) + qb * (32 * DH) + lane * 4;
+#pragma unroll
+    for (int db = 0; db < DH / 32; ++db)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<f32x4_t *>(acc + (db * 4 + q) * 256) =
+            f32x4_t{o[qb][db][4 * q], o[qb][db][4 * q + 1], o[qb][db][4 * q + 2], o[qb][db][4 * q + 3]};
+    if (lane < 32) {
+      a.part_m[at * 64 + qb * 32 + lane] = m[qb];
+      a.part_l[at * 64 + qb * 32 + lane] = ls;
+    }
+  }
+}
+
 template <int DH>
 __device__ __forceinline__ void prefill_workgroup(const PrefillArgs &a, int heads_per_wg, int b, int wave, int lane, unsigned char *smem) {
   constexpr int KC = DH / 16;  // k-steps of the 32x32x16 score MFMA
@@ -235,23 +313,28 @@ __device__ __forceinline__ void prefill_workgroup(const PrefillArgs &a, int head
   const int hkv = a.s.n_kv_heads, hq = a.s.n_q_heads, grp = hq / hkv;
   const int wg_per_work = hq / heads_per_wg;
   const int w = b / wg_per_work;
-  const int seq = a.work[2 * w], qblk = a.work[2 * w + 1];  // block of 64 * (4 / heads_per_wg) query rows
+  const int32_t *work = a.work + (a.cut ? 4 : 2) * w;
+  const int seq = work[0], qblk = work[1];  // block of 64 * (4 / heads_per_wg) query rows
+  // blocks of 32 tokens [t0, t1) of the context (t1 = 0: to its end)
+  const int t0 = a.cut ? work[2] & 0xFFFF : 0, t1 = a.cut ? (int)((unsigned)work[2] >> 16) : 0, state = a.cut ? work[3] : -1;
   const int head = (b % wg_per_work) * heads_per_wg + wave % heads_per_wg;
   const int kvh = head / grp;
   const int r0 = a.row_start[seq], q_len = a.row_start[seq + 1] - r0;
-  const int kv_len = a.kv_len[seq];
+  // tokens are counted from the range's first one: the range ends at kv_len, row 0 of the segment stands at `before`
+  const int whole_len = a.kv_len[seq], before = whole_len - q_len - 32 * t0;
+  const int kv_len = (t1 ? 32 * t1 : whole_len) - 32 * t0;
   const int lr = lane & 31, g2 = lane >> 5;
   // (through the constant address space: nobody writes the page table, and its loads stay on the scalar
   // unit, where a wait for one does not wait for the tiles in flight)
-  const auto *pages = (const __attribute__((address_space(4))) int32_t *)(a.page_ids + a.page_start[seq]);
+  const auto *pages = (const __attribute__((address_space(4))) int32_t *)(a.page_ids + a.page_start[seq]) + 2 * t0;
   const int n_pg = (kv_len + 15) >> 4;
   const int wg_row0 = qblk * 64 * (4 / heads_per_wg);
   const int row_w = wg_row0 + 64 * (wave / heads_per_wg);  // first row of this wavefront
 
   // blocks of 32 tokens that the workgroup walks, and those that this wavefront needs
   const int wg_rows = min(64 * (4 / heads_per_wg), q_len - wg_row0);
-  const int n_wg = (kv_len - q_len + wg_row0 + wg_rows - 1) / 32 + 1;
-  const int n_tb = row_w < q_len ? (kv_len - q_len + min(row_w + 64, q_len) - 1) / 32 + 1 : 0;
+  const int n_wg = t1 ? t1 - t0 : (before + wg_row0 + wg_rows - 1) / 32 + 1;
+  const int n_tb = row_w >= q_len ? 0 : t1 ? t1 - t0 : (before + min(row_w + 64, q_len) - 1) / 32 + 1;
 
   // ---- global -> LDS: wavefront w requests tile w of a block (page w / 2; keys or values) ----
   uint32_t src[LD];  // byte offset within the tile of the chunk that this lane's LDS place holds
@@ -284,7 +367,7 @@ __device__ __forceinline__ void prefill_workgroup(const PrefillArgs &a, int head
   for (int qb = 0; qb < NQ; ++qb) {
     const int row0 = row_w + qb * 32;
     n_q[qb] = min(32, q_len - row0);                       // <= 0: the block does not exist
-    first_pos[qb] = kv_len - q_len + row0;
+    first_pos[qb] = before + row0;
     my_pos[qb] = min(first_pos[qb] + lr, kv_len - 1);
     const bool ok = lr < n_q[qb];
     const uint16_t *p = a.q + (size_t)(r0 + (ok ? row0 + lr : 0)) * (hq * DH) + head * DH + 8 * g2;
@@ -489,7 +572,10 @@ __device__ __forceinline__ void prefill_workgroup(const PrefillArgs &a, int head
   }
   block(n_wg - 1, s_a, s_b, n_wg % 2 == 1, std::true_type{});
   __builtin_amdgcn_s_waitcnt(0x0F70);  // the look-ahead loads have landed before the LDS is released
-  store_prefill_rows<DH>(a, o, l, n_q, r0 + row_w, head, lr, g2);
+  if (state >= 0)
+    store_prefill_state<DH>(a, o, m, l, n_q, ((size_t)state * wg_per_work + b % wg_per_work) * 4 + wave, lane);
+  else
+    store_prefill_rows<DH>(a, o, l, n_q, r0 + row_w, head, lr, g2);
 }
 
 // 64-wide heads: 236 registers and a ring of 64 KB, so two workgroups share a CU (one against two, 32 heads in 8
@@ -810,15 +896,17 @@ hipError_t launch_decode_attn(const DecodeArgs &a, int n_wide, int n_narrow, hip
   return hipGetLastError();
 }
 
-hipError_t launch_decode_merge(const MergeArgs &a, hipStream_t stream) {
-  if (a.n_decode <= 0) return hipSuccess;
-  if (a.s.head_dim != 128 && a.s.head_dim != 64) return hipErrorInvalidValue;
-  const int hpw = 256 / a.s.head_dim;  // heads per wavefront
-  const int units = a.n_decode * ((a.s.n_q_heads + hpw - 1) / hpw);
-  if (a.s.head_dim == 128)
-    hipLaunchKernelGGL((decode_merge_kernel<128>), dim3((units + 3) / 4), dim3(256), 0, stream, a);
+hipError_t launch_merge(const MergeArgs &a, hipStream_t stream) {
+  const int dh = a.s.head_dim, hpw = 256 / dh;  // heads per wavefront
+  const int n_decode_units = a.n_decode * ((a.s.n_q_heads + hpw - 1) / hpw);
+  const int n_units = n_decode_units + (a.n_cut > 0 ? a.n_cut * (a.s.n_q_heads / a.cut_heads) * 4 * 2 * (dh / 8) : 0);
+  if (n_units <= 0) return hipSuccess;
+  if (dh == 128)
+    hipLaunchKernelGGL((merge_kernel<128>), dim3((n_units + 3) / 4), dim3(256), 0, stream, a, n_decode_units, n_units);
+  else if (dh == 64)
+    hipLaunchKernelGGL((merge_kernel<64>), dim3((n_units + 3) / 4), dim3(256), 0, stream, a, n_decode_units, n_units);
   else
-    hipLaunchKernelGGL((decode_merge_kernel<64>), dim3((units + 3) / 4), dim3(256), 0, stream, a);
+    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
@@ -882,6 +970,7 @@ PrefillRoute prefill_route(const AttnShape &s, int n_prefill, const int32_t *row
 
 hipError_t launch_prefill_attn(const PrefillArgs &a, const PrefillRoute &route, hipStream_t stream) {
   if (a.n_work <= 0) return hipSuccess;
+  if (a.cut && route.direct) return hipErrorInvalidValue;
   const int hpw = route.heads, grid = a.n_work * (a.s.n_q_heads / hpw);
   if (route.direct) {
     if (hpw > 2) return hipErrorInvalidValue;

@@ -68,13 +68,25 @@ struct MergeArgs {
   const int32_t *row_start, *part_start;
   const float *part_acc, *part_m, *part_l;
   uint16_t *out;  // [T, Hq*dh]
+  // prefill work whose context is cut (see PrefillArgs): [n_cut][4] = (sequence, block of query rows, first state, states)
+  const int32_t *cut;
+  int n_cut, cut_heads, cut_rows;  // query heads and rows of a prefill workgroup
+  const float *cut_acc, *cut_m, *cut_l;
 };
-hipError_t launch_decode_merge(const MergeArgs &a, hipStream_t stream);
+// n_decode = 0: the prefill work only; n_cut = 0: the decode sequences only
+hipError_t launch_merge(const MergeArgs &a, hipStream_t stream);
 
 struct PrefillArgs {
   AttnShape s;
   const int32_t *work;  // [n_work][2] = (sequence, block of PrefillRoute::rows query rows)
   int n_work;
+  // Cut contexts (ring kernel): work is [n_work][4], with t0 | t1 << 16 and a state number behind the two: a workgroup
+  // walks the blocks of 32 tokens [t0, t1) of the context (t1 = 0: to its end) and leaves its partial softmax state in the
+  // arrays below, unless the number is negative: then it has all of the context.  A range begins at a token that every
+  // query row of the block may see, so no row of a state is empty.
+  bool cut;
+  float *part_acc;          // [states][Hq / heads][4 wavefronts][64 rows x dh, in the order of the accumulators]
+  float *part_m, *part_l;   // [states][Hq / heads][4 wavefronts][64 rows]
   const int32_t *row_start, *kv_len, *page_start, *page_ids;
   const uint16_t *q;
   const uint16_t *kv_pool;

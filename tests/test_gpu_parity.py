@@ -822,3 +822,39 @@ def test_products_on_192_and_128_row_tiles(lib, dims, rows, product, want):
     seqs = [(rows - 33, rows + 20, -1)] + [(1, 20 + 9 * i, -1) for i in range(33)]
     batch = W.assemble_batch(16, seqs, 1, [], np.random.default_rng(rows))
     check_step(lib, shape, batch, W.make_tensors(shape, batch, rows, gains="random"))
+
+
+@pytest.mark.parametrize("heads,dh,segments,n_decode", [
+    # contexts cut into ranges: one row, a row block that ends at, before and behind a block of 32 tokens, ranges that may not
+    # begin behind a block's first row; 64, 128 and 256 rows to a workgroup; whole and cut blocks in one launch
+    ((4, 1), 128, [(1, 520)], 0), ((8, 2), 128, [(64, 1088), (65, 1088), (33, 545), (5, 9)], 0), ((4, 1), 64, [(130, 641), (31, 2047)], 0),
+    ((6, 3), 128, [(129, 1500)], 0), ((3, 1), 64, [(257, 1600), (40, 1040)], 0), ((8, 2), 128, [(200, 2000), (40, 40)], 3),
+    ((4, 1), 64, [(96, 1024)], 2), ((3, 3), 128, [(70, 1100)], 3)])
+def test_prefill_contexts_cut_into_ranges(lib, heads, dh, segments, n_decode):
+    import torch
+    shape = W.LayerShape(256, heads[0], heads[1], dh, 256)
+    rng = np.random.default_rng(len(segments) * 10 + n_decode)
+    seqs = [(q, kv, -1) for q, kv in segments] + [(1, 20 + i, -1) for i in range(n_decode)]
+    batch = W.assemble_batch(16, seqs, len(segments), [], rng)
+    tens = W.make_tensors(shape, batch, 13)
+    q = W.round_to_bf16(rng.standard_normal((batch.n_rows, shape.n_q_heads * dh), dtype=np.float32))
+    layer = lib.Layer(shape, device=0)
+    division = layer.attention_division(batch)
+    cut = division.states - n_decode   # (a decode sequence of one chunk has one state)
+    assert cut > 0 and cut % division.prefill_rows == 0
+    pool = layer.pack_pool(tens.k_pool, tens.v_pool)
+    tq = torch.from_numpy(q).cuda().to(torch.bfloat16)
+    out = layer.attention(batch, tq, pool, batch.n_pages)
+    check_attention(shape, batch, q, tens, to_np(out))
+    assert torch.equal(layer.attention_noalloc(batch, tq, pool, batch.n_pages, torch.zeros_like(out)), out)
+
+
+def test_step_with_cut_prefill_contexts(lib):
+    # the schedules of a step take the same ranges: serial and co-scheduled, one layer and pipelined ones
+    shape = W.LayerShape(512, 8, 2, 128, 1032)
+    batch = W.assemble_batch(16, [(290, 1400, -1), (35, 900, -1)] + [(1, 30 + 7 * i, -1) for i in range(40)], 2, [],
+                             np.random.default_rng(3))
+    assert lib.Layer(shape, device=-1).attention_division(batch).states >= 64
+    tens = W.make_tensors(shape, batch, 3, gains="random")
+    for flags in (0, 1):
+        check_step(lib, shape, batch, tens, flags)

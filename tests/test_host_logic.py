@@ -365,3 +365,17 @@ int main() {}
     csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2411_16102_amd", "csrc")
     r = subprocess.run(["g++", "-std=c++17", "-fsyntax-only", "-I", csrc, str(src)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert r.returncode == 0, r.stdout
+
+
+@pytest.mark.parametrize("segments", [1, 2, 3, 6, 12])
+def test_cut_prefill_contexts_keep_to_the_scratch_array(segments):
+    # both entry points cut alike, and never into more states than the array of bs_attention_noalloc holds beside its
+    # descriptor; host only
+    lay = binding.Layer(W.LLAMA3_8B, device=-1)
+    for rows, cached in ((64, 8000), (700, 3000)):
+        b = W.assemble_batch(16, [(rows, rows + cached, -1)] * segments + [(1, 300, -1)] * 5, segments, [], None)
+        d = lay.attention_division(b)
+        assert _fields(d) == _fields(lay.attention_division(b, noalloc=True))
+        assert d.states * 32 * (128 + 2) * 4 <= (63 << 20) and d.descriptor_words <= NOALLOC_WORDS
+        if segments == 1:
+            assert d.states > 5 * 3
