@@ -36,11 +36,14 @@ using namespace attn_dev;
 // Measured (this launch, 8B heads) against workgroups of four wavefronts and chunks of 64 pages: one sequence
 // of 4000 tokens 48 -> 7 us, 7 of 2000 63 -> 14, 64 of 2000 86 -> 85, 256 of 1024 180 -> 179.
 // Grid order: wide workgroups first, narrow ones
-// after, longest first within a kind.  Where the wide workgroups are at least a third of the
-// grid, one of them alternates with two narrow ones for as long as both kinds last (what is
-// left of the wide kind goes first): a wavefront with 64 query rows spends part of its time
-// on arithmetic, and the narrow wavefronts beside it use the bandwidth it leaves (measured:
-// -9 % with 1280 wide and 2048 narrow workgroups, +2 % with 390 and 1812, hence the rule).
+// after, longest first within a kind; but one wide workgroup alternates with two narrow ones for as long as both kinds last
+// (what is left of the wide kind goes first), in a launch of decode units alone where it is two rounds of 1024 wavefronts or
+// a third of it is wide, and beside prefill workgroups where a quarter is: a wavefront with 64 query rows is bound by its own issue, the narrow ones
+// beside it use the bandwidth it leaves, and wide units of their own at the head of the launch leave memory idle.
+// Measured, alone: 640 sequences in a two-level tree (1792 wide, 5264 narrow units, 70B heads) 375 -> 326 us, 900 behind 30
+// prefixes of 256 163 -> 147, 1000 behind 8 of 2048 952 -> 926, about one round (77 behind three) 171.9 -> 172.9; beside prefill
+// rows: 3072 and 8192 units (70B layer, step) 7087 -> 7022, 1504 and 7248 (8B) 1368 -> 1375, hence the line.  One in five is
+// within 3 % either way; periods of two and four, turned over the XCDs, cost up to a fifth.
 // The period is odd on purpose: workgroups go to the eight XCDs in turn, and a period of
 // four would send every wide workgroup to the same two of them.
 template <int DH, int WPW, bool NT_NARROW>
@@ -49,7 +52,8 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, int n_wide
   constexpr int WQB = 4;  // blocks of 16 query rows of a wide item
   const int hkv = a.s.n_kv_heads;
   const int nw = (n_wide_units + WPW - 1) / WPW, nn = (n_narrow_units + WPW - 1) / WPW;  // workgroups of each kind
-  const int mixed = 2 * nw >= nn ? min(nw, nn >> 1) : 0;                   // periods of one wide + two narrow
+  const bool mix = WPW == 1 ? nw + nn >= 2048 || 2 * nw >= nn : 3 * nw >= nn;
+  const int mixed = mix ? min(nw, nn >> 1) : 0;                            // periods of one wide + two narrow
   const int lead = nw - mixed;                                             // wide workgroups ahead of the mixed part
   bool wide;
   int wg;  // index of this workgroup within its kind

@@ -858,3 +858,22 @@ def test_step_with_cut_prefill_contexts(lib):
     tens = W.make_tensors(shape, batch, 3, gains="random")
     for flags in (0, 1):
         check_step(lib, shape, batch, tens, flags)
+
+
+def test_few_wide_items_among_many_narrow_ones(lib):
+    # two rounds of workgroups: one wide in turn with two narrow ones, and most narrow ones behind them; alone, and with prefill rows,
+    # where so few wide ones go first
+    import torch
+    shape = W.LayerShape(512, 8, 2, 128, 256)
+    for n_prefill in (0, 1):
+        rng = np.random.default_rng(7)
+        seqs = [(7, 40, -1)] * n_prefill + [(1, 16 * 5 + 3 + i % 9, 0) for i in range(20)] + [(1, 30 + i, -1) for i in range(1100)]
+        batch = W.assemble_batch(16, seqs, n_prefill, [(-1, 5)], rng)
+        tens = W.make_tensors(shape, batch, 11)
+        q = W.round_to_bf16(rng.standard_normal((batch.n_rows, shape.n_q_heads * shape.head_dim), dtype=np.float32))
+        layer = lib.Layer(shape, device=0)
+        division = layer.attention_division(batch)
+        assert 0 < 4 * division.wide_items < division.items
+        pool = layer.pack_pool(tens.k_pool, tens.v_pool)
+        out = to_np(layer.attention(batch, torch.from_numpy(q).cuda().to(torch.bfloat16), pool, batch.n_pages))
+        check_attention(shape, batch, q, tens, out)
