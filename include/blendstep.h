@@ -305,7 +305,7 @@ typedef struct bs_division {
 int bs_attention_division(bs_ctx *ctx, const bs_batch *batch, int64_t n_pages, int32_t noalloc, bs_division *out);
 
 /* Host-only: tile shape and number of ranges along K of a layer's QKV (product 0), output (1) or down (2)
- * projection, or of gate/up (3: never cut; where its last columns go out apart on 128x128 tiles, the shape of the
+ * projection, or of gate/up (3: never cut; where its last columns go out apart on tiles of another shape, the shape of the
  * others), over `rows` rows.  Shapes as in bs_set_gemm_tiles, and 4 = 128x256, 5 = 256x128 on the deep weight
  * ring (at most 128 / 256 rows), 7 = the few-row kernel, which cuts K among the wavefronts of a workgroup,
  * 10 = 192x256, 11 = 128x256, gate/up only: 8 = 64x128, 9 = 128x128 on the deep ring. */

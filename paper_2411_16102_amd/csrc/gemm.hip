@@ -1350,6 +1350,51 @@ long round_split_columns(long tm, long tn, int n_cu) {
   return full < 1 || tiles % n_cu == 0 || idle * 4 <= n_cu || cols < 1 || cols >= tn ? 0 : cols;
 }
 
+// Gate/up of more than 512 rows: the shape with the smallest estimate, and that estimate.  Of 182 products of seven layers timed
+// with cold weights it is 0.6 % off the best on average.  1580 rows of the 8B layer: 192x256 tiles 330 us, 160x256 tiles, faster
+// since they have three activation panels, 316.  (Below K = 1024, where nothing was fitted, the relation of rounds in choose_variant.)
+double gate_up_us(int m, int n_b_rows, int k, int n_cu, int *v) {
+  double best_t = 1e300;
+  for (const Shape &c : SHAPES) {
+    double t = whole_us(c, m, n_b_rows, k, n_cu, EPI_SWIGLU);
+    if (c.v == V_BIG) {  // whole rounds on these and the rest of the columns on 128x128 tiles: gemm_round_split
+      const long tm = (m + 255) / 256, tn = (n_b_rows + 255) / 256, cols = round_split_columns(tm, tn, n_cu);
+      if (cols) t = std::min(t, whole_us(c, m, (int)cols * 256, k, n_cu, EPI_SWIGLU) + whole_us(SHAPES[2], m, n_b_rows - (int)cols * 256, k, n_cu, EPI_SWIGLU));
+    }
+    if (t < best_t) { best_t = t; *v = c.v; }
+  }
+  return best_t;
+}
+
+// Two shapes for one product: whole rounds of one of the 256-wide shapes over the first `cols` tile columns, another shape, whose
+// rounds the rest happens to fill, over the others.  Taken where the estimate of the two launches is 3 % below the best single
+// choice, about its own error.  Measured, gate/up of the 8B layer: 800 rows 180 us on 256x256 tiles, 160 as one round of them and
+// 160x256 tiles for the rest; 1580 rows 305 (192x256) -> 300; where less is expected (640, 2048 rows) 2 % either way.
+bool gate_up_pair(int m, int n_b_rows, int k, int n_cu, int *head, int *tail, int *cols) {
+  int single;
+  double best_t = 0.97 * gate_up_us(m, n_b_rows, k, n_cu, &single);
+  bool found = false;
+  for (const Shape &c : SHAPES) {
+    if (c.bn != 256) continue;
+    const long tm = (m + c.bm - 1) / c.bm, tn = (n_b_rows + 255) / 256, full = tm * tn / n_cu;
+    for (long f = std::max(1L, full - 2); f <= full; ++f) {
+      const long n = f * n_cu / tm;
+      if (n < 1 || n >= tn) continue;
+      const double t = whole_us(c, m, (int)n * 256, k, n_cu, EPI_SWIGLU);
+      for (const Shape &c2 : SHAPES) {
+        const double t2 = t + whole_us(c2, m, n_b_rows - (int)n * 256, k, n_cu, EPI_SWIGLU);
+        if (t2 >= best_t) continue;
+        best_t = t2;
+        *head = c.v;
+        *tail = c2.v;
+        *cols = (int)n;
+        found = true;
+      }
+    }
+  }
+  return found;
+}
+
 // Tile shape of a gate/up or plain product, or of any with a forced shape (QKV, output and down projection:
 // gemm_plan).
 // Estimated time of a launch in units of one full round of 256x256 tiles: full rounds of
@@ -1377,21 +1422,10 @@ int choose_variant(int m, int n_b_rows, int k, int epilogue, int dh, int n_cu, i
     // worth it once the single row of tiles fills at least half the chip
     if (2 * n_tiles(m, n_b_rows, sv == V_S128 ? 128 : 256, sv == V_S128 ? 256 : 128) >= n_cu) return sv;
   }
-  // Gate/up of more than 512 rows: the estimate in microseconds.  Of 182 products of seven layers timed with cold weights it is
-  // 0.6 % off the best on average.  1580 rows of the 8B layer: 192x256 tiles 330 us, 160x256 tiles, faster since they have
-  // three activation panels, 316.  (Below K = 1024, where nothing was fitted, the relation of rounds below.)
   const bool estimated = epilogue == EPI_SWIGLU && g_forced_variant == V_AUTO && k >= FIT_MIN_K;
   if (estimated && m > 512) {
-    int best = V_BIG;
-    double best_t = 1e300;
-    for (const Shape &c : SHAPES) {
-      double t = whole_us(c, m, n_b_rows, k, n_cu, EPI_SWIGLU);
-      if (c.v == V_BIG) {  // whole rounds on these and the rest of the columns on 128x128 tiles: gemm_round_split
-        const long tm = (m + 255) / 256, tn = (n_b_rows + 255) / 256, cols = round_split_columns(tm, tn, n_cu);
-        if (cols) t = std::min(t, whole_us(c, m, (int)cols * 256, k, n_cu, EPI_SWIGLU) + whole_us(SHAPES[2], m, n_b_rows - (int)cols * 256, k, n_cu, EPI_SWIGLU));
-      }
-      if (t < best_t) { best_t = t; best = c.v; }
-    }
+    int best;
+    gate_up_us(m, n_b_rows, k, n_cu, &best);
     return best;
   }
   struct Cand { int v, bm, bn, per_cu; double T, a; };
@@ -1473,18 +1507,22 @@ bool gemm_round_split(const GemmArgs &a, int epilogue, int dh, GemmArgs *head, G
   if (epilogue != EPI_SWIGLU || g_forced_variant != V_AUTO || a.k_splits > 1) return false;
   const int n_cols = a.n_count ? a.n_count : a.N;
   if (gemm_streams_weights(a, epilogue)) return false;
-  if (choose_variant(a.M, 2 * n_cols, a.K, epilogue, dh, a.n_cu) != V_BIG) return false;
   const int n_cu = a.n_cu > 0 ? a.n_cu : N_CU;
-  const long tm = (a.M + 255) / 256, tn = (n_cols + 127) / 128;  // a 256x256 tile yields 128 output columns
-  const long cols_big = round_split_columns(tm, tn, n_cu);
-  if (!cols_big) return false;
+  int first, rest, cols;
+  if (a.M <= 512 || a.K < FIT_MIN_K || !gate_up_pair(a.M, 2 * n_cols, a.K, n_cu, &first, &rest, &cols)) {
+    if (choose_variant(a.M, 2 * n_cols, a.K, epilogue, dh, a.n_cu) != V_BIG) return false;
+    cols = (int)round_split_columns((a.M + 255) / 256, (n_cols + 127) / 128, n_cu);  // a 256x256 tile yields 128 output columns
+    if (!cols) return false;
+    first = V_BIG;
+    rest = V_SMALL;  // two workgroups per CU fill the chip best with what is left of a round
+  }
   *head = a;
   *tail = a;
-  head->n_count = (int)cols_big * 128;
+  head->n_count = cols * 128;
   tail->n_begin = a.n_begin + head->n_count;
   tail->n_count = n_cols - head->n_count;
-  head->tile_variant = V_BIG;
-  tail->tile_variant = V_SMALL;  // two workgroups per CU fill the chip best with what is left of a round
+  head->tile_variant = first;
+  tail->tile_variant = rest;
   return true;
 }
 

@@ -877,3 +877,13 @@ def test_few_wide_items_among_many_narrow_ones(lib):
         pool = layer.pack_pool(tens.k_pool, tens.v_pool)
         out = to_np(layer.attention(batch, torch.from_numpy(q).cuda().to(torch.bfloat16), pool, batch.n_pages))
         check_attention(shape, batch, q, tens, out)
+
+
+@pytest.mark.parametrize("rows,tiles", [(521, 2), (663, 2), (800, 2)])
+def test_gate_up_columns_on_two_tile_shapes(lib, rows, tiles):
+    # one round of 160x256 tiles, the other columns on 128x128, 192x256 and 256x256 ones, the last of them partial
+    shape = W.LayerShape(1024, 4, 2, 64, 14344)
+    assert lib.Layer(shape, device=-1).gemm_division("gate_up", rows) == (tiles, 1)
+    seqs = [(rows - 13, rows - 3, -1)] + [(1, 20 + 9 * i, -1) for i in range(13)]
+    batch = W.assemble_batch(16, seqs, 1, [], np.random.default_rng(rows))
+    check_step(lib, shape, batch, W.make_tensors(shape, batch, rows, gains="random"))
