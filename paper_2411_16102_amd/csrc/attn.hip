@@ -220,7 +220,8 @@ __global__ __launch_bounds__(256) void merge_kernel(const MergeArgs a, int n_dec
 // per block and wavefront, a block took 3300 clocks of a CU; its MFMAs need 1024.)  It takes 2200
 // now: issue 1200, of that 900 vector-ALU; 600 waiting for a pipe, 400 for LDS and barriers.
 // Measured, 8B heads: 28 x 64 rows behind 6000 tokens 307 -> 207 us, 8 x 1024 rows 137 -> 111, 32 rows
-// behind 8000 tokens 327 -> 216, 128 x 64 rows 70 -> 65, where starting workgroups is most of it.
+// behind 8000 tokens 327 -> 216 (35 with the context cut into ranges, see prefill_cut in api.hip), 128 x 64 rows 70 -> 65,
+// where starting workgroups is most of it.
 //
 // What then bounds a block is the issue of one wavefront per SIMD (the accumulators of 64 rows x dh
 // 128 leave no room for two): 32 MFMAs of 32 clocks against about 900 clocks of softmax arithmetic.

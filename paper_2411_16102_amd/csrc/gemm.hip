@@ -18,7 +18,7 @@
 // halves fetched separately (measured: 41 against 26 B/clk/CU into LDS).  LDS holds two
 // rings of panels, three weight panels and two activation panels of one k-tile each for a 256x256
 // tile: while tile kt is multiplied, tile kt+1 has landed or is landing and the weight panel of
-// tile kt+2 is in flight; 160x256 tiles have room for a third activation panel.
+// tile kt+2 is in flight; 160x256 and 128x256 tiles have room for a third activation panel.
 // (Of at most 256 rows, what the few-row kernel leaves, gate/up and plain products and the
 // k-ranges of the others, uses a second pipeline where it pays, DEEP in the kernel below: one row
 // of tiles, a few slots for the activation panel and all other LDS for the weight
@@ -1397,7 +1397,8 @@ bool gate_up_pair(int m, int n_b_rows, int k, int n_cu, int *head, int *tail, in
 
 // Tile shape of a gate/up or plain product, or of any with a forced shape (QKV, output and down projection:
 // gemm_plan).
-// Estimated time of a launch in units of one full round of 256x256 tiles: full rounds of
+// Gate/up of more than 512 rows goes by the estimate in microseconds (gate_up_us), the others by that of a launch in
+// units of one full round of 256x256 tiles: full rounds of
 // workgroups (the 128x128 tile runs two per CU) cost T each; a last, partly filled round costs
 // T (a + (1 - a) fill): workgroups that share the chip with fewer others run faster, but not in
 // proportion.  T and a were fitted on MI355X to the four GEMM shapes of the 8B layer at 384 to
