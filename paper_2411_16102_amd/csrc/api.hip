@@ -203,13 +203,6 @@ int ensure_slots(bs_ctx *c, long slots) {
   return BS_OK;
 }
 
-// Partial states that a step may use: any number, or, while the stream is being captured and nothing may be allocated,
-// what the context has.
-long step_slots(const bs_ctx *c, hipStream_t st) {
-  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(st, &status) == hipSuccess && status == hipStreamCaptureStatusNone ? LONG_MAX : c->cap_slots;
-}
-
 int ensure_blob(bs_ctx *c, long ints) {
   if (ints > c->cap_blob) {
     const long cap = ints + ints / 4 + 1024;
@@ -717,6 +710,18 @@ int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chu
     it->page1 = blob[p.off_pages + it->page_off + (it->n_tokens > ps ? 1 : 0)];
   }
   return BS_OK;
+}
+
+// The plan of a step.  While the stream is being captured nothing may be allocated: contexts are then cut only into what the
+// context's state buffer holds.
+int plan_step(bs_ctx *c, const bs_batch *b, Plan &p, hipStream_t st) {
+  const Chunks chunks = chunk_choice(c, b);
+  if (const int rc = build_plan(c, b, p, true, chunks, LONG_MAX)) return rc;
+  if (!p.n_pf_cut || p.n_slots <= c->cap_slots) return BS_OK;
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &status) == hipSuccess && status == hipStreamCaptureStatusNone) return BS_OK;
+  p = Plan{};
+  return build_plan(c, b, p, true, chunks, c->cap_slots);
 }
 
 // floats of the m (and l) array of `slots` partial states in the scratch array of bs_attention_noalloc
@@ -1550,7 +1555,7 @@ int bs_blend_step(bs_ctx *c, const bs_weights *w, const bs_batch *b, const void 
   gemm_force_variant(c->forced_tiles);
   hipStream_t st = (hipStream_t)stream_;
   Plan p;
-  if ((rc = build_plan(c, b, p, true, chunk_choice(c, b), step_slots(c, st)))) return rc;
+  if ((rc = plan_step(c, b, p, st))) return rc;
   if ((rc = ensure_rows(c, p.n_rows))) return rc;
   if ((rc = ensure_slots(c, p.n_slots))) return rc;
   Upload up;
@@ -1575,7 +1580,7 @@ int bs_blend_layers(bs_ctx *c, int32_t n_layers, const bs_weights *w, const bs_b
   gemm_force_variant(c->forced_tiles);
   hipStream_t st = (hipStream_t)stream_;
   Plan p;
-  if ((rc = build_plan(c, b, p, true, chunk_choice(c, b), step_slots(c, st)))) return rc;
+  if ((rc = plan_step(c, b, p, st))) return rc;
   if ((rc = ensure_rows(c, p.n_rows))) return rc;
   if ((rc = ensure_slots(c, p.n_slots))) return rc;
   Upload up;

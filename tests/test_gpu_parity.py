@@ -887,3 +887,31 @@ def test_gate_up_columns_on_two_tile_shapes(lib, rows, tiles):
     seqs = [(rows - 13, rows - 3, -1)] + [(1, 20 + 9 * i, -1) for i in range(13)]
     batch = W.assemble_batch(16, seqs, 1, [], np.random.default_rng(rows))
     check_step(lib, shape, batch, W.make_tensors(shape, batch, rows, gains="random"))
+
+
+def test_captured_step_cuts_into_what_the_context_holds(lib):
+    # a fresh context whose first step has no prefill context to cut: captured, a step that would cut one allocates nothing,
+    # leaves it whole and replays to the same result; eager, it is cut
+    import torch
+    shape = W.LayerShape(512, 8, 2, 128, 1032)
+    rng = np.random.default_rng(5)
+    warm = W.assemble_batch(16, [(40, 40, -1)], 1, [], rng)
+    batch = W.assemble_batch(16, [(40, 1400, -1)], 1, [], rng)
+    assert warm.n_pages <= batch.n_pages
+    tens = W.make_tensors(shape, batch, 5)
+    layer = lib.Layer(shape, device=0)
+    assert layer.attention_division(batch).states > 0 and layer.attention_division(warm).states == 0
+    dev = layer.upload(tens, batch)
+    layer.blend_step(dev, batch)
+    fresh = lib.Layer(shape, device=0)
+    fresh.blend_step(dev, warm)        # every buffer but that of the states has its size
+    eager = to_np(layer.blend_step(dev, batch))   # (the pool as that step left it)
+    y, graph = torch.empty_like(dev.x), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        fresh.blend_step(dev, batch, y=y)
+    for _ in range(3):
+        y.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.abs(to_np(y) - eager).max() <= 2e-2 * np.abs(eager).max()
