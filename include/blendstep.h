@@ -30,6 +30,12 @@
  *     the staging buffer: every replay reads it again.  The last four captured calls of a context can be
  *     replayed, and of calls with short descriptors as many as 5 MiB hold, until a call grows the
  *     workspace that they run in (bs_attention_noalloc has none that grows).
+ *   - Prefill contexts that a call cuts into ranges (see bs_set_chunk_pages) take states of their own.  They
+ *     are never the reason that a call fails or that one captured before loses its workspace: where the device
+ *     has no room the contexts stay whole, their buffer is kept until bs_destroy once a captured call has
+ *     used it, and a call that is being captured cuts only into what the calls before it have made room for.
+ *     Captured behind an eager call of the same batch it is divided like that one, else it may sum in
+ *     another order.
  */
 #ifndef BLENDSTEP_H
 #define BLENDSTEP_H
@@ -280,7 +286,7 @@ int bs_attention(bs_ctx *ctx, const bs_batch *batch, const void *q, void *out,
 
 /*   bs_attention_noalloc: bs_attention for callers that cannot allocate device memory during the call
  *   (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).  Same
- *   arguments, same kernels, same result; the descriptor and the partial softmax states of the call live
+ *   arguments, same kernels, same result (bit for bit outside capture); the descriptor and the partial softmax states of the call live
  *   in a 64 MiB array that is part of the library's code object (every GPU the library runs on holds its
  *   own copy until the process ends) instead of the context's growing workspace.  Limits, checked before
  *   anything is enqueued (BS_EINVAL with a message): the planned descriptor at most 1 MiB, the partial

@@ -13,13 +13,13 @@
 #include <new>
 #include <string>
 #include <utility>
-#include <climits>
 #include <vector>
 
 #include "../../include/blendstep.h"
 #include "attn.hpp"
 #include "gemm.hpp"
 #include "misc.hpp"
+#include "room.hpp"
 #include "staging.hpp"
 
 using namespace bs;
@@ -69,10 +69,10 @@ struct Plan {
   int n_seq = 0, n_prefill = 0, n_rows = 0, n_decode = 0, n_prefill_rows = 0;
   long off_row_start = 0, off_kv_len = 0, off_page_start = 0, off_row_pos = 0, off_row_page = 0, off_row_slot = 0,
        off_part_start = 0, off_pf_work = 0, off_items = 0, off_pages = 0, total_ints = 0;
-  long total_node_pages = 0, n_slots = 0;  // (partial states, in units of one row's: those of decode sequences, then those of cut prefill work)
+  long total_node_pages = 0, n_slots = 0;  // (partial states of decode sequences, a row each)
   int n_pf_work = 0;
   PrefillRoute pf_route{false, 4, 64};
-  long off_pf_cut = 0, n_decode_slots = 0;
+  long off_pf_cut = 0, n_cut_slots = 0, whole_ints = 0;  // n_cut_slots: rows of the partial states of cut prefill work; whole_ints: words without cuts
   int n_pf_cut = 0;  // blocks of query rows whose context is cut (0: the work list has two words an item, else four)
   int n_wide = 0, n_narrow = 0;  // decode items with up to 64 / up to 16 query rows (wide ones first)
 };
@@ -90,6 +90,12 @@ struct bs_ctx {
   float *x1 = nullptr, *rstd1 = nullptr, *rstd2 = nullptr, *ss2 = nullptr;
   long cap_slots = 0;
   float *part_acc = nullptr, *part_m = nullptr, *part_l = nullptr;
+  // The states of cut prefill work stand apart: they grow when no state of a decode sequence does, and graphs that were
+  // captured with those would lose them.  Buffers that a captured call has used are kept to the end.
+  long cap_cut_slots = 0;
+  float *cut_acc = nullptr, *cut_m = nullptr, *cut_l = nullptr;
+  bool cut_captured = false;
+  std::vector<float *> outgrown;
   uint16_t *hid[2] = {nullptr, nullptr};  // activations between the layers of bs_blend_layers
   // descriptor blob: pinned staging memory and one device copy
   long cap_blob = 0;
@@ -200,6 +206,29 @@ int ensure_slots(bs_ctx *c, long slots) {
   if ((rc = dev_alloc(c, &c->part_m, (size_t)cap * hq))) return rc;
   if ((rc = dev_alloc(c, &c->part_l, (size_t)cap * hq))) return rc;
   c->cap_slots = cap;
+  return BS_OK;
+}
+
+// Room for `slots` rows of states of cut prefill work; BS_ENOMEM leaves the context without any.
+int ensure_cut_slots(bs_ctx *c, long slots) {
+  if (slots <= c->cap_cut_slots) return BS_OK;
+  const long cap = slots + slots / 4 + 64;
+  const size_t hq = c->cfg.n_q_heads;
+  float **const arrays[3] = {&c->cut_acc, &c->cut_m, &c->cut_l};
+  if (c->cut_captured) {
+    c->outgrown.reserve(c->outgrown.size() + 3);
+    for (float **a : arrays) { c->outgrown.push_back(*a); *a = nullptr; }
+    c->cut_captured = false;
+  }
+  c->cap_cut_slots = 0;
+  int rc = BS_OK;
+  for (float **a : arrays)
+    if (!rc) rc = dev_alloc(c, a, (size_t)cap * hq * (a == &c->cut_acc ? c->cfg.head_dim : 1));
+  if (rc) {
+    for (float **a : arrays) (void)dev_alloc(c, a, 0);
+    return rc;
+  }
+  c->cap_cut_slots = cap;
   return BS_OK;
 }
 
@@ -498,7 +527,7 @@ void each_prefill_block(const bs_batch *b, int wg_rows, F &&f) {
 // What the launch has to hold beside the prefill work, and the room for the division
 struct CutLimits {
   double decode_us;  // its decode items, on the whole chip
-  long slots, words; // partial states (rows) and descriptor words that may be added
+  CutRoom room;      // states of cut work, words of the work list
 };
 
 // Longest range of a prefill workgroup's context in blocks of 32 tokens (0: contexts stay whole).  A block takes a
@@ -534,7 +563,7 @@ int prefill_cut(bs_ctx *c, const bs_batch *b, const PrefillRoute &route, const C
       items += n;
       if (n > 1) { states += n; ++cuts; }
     });
-    if (states * route.rows > lim.slots || 4 * (items + cuts) > lim.words) break;
+    if (states * route.rows > lim.room.slots || 4 * (items + cuts) > lim.room.words) break;
     const int per_cu = !wide && items * wgs > 256 ? 2 : 1;
     const double block = wide ? 1.0 : per_cu == 2 ? 0.95 : 0.65;
     // CUs that the decode items leave, on average, while the longest workgroup runs
@@ -560,7 +589,9 @@ int prefill_cut(bs_ctx *c, const bs_batch *b, const PrefillRoute &route, const C
   return best_us < 0.95 * whole_us ? best : 0;
 }
 
-int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chunks, long cut_slots, long max_words = LONG_MAX) {
+// `room`: for cut contexts (its words: of the whole descriptor); all_slots: for states of either kind together
+int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chunks, CutRoom room,
+               long all_slots = std::numeric_limits<long>::max()) {
   const int ch = chunks.other;
   const int ps = c->cfg.page_size;
   const int grp = c->cfg.n_q_heads / c->cfg.n_kv_heads;
@@ -660,11 +691,12 @@ int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chu
   for (const DecodeItem &it : c->items) decode_us += 2.9 + 0.97 / 16 * it.n_tokens;
   for (const DecodeItem &it : c->items_wide) decode_us += 6.3 + 0.97 / 16 * it.n_tokens;
   const long other_words = p.off_pf_work + 8L * (long)(c->items.size() + c->items_wide.size()) + p.total_node_pages + n_tab;
-  const CutLimits lim = {decode_us * c->cfg.n_kv_heads / 1024.0, cut_slots - p.n_slots, max_words - other_words};
+  const CutLimits lim = {decode_us * c->cfg.n_kv_heads / 1024.0, {std::min(room.slots, all_slots - p.n_slots), room.words - other_words}};
   const int cut = prefill_cut(c, b, p.pf_route, lim);
-  int n_states = 0;
+  int n_states = 0, n_blocks = 0;
   each_prefill_block(b, p.pf_route.rows, [&](int seq, int k, int blocks, int last_start) {
     const int n = cut ? prefill_ranges(blocks, cut, last_start) : 1;
+    ++n_blocks;
     for (int i = 0; i < n; ++i) {
       const int t0 = (int)((long)blocks * i / n), t1 = (int)((long)blocks * (i + 1) / n);
       order.push_back({t1 - t0, seq, k, t0, i + 1 < n ? t1 : 0, n > 1 ? n_states + i : -1});
@@ -676,8 +708,8 @@ int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chu
   std::stable_sort(order.begin(), order.end(), [](const auto &x, const auto &y) { return x.blocks > y.blocks; });
   p.n_pf_work = (int)order.size();
   p.n_pf_cut = (int)c->pf_cut.size() / 4;
-  p.n_decode_slots = p.n_slots;
-  p.n_slots += (long)n_states * p.pf_route.rows;
+  p.n_cut_slots = (long)n_states * p.pf_route.rows;
+  p.whole_ints = other_words + 2L * n_blocks;
   const int work_words = p.n_pf_cut ? 4 : 2;
   p.off_pf_cut = p.off_pf_work + (long)work_words * p.n_pf_work;
   p.off_items = p.off_pf_cut + 4L * p.n_pf_cut;
@@ -712,16 +744,44 @@ int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chu
   return BS_OK;
 }
 
-// The plan of a step.  While the stream is being captured nothing may be allocated: contexts are then cut only into what the
-// context's state buffer holds.
+// What plan_within asks of a context and a stream; Build plans the call's batch into p.
+template <class Build>
+struct PlanOps {
+  bs_ctx *c;
+  Plan &p;
+  hipStream_t st;
+  Build plan;
+  int build(CutRoom room) { p = Plan{}; return plan(p, room); }
+  long slots() const { return p.n_cut_slots; }
+  long words() const { return whole_units(p.total_ints); }
+  long whole_words() const { return whole_units(p.whole_ints); }
+  long held_slots() const { return c->cap_cut_slots; }
+  long held_words() const { return c->cap_blob / 4 * 4; }
+  long captured_words() const { return c->stage.captured_room(); }
+  bool capturing() const {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(st, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
+  }
+  bool grow(long n) {
+    const bool grown = ensure_cut_slots(c, n) == BS_OK;
+    if (!grown) (void)hipGetLastError();  // (the launches that follow ask for it)
+    return grown;
+  }
+};
+
+// The plan of a call on the context's own buffers, and room in them.
+template <class Build>
+int plan_and_reserve(bs_ctx *c, Plan &p, hipStream_t st, Build &&plan) {
+  PlanOps<Build &> ops{c, p, st, plan};
+  int rc = plan_within(ops);
+  if (rc || (rc = ensure_slots(c, p.n_slots))) return rc;
+  if (p.n_pf_cut && ops.capturing()) c->cut_captured = true;
+  return BS_OK;
+}
+
 int plan_step(bs_ctx *c, const bs_batch *b, Plan &p, hipStream_t st) {
   const Chunks chunks = chunk_choice(c, b);
-  if (const int rc = build_plan(c, b, p, true, chunks, LONG_MAX)) return rc;
-  if (!p.n_pf_cut || p.n_slots <= c->cap_slots) return BS_OK;
-  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &status) == hipSuccess && status == hipStreamCaptureStatusNone) return BS_OK;
-  p = Plan{};
-  return build_plan(c, b, p, true, chunks, c->cap_slots);
+  return plan_and_reserve(c, p, st, [&](Plan &q, CutRoom room) { return build_plan(c, b, q, true, chunks, room); });
 }
 
 // floats of the m (and l) array of `slots` partial states in the scratch array of bs_attention_noalloc
@@ -760,19 +820,16 @@ Chunks attention_chunks(bs_ctx *c, const bs_batch *b) {
   return between;
 }
 
-// Partial states that the scratch array of bs_attention_noalloc holds, for a batch that it accepts; bs_attention keeps to them
-// too, so that the two cut the same contexts.
-long attention_slots(bs_ctx *c, const bs_batch *b, long *max_words) {
-  *max_words = LONG_MAX;
-  if (!noalloc_accepts(c, plan_size(c, b, NOALLOC_CHUNKS))) return LONG_MAX;
-  *max_words = BS_NOALLOC_BLOB_BYTES / sizeof(int32_t);
-  const long per = (long)c->cfg.n_q_heads * (c->cfg.head_dim + 2) * (long)sizeof(float);
-  return ((long)(BS_NOALLOC_SCRATCH_BYTES - BS_NOALLOC_BLOB_BYTES) - 32) / per;  // (32: m and l padded to whole 16-byte units)
-}
-int plan_attention(bs_ctx *c, const bs_batch *b, Plan &p) {
-  long words;
-  const long slots = attention_slots(c, b, &words);
-  return build_plan(c, b, p, false, attention_chunks(c, b), slots, words);
+// Contexts are cut into no more states than the scratch array of bs_attention_noalloc holds beside those of decode sequences, for
+// a batch that it accepts; bs_attention keeps to that too, so that the two cut the same contexts.
+int plan_attention(bs_ctx *c, const bs_batch *b, Plan &p, CutRoom room = {}) {
+  long all_slots = std::numeric_limits<long>::max();
+  if (noalloc_accepts(c, plan_size(c, b, NOALLOC_CHUNKS))) {
+    const long per = (long)c->cfg.n_q_heads * (c->cfg.head_dim + 2) * (long)sizeof(float);
+    all_slots = ((long)(BS_NOALLOC_SCRATCH_BYTES - BS_NOALLOC_BLOB_BYTES) - 32) / per;  // (32: m and l padded to whole 16-byte units)
+    room.words = std::min<long>(room.words, BS_NOALLOC_BLOB_BYTES / sizeof(int32_t));
+  }
+  return build_plan(c, b, p, false, attention_chunks(c, b), room, all_slots);
 }
 
 // The plan of bs_attention_noalloc.  What fits is decided by the fixed division of the contexts, so that it
@@ -785,8 +842,8 @@ int plan_noalloc(bs_ctx *c, const bs_batch *b, Plan &p) {
     return fail(c, BS_EINVAL, "bs_attention_noalloc: %ld partial softmax states (%zu bytes) exceed the limit of %u bytes",
                 z.slots, noalloc_state_bytes(c, z.slots), BS_NOALLOC_STATE_BYTES);
   const int rc = plan_attention(c, b, p);
-  if (!rc && noalloc_state_bytes(c, p.n_slots) > BS_NOALLOC_SCRATCH_BYTES - BS_NOALLOC_BLOB_BYTES)
-    return fail(c, BS_EINVAL, "bs_attention_noalloc: %ld partial softmax states do not fit", p.n_slots);  // (attention_chunks keeps to what fits)
+  if (!rc && noalloc_state_bytes(c, p.n_slots + p.n_cut_slots) > BS_NOALLOC_SCRATCH_BYTES - BS_NOALLOC_BLOB_BYTES)
+    return fail(c, BS_EINVAL, "bs_attention_noalloc: %ld partial softmax states do not fit", p.n_slots + p.n_cut_slots);  // (attention_chunks keeps to what fits)
   return rc;
 }
 
@@ -850,9 +907,8 @@ PrefillArgs prefill_args(const bs_ctx *c, const Plan &p, const uint16_t *q, uint
   a.row_start = c->d_blob + p.off_row_start; a.kv_len = c->d_blob + p.off_kv_len;
   a.page_start = c->d_blob + p.off_page_start; a.page_ids = c->d_blob + p.off_pages + p.total_node_pages;
   a.q = q; a.kv_pool = pool; a.out = out;
-  const size_t first = (size_t)p.n_decode_slots * c->cfg.n_q_heads;
   a.cut = p.n_pf_cut > 0;
-  a.part_acc = c->part_acc + first * c->cfg.head_dim; a.part_m = c->part_m + first; a.part_l = c->part_l + first;
+  a.part_acc = c->cut_acc; a.part_m = c->cut_m; a.part_l = c->cut_l;
   return a;
 }
 
@@ -874,10 +930,9 @@ int run_merge(bs_ctx *c, const Plan &p, bool decode, bool prefill, uint16_t *out
   m.s = attn_shape(c); m.n_prefill = p.n_prefill; m.n_decode = decode ? p.n_decode : 0;
   m.row_start = c->d_blob + p.off_row_start; m.part_start = c->d_blob + p.off_part_start;
   m.part_acc = c->part_acc; m.part_m = c->part_m; m.part_l = c->part_l; m.out = out;
-  const size_t first = (size_t)p.n_decode_slots * c->cfg.n_q_heads;
   m.cut = c->d_blob + p.off_pf_cut; m.n_cut = prefill ? p.n_pf_cut : 0;
   m.cut_heads = p.pf_route.heads; m.cut_rows = p.pf_route.rows;
-  m.cut_acc = c->part_acc + first * c->cfg.head_dim; m.cut_m = c->part_m + first; m.cut_l = c->part_l + first;
+  m.cut_acc = c->cut_acc; m.cut_m = c->cut_m; m.cut_l = c->cut_l;
   SPAN(c, BS_K_ATTN_MERGE, st, HIP_TRY(c, launch_merge(m, st)));
   return BS_OK;
 }
@@ -1279,8 +1334,9 @@ void bs_destroy(bs_ctx *c) {
   (void)hipDeviceSynchronize();
   for (void *p : {(void *)c->rope_cos, (void *)c->rope_sin, (void *)c->xg, (void *)c->qbuf, (void *)c->attn, (void *)c->x1,
                   (void *)c->xg2, (void *)c->act, (void *)c->rstd1, (void *)c->rstd2, (void *)c->ss2, (void *)c->part_acc, (void *)c->part_m,
-                  (void *)c->part_l, (void *)c->d_blob, (void *)c->hid[0], (void *)c->hid[1], (void *)c->sync_words, (void *)c->trace_buf, (void *)c->sk_ws, (void *)c->sk_cnt})
+                  (void *)c->part_l, (void *)c->cut_acc, (void *)c->cut_m, (void *)c->cut_l, (void *)c->d_blob, (void *)c->hid[0], (void *)c->hid[1], (void *)c->sync_words, (void *)c->trace_buf, (void *)c->sk_ws, (void *)c->sk_cnt})
     if (p) (void)hipFree(p);
+  for (float *p : c->outgrown) (void)hipFree(p);
   c->stage.close();
   for (auto &v : c->spans) for (auto &s : v) { (void)hipEventDestroy(s.a); (void)hipEventDestroy(s.b); }
   for (auto e : c->free_events) (void)hipEventDestroy(e);
@@ -1339,7 +1395,7 @@ int bs_resolve_rows(bs_ctx *c, const bs_batch *b, int32_t *page_out, int32_t *sl
   if (rc) return rc;
   if (b->n_rows == 0) return BS_OK;  // (the node arrays of a batch without sequences are not looked at)
   Plan p;
-  if ((rc = build_plan(c, b, p, true, chunk_choice(c, b), 0))) return rc;
+  if ((rc = build_plan(c, b, p, true, chunk_choice(c, b), {0, 0}))) return rc;
   for (int r = 0; r < b->n_rows; ++r) {
     page_out[r] = c->blob[p.off_row_page + r];
     slot_out[r] = c->blob[p.off_row_slot + r];
@@ -1364,7 +1420,7 @@ int bs_attention_division(bs_ctx *c, const bs_batch *b, int64_t n_pages, int32_t
   }
   bs_division d{};
   d.prefill_rows = p.n_pf_work ? p.pf_route.rows : 0;
-  d.wide_items = p.n_wide; d.items = p.n_wide + p.n_narrow; d.states = p.n_slots; d.descriptor_words = p.total_ints;
+  d.wide_items = p.n_wide; d.items = p.n_wide + p.n_narrow; d.states = p.n_slots + p.n_cut_slots; d.descriptor_words = p.total_ints;
   const DecodeItem *it = reinterpret_cast<const DecodeItem *>(c->blob.data() + p.off_items);
   for (int i = 0; i < d.items; ++i)
     d.longest_item_tokens[i < p.n_wide] = std::max(d.longest_item_tokens[i < p.n_wide], it[i].n_tokens);
@@ -1557,7 +1613,6 @@ int bs_blend_step(bs_ctx *c, const bs_weights *w, const bs_batch *b, const void 
   Plan p;
   if ((rc = plan_step(c, b, p, st))) return rc;
   if ((rc = ensure_rows(c, p.n_rows))) return rc;
-  if ((rc = ensure_slots(c, p.n_slots))) return rc;
   Upload up;
   if ((rc = stage_plan(c, p, st, up))) return rc;
   return run_layer(c, p, w, (const uint16_t *)x_, (uint16_t *)y_, (uint16_t *)pool_, st, flags, up);
@@ -1582,7 +1637,6 @@ int bs_blend_layers(bs_ctx *c, int32_t n_layers, const bs_weights *w, const bs_b
   Plan p;
   if ((rc = plan_step(c, b, p, st))) return rc;
   if ((rc = ensure_rows(c, p.n_rows))) return rc;
-  if ((rc = ensure_slots(c, p.n_slots))) return rc;
   Upload up;
   if ((rc = stage_plan(c, p, st, up))) return rc;
   // one descriptor, validated, planned and uploaded once; activations alternate between two
@@ -1618,8 +1672,7 @@ int bs_attention(bs_ctx *c, const bs_batch *b, const void *q, void *out, const v
   HIP_TRY(c, hipSetDevice(c->device));
   hipStream_t st = (hipStream_t)stream_;
   Plan p;
-  if ((rc = plan_attention(c, b, p))) return rc;
-  if ((rc = ensure_slots(c, p.n_slots))) return rc;
+  if ((rc = plan_and_reserve(c, p, st, [&](Plan &q, CutRoom room) { return plan_attention(c, b, q, room); }))) return rc;
   Upload up;
   if ((rc = stage_plan(c, p, st, up))) return rc;
   HIP_TRY(c, launch_upload(up, st));
@@ -1644,23 +1697,27 @@ int bs_attention_noalloc(bs_ctx *c, const bs_batch *b, const void *q, void *out,
   hipStream_t st = (hipStream_t)stream_;
   Plan p;
   if ((rc = plan_noalloc(c, b, p))) return rc;
-  // Layout of the scratch array: descriptor blob | m | l | acc of the partial states (m and l padded
-  // to whole 16-byte units, so that the accumulators after them stay 16-byte aligned).
-  const size_t ml_floats = noalloc_ml_floats(c, p.n_slots);
+  // Layout of the scratch array: descriptor blob | m | l | acc of the partial states, those of decode sequences and behind
+  // them those of cut prefill work (m and l padded to whole 16-byte units, so that the accumulators after them stay
+  // 16-byte aligned).
+  const size_t ml_floats = noalloc_ml_floats(c, p.n_slots + p.n_cut_slots), first = (size_t)p.n_slots * c->cfg.n_q_heads;
   // the kernels take their buffers from the context; for this call they are parts of the scratch array
   int32_t *const blob0 = c->d_blob;
   float *const acc0 = c->part_acc, *const m0 = c->part_m, *const l0 = c->part_l;
+  float *const cut_acc0 = c->cut_acc, *const cut_m0 = c->cut_m, *const cut_l0 = c->cut_l;
   unsigned char *ptr = c->scratch_ptr;
   c->d_blob = reinterpret_cast<int32_t *>(ptr);
   c->part_m = reinterpret_cast<float *>(ptr + BS_NOALLOC_BLOB_BYTES);
   c->part_l = c->part_m + ml_floats;
   c->part_acc = c->part_l + ml_floats;
+  c->cut_acc = c->part_acc + first * c->cfg.head_dim; c->cut_m = c->part_m + first; c->cut_l = c->part_l + first;
   Upload up;
   rc = stage_plan(c, p, st, up, c->d_blob, BS_NOALLOC_BLOB_BYTES / sizeof(int32_t));
   if (!rc && launch_upload(up, st) != hipSuccess) rc = fail(c, BS_EHIP, "the descriptor's upload could not be launched");
   if (!rc) rc = run_attention(c, p, (const uint16_t *)q, (uint16_t *)out, (const uint16_t *)pool, st);
   c->d_blob = blob0;
   c->part_acc = acc0; c->part_m = m0; c->part_l = l0;
+  c->cut_acc = cut_acc0; c->cut_m = cut_m0; c->cut_l = cut_l0;
   return rc;
   });
 }

@@ -77,6 +77,9 @@ class Staging {
       if (ev) (void)rt_.destroy(ev);
   }
 
+  // the longest descriptor of a captured call that place() needs no memory for, in whole units
+  long captured_room() const { return ring_ / 5 / 4 * 4; }
+
   // Room for `words`, a multiple of four: whole 16-byte units, on a 16-byte boundary.  They may be read by what `stream`
   // is given next.
   int place(long words, typename Rt::Stream stream, int32_t **out) {

@@ -915,3 +915,67 @@ def test_captured_step_cuts_into_what_the_context_holds(lib):
         graph.replay()
         torch.cuda.synchronize()
         assert np.abs(to_np(y) - eager).max() <= 2e-2 * np.abs(eager).max()
+
+
+def test_captured_attention_cuts_into_what_the_context_holds(lib):
+    # a prefill-only call needs no states without cuts, and is captured on a context that has none; on one that a shorter
+    # batch has grown, whose descriptor buffer or states are short, and on one that has all: each replays to the same result
+    import torch
+    shape = W.LayerShape(256, 8, 2, 128, 256)
+    rng = np.random.default_rng(5)
+    batch = W.assemble_batch(16, [(40, 1400, -1), (9, 2100, -1)], 2, [], rng)
+    warm = [W.assemble_batch(16, [(40, 40, -1)], 1, [], rng), W.assemble_batch(16, [(1, 530, -1)], 1, [], rng), batch]
+    host = lib.Layer(shape, device=-1)
+    assert [host.attention_division(b).states > 0 for b in warm] == [False, True, True]
+    assert host.attention_division(batch).states > 2 * host.attention_division(warm[1]).states
+    tens = W.make_tensors(shape, batch, 5)
+    q = W.round_to_bf16(rng.standard_normal((batch.n_rows, shape.n_q_heads * shape.head_dim), dtype=np.float32))
+    tq = torch.from_numpy(q).cuda().to(torch.bfloat16)
+    for first in warm:
+        layer = lib.Layer(shape, device=0)
+        pool = layer.pack_pool(tens.k_pool, tens.v_pool)
+        layer.attention(first, tq[:first.n_rows], pool, batch.n_pages)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            out = layer.attention(batch, tq, pool, batch.n_pages)
+        for _ in range(3):
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            check_attention(shape, batch, q, tens, to_np(out))
+            layer.attention(warm[2], tq, pool, batch.n_pages)  # grows the states between the replays
+
+
+def test_cut_contexts_leave_captured_calls_their_workspace(lib):
+    # a decode call and a cut prefill call are captured; calls that cut more grow the states between the replays
+    import torch
+    shape = W.LayerShape(256, 8, 2, 128, 256)
+    rng = np.random.default_rng(6)
+    decode = W.assemble_batch(16, [(1, 300 + 40 * i, -1) for i in range(6)], 0, [], rng)
+    small = W.assemble_batch(16, [(9, 700, -1)], 1, [], rng)
+    larger = [W.assemble_batch(16, [(33, 2500, -1)] * n, n, [], rng) for n in (1, 3)]
+    layer = lib.Layer(shape, device=0)
+    states = [layer.attention_division(b).states for b in [small] + larger]
+    assert 0 < states[0] and 2 * states[0] + 64 < states[1] and 2 * states[1] < states[2]
+    assert all(layer.attention_division(b).descriptor_words < 1024 for b in larger)  # (the descriptor's buffer stays)
+    calls = []
+    for b in [decode, small] + larger:
+        t = W.make_tensors(shape, b, 6)
+        q = W.round_to_bf16(rng.standard_normal((b.n_rows, shape.n_q_heads * shape.head_dim), dtype=np.float32))
+        calls.append((b, t, q, torch.from_numpy(q).cuda().to(torch.bfloat16), layer.pack_pool(t.k_pool, t.v_pool)))
+    graphs = []
+    for b, t, q, tq, pool in calls[:2]:
+        layer.attention(b, tq, pool, b.n_pages)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            out = layer.attention(b, tq, pool, b.n_pages)
+        graphs.append((graph, out))
+    for b, t, q, tq, pool in calls[2:]:
+        check_attention(shape, b, q, t, to_np(layer.attention(b, tq, pool, b.n_pages)))
+        for (graph, out), (cb, ct, cq, _, _) in zip(graphs, calls):
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            check_attention(shape, cb, cq, ct, to_np(out))

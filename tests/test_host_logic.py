@@ -379,3 +379,53 @@ def test_cut_prefill_contexts_keep_to_the_scratch_array(segments):
         assert d.states * 32 * (128 + 2) * 4 <= (63 << 20) and d.descriptor_words <= NOALLOC_WORDS
         if segments == 1:
             assert d.states > 5 * 3
+
+
+@pytest.mark.parametrize("want,held,captured_words,capturing,free,got", [
+    # want / held / got: states of cut contexts and descriptor words (the descriptor without cuts has 90)
+    ((64, 120), (0, 100), 500, True, 0, (0, 90)),         # captured on a context without states: whole
+    ((64, 120), (64, 128), 500, True, 0, (64, 120)),      # ... that holds them: cut as outside capture
+    ((64, 120), (64, 100), 500, True, 0, (32, 100)),      # ... whose descriptor buffer is too short for that many
+    ((64, 120), (64, 128), 100, True, 0, (32, 100)),      # ... whose ring of captured descriptors is
+    ((64, 120), (0, 128), 500, False, 64, (64, 120)),     # outside capture the states grow
+    ((64, 120), (0, 128), 500, False, 63, (0, 90)),       # ... and what the device has no room for stays whole
+    ((64, 120), (0, 100), 500, False, 64, (32, 100)),     # a descriptor that fits without the cut makes none grow
+    ((64, 120), (0, 80), 500, False, 64, (64, 120)),      # ... one that does not grows anyway
+    ((64, 120), (64, 128), 100, False, 0, (64, 120)),     # the ring is for captured calls
+    ((0, 90), (0, 0), 0, True, 0, (0, 90))])              # nothing to cut: nothing is asked
+def test_what_a_call_cuts_into(tmp_path, want, held, captured_words, capturing, free, got):
+    import subprocess
+    src = tmp_path / "room.cpp"
+    src.write_text("""
+#include <cstdio>
+#include "room.hpp"
+struct Ops {
+  long ws, ww, hs, hw, cw, free_slots;
+  bool cap;
+  long s = 0, w = 0;
+  bool grew = false, asked = false;
+  int build(bs::CutRoom r) {  // half of the cuts where all of them do not fit
+    s = ws; w = ww;
+    if (s > r.slots || w > r.words) { s = ws / 2; w = 100; }
+    if (s > r.slots || w > r.words) { s = 0; w = 90; }
+    return 0;
+  }
+  long slots() const { return s; }
+  long words() const { return w; }
+  long whole_words() const { return 90; }
+  long held_slots() const { return hs; }
+  long held_words() const { return hw; }
+  long captured_words() const { return cw; }
+  bool capturing() { asked = true; return cap; }
+  bool grow(long n) { grew = true; return n <= free_slots; }
+};
+int main() {
+  Ops o{%d, %d, %d, %d, %d, %d, %s};
+  if (bs::plan_within(o)) return 1;
+  std::printf("%%ld %%ld %%d %%d", o.s, o.w, o.cap && o.grew, o.asked && o.ws == 0);
+}
+""" % (*want, *held, captured_words, free, "true" if capturing else "false"))
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2411_16102_amd", "csrc")
+    subprocess.check_call(["g++", "-std=c++17", "-I", csrc, str(src), "-o", str(tmp_path / "room")])
+    out = subprocess.check_output([str(tmp_path / "room")], text=True).split()
+    assert out == [str(got[0]), str(got[1]), "0", "0"]
