@@ -1614,17 +1614,19 @@ void gemm_plan(GemmArgs &a, int epilogue) {
       for (long s = 2; !few && s <= max_splits(tiles, slots); ++s) offer(cut_us(c, a.M, a.N, a.K, (int)s, n_cu, epilogue), c.v, s);
     }
   }
-  // Shared 256x256 tiles: the chip's worth of k-tile iterations with nothing idle, and 75 us for the cuts (a
-  // workgroup passes up to two partial tiles through memory).  Where the tiles beyond whole rounds are no
-  // multiple of a quarter round, the workgroups walk K in eight and more phases and share fewer panels in L2:
-  // a tenth of a microsecond more per k-tile.  Only where K is long, and more than one round of tiles cannot be
-  // cut evenly (the down projection of the 70B layer at 5120 rows, 2.5 rounds of 448 k-tiles: 1772 us, 1807 on whole 160x256
-  // tiles; its output projection, 128 k-tiles, 584 against 537).
+  // Shared 256x256 tiles: the chip's worth of k-tile iterations with nothing idle, and 22 us for the cuts (a
+  // workgroup passes up to two partial tiles through memory).  Only where K is long, more than one round of tiles cannot be
+  // cut evenly, and the tiles beyond whole rounds are a multiple of a quarter round: else the workgroups walk K in
+  // eight and more phases and share few panels in L2 (QKV of 12288 columns, K = 4096, 5600 rows: 522 us, 461 on whole
+  // 256x256 tiles; down projection of the 70B layer, 6695 rows: 2847 against 2581; of 124 such products two are
+  // ahead of the best other choice, by 1 %, and all are 31 % behind it on average).  Four phases cost 4 % more per k-tile than one
+  // or two.  Fitted to the 67 products of up to four phases in steps of six layers; it takes the eleven on which these tiles are ahead: 70B down projection of 5120 rows 1760 us (1828 on the best
+  // other tiles), of 7012 rows 2454 (2608), N = 5120, K = 13824 at 4029 rows 452 (484).
   if (may_share && a.K >= 4096 && a.M > 256) {
-    const long tiles = n_tiles(a.M, a.N, 256, 256), rem = tiles % n_cu;
-    const double phases = rem ? (double)(n_cu / std::gcd((long)n_cu, rem)) : 1.0;
-    const double t = (double)nk * (1.51 * (double)tiles / (double)n_cu + (phases <= 4 ? 0.0 : phases <= 8 ? 0.1 : 0.11)) + 75.0;
-    if (rem && t < best) { a.tile_variant = V_SHARED; a.k_splits = 1; }
+    const long tiles = n_tiles(a.M, a.N, 256, 256), rem = tiles % n_cu, phases = rem ? n_cu / std::gcd((long)n_cu, rem) : 1;
+    const double t = (double)nk * (phases <= 2 ? 1.49 : 1.545) * (double)tiles / (double)n_cu + 22.0 +
+                     SHAPES[0].round[epi_column(epilogue)] * (double)((tiles + n_cu - 1) / n_cu);
+    if (rem && tiles > n_cu && phases <= 4 && t < best) { a.tile_variant = V_SHARED; a.k_splits = 1; }
   }
 }
 

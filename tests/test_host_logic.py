@@ -296,6 +296,18 @@ def test_gemm_division_narrow_short_and_large(shape, product, rows, want):
     assert binding.Layer(shape, device=-1).gemm_division(product, rows) == want
 
 
+@pytest.mark.parametrize("shape,product,rows,shared", [
+    # tiles beyond whole rounds no multiple of a quarter round: slower on shared tiles by 5 to 20 %, in a step or alone
+    (W.LayerShape(4096, 32, 32, 128, 11008), "qkv", 5600, False), (W.LLAMA3_70B, "down", 3170, False), (W.LLAMA3_70B, "down", 4782, False),
+    (W.LLAMA3_70B, "qkv", 3584, False), (W.LLAMA3_70B, "o", 6695, False), (W.LayerShape(5120, 40, 8, 128, 13824), "down", 7300, False),
+    # a multiple of a quarter round: slower where there are many rounds of a short K, ahead where K is long
+    (W.LayerShape(4096, 32, 32, 128, 11008), "qkv", 7012, False), (W.LLAMA3_70B, "down", 3535, False),
+    (W.LayerShape(4096, 32, 32, 128, 11008), "qkv", 3072, False), (W.LayerShape(5120, 40, 8, 128, 13824), "down", 4029, True),
+    (W.LLAMA3_70B, "qkv", 2048, True), (W.LLAMA3_70B, "down", 7012, True), (W.LLAMA3_70B, "qkv", 4096, True)])
+def test_shared_tiles_where_they_are_the_faster_ones(shape, product, rows, shared):
+    assert (binding.Layer(shape, device=-1).gemm_division(product, rows) == (6, 1)) == shared
+
+
 @pytest.mark.parametrize("heads,n,tail,groups,pages,want", [
     ((24, 8), 287, 32, 6, 151, (32, 512)), ((32, 8), 640, 400, 4, 128, (400, 1024)),   # large steps: by rounds of the wide units
     ((32, 8), 20, 16, 2, 64, (16, 128)), ((64, 8), 105, 181, 6, 5, (181, 80)),        # few: cut; tails beside wide nodes stay whole
