@@ -1350,29 +1350,36 @@ long round_split_columns(long tm, long tn, int n_cu) {
   return full < 1 || tiles % n_cu == 0 || idle * 4 <= n_cu || cols < 1 || cols >= tn ? 0 : cols;
 }
 
-// Gate/up of more than 512 rows: the shape with the smallest estimate, and that estimate.  Of 182 products of seven layers timed
+// What the second launch of a product in two costs beside its rounds.  Of 386 gate/up products of eight layers, timed in steps whole and
+// in two launches, the choice is 0.3 % off the best on average and 4 % at most with 2 to 3; with none, products of 45 to 80 us
+// went out as two launches for an expected 2 us and took 3 to 6 more (K = 1024, 2 x 4096 columns, 2056 rows: 48.0 us, whole 42.3).
+constexpr double SECOND_LAUNCH_US = 2.0;
+
+// Gate/up of more than 512 rows: the shape with the smallest estimate, and that estimate.  *cols: 0, or the columns of 256x256 tiles
+// that go out in whole rounds of their own, the rest behind them on 128x128 tiles, where that is expected to be shorter than whole
+// (timed both ways, 8B layer: 1160 rows 254 us whole, 237 in two launches; 3300 rows 553 and 570).  Of 182 products of seven layers timed
 // with cold weights it is 0.6 % off the best on average.  1580 rows of the 8B layer: 192x256 tiles 330 us, 160x256 tiles, faster
 // since they have three activation panels, 316.  (Below K = 1024, where nothing was fitted, the relation of rounds in choose_variant.)
-double gate_up_us(int m, int n_b_rows, int k, int n_cu, int *v) {
+double gate_up_us(int m, int n_b_rows, int k, int n_cu, int *v, int *cols) {
   double best_t = 1e300;
-  for (const Shape &c : SHAPES) {
-    double t = whole_us(c, m, n_b_rows, k, n_cu, EPI_SWIGLU);
-    if (c.v == V_BIG) {  // whole rounds on these and the rest of the columns on 128x128 tiles: gemm_round_split
-      const long tm = (m + 255) / 256, tn = (n_b_rows + 255) / 256, cols = round_split_columns(tm, tn, n_cu);
-      if (cols) t = std::min(t, whole_us(c, m, (int)cols * 256, k, n_cu, EPI_SWIGLU) + whole_us(SHAPES[2], m, n_b_rows - (int)cols * 256, k, n_cu, EPI_SWIGLU));
-    }
-    if (t < best_t) { best_t = t; *v = c.v; }
-  }
+  auto offer = [&](double t, int variant, int columns) {
+    if (t < best_t) { best_t = t; *v = variant; *cols = columns; }
+  };
+  for (const Shape &c : SHAPES) offer(whole_us(c, m, n_b_rows, k, n_cu, EPI_SWIGLU), c.v, 0);
+  const int split = (int)round_split_columns((m + 255) / 256, (n_b_rows + 255) / 256, n_cu);
+  if (split)
+    offer(whole_us(SHAPES[0], m, split * 256, k, n_cu, EPI_SWIGLU) + whole_us(SHAPES[2], m, n_b_rows - split * 256, k, n_cu, EPI_SWIGLU) +
+              SECOND_LAUNCH_US, V_BIG, split);
   return best_t;
 }
 
 // Two shapes for one product: whole rounds of one of the 256-wide shapes over the first `cols` tile columns, another shape, whose
 // rounds the rest happens to fill, over the others.  Taken where the estimate of the two launches is 3 % below the best single
-// choice, about its own error.  Measured, gate/up of the 8B layer: 800 rows 180 us on 256x256 tiles, 160 as one round of them and
-// 160x256 tiles for the rest; 1580 rows 305 (192x256) -> 300; where less is expected (640, 2048 rows) 2 % either way.
+// choice, about its own error.  Measured in steps, 8B layer: 776 rows 192 us on one shape, 170 as one round of 160x256 tiles and
+// 256x256 ones for the rest; 1288 rows 269 -> 251.
 bool gate_up_pair(int m, int n_b_rows, int k, int n_cu, int *head, int *tail, int *cols) {
-  int single;
-  double best_t = 0.97 * gate_up_us(m, n_b_rows, k, n_cu, &single);
+  int single, single_cols;
+  double best_t = 0.97 * gate_up_us(m, n_b_rows, k, n_cu, &single, &single_cols);
   bool found = false;
   for (const Shape &c : SHAPES) {
     if (c.bn != 256) continue;
@@ -1380,7 +1387,7 @@ bool gate_up_pair(int m, int n_b_rows, int k, int n_cu, int *head, int *tail, in
     for (long f = std::max(1L, full - 2); f <= full; ++f) {
       const long n = f * n_cu / tm;
       if (n < 1 || n >= tn) continue;
-      const double t = whole_us(c, m, (int)n * 256, k, n_cu, EPI_SWIGLU);
+      const double t = whole_us(c, m, (int)n * 256, k, n_cu, EPI_SWIGLU) + SECOND_LAUNCH_US;
       for (const Shape &c2 : SHAPES) {
         const double t2 = t + whole_us(c2, m, n_b_rows - (int)n * 256, k, n_cu, EPI_SWIGLU);
         if (t2 >= best_t) continue;
@@ -1425,8 +1432,8 @@ int choose_variant(int m, int n_b_rows, int k, int epilogue, int dh, int n_cu, i
   }
   const bool estimated = epilogue == EPI_SWIGLU && g_forced_variant == V_AUTO && k >= FIT_MIN_K;
   if (estimated && m > 512) {
-    int best;
-    gate_up_us(m, n_b_rows, k, n_cu, &best);
+    int best, cols;
+    gate_up_us(m, n_b_rows, k, n_cu, &best, &cols);
     return best;
   }
   struct Cand { int v, bm, bn, per_cu; double T, a; };
@@ -1510,9 +1517,14 @@ bool gemm_round_split(const GemmArgs &a, int epilogue, int dh, GemmArgs *head, G
   if (gemm_streams_weights(a, epilogue)) return false;
   const int n_cu = a.n_cu > 0 ? a.n_cu : N_CU;
   int first, rest, cols;
-  if (a.M <= 512 || a.K < FIT_MIN_K || !gate_up_pair(a.M, 2 * n_cols, a.K, n_cu, &first, &rest, &cols)) {
-    if (choose_variant(a.M, 2 * n_cols, a.K, epilogue, dh, a.n_cu) != V_BIG) return false;
-    cols = (int)round_split_columns((a.M + 255) / 256, (n_cols + 127) / 128, n_cu);  // a 256x256 tile yields 128 output columns
+  const bool estimated = a.M > 512 && a.K >= FIT_MIN_K;
+  if (!estimated || !gate_up_pair(a.M, 2 * n_cols, a.K, n_cu, &first, &rest, &cols)) {
+    if (estimated) {
+      gate_up_us(a.M, 2 * n_cols, a.K, n_cu, &first, &cols);
+    } else {
+      if (choose_variant(a.M, 2 * n_cols, a.K, epilogue, dh, a.n_cu) != V_BIG) return false;
+      cols = (int)round_split_columns((a.M + 255) / 256, (n_cols + 127) / 128, n_cu);  // a 256x256 tile yields 128 output columns
+    }
     if (!cols) return false;
     first = V_BIG;
     rest = V_SMALL;  // two workgroups per CU fill the chip best with what is left of a round
@@ -1620,8 +1632,9 @@ void gemm_plan(GemmArgs &a, int epilogue) {
   // eight and more phases and share few panels in L2 (QKV of 12288 columns, K = 4096, 5600 rows: 522 us, 461 on whole
   // 256x256 tiles; down projection of the 70B layer, 6695 rows: 2847 against 2581; of 124 such products two are
   // ahead of the best other choice, by 1 %, and all are 31 % behind it on average).  Four phases cost 4 % more per k-tile than one
-  // or two.  Fitted to the 67 products of up to four phases in steps of six layers; it takes the eleven on which these tiles are ahead: 70B down projection of 5120 rows 1760 us (1828 on the best
-  // other tiles), of 7012 rows 2454 (2608), N = 5120, K = 13824 at 4029 rows 452 (484).
+  // or two.  Fitted to the 67 products of up to four phases in steps of six layers; it takes the eleven on which these tiles
+  // are ahead: 70B down projection of 5120 rows 1760 us (1828 on the best other tiles), of 7012 rows 2454 (2608), N = 5120,
+  // K = 13824 at 4029 rows 452 (484).
   if (may_share && a.K >= 4096 && a.M > 256) {
     const long tiles = n_tiles(a.M, a.N, 256, 256), rem = tiles % n_cu, phases = rem ? n_cu / std::gcd((long)n_cu, rem) : 1;
     const double t = (double)nk * (phases <= 2 ? 1.49 : 1.545) * (double)tiles / (double)n_cu + 22.0 +

@@ -91,8 +91,8 @@ int gemm_ss_parts(const GemmArgs &a, int epilogue, int dh);
 // Whether a product of these sizes goes to the few-row kernel (with the forced shapes in mind; GemmArgs::ss_in is for it).
 bool gemm_streams_weights(const GemmArgs &a, int epilogue);
 // Whole rounds first: when the last round of a gate/up GEMM would leave much of the chip idle, or another shape's
-// rounds fit what whole rounds of one leave, returns true and the two column ranges to launch instead, tile shapes set:
-// `head` = the tile columns of the whole rounds, `tail` = the rest.
+// rounds fit what whole rounds of one leave, and two launches are expected to be shorter than one, returns true and
+// the two column ranges to launch instead, tile shapes set: `head` = the tile columns of the whole rounds, `tail` = the rest.
 bool gemm_round_split(const GemmArgs &a, int epilogue, int dh, GemmArgs *head, GemmArgs *tail);
 // Tile shape and number of k-ranges of a product whose epilogue can follow a split (QKV, RESID,
 // RESID_NORM): sets a.tile_variant and a.k_splits.  Call it once M, N, K, n_cu and the workspace are set.

@@ -879,10 +879,11 @@ def test_few_wide_items_among_many_narrow_ones(lib):
         check_attention(shape, batch, q, tens, out)
 
 
-@pytest.mark.parametrize("rows,tiles", [(521, 2), (663, 2), (800, 2)])
-def test_gate_up_columns_on_two_tile_shapes(lib, rows, tiles):
-    # one round of 160x256 tiles, the other columns on 128x128, 192x256 and 256x256 ones, the last of them partial
-    shape = W.LayerShape(1024, 4, 2, 64, 14344)
+@pytest.mark.parametrize("d_ffn,rows,tiles", [(8200, 907, 10), (14344, 800, 2), (14344, 805, 10), (6920, 1929, 1)])
+def test_gate_up_columns_on_two_tile_shapes(lib, d_ffn, rows, tiles):
+    # one round of 192x256, 160x256, 192x256 and 256x256 tiles, the other columns on 128x128, 256x256 (twice) and 192x256 ones, the last
+    # of them partial (521 and 663 rows of 2 x 14344 columns, which stood here, are 4 to 10 % faster on one shape)
+    shape = W.LayerShape(1024, 4, 2, 64, d_ffn)
     assert lib.Layer(shape, device=-1).gemm_division("gate_up", rows) == (tiles, 1)
     seqs = [(rows - 13, rows - 3, -1)] + [(1, 20 + 9 * i, -1) for i in range(13)]
     batch = W.assemble_batch(16, seqs, 1, [], np.random.default_rng(rows))
@@ -979,3 +980,16 @@ def test_cut_contexts_leave_captured_calls_their_workspace(lib):
             graph.replay()
             torch.cuda.synchronize()
             check_attention(shape, cb, cq, ct, to_np(out))
+
+
+@pytest.mark.parametrize("d_ffn,rows,launches", [(8200, 907, 2), (14344, 800, 2), (14344, 805, 2), (6920, 1929, 2),  # two shapes
+                                                 (14344, 1216, 2), (14344, 1500, 1), (14344, 663, 1)])
+def test_gate_up_in_as_many_launches_as_are_expected_to_be_shorter(lib, d_ffn, rows, launches):
+    # 1216 rows: whole rounds of 256x256 tiles and 128x128 ones for the rest; 1500: these would take longer than whole tiles
+    shape = W.LayerShape(1024, 4, 2, 64, d_ffn)
+    layer = lib.Layer(shape, device=0)
+    batch = W.assemble_batch(16, [(rows, rows, -1)], 1, [], np.random.default_rng(rows))
+    dev = layer.upload(W.make_tensors(shape, batch, rows), batch)
+    layer.profile(True)
+    layer.blend_step(dev, batch)
+    assert layer.profile_read()["gemm_gate_up"][1] == launches

@@ -441,3 +441,11 @@ int main() {
     subprocess.check_call(["g++", "-std=c++17", "-I", csrc, str(src), "-o", str(tmp_path / "room")])
     out = subprocess.check_output([str(tmp_path / "room")], text=True).split()
     assert out == [str(got[0]), str(got[1]), "0", "0"]
+
+
+@pytest.mark.parametrize("rows,tiles", [(2606, 10), (4100, 10), (3300, 10), (5140, 1)])
+def test_gate_up_on_one_shape_where_a_second_would_cost_more(rows, tiles):
+    # K = 1024, 2 x 4096 columns: two shapes for an expected gain of 2 to 3 us take 3 to 5 us longer than the one shape (2606 and
+    # 4100 rows: whole 192x256 tiles, not 160x256 ones first); an expected 4 us and more than
+    # 3 % beside that cost pays
+    assert binding.Layer(W.LayerShape(1024, 4, 2, 64, 4096), device=-1).gemm_division("gate_up", rows)[0] == tiles
