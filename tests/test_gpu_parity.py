@@ -810,7 +810,7 @@ def test_gate_up_on_192_row_tiles(lib, d_model, d_ffn, rows, tiles):
     # QKV on whole 160x256, 192x256 and 128x256 tiles, a last row of tiles with one row or an odd number of them, K no multiple of 64
     ((264, 64, 64, 64, 1032), 700, "qkv", (2, 1)), ((264, 32, 8, 128, 1032), 1281, "qkv", (2, 1)),
     ((264, 32, 8, 128, 1032), 1700, "qkv", (10, 1)), ((264, 40, 8, 128, 1032), 1537, "qkv", (10, 1)),
-    ((1032, 40, 8, 128, 1032), 513, "qkv", (11, 1)),
+    ((1032, 40, 8, 128, 1032), 513, "qkv", (11, 1)), ((776, 96, 8, 64, 1032), 700, "qkv", (11, 1)), ((264, 96, 8, 64, 1032), 1601, "qkv", (10, 1)),
     # output and down projection on 128x256 and 192x256 tiles, whole and cut along K
     ((1032, 24, 8, 64, 1032), 2049, "o", (11, 2)), ((2056, 4, 2, 64, 1032), 2049, "down", (11, 1)),
     ((520, 4, 2, 64, 8200), 1700, "down", (11, 6)), ((1032, 4, 2, 64, 8200), 1281, "down", (10, 7)),
@@ -822,6 +822,17 @@ def test_products_on_192_and_128_row_tiles(lib, dims, rows, product, want):
     seqs = [(rows - 33, rows + 20, -1)] + [(1, 20 + 9 * i, -1) for i in range(33)]
     batch = W.assemble_batch(16, seqs, 1, [], np.random.default_rng(rows))
     check_step(lib, shape, batch, W.make_tensors(shape, batch, rows, gains="random"))
+
+
+@pytest.mark.parametrize("d_model", [8, 64, 72, 128, 192, 200, 256, 320, 456])
+@pytest.mark.parametrize("heads,dh", [((96, 8), 64), ((48, 4), 128)])
+def test_qkv_on_192_row_tiles_around_the_look_ahead(lib, heads, dh, d_model):
+    # one to eight k-tiles, whole and ragged, on the ring of two activation and three weight panels; the last row of tiles
+    # has one row
+    shape = W.LayerShape(d_model, heads[0], heads[1], dh, 64)
+    assert lib.Layer(shape, device=-1).gemm_division("qkv", 1537) == (10, 1)
+    batch = W.assemble_batch(16, [(53, 53, -1)] * 29, 29, [], np.random.default_rng(d_model))
+    check_step(lib, shape, batch, W.make_tensors(shape, batch, d_model, gains="random"))
 
 
 @pytest.mark.parametrize("heads,dh,segments,n_decode", [
@@ -850,14 +861,33 @@ def test_prefill_contexts_cut_into_ranges(lib, heads, dh, segments, n_decode):
 
 
 def test_step_with_cut_prefill_contexts(lib):
-    # the schedules of a step take the same ranges: serial and co-scheduled, one layer and pipelined ones
+    # the schedules of a step take the same ranges: serial, co-scheduled (the states of the prefill rows are merged apart
+    # from those of the decode sequences), and pipelined layers
     shape = W.LayerShape(512, 8, 2, 128, 1032)
-    batch = W.assemble_batch(16, [(290, 1400, -1), (35, 900, -1)] + [(1, 30 + 7 * i, -1) for i in range(40)], 2, [],
-                             np.random.default_rng(3))
-    assert lib.Layer(shape, device=-1).attention_division(batch).states >= 64
+    prefill, decode = [(290, 1400, -1), (35, 900, -1)], [(1, 30 + 7 * i, -1) for i in range(40)]
+    rng = np.random.default_rng(3)
+    batch = W.assemble_batch(16, prefill + decode, 2, [], rng)
+    host = lib.Layer(shape, device=-1)
+    division = host.attention_division(batch)
+    cut = division.states - host.attention_division(W.assemble_batch(16, decode, 0, [], rng)).states
+    assert cut > 0 and cut % division.prefill_rows == 0
     tens = W.make_tensors(shape, batch, 3, gains="random")
-    for flags in (0, 1):
-        check_step(lib, shape, batch, tens, flags)
+    y, ref = check_step(lib, shape, batch, tens)
+    layer = lib.Layer(shape, device=0)
+    layer.set_overlap(head_cus_min=8, tail_workgroups=16, min_prefill_rows=1, always=1)
+    layer.profile(True)
+    y1 = layer.blend_step(layer.upload(tens, batch), batch, flags=lib.FLAG_OVERLAP)
+    check(to_np(y1), ref["y"], O.layer_step(shape, tens, batch, storage="bf16")["y"], "co-scheduled")
+    prof = layer.profile_read()
+    assert prof["gemm_decode_rows"][1] > 0 and prof["attn_merge"][1] == 2
+    out = []
+    for flags in (lib.FLAG_SERIAL, lib.FLAG_OVERLAP | lib.FLAG_PIPELINE):
+        devs = [layer.upload(W.make_tensors(shape, batch, 3 + l, gains="random"), batch) for l in range(3)]
+        layer.profile(True)
+        out.append(layer.blend_layers(devs, batch, flags=flags))
+        prof = layer.profile_read()
+        assert prof["attn_merge"][1] == (6 if flags else 3) and prof["gemm_down"][1] == 3
+    assert errs(to_np(out[1]), to_np(out[0]))[0] <= MAXREL
 
 
 def test_few_wide_items_among_many_narrow_ones(lib):
@@ -882,7 +912,7 @@ def test_few_wide_items_among_many_narrow_ones(lib):
 @pytest.mark.parametrize("d_ffn,rows,tiles", [(8200, 907, 10), (14344, 800, 2), (14344, 805, 10), (6920, 1929, 1)])
 def test_gate_up_columns_on_two_tile_shapes(lib, d_ffn, rows, tiles):
     # one round of 192x256, 160x256, 192x256 and 256x256 tiles, the other columns on 128x128, 256x256 (twice) and 192x256 ones, the last
-    # of them partial (521 and 663 rows of 2 x 14344 columns, which stood here, are 4 to 10 % faster on one shape)
+    # of them partial
     shape = W.LayerShape(1024, 4, 2, 64, d_ffn)
     assert lib.Layer(shape, device=-1).gemm_division("gate_up", rows) == (tiles, 1)
     seqs = [(rows - 13, rows - 3, -1)] + [(1, 20 + 9 * i, -1) for i in range(13)]
