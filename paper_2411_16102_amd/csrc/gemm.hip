@@ -1486,8 +1486,10 @@ hipError_t launch_variant(const GemmArgs &a, int v, hipStream_t stream) {
     if (v == V_S128) return launch_one<128, 256, 2, 4, EPI, 64, DEEP_X>(a, stream);
     if (v == V_S256) return launch_one<256, 128, 4, 2, EPI, 64, DEEP_X>(a, stream);
   }
-  if (v == V_MID) return launch_one<192, 256, 2, 4, EPI, 64>(a, stream);
-  if (v == V_WIDE) return launch_one<128, 256, 2, 4, EPI, 64>(a, stream);
+  if constexpr (EPI != EPI_PLAIN) {  // (no plain product is given these)
+    if (v == V_MID) return launch_one<192, 256, 2, 4, EPI, 64>(a, stream);
+    if (v == V_WIDE) return launch_one<128, 256, 2, 4, EPI, 64>(a, stream);
+  }
   return launch_one<128, 128, 2, 2, EPI, 64>(a, stream);
 }
 
