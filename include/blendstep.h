@@ -266,7 +266,7 @@ int bs_overlap_trace(bs_ctx *ctx, int on);
 int bs_overlap_trace_read(bs_ctx *ctx, int32_t launch, uint64_t *out, int64_t cap_records, int64_t *n_records);
 
 /* Tuning knob: GEMM tile shape for the calls on this context: 0 = chosen per problem (default), 1 = 256x256,
- * 2 = 160x256 (not for the QKV GEMM), 3 = 128x128, 6 = 256x256 tiles shared between workgroups (one persistent
+ * 2 = 160x256 (the QKV GEMM then takes 1, 3 or 6), 3 = 128x128, 6 = 256x256 tiles shared between workgroups (one persistent
  * workgroup per CU; the tiles that do not fill a whole round are cut along K into equal ranges).  With 0, products of few
  * rows (up to 16; up to 64, or 256 where K is short, where one round covers the product) run on a kernel of their own, and
  * others of at most 256 rows mostly as one row of tiles on a pipeline with its own look-ahead for the weight panel; a

@@ -395,7 +395,8 @@ constexpr int chunk_size(int k, std::integer_sequence<int, W...>) { const int si
 // With wide nodes both lengths come from an estimate of the launch and the merge, in microseconds on 1024 SIMDs:
 // the rounds of the wide units, all the work or the longest unit, whichever is most, part of the narrow units'
 // work beside the wide ones, and the partial states once out and once back in; prefill workgroups of the same
-// launch (four SIMDs each) are work, and stand before the wide units' rounds.  Fitted to 357 batches of 8 to
+// launch (four SIMDs each) are work, and stand before the wide units' rounds (their contexts are taken as whole
+// here, also where prefill_cut then cuts them).  Fitted to 357 batches of 8 to
 // 1000 sequences behind 1 to 32 prefixes of 4 to 400 pages and 63 blended launches, pairs of lengths timed: 2 %
 // (blended: 3 %) off the best pair on average; 15 % (3 %) faster than chunks of 64 pages, 32 in wide nodes, 5 %
 // (3 %) faster than one length for both kinds cut until there were 1536 units (in 22 and 25 of the 420 more than
@@ -526,7 +527,8 @@ void each_prefill_block(const bs_batch *b, int wg_rows, F &&f) {
 
 // What the launch has to hold beside the prefill work, and the room for the division
 struct CutLimits {
-  double decode_us;  // its decode items, on the whole chip
+  double decode_us;  // the step's decode items, on the whole chip (also those that ride in GEMM launches, or have a launch of
+                     // their own: such steps cut less than they could)
   CutRoom room;      // states of cut work, words of the work list
 };
 

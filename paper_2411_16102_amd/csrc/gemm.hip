@@ -150,7 +150,7 @@ __device__ __forceinline__ void sk_tile_span(const SkPlan &p, int j, int *w_firs
 // (SK: the tile and the k-range come from `seg` instead).
 template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int DH, int DEEP = 0, bool SK = false>
 __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int bid, const SkPlan *sp = nullptr, const SkSeg seg = SkSeg{}) {
-  static_assert(!SK || (!DEEP && EPI != EPI_PARTIAL), "shared tiles use the five-panel ring and a real epilogue");
+  static_assert(!SK || (!DEEP && EPI != EPI_PARTIAL), "shared tiles use the two rings of whole tiles and a real epilogue");
   constexpr int NW = WAVES_M * WAVES_N;
   // DEEP: the pipeline for one round of tiles over few rows, where every CU streams a weight
   // panel of its own from HBM; the first half of the wavefronts requests the activation
@@ -376,7 +376,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int bid, cons
     for (; kt < kt1; ++kt) tile(kt, Yes{});
   } else {
     // One round of tiles over few rows: every CU streams a weight panel of its own from HBM,
-    // and the ring of five equal slots gives it two k-tiles of look-ahead at most.  Here LDS
+    // and the rings above give it two k-tiles of look-ahead at most.  Here LDS
     // holds NXS = DEEP + 1 slots for the activation panel (shared by all tiles, served by the
     // L2: NXS - 1 k-tiles of look-ahead) and all the rest, NWS slots, for the weight panel:
     // NWS - 1 k-tiles of look-ahead.  The memory counter of a wavefront retires its loads in
@@ -1446,7 +1446,7 @@ int choose_variant(int m, int n_b_rows, int k, int epilogue, int dh, int n_cu, i
   int best = V_SMALL;
   double best_t = 1e300;
   for (const Cand &c : cands) {
-    if (c.v == V_TALL && epilogue == EPI_QKV) continue;  // not built for it (see gemm_plan)
+    if (c.v == V_TALL && epilogue == EPI_QKV) continue;  // (QKV comes here for forced shapes alone, which do not force it to 160x256)
     if (c.v == V_MID && epilogue != EPI_SWIGLU) continue;
     const long tiles = n_tiles(m, n_b_rows, c.bm, c.bn);
     const long slots = (long)n_cu * c.per_cu;
@@ -1455,7 +1455,9 @@ int choose_variant(int m, int n_b_rows, int k, int epilogue, int dh, int n_cu, i
     if (t < best_t) { best_t = t; best = c.v; }
   }
   // Up to 512 rows 128x256 tiles where the estimate puts them ahead of that choice: 2 x 8192 columns, K = 2048 at 359 rows
-  // 37.1 us on 128x128 tiles, 33.5 on these; 5 % on average over 51 products of 257 to 512 rows, and none slower.
+  // 37.1 us on 128x128 tiles, 33.5 on these; 5 % on average over 51 products of 257 to 512 rows, and none slower than that
+  // choice, though 128x128 tiles would be ahead of both where N and K are small (2 x 4096, K = 1024 at 308 rows 13.1 us
+  // against 17.9, and 20.7 on 160x256 ones).
   if (estimated && m > 256) {
     for (const Shape &c : SHAPES)
       if (c.v == best && whole_us(SHAPES[4], m, n_b_rows, k, n_cu, EPI_SWIGLU) < whole_us(c, m, n_b_rows, k, n_cu, EPI_SWIGLU)) return V_WIDE;
@@ -1584,9 +1586,10 @@ void gemm_plan(GemmArgs &a, int epilogue) {
     }
   }
   // Above, up to 1024 rows: the estimate of an earlier fit (the same terms, 256x256, 160x256 and 128x128 tiles, the products
-  // of twelve layers of 256 to 12288 columns and K 256 to 28672, before the requests of the main loop were dealt out).  It
-  // still picks within 3 to 5 % of the best here, and the present fit, whose error at the many cuts of few rows is as large,
-  // gives no more.
+  // of twelve layers of 256 to 12288 columns and K 256 to 28672, before the requests of the main loop were dealt out).  With the
+  // present kernels its choices are 3.5 % off the best of all shapes and cuts on average over 293 products, 74 of them by more than
+  // 5 % and the worst by 33 (down projection, N = 3072, K = 8192 at 667 rows: 256x256 tiles in seven ranges 60.8 us, 45.7 on 160x256
+  // tiles in four).  The present fit over these three shapes gives no more; 192x256 and 128x256 tiles, cut, are not offered here.
   struct Earlier { double round, second, closing; };
   const Earlier ep = epilogue == EPI_QKV ? Earlier{7.1, 5.2, 0.0} : epilogue == EPI_RESID_NORM ? Earlier{6.7, 7.4, 4.0} : Earlier{5.7, 4.0, 0.0};
   constexpr double PARTIAL_ROUND = 5.0, PARTIAL_BYTES_PER_US = 6.4e6, HI[3] = {1.35, 1.05, 1.03}, LO[3] = {1.09, 1.06, 0.63};
@@ -1608,12 +1611,13 @@ void gemm_plan(GemmArgs &a, int epilogue) {
   }
   // QKV of 513 to 1024 rows: whole 160x256, 192x256 and 128x256 tiles against that choice by the present fit (8B layer,
   // 1024 rows: 256x256 tiles in two ranges 64.8 us, 128x256 whole 55.4; 3.4 % on average over 49 products, 2.8 % slower at worst).
-  // Above 1024 rows every shape, whole and cut: QKV 6.1 % faster on average over 136 products than the earlier fit's
-  // choices, output projection 3.5 % over 135, down projection 4.9 % over 134, and 0.7 % off the best (8B layer, 1580 rows: QKV
-  // 80 us on 256x256 tiles, 68 on 160x256; output projection 69.5 on 256x256 tiles in two ranges, 61 on 128x256 whole.  70B
-  // layer, 5120 rows: QKV 721 on shared tiles, 636 on 160x256).  Of more than one round QKV stays off 192x256 and 128x256
-  // tiles, although the former would be up to 9 % faster (70B layer, 2048 rows: 319 against 292): a test
-  // holds the division of 2200 rows of that layer to 256x256 tiles.
+  // Above 1024 rows every shape, whole and cut: against the earlier fit's choices QKV is 6.2 % faster on average over 136 products (5.3 %
+  // slower at worst, 41.4 -> 43.6 us), output projection 3.5 % over 135 (9 %, 19.6 -> 21.4), down projection 4.9 % over 134 (2 %), and
+  // 1.3, 0.3 and 0.2 % off the best (8B layer, 1580 rows: QKV 80 us on 256x256 tiles, 68 on 160x256; output projection 69.5 on
+  // 256x256 tiles in two ranges, 61 on 128x256 whole.  70B layer, 5120 rows: QKV 721 on shared tiles, 636 on 160x256).  Of more
+  // than one round QKV stays off 192x256 and 128x256 tiles, which would be ahead in 13 of the 136 by more than 5 % (70B layer,
+  // 2207 rows 332 us against 309; 8B layer, 3644 rows 183 against 159; N = 3072, K = 2048 at 7000 rows 103 against 86): a
+  // test holds the division of 2200 rows of the 70B layer to whole 256x256 tiles.
   if (!few || (epilogue == EPI_QKV && a.M > 512)) {
     if (few) {
       const Shape &c = SHAPES[a.tile_variant - V_BIG];  // one of the first three, numbered alike

@@ -291,8 +291,8 @@ def test_prefill_kernel_by_chunks(heads, dh, segments, rows, cached, want):
     (W.LLAMA3_8B, "down", 1580, (1, 2)), (W.LLAMA3_8B, "o", 5120, (2, 1)), (W.LLAMA3_70B, "down", 5120, (6, 1)),
     (W.LLAMA3_70B, "qkv", 2200, (1, 1)), (W.LLAMA3_70B, "o", 77, (4, 8)), (W.LLAMA3_8B, "o", 77, (3, 8)), (W.TINY, "o", 257, (3, 1))])
 def test_gemm_division_narrow_short_and_large(shape, product, rows, want):
-    # the measured best or within 5 % of it: narrow and short products that a cost fitted to large ones left
-    # whole, long ones cut, and the products that stay whole
+    # the measured best or within 5 % of it (QKV of 2200 rows of the 70B layer: 7.6 %, 192x256 tiles are not offered to it):
+    # narrow and short products that a cost fitted to large ones left whole, long ones cut, and the products that stay whole
     assert binding.Layer(shape, device=-1).gemm_division(product, rows) == want
 
 
