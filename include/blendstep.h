@@ -32,8 +32,9 @@
  *     workspace that they run in (bs_attention_noalloc has none that grows).
  *   - Prefill contexts that a call cuts into ranges (see bs_set_chunk_pages) take states of their own.  They
  *     are never the reason that a call fails or that one captured before loses its workspace: where the device
- *     has no room the contexts stay whole, their buffer is kept until bs_destroy once a captured call has
- *     used it, and a call that is being captured cuts only into what the calls before it have made room for.
+ *     has no room the contexts stay whole, the buffers of these states and of the descriptor are kept until
+ *     bs_destroy once a captured call has used them, and a call that is being captured cuts only into what the
+ *     calls before it have made room for.
  *     Captured behind an eager call of the same batch it is divided like that one, else it may sum in
  *     another order.
  */

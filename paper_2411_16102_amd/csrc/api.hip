@@ -72,7 +72,7 @@ struct Plan {
   long total_node_pages = 0, n_slots = 0;  // (partial states of decode sequences, a row each)
   int n_pf_work = 0;
   PrefillRoute pf_route{false, 4, 64};
-  long off_pf_cut = 0, n_cut_slots = 0, whole_ints = 0;  // n_cut_slots: rows of the partial states of cut prefill work; whole_ints: words without cuts
+  long off_pf_cut = 0, n_cut_slots = 0;  // n_cut_slots: rows of the partial states of cut prefill work
   int n_pf_cut = 0;  // blocks of query rows whose context is cut (0: the work list has two words an item, else four)
   int n_wide = 0, n_narrow = 0;  // decode items with up to 64 / up to 16 query rows (wide ones first)
 };
@@ -91,15 +91,17 @@ struct bs_ctx {
   long cap_slots = 0;
   float *part_acc = nullptr, *part_m = nullptr, *part_l = nullptr;
   // The states of cut prefill work stand apart: they grow when no state of a decode sequence does, and graphs that were
-  // captured with those would lose them.  Buffers that a captured call has used are kept to the end.
+  // captured with those would lose them.  Buffers that a captured call has used are kept to the end, and so are those of
+  // descriptors, which a cut makes longer (each is at most four fifths of the next).
   long cap_cut_slots = 0;
   float *cut_acc = nullptr, *cut_m = nullptr, *cut_l = nullptr;
   bool cut_captured = false;
-  std::vector<float *> outgrown;
+  std::vector<void *> outgrown;
   uint16_t *hid[2] = {nullptr, nullptr};  // activations between the layers of bs_blend_layers
   // descriptor blob: pinned staging memory and one device copy
   long cap_blob = 0;
   int32_t *d_blob = nullptr;
+  bool blob_captured = false;
   Staging<HipRuntime> stage;
   // host scratch reused across calls
   std::vector<int32_t> refcount, path_pages, path_chunks, members, tail_pages, blob;
@@ -235,6 +237,11 @@ int ensure_cut_slots(bs_ctx *c, long slots) {
 int ensure_blob(bs_ctx *c, long ints) {
   if (ints > c->cap_blob) {
     const long cap = ints + ints / 4 + 1024;
+    if (c->blob_captured) {
+      c->outgrown.push_back(c->d_blob);
+      c->d_blob = nullptr;
+      c->blob_captured = false;
+    }
     c->cap_blob = 0;
     int rc = dev_alloc(c, &c->d_blob, (size_t)cap);
     if (rc) return rc;
@@ -695,10 +702,9 @@ int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chu
   const long other_words = p.off_pf_work + 8L * (long)(c->items.size() + c->items_wide.size()) + p.total_node_pages + n_tab;
   const CutLimits lim = {decode_us * c->cfg.n_kv_heads / 1024.0, {std::min(room.slots, all_slots - p.n_slots), room.words - other_words}};
   const int cut = prefill_cut(c, b, p.pf_route, lim);
-  int n_states = 0, n_blocks = 0;
+  int n_states = 0;
   each_prefill_block(b, p.pf_route.rows, [&](int seq, int k, int blocks, int last_start) {
     const int n = cut ? prefill_ranges(blocks, cut, last_start) : 1;
-    ++n_blocks;
     for (int i = 0; i < n; ++i) {
       const int t0 = (int)((long)blocks * i / n), t1 = (int)((long)blocks * (i + 1) / n);
       order.push_back({t1 - t0, seq, k, t0, i + 1 < n ? t1 : 0, n > 1 ? n_states + i : -1});
@@ -711,7 +717,6 @@ int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chu
   p.n_pf_work = (int)order.size();
   p.n_pf_cut = (int)c->pf_cut.size() / 4;
   p.n_cut_slots = (long)n_states * p.pf_route.rows;
-  p.whole_ints = other_words + 2L * n_blocks;
   const int work_words = p.n_pf_cut ? 4 : 2;
   p.off_pf_cut = p.off_pf_work + (long)work_words * p.n_pf_work;
   p.off_items = p.off_pf_cut + 4L * p.n_pf_cut;
@@ -756,7 +761,6 @@ struct PlanOps {
   int build(CutRoom room) { p = Plan{}; return plan(p, room); }
   long slots() const { return p.n_cut_slots; }
   long words() const { return whole_units(p.total_ints); }
-  long whole_words() const { return whole_units(p.whole_ints); }
   long held_slots() const { return c->cap_cut_slots; }
   long held_words() const { return c->cap_blob / 4 * 4; }
   long captured_words() const { return c->stage.captured_room(); }
@@ -764,8 +768,8 @@ struct PlanOps {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     return hipStreamIsCapturing(st, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
   }
-  bool grow(long n) {
-    const bool grown = ensure_cut_slots(c, n) == BS_OK;
+  bool grow(long slots, long words) {
+    const bool grown = ensure_cut_slots(c, slots) == BS_OK && ensure_blob(c, words) == BS_OK;
     if (!grown) (void)hipGetLastError();  // (the launches that follow ask for it)
     return grown;
   }
@@ -775,10 +779,8 @@ struct PlanOps {
 template <class Build>
 int plan_and_reserve(bs_ctx *c, Plan &p, hipStream_t st, Build &&plan) {
   PlanOps<Build &> ops{c, p, st, plan};
-  int rc = plan_within(ops);
-  if (rc || (rc = ensure_slots(c, p.n_slots))) return rc;
-  if (p.n_pf_cut && ops.capturing()) c->cut_captured = true;
-  return BS_OK;
+  const int rc = plan_within(ops);
+  return rc ? rc : ensure_slots(c, p.n_slots);
 }
 
 int plan_step(bs_ctx *c, const bs_batch *b, Plan &p, hipStream_t st) {
@@ -863,7 +865,12 @@ int stage_plan(bs_ctx *c, const Plan &p, hipStream_t stream, Upload &up, int32_t
   if (p.total_ints == 0) return BS_OK;
   if (units > std::numeric_limits<int>::max() - 256) return fail(c, BS_EINVAL, "descriptor of %ld words", p.total_ints);
   int32_t *src = nullptr;
-  if (const int e = c->stage.place(words, stream, &src)) return staging_failed(c, e);
+  bool captured = false;
+  if (const int e = c->stage.place(words, stream, &src, &captured)) return staging_failed(c, e);
+  if (captured && !dst) {
+    c->blob_captured = true;
+    if (p.n_pf_cut) c->cut_captured = true;
+  }
   std::memcpy(src, c->blob.data(), sizeof(int32_t) * p.total_ints);
   up.src = reinterpret_cast<const uint4 *>(src);
   up.dst = reinterpret_cast<uint4 *>(dst ? dst : c->d_blob);
@@ -1338,7 +1345,7 @@ void bs_destroy(bs_ctx *c) {
                   (void *)c->xg2, (void *)c->act, (void *)c->rstd1, (void *)c->rstd2, (void *)c->ss2, (void *)c->part_acc, (void *)c->part_m,
                   (void *)c->part_l, (void *)c->cut_acc, (void *)c->cut_m, (void *)c->cut_l, (void *)c->d_blob, (void *)c->hid[0], (void *)c->hid[1], (void *)c->sync_words, (void *)c->trace_buf, (void *)c->sk_ws, (void *)c->sk_cnt})
     if (p) (void)hipFree(p);
-  for (float *p : c->outgrown) (void)hipFree(p);
+  for (void *p : c->outgrown) (void)hipFree(p);
   c->stage.close();
   for (auto &v : c->spans) for (auto &s : v) { (void)hipEventDestroy(s.a); (void)hipEventDestroy(s.b); }
   for (auto e : c->free_events) (void)hipEventDestroy(e);

@@ -13,26 +13,21 @@ struct CutRoom {
 
 // Cutting is optional, so it asks for nothing that the call would not get without it.  Ops, on one batch:
 //   build(room)     plans, cutting into no more than `room`; 0 or an error
-//   slots(), words(), whole_words()   of that plan: its states of cut contexts, its descriptor, the descriptor without cuts
+//   slots(), words()   of that plan: its states of cut contexts, its descriptor
 //   held_slots(), held_words()        what the context's buffers hold
 //   captured_words()                  the longest descriptor that a captured call places without an allocation
 //   capturing()     whether the call is being captured into a graph: then nothing may be allocated
-//   grow(slots)     makes room for so many states; false where the device has none
+//   grow(slots, words)   makes room for so many; false where the device has none
 // - Under capture contexts are cut only into what the context holds.
-// - A cut that the device has no states for is not made.
-// - The descriptor's buffer does not grow for the sake of a cut: graphs that were captured read it.
+// - A cut that the device has no room for is not made.
 template <class Ops>
 int plan_within(Ops &&ops) {
   if (const int rc = ops.build(CutRoom{})) return rc;
   if (ops.slots() == 0) return 0;
-  const bool longer = ops.words() > ops.held_words(), captured_longer = ops.words() > ops.captured_words();
-  if (ops.slots() <= ops.held_slots() && !longer && !captured_longer) return 0;
+  const bool held = ops.slots() <= ops.held_slots() && ops.words() <= ops.held_words();
+  if (held && ops.words() <= ops.captured_words()) return 0;
   if (ops.capturing()) return ops.build(CutRoom{ops.held_slots(), std::min(ops.held_words(), ops.captured_words())});
-  if (longer && ops.whole_words() <= ops.held_words()) {
-    if (const int rc = ops.build(CutRoom{std::numeric_limits<long>::max(), ops.held_words()})) return rc;
-    if (ops.slots() == 0) return 0;
-  }
-  if (ops.slots() <= ops.held_slots() || ops.grow(ops.slots())) return 0;
+  if (held || ops.grow(ops.slots(), ops.words())) return 0;
   return ops.build(CutRoom{0, std::numeric_limits<long>::max()});
 }
 

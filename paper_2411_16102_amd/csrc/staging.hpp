@@ -81,10 +81,11 @@ class Staging {
   long captured_room() const { return ring_ / 5 / 4 * 4; }
 
   // Room for `words`, a multiple of four: whole 16-byte units, on a 16-byte boundary.  They may be read by what `stream`
-  // is given next.
-  int place(long words, typename Rt::Stream stream, int32_t **out) {
+  // is given next.  *is_captured: whether by a graph.
+  int place(long words, typename Rt::Stream stream, int32_t **out, bool *is_captured = nullptr) {
     bool captured = false;
     if (const int e = rt_.capturing(stream, &captured)) return e;
+    if (is_captured) *is_captured = captured;
     if (captured) return keep(words, out);
     if (words > half_) {
       const long want = whole_units(words + words / 4 + 1024);  // (the second half starts on a unit too)

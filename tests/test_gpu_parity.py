@@ -1012,6 +1012,40 @@ def test_cut_contexts_leave_captured_calls_their_workspace(lib):
             check_attention(shape, cb, cq, ct, to_np(out))
 
 
+def test_cut_contexts_on_a_context_whose_descriptor_buffer_holds_the_whole_ones(lib):
+    # a short call leaves a descriptor buffer that would do for whole contexts: the same ranges as on a new context, and as
+    # bs_attention_noalloc takes; a call that was captured with that buffer replays to the same result
+    import torch
+    shape = W.LayerShape(256, 8, 2, 128, 256)
+    rng = np.random.default_rng(9)
+    first, batch = W.assemble_batch(16, [(9, 9, -1)], 1, [], rng), W.assemble_batch(16, [(9, 1409, -1)] * 8, 8, [], rng)
+    layer = lib.Layer(shape, device=0)
+    held = (layer.attention_division(first).descriptor_words + 3) // 4 * 5 + 1024
+    whole = lib.Layer(shape, device=-1)
+    whole.set_chunk_pages(64)
+    assert whole.attention_division(batch).descriptor_words <= held - 4 and held < layer.attention_division(batch).descriptor_words
+    calls = []
+    for b in (first, batch):
+        t = W.make_tensors(shape, b, 9)
+        q = W.round_to_bf16(rng.standard_normal((b.n_rows, shape.n_q_heads * shape.head_dim), dtype=np.float32))
+        calls.append((b, t, q, torch.from_numpy(q).cuda().to(torch.bfloat16), layer.pack_pool(t.k_pool, t.v_pool)))
+    (fb, ft, fq, ftq, fpool), (b, t, q, tq, pool) = calls
+    layer.attention(fb, ftq, fpool, fb.n_pages)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        captured = layer.attention(fb, ftq, fpool, fb.n_pages)
+    for _ in range(2):
+        out = layer.attention(b, tq, pool, b.n_pages)
+        check_attention(shape, b, q, t, to_np(out))
+        assert torch.equal(lib.Layer(shape, device=0).attention(b, tq, pool, b.n_pages), out)
+        assert torch.equal(layer.attention_noalloc(b, tq, pool, b.n_pages, torch.zeros_like(out)), out)
+        captured.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        check_attention(shape, fb, fq, ft, to_np(captured))
+
+
 @pytest.mark.parametrize("d_ffn,rows,launches", [(8200, 907, 2), (14344, 800, 2), (14344, 805, 2), (6920, 1929, 2),  # two shapes
                                                  (14344, 1216, 2), (14344, 1500, 1), (14344, 663, 1)])
 def test_gate_up_in_as_many_launches_as_are_expected_to_be_shorter(lib, d_ffn, rows, launches):

@@ -394,15 +394,17 @@ def test_cut_prefill_contexts_keep_to_the_scratch_array(segments):
 
 
 @pytest.mark.parametrize("want,held,captured_words,capturing,free,got", [
-    # want / held / got: states of cut contexts and descriptor words (the descriptor without cuts has 90)
+    # want / held / got: states of cut contexts and descriptor words (the descriptor without cuts has 90); free: states that
+    # the device has room for
     ((64, 120), (0, 100), 500, True, 0, (0, 90)),         # captured on a context without states: whole
     ((64, 120), (64, 128), 500, True, 0, (64, 120)),      # ... that holds them: cut as outside capture
     ((64, 120), (64, 100), 500, True, 0, (32, 100)),      # ... whose descriptor buffer is too short for that many
     ((64, 120), (64, 128), 100, True, 0, (32, 100)),      # ... whose ring of captured descriptors is
     ((64, 120), (0, 128), 500, False, 64, (64, 120)),     # outside capture the states grow
     ((64, 120), (0, 128), 500, False, 63, (0, 90)),       # ... and what the device has no room for stays whole
-    ((64, 120), (0, 100), 500, False, 64, (32, 100)),     # a descriptor that fits without the cut makes none grow
-    ((64, 120), (0, 80), 500, False, 64, (64, 120)),      # ... one that does not grows anyway
+    ((64, 120), (0, 100), 500, False, 64, (64, 120)),     # ... and the descriptor's buffer, also where it would do without the cut
+    ((64, 120), (64, 100), 500, False, 64, (64, 120)),
+    ((64, 120), (64, 100), 500, False, 0, (0, 90)),
     ((64, 120), (64, 128), 100, False, 0, (64, 120)),     # the ring is for captured calls
     ((0, 90), (0, 0), 0, True, 0, (0, 90))])              # nothing to cut: nothing is asked
 def test_what_a_call_cuts_into(tmp_path, want, held, captured_words, capturing, free, got):
@@ -415,7 +417,7 @@ struct Ops {
   long ws, ww, hs, hw, cw, free_slots;
   bool cap;
   long s = 0, w = 0;
-  bool grew = false, asked = false;
+  bool grew = false, asked = false, room = false;
   int build(bs::CutRoom r) {  // half of the cuts where all of them do not fit
     s = ws; w = ww;
     if (s > r.slots || w > r.words) { s = ws / 2; w = 100; }
@@ -424,17 +426,16 @@ struct Ops {
   }
   long slots() const { return s; }
   long words() const { return w; }
-  long whole_words() const { return 90; }
   long held_slots() const { return hs; }
   long held_words() const { return hw; }
   long captured_words() const { return cw; }
   bool capturing() { asked = true; return cap; }
-  bool grow(long n) { grew = true; return n <= free_slots; }
+  bool grow(long n, long words) { grew = true; return room = n <= free_slots && words == ww; }
 };
 int main() {
   Ops o{%d, %d, %d, %d, %d, %d, %s};
   if (bs::plan_within(o)) return 1;
-  std::printf("%%ld %%ld %%d %%d", o.s, o.w, o.cap && o.grew, o.asked && o.ws == 0);
+  std::printf("%%ld %%ld %%d %%d", o.s, o.w, o.cap && o.grew, (o.asked && o.ws == 0) || (!o.cap && o.s > o.hs && !o.room));
 }
 """ % (*want, *held, captured_words, free, "true" if capturing else "false"))
     csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2411_16102_amd", "csrc")
