@@ -89,12 +89,12 @@ struct bs_ctx {
   uint16_t *xg = nullptr, *qbuf = nullptr, *attn = nullptr, *xg2 = nullptr, *act = nullptr;
   float *x1 = nullptr, *rstd1 = nullptr, *rstd2 = nullptr, *ss2 = nullptr;
   long cap_slots = 0;
-  float *part_acc = nullptr, *part_m = nullptr, *part_l = nullptr;
+  float *part_acc = nullptr, *part_m = nullptr, *part_l = nullptr;  // (one allocation)
   // The states of cut prefill work stand apart: they grow when no state of a decode sequence does, and graphs that were
   // captured with those would lose them.  Buffers that a captured call has used are kept to the end, and so are those of
   // descriptors, which a cut makes longer (each is at most four fifths of the next).
   long cap_cut_slots = 0;
-  float *cut_acc = nullptr, *cut_m = nullptr, *cut_l = nullptr;
+  float *cut_acc = nullptr, *cut_m = nullptr, *cut_l = nullptr;  // (one allocation)
   bool cut_captured = false;
   std::vector<void *> outgrown;
   uint16_t *hid[2] = {nullptr, nullptr};  // activations between the layers of bs_blend_layers
@@ -198,15 +198,20 @@ int ensure_rows(bs_ctx *c, int rows) {
   return BS_OK;
 }
 
+// `slots` rows of partial states in one allocation, in the place of *acc: a first pass pays for each allocation
+int alloc_states(bs_ctx *c, long slots, float **acc, float **m, float **l) {
+  const size_t n = (size_t)whole_units(slots * c->cfg.n_q_heads), n_acc = (size_t)slots * c->cfg.n_q_heads * c->cfg.head_dim;
+  if (const int rc = dev_alloc(c, acc, n_acc + 2 * n)) return rc;
+  *m = *acc + n_acc;
+  *l = *m + n;
+  return BS_OK;
+}
+
 int ensure_slots(bs_ctx *c, long slots) {
   if (slots <= c->cap_slots) return BS_OK;
   const long cap = slots + slots / 4 + 64;
-  const size_t hq = c->cfg.n_q_heads;
-  int rc;
   c->cap_slots = 0;
-  if ((rc = dev_alloc(c, &c->part_acc, (size_t)cap * hq * c->cfg.head_dim))) return rc;
-  if ((rc = dev_alloc(c, &c->part_m, (size_t)cap * hq))) return rc;
-  if ((rc = dev_alloc(c, &c->part_l, (size_t)cap * hq))) return rc;
+  if (const int rc = alloc_states(c, cap, &c->part_acc, &c->part_m, &c->part_l)) return rc;
   c->cap_slots = cap;
   return BS_OK;
 }
@@ -215,21 +220,13 @@ int ensure_slots(bs_ctx *c, long slots) {
 int ensure_cut_slots(bs_ctx *c, long slots) {
   if (slots <= c->cap_cut_slots) return BS_OK;
   const long cap = slots + slots / 4 + 64;
-  const size_t hq = c->cfg.n_q_heads;
-  float **const arrays[3] = {&c->cut_acc, &c->cut_m, &c->cut_l};
   if (c->cut_captured) {
-    c->outgrown.reserve(c->outgrown.size() + 3);
-    for (float **a : arrays) { c->outgrown.push_back(*a); *a = nullptr; }
+    c->outgrown.push_back(c->cut_acc);
+    c->cut_acc = nullptr;
     c->cut_captured = false;
   }
   c->cap_cut_slots = 0;
-  int rc = BS_OK;
-  for (float **a : arrays)
-    if (!rc) rc = dev_alloc(c, a, (size_t)cap * hq * (a == &c->cut_acc ? c->cfg.head_dim : 1));
-  if (rc) {
-    for (float **a : arrays) (void)dev_alloc(c, a, 0);
-    return rc;
-  }
+  if (const int rc = alloc_states(c, cap, &c->cut_acc, &c->cut_m, &c->cut_l)) return rc;
   c->cap_cut_slots = cap;
   return BS_OK;
 }
@@ -1342,8 +1339,8 @@ void bs_destroy(bs_ctx *c) {
   (void)hipSetDevice(c->device);
   (void)hipDeviceSynchronize();
   for (void *p : {(void *)c->rope_cos, (void *)c->rope_sin, (void *)c->xg, (void *)c->qbuf, (void *)c->attn, (void *)c->x1,
-                  (void *)c->xg2, (void *)c->act, (void *)c->rstd1, (void *)c->rstd2, (void *)c->ss2, (void *)c->part_acc, (void *)c->part_m,
-                  (void *)c->part_l, (void *)c->cut_acc, (void *)c->cut_m, (void *)c->cut_l, (void *)c->d_blob, (void *)c->hid[0], (void *)c->hid[1], (void *)c->sync_words, (void *)c->trace_buf, (void *)c->sk_ws, (void *)c->sk_cnt})
+                  (void *)c->xg2, (void *)c->act, (void *)c->rstd1, (void *)c->rstd2, (void *)c->ss2, (void *)c->part_acc,
+                  (void *)c->cut_acc, (void *)c->d_blob, (void *)c->hid[0], (void *)c->hid[1], (void *)c->sync_words, (void *)c->trace_buf, (void *)c->sk_ws, (void *)c->sk_cnt})
     if (p) (void)hipFree(p);
   for (void *p : c->outgrown) (void)hipFree(p);
   c->stage.close();
