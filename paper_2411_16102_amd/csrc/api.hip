@@ -544,6 +544,9 @@ struct CutLimits {
 // rounds of workgroups that it makes, whichever is most; a state costs its way out and back.  Measured, 8B heads, launch and
 // merge: 32 rows behind 8000 tokens 221 -> 34 us, 1024 behind 2000 97 -> 71, 8 x 100 behind 6000 180 -> 114, 500 behind 5000
 // beside 200 decode sequences of 1000 240 -> 207; 2 x 1024 behind 9000 (224 workgroups of one length) stay whole, 305.
+// Of 858 batches of five head shapes that are cut or were, timed both ways, 43 % shorter on average than whole and 0.2 % off the better of
+// the two; seven are 3 % and more longer, the worst 11 (97 -> 107 us).  With 0.95 us a block for all whole contexts of 64-wide heads
+// 26 were, by up to 16 % (four chunks of 250 rows without cached tokens 34 -> 38 us, one of 3662 108 -> 120).
 int prefill_cut(bs_ctx *c, const bs_batch *b, const PrefillRoute &route, const CutLimits &lim) {
   constexpr int SHORTEST = 16;  // blocks of a context that is not worth a cut
   // (a caller that has fixed the length of decode chunks has the division in hand: contexts stay whole)
@@ -571,7 +574,9 @@ int prefill_cut(bs_ctx *c, const bs_batch *b, const PrefillRoute &route, const C
     });
     if (states * route.rows > lim.room.slots || 4 * (items + cuts) > lim.room.words) break;
     const int per_cu = !wide && items * wgs > 256 ? 2 : 1;
-    const double block = wide ? 1.0 : per_cu == 2 ? 0.95 : 0.65;
+    double block = wide ? 1.0 : per_cu == 2 ? 0.95 : 0.65;
+    // (whole contexts end one after the other: the longest shares its CU only where many run beside it)
+    if (!wide && length == lengths[0]) block = std::min(block, 0.65 + 0.3 * std::max(0.0, (sum * wgs / longest - 200.0) / 120.0));
     // CUs that the decode items leave, on average, while the longest workgroup runs
     double work = 0.0, rounds = 0.0, first = 0.0;
     long seen = 0, slots = 0;
