@@ -106,7 +106,7 @@ struct bs_ctx {
   // host scratch reused across calls
   std::vector<int32_t> refcount, path_pages, path_chunks, members, tail_pages, blob;
   std::vector<DecodeItem> items, items_wide;
-  struct PrefillItem { int blocks, seq, block, t0, t1, state; };
+  struct PrefillItem { int tokens, seq, block, t0, t1, state; };
   std::vector<PrefillItem> pf_order;
   std::vector<int32_t> pf_cut;
   unsigned char *scratch_ptr = nullptr;  // this device's copy of the static scratch array
@@ -546,7 +546,7 @@ struct CutLimits {
 // beside 200 decode sequences of 1000 240 -> 207; 2 x 1024 behind 9000 (224 workgroups of one length) stay whole, 305.
 // Of 858 batches of five head shapes that are cut or were, timed both ways, 43 % shorter on average than whole and 0.2 % off the better of
 // the two; seven are 3 % and more longer, the worst 11 (97 -> 107 us).  With 0.95 us a block for all whole contexts of 64-wide heads
-// 26 were, by up to 16 % (four chunks of 250 rows without cached tokens 34 -> 38 us, one of 3662 108 -> 120).
+// 26 were, by up to 16 % (3928 rows in eleven chunks without cached tokens 34 -> 38 us, one chunk of 3662 rows 108 -> 120).
 int prefill_cut(bs_ctx *c, const bs_batch *b, const PrefillRoute &route, const CutLimits &lim) {
   constexpr int SHORTEST = 16;  // blocks of a context that is not worth a cut
   // (a caller that has fixed the length of decode chunks has the division in hand: contexts stay whole)
@@ -692,7 +692,8 @@ int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chu
       }
     }
   }
-  // prefill work: (sequence, block of query rows of one workgroup), longest contexts first; a context that would outlast
+  // prefill work: (sequence, block of query rows of one workgroup), longest contexts first, in tokens (in blocks of 32 the last few
+  // rows of a chunk tie with the whole block before them: 20 x 200 rows behind 300 tokens 68 -> 73 us); a context that would outlast
   // the rest of the launch is cut into ranges, workgroups of their own
   p.pf_route = prefill_route(attn_shape(c), b->n_prefill, b->row_start, b->kv_len);
   std::vector<bs_ctx::PrefillItem> &order = c->pf_order;
@@ -707,15 +708,16 @@ int build_plan(bs_ctx *c, const bs_batch *b, Plan &p, bool with_rows, Chunks chu
   int n_states = 0;
   each_prefill_block(b, p.pf_route.rows, [&](int seq, int k, int blocks, int last_start) {
     const int n = cut ? prefill_ranges(blocks, cut, last_start) : 1;
+    const int q = b->row_start[seq + 1] - b->row_start[seq], tokens = b->kv_len[seq] - q + std::min(q, (k + 1) * p.pf_route.rows);
     for (int i = 0; i < n; ++i) {
       const int t0 = (int)((long)blocks * i / n), t1 = (int)((long)blocks * (i + 1) / n);
-      order.push_back({t1 - t0, seq, k, t0, i + 1 < n ? t1 : 0, n > 1 ? n_states + i : -1});
+      order.push_back({(i + 1 < n ? 32 * t1 : tokens) - 32 * t0, seq, k, t0, i + 1 < n ? t1 : 0, n > 1 ? n_states + i : -1});
     }
     if (n == 1) return;
     c->pf_cut.insert(c->pf_cut.end(), {seq, k, n_states, n});
     n_states += n;
   });
-  std::stable_sort(order.begin(), order.end(), [](const auto &x, const auto &y) { return x.blocks > y.blocks; });
+  std::stable_sort(order.begin(), order.end(), [](const auto &x, const auto &y) { return x.tokens > y.tokens; });
   p.n_pf_work = (int)order.size();
   p.n_pf_cut = (int)c->pf_cut.size() / 4;
   p.n_cut_slots = (long)n_states * p.pf_route.rows;
