@@ -36,14 +36,17 @@ using namespace attn_dev;
 // Measured (this launch, 8B heads) against workgroups of four wavefronts and chunks of 64 pages: one sequence
 // of 4000 tokens 48 -> 7 us, 7 of 2000 63 -> 14, 64 of 2000 86 -> 85, 256 of 1024 180 -> 179.
 // Grid order: wide workgroups first, narrow ones
-// after, longest first within a kind; but one wide workgroup alternates with two narrow ones for as long as both kinds last
-// (what is left of the wide kind goes first), in a launch of decode units alone where it is two rounds of 1024 wavefronts or
-// a third of it is wide, and beside prefill workgroups where a quarter is: a wavefront with 64 query rows is bound by its own issue, the narrow ones
-// beside it use the bandwidth it leaves, and wide units of their own at the head of the launch leave memory idle.
-// Measured, alone: 640 sequences in a two-level tree (1792 wide, 5264 narrow units, 70B heads) 375 -> 326 us, 900 behind 30
-// prefixes of 256 163 -> 147, 1000 behind 8 of 2048 952 -> 926, about one round (77 behind three) 171.9 -> 172.9; beside prefill
-// rows: 3072 and 8192 units (70B layer, step) 7087 -> 7022, 1504 and 7248 (8B) 1368 -> 1375, hence the line.  One in five is
-// within 3 % either way; periods of two and four, turned over the XCDs, cost up to a fifth.
+// after, longest first within a kind; but one wide workgroup alternates with two narrow ones to the last wide one
+// where there are at least two narrow ones for each and, alone, the launch is long (three and a half rounds of 1024 wavefronts) with wide
+// units for half the SIMDs, beside prefill workgroups wide units for one and a half rounds: a wavefront with 64 query rows is bound by its
+// own issue, the narrow ones beside it use the bandwidth it leaves, and many wide units of their own at the head of the launch leave memory
+// idle.  Few wide units leave SIMDs to the narrow ones anyway, and in a short launch, or among few narrow ones, the last wide ones begin too late.
+// Measured, alone: 640 sequences in a two-level tree (1792 wide, 5264 narrow units, 70B heads) 375 -> 326 us, 960 and 7592 units
+// 137 -> 125; 608 and 2648 (24 heads) 49.6 wide first, 52.6 in turn; beside prefill rows: 3072 and 8192 units (70B layer,
+// step) 7087 -> 7022; 1504 and 7248 (8B) 1361 wide first, 1374 in turn; 64-wide heads behind 23 prefixes 32.5 and 40.1.  Of 4482 launches of
+// decode units and 1452 beside prefill rows, timed in both orders, the choice is 0.3 and 0.4 % off the better one on average and 11 and 13 % at
+// worst (in turn from two rounds of units of either kind or a third of them wide, from a quarter beside prefill rows: 0.9 and 1.2 %, 27 and 32 %).
+// Periods of two and four, turned over the XCDs, cost up to a fifth.
 // The period is odd on purpose: workgroups go to the eight XCDs in turn, and a period of
 // four would send every wide workgroup to the same two of them.
 template <int DH, int WPW, bool NT_NARROW>
@@ -52,21 +55,16 @@ __device__ __forceinline__ void decode_workgroup(const DecodeArgs &a, int n_wide
   constexpr int WQB = 4;  // blocks of 16 query rows of a wide item
   const int hkv = a.s.n_kv_heads;
   const int nw = (n_wide_units + WPW - 1) / WPW, nn = (n_narrow_units + WPW - 1) / WPW;  // workgroups of each kind
-  const bool mix = WPW == 1 ? nw + nn >= 2048 || 2 * nw >= nn : 3 * nw >= nn;
-  const int mixed = mix ? min(nw, nn >> 1) : 0;                            // periods of one wide + two narrow
-  const int lead = nw - mixed;                                             // wide workgroups ahead of the mixed part
+  const bool mix = 2 * nw <= nn && (WPW == 1 ? nw >= 512 && nw + nn >= 3584 : nw >= 384);
   bool wide;
   int wg;  // index of this workgroup within its kind
-  if (b < lead) {
-    wide = true;
-    wg = b;
-  } else if (b - lead < 3 * mixed) {
-    const int per = (b - lead) / 3, pos = (b - lead) % 3;
+  if (mix && b < 3 * nw) {
+    const int per = b / 3, pos = b % 3;
     wide = pos == 0;
-    wg = wide ? lead + per : 2 * per + pos - 1;
+    wg = wide ? per : 2 * per + pos - 1;
   } else {
-    wide = false;
-    wg = 2 * mixed + (b - lead - 3 * mixed);
+    wide = !mix && b < nw;
+    wg = wide ? b : b - nw;
   }
   const int unit = wg * WPW + wave;
   if (wide) {

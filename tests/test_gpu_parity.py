@@ -240,8 +240,8 @@ def test_attention_node_member_counts(lib, shape, members):
 @pytest.mark.parametrize("root_pages,n_members", [(20, 40), (14, 41)])
 def test_attention_wide_items_alternate_with_narrow_ones(lib, root_pages, n_members):
     # one long shared root cut into chunks of two pages, short private tails: the workgroups of
-    # 64-row items are more than a third of the launch, so the grid takes its mixed order (some
-    # wide workgroups ahead, then one wide and two narrow in turn, then what is left)
+    # 64-row items are more than a third of the launch (they go first; many of them in turn with
+    # narrow ones: test_wide_items_in_turn_with_narrow_ones)
     import torch
     shape = W.LayerShape(512, 8, 2, 128, 256)
     rng = np.random.default_rng(root_pages * 100 + n_members)
@@ -891,8 +891,7 @@ def test_step_with_cut_prefill_contexts(lib):
 
 
 def test_few_wide_items_among_many_narrow_ones(lib):
-    # two rounds of workgroups: one wide in turn with two narrow ones, and most narrow ones behind them; alone, and with prefill rows,
-    # where so few wide ones go first
+    # so few wide ones go first, alone and with prefill rows
     import torch
     shape = W.LayerShape(512, 8, 2, 128, 256)
     for n_prefill in (0, 1):
@@ -907,6 +906,28 @@ def test_few_wide_items_among_many_narrow_ones(lib):
         pool = layer.pack_pool(tens.k_pool, tens.v_pool)
         out = to_np(layer.attention(batch, torch.from_numpy(q).cuda().to(torch.bfloat16), pool, batch.n_pages))
         check_attention(shape, batch, q, tens, out)
+
+
+@pytest.mark.parametrize("n_prefill,groups,loose", [(0, 112, 0), (0, 111, 0), (0, 64, 192), (0, 63, 200), (0, 130, 37), (1, 192, 3), (1, 191, 0)])
+def test_wide_items_in_turn_with_narrow_ones(lib, n_prefill, groups, loose):
+    # 8 KV heads; 3584 units and more of which 512 are wide alone, 1536 wide ones beside prefill rows: one wide in turn with two narrow
+    # ones, the rest behind; one group less: wide ones first
+    import torch
+    shape = W.LayerShape(64, 64, 8, 128, 64)
+    rng = np.random.default_rng(groups)
+    seqs = [(7, 40, -1)] * n_prefill + [(1, 16 + 3 + (5 * i) % 29, i // 3) for i in range(3 * groups)] + [(1, 30 + i, -1) for i in range(loose)]
+    batch = W.assemble_batch(16, seqs, n_prefill, [(-1, 1)] * groups, rng)
+    layer = lib.Layer(shape, device=0)
+    division = layer.attention_division(batch)
+    assert division.wide_items == groups and 2 * groups <= division.items - groups
+    assert (groups >= 192 if n_prefill else groups >= 64 and division.items >= 448) == (groups not in (63, 111, 191))
+    tens = W.make_tensors(shape, batch, 12)
+    q = W.round_to_bf16(rng.standard_normal((batch.n_rows, shape.n_q_heads * shape.head_dim), dtype=np.float32))
+    pool = layer.pack_pool(tens.k_pool, tens.v_pool)
+    tq = torch.from_numpy(q).cuda().to(torch.bfloat16)
+    out = layer.attention(batch, tq, pool, batch.n_pages)
+    check_attention(shape, batch, q, tens, to_np(out))
+    assert torch.equal(layer.attention(batch, tq, pool, batch.n_pages), out)
 
 
 @pytest.mark.parametrize("d_ffn,rows,tiles", [(8200, 907, 10), (14344, 800, 2), (14344, 805, 10), (6920, 1929, 1), (14344, 521, 2), (14344, 663, 10)])
